@@ -116,7 +116,6 @@ size_t mx_scale_bytes(int64_t rows, int64_t cols, int axis);
  * ceil(L/32) whole blocks: elems [..][ceil(L/32)*32*bits/8], scales
  * [..][ceil(L/32)], which is what mx_elem_bytes / mx_scale_bytes return.  Such
  * a tensor is a valid mx_gemm operand with K = 32*ceil(L/32): the fill adds 0.
- * (Whole blocks take the fast kernels; a ragged length takes the generic one.)
  * Per block: scale byte = clamp(floor(log2 max|V|) - emax_elem + 127, 0, 254)
  * over the normal finite inputs (0 if there are none); Float32-subnormal inputs
  * give P = 0; finite values beyond the largest normal clamp to it with their
@@ -186,8 +185,7 @@ int mx_quantize_dual(const void *src, mx_dtype_t src_dt, int64_t rows, int64_t c
  *       [d0][ceil(d1/32)][d2] or [ceil(d0/32)][d1][d2].  A partial last block
  *       is cast as if filled up with zeros; nothing is stored for the fill.
  * rnd: not MX_ROUND_STOCHASTIC.  Outputs 16-byte aligned device memory.
- * keep_order = 0 with axis 1, or with axis 0 and stride1 != d2, issues one
- * launch per slice (d0 or d1 of them); everything else is a single launch
+ * Slices go through one launch (one per 65535 of them)
  * (MX_ERR_UNSUPPORTED beyond 65535 * 32 rows along the block axis with
  * keep_order = 1).
  */
@@ -203,8 +201,7 @@ int mx_quantize_3d(const void *src, mx_dtype_t src_dt,
  * (elements; stride1 >= d2, stride0 >= d1*stride1, dst 16-byte aligned and both
  * strides a multiple of 16 bytes).  Nothing outside the tensor's elements is
  * written.  A scale byte 0xFF gives NaN for its block; fill positions of a
- * partial last block (keep_order = 0) are skipped.  keep_order = 0 with axis 1,
- * or with axis 0 / 2 and padded rows, issues one launch per slice.
+ * partial last block (keep_order = 0) are skipped.
  */
 int mx_dequantize_3d(const void *elems, const uint8_t *scales, mx_format_t fmt,
                      int64_t d0, int64_t d1, int64_t d2, int axis, int keep_order,

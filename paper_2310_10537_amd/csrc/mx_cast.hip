@@ -21,9 +21,9 @@ namespace mx {
 // cols read as zero.
 // ---------------------------------------------------------------------------
 template <int SRC, int FMT, int RND, int EPL>
-__global__ __launch_bounds__(256) void cast_row_kernel(const void *__restrict__ src, int64_t cols, int64_t pcols, int64_t ld,
-                                                       uint8_t *__restrict__ elems, uint8_t *__restrict__ scales,
-                                                       int64_t n_units, uint64_t seed)
+__global__ __launch_bounds__(256) void cast_row_kernel(const void *__restrict__ src, int64_t rows, int64_t cols, int64_t pcols,
+                                                       int64_t ld, int64_t stride0, uint8_t *__restrict__ elems,
+                                                       uint8_t *__restrict__ scales, int64_t n_units, uint64_t seed)
 {
     constexpr int G = BLOCK / EPL;
     constexpr int w = Fmt<FMT>::bits;
@@ -31,7 +31,7 @@ __global__ __launch_bounds__(256) void cast_row_kernel(const void *__restrict__ 
     constexpr int ND = EPL * w / 32;
     const int64_t stride = (int64_t)gridDim.x * 256;
     const int64_t units_per_row = pcols / EPL;
-    const bool flat = (ld == cols && cols == pcols);
+    const bool flat = (ld == cols && cols == pcols && stride0 == rows * ld);
 
     for (int64_t u = (int64_t)blockIdx.x * 256 + threadIdx.x; u < n_units; u += stride) {
         int64_t off;     // element offset of this lane's first element in the source
@@ -40,8 +40,8 @@ __global__ __launch_bounds__(256) void cast_row_kernel(const void *__restrict__ 
         if (flat) {
             off = e0 = u * EPL;
         } else {
-            const int64_t r = u / units_per_row, c0 = (u - r * units_per_row) * EPL;
-            off = r * ld + c0;
+            const int64_t r = u / units_per_row, c0 = (u - r * units_per_row) * EPL, i0 = r / rows;
+            off = i0 * stride0 + (r - i0 * rows) * ld + c0;
             e0 = r * cols + c0;
             n_valid = cols - c0 >= EPL ? EPL : cols - c0 > 0 ? (int)(cols - c0) : 0;
         }
@@ -82,9 +82,12 @@ __global__ __launch_bounds__(256) void cast_row_kernel(const void *__restrict__ 
 template <int SRC, int FMT, int RND>
 __global__ __launch_bounds__(256) void cast_col_simple_kernel(const void *__restrict__ src, int64_t rows, int64_t cols,
                                                               int64_t ld, uint8_t *__restrict__ elems,
-                                                              uint8_t *__restrict__ scales, uint64_t seed)
+                                                              uint8_t *__restrict__ scales, uint64_t seed, Batch batch)
 {
     constexpr int w = Fmt<FMT>::bits;
+    src = static_cast<const char *>(src) + blockIdx.z * batch.src * (SRC == DT_BF16 ? 2 : 4);
+    elems += blockIdx.z * batch.elems;
+    scales += blockIdx.z * batch.scales;
     const int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const int64_t rb = blockIdx.y;
     if (c >= cols) return;
@@ -145,66 +148,72 @@ __global__ __launch_bounds__(256) void cast_col_simple_kernel(const void *__rest
 // ---------------------------------------------------------------------------
 template <int SRC, int FMT, int RND>
 static hipError_t launch_row(const void *src, int64_t rows, int64_t cols, int64_t ld, uint8_t *elems, uint8_t *scales,
-                             uint64_t seed, hipStream_t st)
+                             uint64_t seed, hipStream_t st, const Batch &batch)
 {
     // FP6 needs at least 16 elements per lane to store whole dwords
     constexpr int EPL = (Fmt<FMT>::bits == 6) ? 16 : 8;
     const int64_t pcols = (cols + BLOCK - 1) / BLOCK * BLOCK;
-    const int64_t n_units = rows * pcols / EPL;
+    const int64_t n_units = batch.n * rows * pcols / EPL;
     int64_t nb = (n_units + 255) / 256;
     const int64_t cap = 256 * 32;   // enough work-groups to fill 256 CUs several times over
     if (nb > cap) nb = cap;
-    hipLaunchKernelGGL((cast_row_kernel<SRC, FMT, RND, EPL>), dim3((unsigned)nb), dim3(256), 0, st, src, cols, pcols, ld,
-                       elems, scales, n_units, seed);
+    hipLaunchKernelGGL((cast_row_kernel<SRC, FMT, RND, EPL>), dim3((unsigned)nb), dim3(256), 0, st, src, rows, cols, pcols, ld,
+                       batch.n > 1 ? batch.src : rows * ld, elems, scales, n_units, seed);
     return hipGetLastError();
 }
 
 template <int SRC, int FMT, int RND>
 static hipError_t launch_col(const void *src, int64_t rows, int64_t cols, int64_t ld, uint8_t *elems, uint8_t *scales,
-                             uint64_t seed, hipStream_t st)
+                             uint64_t seed, hipStream_t st, const Batch &batch)
 {
-    dim3 grid((unsigned)((cols + 255) / 256), (unsigned)((rows + BLOCK - 1) / BLOCK));
-    hipLaunchKernelGGL((cast_col_simple_kernel<SRC, FMT, RND>), grid, dim3(256), 0, st, src, rows, cols, ld, elems, scales,
-                       seed);
-    return hipGetLastError();
+    for (int64_t i = 0; i < batch.n; i += 65535) {
+        const dim3 grid((unsigned)((cols + 255) / 256), (unsigned)((rows + BLOCK - 1) / BLOCK),
+                        (unsigned)(batch.n - i < 65535 ? batch.n - i : 65535));
+        hipLaunchKernelGGL((cast_col_simple_kernel<SRC, FMT, RND>), grid, dim3(256), 0, st,
+                           static_cast<const char *>(src) + i * batch.src * (SRC == DT_BF16 ? 2 : 4), rows, cols, ld,
+                           elems + i * batch.elems, scales + i * batch.scales, seed, batch);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 template <int SRC, int FMT>
 static hipError_t dispatch_rnd(int rnd, uint64_t seed, int axis, const void *src, int64_t rows, int64_t cols, int64_t ld,
-                               uint8_t *elems, uint8_t *scales, hipStream_t st)
+                               uint8_t *elems, uint8_t *scales, hipStream_t st, const Batch &batch)
 {
     if (axis == 1) {
         switch (rnd) {
-            case ROUND_RNE:         return launch_row<SRC, FMT, ROUND_RNE>(src, rows, cols, ld, elems, scales, seed, st);
-            case ROUND_HALF_AWAY:   return launch_row<SRC, FMT, ROUND_HALF_AWAY>(src, rows, cols, ld, elems, scales, seed, st);
-            case ROUND_TOWARD_ZERO: return launch_row<SRC, FMT, ROUND_TOWARD_ZERO>(src, rows, cols, ld, elems, scales, seed, st);
-            default:                return launch_row<SRC, FMT, ROUND_STOCHASTIC>(src, rows, cols, ld, elems, scales, seed, st);
+            case ROUND_RNE:         return launch_row<SRC, FMT, ROUND_RNE>(src, rows, cols, ld, elems, scales, seed, st, batch);
+            case ROUND_HALF_AWAY:   return launch_row<SRC, FMT, ROUND_HALF_AWAY>(src, rows, cols, ld, elems, scales, seed, st, batch);
+            case ROUND_TOWARD_ZERO: return launch_row<SRC, FMT, ROUND_TOWARD_ZERO>(src, rows, cols, ld, elems, scales, seed, st, batch);
+            default:                return launch_row<SRC, FMT, ROUND_STOCHASTIC>(src, rows, cols, ld, elems, scales, seed, st, batch);
         }
     }
     switch (rnd) {
-        case ROUND_RNE:         return launch_col<SRC, FMT, ROUND_RNE>(src, rows, cols, ld, elems, scales, seed, st);
-        case ROUND_HALF_AWAY:   return launch_col<SRC, FMT, ROUND_HALF_AWAY>(src, rows, cols, ld, elems, scales, seed, st);
-        case ROUND_TOWARD_ZERO: return launch_col<SRC, FMT, ROUND_TOWARD_ZERO>(src, rows, cols, ld, elems, scales, seed, st);
-        default:                return launch_col<SRC, FMT, ROUND_STOCHASTIC>(src, rows, cols, ld, elems, scales, seed, st);
+        case ROUND_RNE:         return launch_col<SRC, FMT, ROUND_RNE>(src, rows, cols, ld, elems, scales, seed, st, batch);
+        case ROUND_HALF_AWAY:   return launch_col<SRC, FMT, ROUND_HALF_AWAY>(src, rows, cols, ld, elems, scales, seed, st, batch);
+        case ROUND_TOWARD_ZERO: return launch_col<SRC, FMT, ROUND_TOWARD_ZERO>(src, rows, cols, ld, elems, scales, seed, st, batch);
+        default:                return launch_col<SRC, FMT, ROUND_STOCHASTIC>(src, rows, cols, ld, elems, scales, seed, st, batch);
     }
 }
 
 template <int SRC>
 static hipError_t dispatch_fmt(int fmt, int rnd, uint64_t seed, int axis, const void *src, int64_t rows, int64_t cols,
-                               int64_t ld, uint8_t *elems, uint8_t *scales, hipStream_t st)
+                               int64_t ld, uint8_t *elems, uint8_t *scales, hipStream_t st, const Batch &batch)
 {
     switch (fmt) {
-        case FP8_E4M3: return dispatch_rnd<SRC, FP8_E4M3>(rnd, seed, axis, src, rows, cols, ld, elems, scales, st);
-        case FP8_E5M2: return dispatch_rnd<SRC, FP8_E5M2>(rnd, seed, axis, src, rows, cols, ld, elems, scales, st);
-        case FP6_E3M2: return dispatch_rnd<SRC, FP6_E3M2>(rnd, seed, axis, src, rows, cols, ld, elems, scales, st);
-        case FP6_E2M3: return dispatch_rnd<SRC, FP6_E2M3>(rnd, seed, axis, src, rows, cols, ld, elems, scales, st);
-        case FP4_E2M1: return dispatch_rnd<SRC, FP4_E2M1>(rnd, seed, axis, src, rows, cols, ld, elems, scales, st);
-        default:       return dispatch_rnd<SRC, INT8>(rnd, seed, axis, src, rows, cols, ld, elems, scales, st);
+        case FP8_E4M3: return dispatch_rnd<SRC, FP8_E4M3>(rnd, seed, axis, src, rows, cols, ld, elems, scales, st, batch);
+        case FP8_E5M2: return dispatch_rnd<SRC, FP8_E5M2>(rnd, seed, axis, src, rows, cols, ld, elems, scales, st, batch);
+        case FP6_E3M2: return dispatch_rnd<SRC, FP6_E3M2>(rnd, seed, axis, src, rows, cols, ld, elems, scales, st, batch);
+        case FP6_E2M3: return dispatch_rnd<SRC, FP6_E2M3>(rnd, seed, axis, src, rows, cols, ld, elems, scales, st, batch);
+        case FP4_E2M1: return dispatch_rnd<SRC, FP4_E2M1>(rnd, seed, axis, src, rows, cols, ld, elems, scales, st, batch);
+        default:       return dispatch_rnd<SRC, INT8>(rnd, seed, axis, src, rows, cols, ld, elems, scales, st, batch);
     }
 }
 
 hipError_t launch_cast(const void *src, int src_dt, int64_t rows, int64_t cols, int64_t ld, int axis, int fmt, int rnd,
-                       uint8_t *elems, uint8_t *scales, hipStream_t st, uint64_t seed)
+                       uint8_t *elems, uint8_t *scales, hipStream_t st, uint64_t seed, const Batch &batch)
 {
     // The fast kernels store scale bytes 4 and 16 at a time; a scale array that starts at an odd
     // address (a slice of a larger output, see launch_cast_3d) takes the generic kernels, which
@@ -212,16 +221,15 @@ hipError_t launch_cast(const void *src, int src_dt, int64_t rows, int64_t cols, 
     const bool scales_aligned = (reinterpret_cast<uintptr_t>(scales) & 15u) == 0;
     // the kernels built on the hardware converts round to nearest only
     if (scales_aligned && src_dt == DT_BF16 && (rnd == ROUND_RNE || rnd == ROUND_HALF_AWAY)) {
-        hipError_t e = launch_cast_bf16_fast(src, rows, cols, ld, axis, fmt, rnd, elems, scales, st);
+        hipError_t e = launch_cast_bf16_fast(src, rows, cols, ld, axis, fmt, rnd, elems, scales, st, batch);
         if (e != hipErrorNotSupported) return e;
     }
-    if (scales_aligned && src_dt == DT_F32) {
-        hipError_t e = axis == 0 ? launch_cast_col_f32_fast(src, rows, cols, ld, fmt, rnd, elems, scales, st)
-                                 : launch_cast_row_f32_fast(src, rows, cols, ld, fmt, rnd, elems, scales, st);
+    if (scales_aligned && src_dt == DT_F32 && (rnd == ROUND_RNE || rnd == ROUND_HALF_AWAY)) {
+        hipError_t e = launch_cast_f32_fast(src, rows, cols, ld, axis, fmt, rnd, elems, scales, st, batch);
         if (e != hipErrorNotSupported) return e;
     }
-    return src_dt == DT_BF16 ? dispatch_fmt<DT_BF16>(fmt, rnd, seed, axis, src, rows, cols, ld, elems, scales, st)
-                             : dispatch_fmt<DT_F32>(fmt, rnd, seed, axis, src, rows, cols, ld, elems, scales, st);
+    return src_dt == DT_BF16 ? dispatch_fmt<DT_BF16>(fmt, rnd, seed, axis, src, rows, cols, ld, elems, scales, st, batch)
+                             : dispatch_fmt<DT_F32>(fmt, rnd, seed, axis, src, rows, cols, ld, elems, scales, st, batch);
 }
 
 }  // namespace mx

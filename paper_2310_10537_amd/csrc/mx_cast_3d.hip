@@ -1,8 +1,7 @@
 // Algorithm 1 along any axis of a strided 3-D tensor (Section 3 of arXiv 2310.10537: the
 // "principal axis" of a multi-dimensional tensor), in two output layouts.
 //   block-major   the block axis is moved last (the 2-D cast of the permuted tensor): served by
-//                 the 2-D cast kernels, one launch per slice where the strides do not let one
-//                 launch cover everything;
+//                 the 2-D cast kernels, which take a batch of slices in one launch;
 //   source order  codes stay where their elements are, packed along the last axis, and the scale
 //                 array is the source shape with the block axis replaced by its block count:
 //                 cast_keep_kernel below (blocks along the last axis are the same in both layouts).
@@ -204,8 +203,6 @@ hipError_t launch_cast_3d(const void *src, int src_dt, int64_t d0, int64_t d1, i
                           int axis, int fmt, int rnd, bool keep_order, uint8_t *elems, uint8_t *scales, hipStream_t st)
 {
     const int w = fmt_bits(fmt);
-    const int esz = src_dt == DT_BF16 ? 2 : 4;
-    const char *s8 = static_cast<const char *>(src);
     const int64_t dim[3] = {d0, d1, d2};
     const int64_t nblk = (dim[axis] + BLOCK - 1) / BLOCK, line_bytes = nblk * BLOCK * w / 8;
     if (axis == 2 && keep_order && d2 % BLOCK) {     // the block-major layout would store the fill of the last block
@@ -214,14 +211,11 @@ hipError_t launch_cast_3d(const void *src, int src_dt, int64_t d0, int64_t d1, i
         return src_dt == DT_BF16 ? keep_last_fmt<DT_BF16>(fmt, rnd, (unsigned)nb, st, src, d1, d2, stride0, stride1, n_units, elems, scales)
                                  : keep_last_fmt<DT_F32>(fmt, rnd, (unsigned)nb, st, src, d1, d2, stride0, stride1, n_units, elems, scales);
     }
-    if (axis == 2) {        // whole blocks along the last axis: both layouts coincide
+    Batch b;
+    if (axis == 2) {        // whole blocks along the last axis: both layouts coincide; the outputs are dense
         if (stride0 == d1 * stride1) return launch_cast(src, src_dt, d0 * d1, d2, stride1, 1, fmt, rnd, elems, scales, st);
-        for (int64_t i = 0; i < d0; i++) {
-            const hipError_t e = launch_cast(s8 + i * stride0 * esz, src_dt, d1, d2, stride1, 1, fmt, rnd, elems + i * d1 * line_bytes,
-                                             scales + i * d1 * nblk, st);
-            if (e != hipSuccess) return e;
-        }
-        return hipSuccess;
+        b.n = d0; b.src = stride0;
+        return launch_cast(src, src_dt, d1, d2, stride1, 1, fmt, rnd, elems, scales, st, 0, b);
     }
     if (keep_order) {
         const int64_t row_bytes = d2 * w / 8;
@@ -230,22 +224,16 @@ hipError_t launch_cast_3d(const void *src, int src_dt, int64_t d0, int64_t d1, i
         // axis 0, per i1: blocks down the d0 "rows" (pitch stride0); output row (i0, i1); scales [nblk][d1][d2]
         return launch_keep(src, src_dt, d1, d0, d2, stride0, stride1, fmt, rnd, elems, d1 * row_bytes, row_bytes, scales, d1 * d2, d2, st);
     }
+    b.elems = d2 * line_bytes;
+    b.scales = d2 * nblk;
     if (axis == 1) {        // per i0 the axis-0 cast of the [d1][d2] slice: elems [d0][d2][line], scales [d0][d2][nblk]
-        for (int64_t i = 0; i < d0; i++) {
-            const hipError_t e = launch_cast(s8 + i * stride0 * esz, src_dt, d1, d2, stride1, 0, fmt, rnd, elems + i * d2 * line_bytes,
-                                             scales + i * d2 * nblk, st);
-            if (e != hipSuccess) return e;
-        }
-        return hipSuccess;
+        b.n = d0; b.src = stride0;
+        return launch_cast(src, src_dt, d1, d2, stride1, 0, fmt, rnd, elems, scales, st, 0, b);
     }
     // axis 0: elems [d1][d2][line]; with dense inner rows the tensor is the 2-D [d0][d1 * d2]
     if (stride1 == d2) return launch_cast(src, src_dt, d0, d1 * d2, stride0, 0, fmt, rnd, elems, scales, st);
-    for (int64_t i = 0; i < d1; i++) {
-        const hipError_t e = launch_cast(s8 + i * stride1 * esz, src_dt, d0, d2, stride0, 0, fmt, rnd, elems + i * d2 * line_bytes,
-                                         scales + i * d2 * nblk, st);
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+    b.n = d1; b.src = stride1;
+    return launch_cast(src, src_dt, d0, d2, stride0, 0, fmt, rnd, elems, scales, st, 0, b);
 }
 
 }  // namespace mx

@@ -38,17 +38,12 @@ __device__ __forceinline__ void wave_lds_sync()
 constexpr int ROW_CHUNKS = 4;                 // 16-byte loads in flight per lane (8 measured the same, 16 slower)
 constexpr int ROW_WAVE_ELEMS = 64 * 8 * ROW_CHUNKS;   // 2048 elements = 64 blocks per wave
 
-// element offset of linear element index e in a [rows][cols] tensor with pitch ld
-template <bool FLAT>
-__device__ __forceinline__ int64_t src_offset(int64_t e, int64_t cols, int64_t ld)
-{
-    if (FLAT) return e;
-    int64_t r = e / cols;
-    return r * ld + (e - r * cols);
-}
-
-template <int FMT, int RND, bool FLAT, bool WHOLE = false, int CH = ROW_CHUNKS>   // WHOLE: every wave's elements lie inside the tensor
-__global__ __launch_bounds__(256) void cast_row_bf16_kernel(const uint16_t *__restrict__ src, int64_t cols, int64_t ld,
+// FLAT: dense rows of whole blocks, one run of n_elems elements.  Otherwise the rows are those of `geom`
+// (padded pitch, a batch of matrices, a partial last block that is filled up with zeros) and n_elems counts
+// the fill: the outputs are one run in either form.  (5120 x 5000 -> E4M3: 14 us, 5.4 TB/s; the generic
+// kernel, which rows of partial blocks used to take, 28 us.)  WHOLE: every wave's elements lie inside the tensor.
+template <int FMT, int RND, bool FLAT, bool WHOLE = false, int CH = ROW_CHUNKS>
+__global__ __launch_bounds__(256) void cast_row_bf16_kernel(const uint16_t *__restrict__ src, RowGeom geom,
                                                             uint8_t *__restrict__ elems, uint8_t *__restrict__ scales,
                                                             int64_t n_elems)
 {
@@ -76,7 +71,20 @@ __global__ __launch_bounds__(256) void cast_row_bf16_kernel(const uint16_t *__re
         const int64_t e = e0 + u * 512 + lane * 8;
         valid[u] = WHOLE || e < n_elems;
         uint4 t = make_uint4(0, 0, 0, 0);
-        if (valid[u]) t = ld16_nt(src + src_offset<FLAT>(e, cols, ld));
+        if constexpr (FLAT) {
+            if (valid[u]) t = ld16_nt(src + e);
+        } else if (valid[u]) {
+            int n;
+            const uint16_t *g = src + geom.at((uint32_t)(e >> 3), 8, n);
+            if (n == 8) {
+                t = ld16_nt(g);
+            } else if (n > 0) {
+                uint32_t h[8];
+#pragma unroll
+                for (int i = 0; i < 8; i++) h[i] = i < n ? g[i] : 0u;
+                t = make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16));
+            }
+        }
         d[u][0] = t.x; d[u][1] = t.y; d[u][2] = t.z; d[u][3] = t.w;
     }
 
@@ -181,15 +189,21 @@ constexpr int COL_TILE_C = 64;    // columns of a tile of the Float32 kernel
 // 8192 x 8192 tensor: 128 x 64 tiles 38.6 us, 256 x 64 37.2, 128 x 128 35.9, 256 x 128 40.5,
 // 64 x 256 37.8; walking several adjacent strips abreast, which paid before the loads became
 // non-temporal, now costs 1-2 us.  The kernel runs within 5 % of its pattern.)
+// Row and column remainders take the form with bounds checks (5000 x 5120 -> E4M3 22 us, 3.5 TB/s; the
+// generic one-lane-per-block kernel, which partial blocks used to take, 43 us), and a batch of matrices
+// is one launch (128 matrices of 2048 x 128: a launch each cost 3.5 us apiece).
 template <int FMT, int RND, int TC, bool WHOLE>   // WHOLE: every tile lies inside the tensor (no bounds checks)
 __global__ __launch_bounds__(256) void cast_col_bf16_kernel(const uint16_t *__restrict__ src, int64_t rows, int64_t cols,
                                                             int64_t ld, uint8_t *__restrict__ elems,
                                                             uint8_t *__restrict__ scales, int64_t row_tiles,
-                                                            int64_t n_tiles, int64_t per_xcd)
+                                                            int64_t n_tiles, int64_t per_xcd, Batch batch)
 {
     if constexpr (FMT == FP8_E4M3 || FMT == FP8_E5M2) fp8_saturate_mode();
     constexpr int w = Fmt<FMT>::bits;
     constexpr int PITCH = TC * 2;                        // bytes per tile row in LDS
+    src += blockIdx.z * batch.src;                       // one launch for all matrices of a batch
+    elems += blockIdx.z * batch.elems;
+    scales += blockIdx.z * batch.scales;
     __shared__ __attribute__((aligned(16))) uint8_t tile[COL_TILE_R * PITCH];
     __shared__ __attribute__((aligned(16))) uint32_t xch[(w == 6 && WHOLE) ? 256 * 6 : 4];   // FP6 codes on their way out
     const int t = threadIdx.x;
@@ -229,7 +243,8 @@ __global__ __launch_bounds__(256) void cast_col_bf16_kernel(const uint16_t *__re
     __syncthreads();
 
     // ---- lane (column c, row block rb): 32 values down the column, packed in pairs
-    const int64_t n_rb = rows / BLOCK;
+    // (rows beyond the tensor were staged as zeros: the fill of a partial last block)
+    const int64_t n_rb = WHOLE ? rows / BLOCK : (rows + BLOCK - 1) / BLOCK;
     const bool quad = WHOLE || (n_rb & 3) == 0;          // scale dwords are aligned
 #pragma unroll
     for (int q = 0; q < TC / 64; q++) {
@@ -290,8 +305,8 @@ __global__ __launch_bounds__(256) void cast_col_bf16_kernel(const uint16_t *__re
 }
 
 // ---------------------------------------------------------------------------
-// Column cast of a Float32 source made of whole 128 x 64 tiles (weights are cast from Float32,
-// along the reduction axis of their GEMM, i.e. along dimension 0 of a [K][N] tensor).  Same plan
+// Column cast of a Float32 source (weights are cast from Float32, along the reduction axis of
+// their GEMM, i.e. along dimension 0 of a [K][N] tensor).  Same plan
 // as the bf16 kernel: coalesced row loads into an LDS tile (here 16 lanes x 16 bytes per 256-byte
 // row segment), then lane (column c, row block rb) walks 32 values down its column, and the four
 // lanes of a column write its four consecutive blocks.  Row block rb keeps its rows rotated by
@@ -299,14 +314,17 @@ __global__ __launch_bounds__(256) void cast_col_bf16_kernel(const uint16_t *__re
 // The one-lane-per-(block, column) kernel without LDS leaves every output line to eight
 // work-groups that run far apart in time: 3.3 TB/s on 8192 x 28672 -> E2M1.
 // ---------------------------------------------------------------------------
-template <int FMT, int RND>
+template <int FMT, int RND, bool WHOLE>   // WHOLE: every tile lies inside the tensor (no bounds checks)
 __global__ __launch_bounds__(256) void cast_col_f32_kernel(const float *__restrict__ src, int64_t rows, int64_t cols, int64_t ld,
                                                            uint8_t *__restrict__ elems, uint8_t *__restrict__ scales,
-                                                           int64_t row_tiles, int64_t n_tiles, int64_t per_xcd)
+                                                           int64_t row_tiles, int64_t n_tiles, int64_t per_xcd, Batch batch)
 {
     if constexpr (FMT == FP8_E4M3 || FMT == FP8_E5M2) fp8_saturate_mode();
     constexpr int w = Fmt<FMT>::bits;
     __shared__ __attribute__((aligned(16))) uint32_t tile[COL_TILE_R * COL_TILE_C];   // 32 KB, rows of 64 floats
+    src += blockIdx.z * batch.src;
+    elems += blockIdx.z * batch.elems;
+    scales += blockIdx.z * batch.scales;
     const int t = threadIdx.x;
     const int64_t tile_id = (int64_t)(blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
     if ((int64_t)(blockIdx.x >> 3) >= per_xcd || tile_id >= n_tiles) return;   // uniform over the work-group
@@ -314,9 +332,23 @@ __global__ __launch_bounds__(256) void cast_col_f32_kernel(const float *__restri
     const int64_t ct = tile_id / row_tiles, rt = tile_id % row_tiles;
     const int64_t c0 = ct * COL_TILE_C, r0 = rt * COL_TILE_R;
     const int lr = t >> 4, lc = t & 15;
+    const bool full_cols = WHOLE || c0 + COL_TILE_C <= cols;
     uint4 v[COL_TILE_R / 16];
 #pragma unroll
-    for (int p = 0; p < COL_TILE_R / 16; p++) v[p] = ld16_nt(src + (r0 + p * 16 + lr) * ld + c0 + lc * 4);
+    for (int p = 0; p < COL_TILE_R / 16; p++) {
+        v[p] = make_uint4(0, 0, 0, 0);                // rows beyond the tensor: the fill of a partial last block
+        if (WHOLE || r0 + p * 16 + lr < rows) {
+            const float *g = src + (r0 + p * 16 + lr) * ld + c0 + lc * 4;
+            if (full_cols || c0 + lc * 4 + 4 <= cols) {
+                v[p] = ld16_nt(g);
+            } else {
+                uint32_t h[4];
+#pragma unroll
+                for (int i = 0; i < 4; i++) h[i] = (c0 + lc * 4 + i < cols) ? __float_as_uint(g[i]) : 0u;
+                v[p] = make_uint4(h[0], h[1], h[2], h[3]);
+            }
+        }
+    }
 #pragma unroll
     for (int p = 0; p < COL_TILE_R / 16; p++) {
         const int r = p * 16 + lr;                    // row inside the tile; its 32-row block is r / 32
@@ -324,11 +356,12 @@ __global__ __launch_bounds__(256) void cast_col_f32_kernel(const float *__restri
     }
     __syncthreads();
     const int c = t >> 2, rb = t & 3;
-    const int64_t col = c0 + c, n_rb = rows / BLOCK, row_blk = r0 / BLOCK + rb;
+    const int64_t col = c0 + c, n_rb = WHOLE ? rows / BLOCK : (rows + BLOCK - 1) / BLOCK, row_blk = r0 / BLOCK + rb;
     uint32_t out[w];
     const uint32_t s = quantize_block_lds<FMT, RND>(tile + rb * 32 * COL_TILE_C + ((c + rb * 16) & 63), COL_TILE_C, out);
     const uint32_t s4 = s | ((uint32_t)__shfl_down((int)s, 1) << 8) | ((uint32_t)__shfl_down((int)s, 2) << 16) |
                         ((uint32_t)__shfl_down((int)s, 3) << 24);
+    if (!WHOLE && (col >= cols || row_blk >= n_rb)) return;
     uint8_t *o = elems + (col * n_rb + row_blk) * (BLOCK * w / 8);
     if constexpr (w == 8) {
         st16(o, make_uint4(out[0], out[1], out[2], out[3]));
@@ -340,43 +373,67 @@ __global__ __launch_bounds__(256) void cast_col_f32_kernel(const float *__restri
     } else {
         st16(o, make_uint4(out[0], out[1], out[2], out[3]));
     }
-    if (rb == 0) *reinterpret_cast<uint32_t *>(scales + col * n_rb + row_blk) = s4;   // n_rb is a multiple of 4: aligned
+    // four consecutive scale bytes leave as one dword when they exist and the address is aligned
+    if (WHOLE || ((n_rb & 3) == 0 && r0 / BLOCK + 4 <= n_rb)) {
+        if (rb == 0) *reinterpret_cast<uint32_t *>(scales + col * n_rb + row_blk) = s4;
+    } else {
+        scales[col * n_rb + row_blk] = (uint8_t)s;
+    }
 }
 
 // ---------------------------------------------------------------------------
 // Launchers.  Return hipErrorNotSupported when the fast path does not apply.
 // ---------------------------------------------------------------------------
-template <int FMT>
-static hipError_t launch_col_f32_r(int rnd, const float *src, int64_t rows, int64_t cols, int64_t ld, uint8_t *elems,
-                                   uint8_t *scales, hipStream_t st)
+// gridDim.z walks a batch, at most 65535 matrices per launch
+template <typename F>
+static hipError_t for_batch(const Batch &b, int src_bytes, const void *src, uint8_t *elems, uint8_t *scales, F go)
 {
-    const int64_t row_tiles = rows / COL_TILE_R, n_tiles = row_tiles * (cols / COL_TILE_C), per_xcd = (n_tiles + 7) / 8;
+    for (int64_t i = 0; i < b.n; i += 65535) {
+        go((unsigned)(b.n - i < 65535 ? b.n - i : 65535), static_cast<const char *>(src) + i * b.src * src_bytes, elems + i * b.elems,
+           scales + i * b.scales);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+template <int FMT, int RND>
+static hipError_t launch_col_f32_r(const void *src, int64_t rows, int64_t cols, int64_t ld, uint8_t *elems, uint8_t *scales,
+                                   hipStream_t st, const Batch &batch)
+{
+    const int64_t row_tiles = (rows + COL_TILE_R - 1) / COL_TILE_R, n_tiles = row_tiles * ((cols + COL_TILE_C - 1) / COL_TILE_C);
+    const int64_t per_xcd = (n_tiles + 7) / 8;
     if (per_xcd * 8 > 0x7FFFFFFF) return hipErrorNotSupported;
-    if (rnd == ROUND_RNE)
-        hipLaunchKernelGGL((cast_col_f32_kernel<FMT, ROUND_RNE>), dim3((unsigned)(per_xcd * 8)), dim3(256), 0, st, src, rows, cols,
-                           ld, elems, scales, row_tiles, n_tiles, per_xcd);
-    else
-        hipLaunchKernelGGL((cast_col_f32_kernel<FMT, ROUND_HALF_AWAY>), dim3((unsigned)(per_xcd * 8)), dim3(256), 0, st, src, rows,
-                           cols, ld, elems, scales, row_tiles, n_tiles, per_xcd);
-    return hipGetLastError();
+    const bool whole = rows % COL_TILE_R == 0 && cols % COL_TILE_C == 0;
+    return for_batch(batch, 4, src, elems, scales, [&](unsigned nz, const char *s, uint8_t *e, uint8_t *sc) {
+        const dim3 grid((unsigned)(per_xcd * 8), 1, nz);
+        const float *p = reinterpret_cast<const float *>(s);
+        if (whole)
+            hipLaunchKernelGGL((cast_col_f32_kernel<FMT, RND, true>), grid, dim3(256), 0, st, p, rows, cols, ld, e, sc, row_tiles, n_tiles,
+                               per_xcd, batch);
+        else
+            hipLaunchKernelGGL((cast_col_f32_kernel<FMT, RND, false>), grid, dim3(256), 0, st, p, rows, cols, ld, e, sc, row_tiles, n_tiles,
+                               per_xcd, batch);
+    });
 }
 
 // ---------------------------------------------------------------------------
-// Row cast of a dense Float32 tensor (blocks along the contiguous axis; configs that cast Float32
-// sources along rows: the round trip of a Float32 tensor, weights kept in Float32).  A wave takes
-// 2048 consecutive elements = 64 blocks as eight fully coalesced 16-byte-per-lane loads (all in flight
-// at once), parks them in a wave-private LDS region with a pitch of 36 dwords per block -- lane l then
-// owns block l and reads it back with 16-byte reads that are free of bank conflicts (36 l mod 64 takes
-// 16 different multiples of 4 over any 16 consecutive lanes) -- and quantizes it with the Float32
-// block quantizer of the column kernel and the GEMM epilogue (hardware converts; the exact encoder
-// for the rare blocks they cannot take).  No work-group barrier: waves are independent.
+// Row cast of a Float32 tensor (blocks along the contiguous axis; the round trip of a Float32 tensor,
+// weights kept in Float32).  A wave takes 2048 consecutive elements = 64 blocks as eight fully
+// coalesced 16-byte-per-lane loads (all in flight at once), parks them in a wave-private LDS region with
+// a pitch of 36 dwords per block -- lane l then owns block l and reads it back with 16-byte reads that are
+// free of bank conflicts (36 l mod 64 takes 16 different multiples of 4 over any 16 consecutive lanes) --
+// and quantizes it with the Float32 block quantizer of the column kernel and the GEMM epilogue (hardware
+// converts; the exact encoder for the rare blocks they cannot take).  No work-group barrier: waves are
+// independent.  WHOLE: dense rows of whole blocks and a whole number of 2048-element runs; otherwise the
+// rows are those of `geom` (see the bf16 kernel) and the last wave may have fewer than 64 blocks.
 // ---------------------------------------------------------------------------
 constexpr int RF_CHUNKS = 8;                       // 16-byte loads in flight per lane
 constexpr int RF_WAVE_ELEMS = 64 * 4 * RF_CHUNKS;  // 2048 elements = 64 blocks per wave
 constexpr int RF_PITCH = 36;                       // dwords per block in LDS
 
-template <int FMT, int RND>
-__global__ __launch_bounds__(256) void cast_row_f32_kernel(const float *__restrict__ src, uint8_t *__restrict__ elems,
+template <int FMT, int RND, bool WHOLE>
+__global__ __launch_bounds__(256) void cast_row_f32_kernel(const float *__restrict__ src, RowGeom geom, uint8_t *__restrict__ elems,
                                                            uint8_t *__restrict__ scales, int64_t n_waves)
 {
     if constexpr (FMT == FP8_E4M3 || FMT == FP8_E5M2) fp8_saturate_mode();
@@ -390,7 +447,26 @@ __global__ __launch_bounds__(256) void cast_row_f32_kernel(const float *__restri
 
     uint4 v[RF_CHUNKS];
 #pragma unroll
-    for (int u = 0; u < RF_CHUNKS; u++) v[u] = ld16_nt(src + e0 + u * 256 + lane * 4);
+    for (int u = 0; u < RF_CHUNKS; u++) {
+        const int64_t e = e0 + u * 256 + lane * 4;
+        if constexpr (WHOLE) {
+            v[u] = ld16_nt(src + e);
+        } else {
+            v[u] = make_uint4(0, 0, 0, 0);
+            if ((e >> 2) < (int64_t)geom.n_units) {
+                int n;
+                const float *g = src + geom.at((uint32_t)(e >> 2), 4, n);
+                if (n == 4) {
+                    v[u] = ld16_nt(g);
+                } else if (n > 0) {
+                    uint32_t h[4];
+#pragma unroll
+                    for (int i = 0; i < 4; i++) h[i] = i < n ? __float_as_uint(g[i]) : 0u;
+                    v[u] = make_uint4(h[0], h[1], h[2], h[3]);
+                }
+            }
+        }
+    }
 #pragma unroll
     for (int u = 0; u < RF_CHUNKS; u++) {
         const int f = u * 256 + lane * 4;              // element of the wave's run: block f / 32, position f % 32
@@ -399,6 +475,7 @@ __global__ __launch_bounds__(256) void cast_row_f32_kernel(const float *__restri
     wave_lds_sync();
     uint32_t out[w];
     const uint32_t s = quantize_block_lds<FMT, RND>(lds + lane * RF_PITCH, 1, out);
+    if (!WHOLE && blk0 + lane >= (int64_t)geom.n_units / (BLOCK / 4)) return;
     uint8_t *o = elems + (blk0 + lane) * (BLOCK * w / 8);
     if constexpr (w == 8) {
         st16(o, make_uint4(out[0], out[1], out[2], out[3]));
@@ -413,110 +490,125 @@ __global__ __launch_bounds__(256) void cast_row_f32_kernel(const float *__restri
     scales[blk0 + lane] = (uint8_t)s;                  // 64 consecutive bytes per wave
 }
 
+// A row kernel numbers its units in 31 bits: slices of a batch, then runs of rows, go to one launch each
+// (multiples of 16 lines, so that the scale bytes of a run stay 16-byte aligned).  go(batch, rows, src, lines
+// before it); hipErrorNotSupported where a single run of 16 rows is too long.
+template <typename F>
+static hipError_t for_rows(const Batch &b, int64_t rows, int64_t cols, int64_t ld, int epu, int src_bytes, const void *src, F go)
+{
+    const int64_t upr = (cols + BLOCK - 1) / BLOCK * (BLOCK / epu), most = 0x7FFFFFFF / upr;
+    const char *p = static_cast<const char *>(src);
+    if (b.n * rows <= most) return go(b.n, rows, p, (int64_t)0);
+    if (most < 16 || (b.n > 1 && rows % 16)) return hipErrorNotSupported;
+    for (int64_t i = 0; i < b.n; i++)
+        for (int64_t r = 0; r < rows; r += most & ~(int64_t)15) {
+            const int64_t n = rows - r < (most & ~(int64_t)15) ? rows - r : (most & ~(int64_t)15);
+            const hipError_t e = go((int64_t)1, n, p + (i * b.src + r * ld) * src_bytes, i * rows + r);
+            if (e != hipSuccess) return e;
+        }
+    return hipSuccess;
+}
+
+template <int FMT, int RND>
+static hipError_t launch_row_f32_r(const void *src, int64_t rows, int64_t cols, int64_t ld, uint8_t *elems, uint8_t *scales, hipStream_t st,
+                                   const Batch &batch)
+{
+    const int64_t nblk = (cols + BLOCK - 1) / BLOCK;
+    return for_rows(batch, rows, cols, ld, 4, 4, src, [&](int64_t nb, int64_t nr, const char *p, int64_t line0) {
+        const int64_t blocks = nb * nr * nblk, n_waves = (blocks + 63) / 64, wgs = (n_waves + 3) / 4;
+        const RowGeom geom = row_geom(nb, nr, cols, ld, nb > 1 ? batch.src : nr * ld, 4);
+        uint8_t *e = elems + line0 * nblk * (BLOCK * Fmt<FMT>::bits / 8), *sc = scales + line0 * nblk;
+        const float *s = reinterpret_cast<const float *>(p);
+        if (ld == cols && cols % BLOCK == 0 && (nb == 1 || batch.src == nr * ld) && blocks % 64 == 0)
+            hipLaunchKernelGGL((cast_row_f32_kernel<FMT, RND, true>), dim3((unsigned)wgs), dim3(256), 0, st, s, geom, e, sc, n_waves);
+        else
+            hipLaunchKernelGGL((cast_row_f32_kernel<FMT, RND, false>), dim3((unsigned)wgs), dim3(256), 0, st, s, geom, e, sc, n_waves);
+        return hipGetLastError();
+    });
+}
+
 template <int FMT>
-static hipError_t launch_row_f32_r(int rnd, const float *src, int64_t n, uint8_t *elems, uint8_t *scales, hipStream_t st)
+static hipError_t launch_f32_fmt(int rnd, const void *src, int64_t rows, int64_t cols, int64_t ld, int axis, uint8_t *elems,
+                                 uint8_t *scales, hipStream_t st, const Batch &batch)
 {
-    const int64_t n_waves = n / RF_WAVE_ELEMS, nb = (n_waves + 3) / 4;
-    if (nb > 0x7FFFFFFF) return hipErrorNotSupported;
-    if (rnd == ROUND_RNE)
-        hipLaunchKernelGGL((cast_row_f32_kernel<FMT, ROUND_RNE>), dim3((unsigned)nb), dim3(256), 0, st, src, elems, scales, n_waves);
-    else
-        hipLaunchKernelGGL((cast_row_f32_kernel<FMT, ROUND_HALF_AWAY>), dim3((unsigned)nb), dim3(256), 0, st, src, elems, scales, n_waves);
-    return hipGetLastError();
+    if (axis == 0)
+        return rnd == ROUND_RNE ? launch_col_f32_r<FMT, ROUND_RNE>(src, rows, cols, ld, elems, scales, st, batch)
+                                : launch_col_f32_r<FMT, ROUND_HALF_AWAY>(src, rows, cols, ld, elems, scales, st, batch);
+    return rnd == ROUND_RNE ? launch_row_f32_r<FMT, ROUND_RNE>(src, rows, cols, ld, elems, scales, st, batch)
+                            : launch_row_f32_r<FMT, ROUND_HALF_AWAY>(src, rows, cols, ld, elems, scales, st, batch);
 }
 
-// Float32 source, blocks along the last axis, dense rows of whole blocks and a whole number of
-// 2048-element runs, round to nearest; hipErrorNotSupported otherwise
-hipError_t launch_cast_row_f32_fast(const void *src, int64_t rows, int64_t cols, int64_t ld, int fmt, int rnd, uint8_t *elems,
-                                    uint8_t *scales, hipStream_t st)
+hipError_t launch_cast_f32_fast(const void *src, int64_t rows, int64_t cols, int64_t ld, int axis, int fmt, int rnd,
+                                uint8_t *elems, uint8_t *scales, hipStream_t st, const Batch &batch)
 {
-    const int64_t n = rows * cols;
-    if (ld != cols || cols % BLOCK || n == 0 || n % RF_WAVE_ELEMS || (rnd != ROUND_RNE && rnd != ROUND_HALF_AWAY))
-        return hipErrorNotSupported;
-    const float *p = static_cast<const float *>(src);
     switch (fmt) {
-        case FP8_E4M3: return launch_row_f32_r<FP8_E4M3>(rnd, p, n, elems, scales, st);
-        case FP8_E5M2: return launch_row_f32_r<FP8_E5M2>(rnd, p, n, elems, scales, st);
-        case FP6_E3M2: return launch_row_f32_r<FP6_E3M2>(rnd, p, n, elems, scales, st);
-        case FP6_E2M3: return launch_row_f32_r<FP6_E2M3>(rnd, p, n, elems, scales, st);
-        case FP4_E2M1: return launch_row_f32_r<FP4_E2M1>(rnd, p, n, elems, scales, st);
-        default:       return launch_row_f32_r<INT8>(rnd, p, n, elems, scales, st);
-    }
-}
-
-// Float32 source, blocks along dimension 0, whole 128 x 64 tiles, round to nearest
-hipError_t launch_cast_col_f32_fast(const void *src, int64_t rows, int64_t cols, int64_t ld, int fmt, int rnd, uint8_t *elems,
-                                    uint8_t *scales, hipStream_t st)
-{
-    if (rows % COL_TILE_R || cols % COL_TILE_C || rows == 0 || cols == 0 || (rnd != ROUND_RNE && rnd != ROUND_HALF_AWAY))
-        return hipErrorNotSupported;
-    const float *p = static_cast<const float *>(src);
-    switch (fmt) {
-        case FP8_E4M3: return launch_col_f32_r<FP8_E4M3>(rnd, p, rows, cols, ld, elems, scales, st);
-        case FP8_E5M2: return launch_col_f32_r<FP8_E5M2>(rnd, p, rows, cols, ld, elems, scales, st);
-        case FP6_E3M2: return launch_col_f32_r<FP6_E3M2>(rnd, p, rows, cols, ld, elems, scales, st);
-        case FP6_E2M3: return launch_col_f32_r<FP6_E2M3>(rnd, p, rows, cols, ld, elems, scales, st);
-        case FP4_E2M1: return launch_col_f32_r<FP4_E2M1>(rnd, p, rows, cols, ld, elems, scales, st);
-        default:       return launch_col_f32_r<INT8>(rnd, p, rows, cols, ld, elems, scales, st);
+        case FP8_E4M3: return launch_f32_fmt<FP8_E4M3>(rnd, src, rows, cols, ld, axis, elems, scales, st, batch);
+        case FP8_E5M2: return launch_f32_fmt<FP8_E5M2>(rnd, src, rows, cols, ld, axis, elems, scales, st, batch);
+        case FP6_E3M2: return launch_f32_fmt<FP6_E3M2>(rnd, src, rows, cols, ld, axis, elems, scales, st, batch);
+        case FP6_E2M3: return launch_f32_fmt<FP6_E2M3>(rnd, src, rows, cols, ld, axis, elems, scales, st, batch);
+        case FP4_E2M1: return launch_f32_fmt<FP4_E2M1>(rnd, src, rows, cols, ld, axis, elems, scales, st, batch);
+        default:       return launch_f32_fmt<INT8>(rnd, src, rows, cols, ld, axis, elems, scales, st, batch);
     }
 }
 
 template <int FMT, int RND>
 static hipError_t launch_fast_t(const void *src, int64_t rows, int64_t cols, int64_t ld, int axis, uint8_t *elems,
-                                uint8_t *scales, hipStream_t st)
+                                uint8_t *scales, hipStream_t st, const Batch &batch)
 {
-    const uint16_t *s16 = static_cast<const uint16_t *>(src);
     if (axis == 1) {
-        const int64_t n = rows * cols;
-        const int64_t waves = (n + ROW_WAVE_ELEMS - 1) / ROW_WAVE_ELEMS;
-        const int64_t nb = (waves + 3) / 4;
-        if (nb > 0x7FFFFFFF) return hipErrorNotSupported;
-        if (ld == cols && n % (4 * ROW_WAVE_ELEMS) == 0)
-            hipLaunchKernelGGL((cast_row_bf16_kernel<FMT, RND, true, true>), dim3((unsigned)nb), dim3(256), 0, st, s16, cols, ld,
-                               elems, scales, n);
-        else if (ld == cols)
-            hipLaunchKernelGGL((cast_row_bf16_kernel<FMT, RND, true>), dim3((unsigned)nb), dim3(256), 0, st, s16, cols, ld,
-                               elems, scales, n);
-        else
-            hipLaunchKernelGGL((cast_row_bf16_kernel<FMT, RND, false>), dim3((unsigned)nb), dim3(256), 0, st, s16, cols, ld,
-                               elems, scales, n);
-        return hipGetLastError();
+        const int64_t pcols = (cols + BLOCK - 1) / BLOCK * BLOCK;
+        return for_rows(batch, rows, cols, ld, 8, 2, src, [&](int64_t nb, int64_t nr, const char *q, int64_t line0) {
+            const int64_t n = nb * nr * pcols, wgs = (n + 4 * ROW_WAVE_ELEMS - 1) / (4 * ROW_WAVE_ELEMS);
+            const RowGeom geom = row_geom(nb, nr, cols, ld, nb > 1 ? batch.src : nr * ld, 8);
+            uint8_t *e = elems + line0 * (pcols * Fmt<FMT>::bits / 8), *sc = scales + line0 * (pcols / BLOCK);
+            const uint16_t *p = reinterpret_cast<const uint16_t *>(q);
+            const bool flat = ld == cols && pcols == cols && (nb == 1 || batch.src == nr * ld);
+            if (flat && n % (4 * ROW_WAVE_ELEMS) == 0)
+                hipLaunchKernelGGL((cast_row_bf16_kernel<FMT, RND, true, true>), dim3((unsigned)wgs), dim3(256), 0, st, p, geom, e, sc, n);
+            else if (flat)
+                hipLaunchKernelGGL((cast_row_bf16_kernel<FMT, RND, true>), dim3((unsigned)wgs), dim3(256), 0, st, p, geom, e, sc, n);
+            else
+                hipLaunchKernelGGL((cast_row_bf16_kernel<FMT, RND, false>), dim3((unsigned)wgs), dim3(256), 0, st, p, geom, e, sc, n);
+            return hipGetLastError();
+        });
     }
     const int64_t row_tiles = (rows + COL_TILE_R - 1) / COL_TILE_R;
     // 128-column tiles once they still give every compute unit several work-groups
-    const bool wide = row_tiles * ((cols + 127) / 128) >= 1024;
+    const bool wide = row_tiles * ((cols + 127) / 128) * batch.n >= 1024;
     const int64_t n_tiles = row_tiles * (wide ? (cols + 127) / 128 : (cols + 63) / 64);
     const int64_t per_xcd = (n_tiles + 7) / 8;
     if (per_xcd * 8 > 0x7FFFFFFF) return hipErrorNotSupported;
     const bool whole = rows % COL_TILE_R == 0 && cols % (wide ? 128 : 64) == 0;
 #define MX_COL_GO(TC_, WHOLE_)                                                                                               \
-    hipLaunchKernelGGL((cast_col_bf16_kernel<FMT, RND, TC_, WHOLE_>), dim3((unsigned)(per_xcd * 8)), dim3(256), 0, st, s16, rows, cols, \
-                       ld, elems, scales, row_tiles, n_tiles, per_xcd)
-    if (wide) { if (whole) MX_COL_GO(128, true); else MX_COL_GO(128, false); }
-    else      { if (whole) MX_COL_GO(64, true); else MX_COL_GO(64, false); }
+    hipLaunchKernelGGL((cast_col_bf16_kernel<FMT, RND, TC_, WHOLE_>), grid, dim3(256), 0, st, p, rows, cols, ld, e, sc, row_tiles, n_tiles, \
+                       per_xcd, batch)
+    return for_batch(batch, 2, src, elems, scales, [&](unsigned nz, const char *s, uint8_t *e, uint8_t *sc) {
+        const dim3 grid((unsigned)(per_xcd * 8), 1, nz);
+        const uint16_t *p = reinterpret_cast<const uint16_t *>(s);
+        if (wide) { if (whole) MX_COL_GO(128, true); else MX_COL_GO(128, false); }
+        else      { if (whole) MX_COL_GO(64, true); else MX_COL_GO(64, false); }
+    });
 #undef MX_COL_GO
-    return hipGetLastError();
 }
 
 template <int FMT>
 static hipError_t launch_fast_r(int rnd, const void *src, int64_t rows, int64_t cols, int64_t ld, int axis, uint8_t *elems,
-                                uint8_t *scales, hipStream_t st)
+                                uint8_t *scales, hipStream_t st, const Batch &batch)
 {
-    return rnd == ROUND_RNE ? launch_fast_t<FMT, ROUND_RNE>(src, rows, cols, ld, axis, elems, scales, st)
-                            : launch_fast_t<FMT, ROUND_HALF_AWAY>(src, rows, cols, ld, axis, elems, scales, st);
+    return rnd == ROUND_RNE ? launch_fast_t<FMT, ROUND_RNE>(src, rows, cols, ld, axis, elems, scales, st, batch)
+                            : launch_fast_t<FMT, ROUND_HALF_AWAY>(src, rows, cols, ld, axis, elems, scales, st, batch);
 }
 
 hipError_t launch_cast_bf16_fast(const void *src, int64_t rows, int64_t cols, int64_t ld, int axis, int fmt, int rnd,
-                                 uint8_t *elems, uint8_t *scales, hipStream_t st)
+                                 uint8_t *elems, uint8_t *scales, hipStream_t st, const Batch &batch)
 {
-    if ((axis == 1 ? cols : rows) % BLOCK) return hipErrorNotSupported;   // whole blocks only
     switch (fmt) {
-        case FP8_E4M3: return launch_fast_r<FP8_E4M3>(rnd, src, rows, cols, ld, axis, elems, scales, st);
-        case FP8_E5M2: return launch_fast_r<FP8_E5M2>(rnd, src, rows, cols, ld, axis, elems, scales, st);
-        case FP6_E3M2: return launch_fast_r<FP6_E3M2>(rnd, src, rows, cols, ld, axis, elems, scales, st);
-        case FP6_E2M3: return launch_fast_r<FP6_E2M3>(rnd, src, rows, cols, ld, axis, elems, scales, st);
-        case FP4_E2M1: return launch_fast_r<FP4_E2M1>(rnd, src, rows, cols, ld, axis, elems, scales, st);
-        default:       return launch_fast_r<INT8>(rnd, src, rows, cols, ld, axis, elems, scales, st);
+        case FP8_E4M3: return launch_fast_r<FP8_E4M3>(rnd, src, rows, cols, ld, axis, elems, scales, st, batch);
+        case FP8_E5M2: return launch_fast_r<FP8_E5M2>(rnd, src, rows, cols, ld, axis, elems, scales, st, batch);
+        case FP6_E3M2: return launch_fast_r<FP6_E3M2>(rnd, src, rows, cols, ld, axis, elems, scales, st, batch);
+        case FP6_E2M3: return launch_fast_r<FP6_E2M3>(rnd, src, rows, cols, ld, axis, elems, scales, st, batch);
+        case FP4_E2M1: return launch_fast_r<FP4_E2M1>(rnd, src, rows, cols, ld, axis, elems, scales, st, batch);
+        default:       return launch_fast_r<INT8>(rnd, src, rows, cols, ld, axis, elems, scales, st, batch);
     }
 }
 

@@ -76,76 +76,6 @@ __device__ __forceinline__ void decode8_hw(const uint8_t *p, uint32_t s, float (
     }
 }
 
-// TR = false: dst[o][l .. l+7] contiguous (blocks along the last axis).
-// TR = true : the MX tensor is the cast of the transpose; value (o, l) goes to dst[l][o].
-// len is the block-axis length of the result; the MX tensor stores whole blocks (plen = len
-// rounded up to 32 positions per line) and the positions at or beyond len are not written.
-template <int FMT, int DST, bool TR>
-__global__ __launch_bounds__(256) void dequant_kernel(const uint8_t *__restrict__ elems,
-                                                      const uint8_t *__restrict__ scales, void *__restrict__ dst,
-                                                      int64_t n_out, int64_t len, int64_t plen, int64_t ld)
-{
-    constexpr int w = Fmt<FMT>::bits;
-    // (Float32 rows leave as two 16-byte stores per lane.  Letting two lanes share a unit, so that
-    // each store instruction writes 1 KB without gaps, measured slower -- 107 against 94 us on 8192 x
-    // 8192: a result that is four times the input runs at about 3.6 TB/s either way.)
-    const int64_t units_per_row = plen / 8;
-    const int64_t n_units = n_out * units_per_row;
-    const int64_t stride = (int64_t)gridDim.x * 256;
-    for (int64_t u = (int64_t)blockIdx.x * 256 + threadIdx.x; u < n_units; u += stride) {
-        int64_t o, l;
-        if (TR) {   // adjacent lanes take adjacent o so that the strided stores coalesce across the wave
-            l = (u / n_out) * 8;
-            o = u % n_out;
-        } else {
-            o = u / units_per_row;
-            l = (u % units_per_row) * 8;
-        }
-        if (l >= len) continue;   // fill positions of a partial last block
-        const int64_t unit_in_tensor = o * units_per_row + l / 8;
-        const uint32_t s = scales[unit_in_tensor / 4];
-        float f[8];
-        constexpr bool HW = FMT != INT8;
-        if (HW && s != SCALE_NAN) {
-            decode8_hw<FMT>(elems + unit_in_tensor * w, s, f);
-        } else {
-            uint32_t c[8];
-            load_codes8<FMT>(elems + unit_in_tensor * w, c);
-#pragma unroll
-            for (int i = 0; i < 8; i++) f[i] = decode_scaled<FMT>(c[i], s);
-        }
-        if (!TR && l + 8 > len) {
-#pragma unroll
-            for (int i = 0; i < 8; i++) {
-                if (l + i >= len) break;
-                if (DST == DT_F32) reinterpret_cast<float *>(dst)[o * ld + l + i] = f[i];
-                else reinterpret_cast<uint16_t *>(dst)[o * ld + l + i] = (uint16_t)f32_to_bf16_bits(f[i]);
-            }
-        } else if (!TR) {
-            if (DST == DT_F32) {
-                float *d = reinterpret_cast<float *>(dst) + o * ld + l;
-                *reinterpret_cast<float4 *>(d) = make_float4(f[0], f[1], f[2], f[3]);
-                *reinterpret_cast<float4 *>(d + 4) = make_float4(f[4], f[5], f[6], f[7]);
-            } else {
-                uint32_t h[4];   // hardware packed convert: round to nearest even, NaN stays NaN
-#pragma unroll
-                for (int i = 0; i < 4; i++) {
-                    const f32x2_t pr = {f[2 * i], f[2 * i + 1]};
-                    h[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pr, bf16x2_t_));
-                }
-                st16(reinterpret_cast<uint16_t *>(dst) + o * ld + l, make_uint4(h[0], h[1], h[2], h[3]));
-            }
-        } else {
-#pragma unroll
-            for (int i = 0; i < 8; i++) {
-                if (l + i >= len) break;
-                if (DST == DT_F32) reinterpret_cast<float *>(dst)[(l + i) * ld + o] = f[i];
-                else reinterpret_cast<uint16_t *>(dst)[(l + i) * ld + o] = (uint16_t)f32_to_bf16_bits(f[i]);
-            }
-        }
-    }
-}
-
 // 8 codes already in registers (lo: the first 32 bits of the w-byte unit, hi: the rest) times X
 template <int FMT>
 __device__ __forceinline__ void decode8_regs(uint32_t lo, uint32_t hi, uint32_t s, float (&f)[8])
@@ -187,14 +117,46 @@ __device__ __forceinline__ void decode8_regs(uint32_t lo, uint32_t hi, uint32_t 
     }
 }
 
-// Blocks along the last axis of a dense result (ld == len, whole blocks): the tensor is one run of
-// 8-code units, unit u -> dst[8u .. 8u+7], no row arithmetic.  A thread takes U units 256 apart and
-// requests all of them (streaming loads) before it converts the first, so that a wave has U loads in
-// flight; adjacent lanes write adjacent 16 (bf16) or 32 (Float32) bytes.
+template <int DST>
+__device__ __forceinline__ void store8(void *dst, int64_t at, const float (&f)[8], int n = 8)
+{
+    uint32_t h[4];   // hardware packed convert: round to nearest even, NaN stays NaN
+#pragma unroll
+    for (int k = 0; k < 4; k++) {
+        const f32x2_t pr = {f[2 * k], f[2 * k + 1]};
+        h[k] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pr, bf16x2_t_));
+    }
+    if (DST == DT_F32) {
+        float *d = reinterpret_cast<float *>(dst) + at;
+        if (n == 8) {
+            *reinterpret_cast<float4 *>(d) = make_float4(f[0], f[1], f[2], f[3]);
+            *reinterpret_cast<float4 *>(d + 4) = make_float4(f[4], f[5], f[6], f[7]);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 8; i++)
+                if (i < n) d[i] = f[i];
+        }
+    } else {
+        uint16_t *d = reinterpret_cast<uint16_t *>(dst) + at;
+        if (n == 8) {
+            st16(d, make_uint4(h[0], h[1], h[2], h[3]));
+        } else {
+#pragma unroll
+            for (int i = 0; i < 8; i++)
+                if (i < n) d[i] = (uint16_t)(h[i >> 1] >> (16 * (i & 1)));
+        }
+    }
+}
+
+// Blocks along the last axis: the tensor is one run of 8-code units (the fill of partial last blocks
+// included).  FLAT, a dense result of whole blocks: unit u -> dst[8u .. 8u+7], no row arithmetic.
+// Otherwise the rows of the result are those of `geom` and the fill is skipped.  A thread takes U
+// units 256 apart and requests all of them (streaming loads) before it converts the first, so that a
+// wave has U loads in flight; adjacent lanes write adjacent 16 (bf16) or 32 (Float32) bytes.
 constexpr int DQ_U = 4;
-template <int FMT, int DST>
-__global__ __launch_bounds__(256) void dequant_flat_kernel(const uint8_t *__restrict__ elems, const uint8_t *__restrict__ scales,
-                                                           void *__restrict__ dst, int64_t n_units)
+template <int FMT, int DST, bool FLAT>
+__global__ __launch_bounds__(256) void dequant_row_kernel(const uint8_t *__restrict__ elems, const uint8_t *__restrict__ scales,
+                                                          void *__restrict__ dst, int64_t n_units, RowGeom geom)
 {
     constexpr int w = Fmt<FMT>::bits;
     const int64_t base = (int64_t)blockIdx.x * (256 * DQ_U) + threadIdx.x;
@@ -217,18 +179,12 @@ __global__ __launch_bounds__(256) void dequant_flat_kernel(const uint8_t *__rest
         if (u >= n_units) continue;
         float f[8];
         decode8_regs<FMT>(lo[i], hi[i], s[i], f);
-        if (DST == DT_F32) {
-            float *d = reinterpret_cast<float *>(dst) + u * 8;
-            *reinterpret_cast<float4 *>(d) = make_float4(f[0], f[1], f[2], f[3]);
-            *reinterpret_cast<float4 *>(d + 4) = make_float4(f[4], f[5], f[6], f[7]);
+        if (FLAT) {
+            store8<DST>(dst, u * 8, f);
         } else {
-            uint32_t h[4];   // hardware packed convert: round to nearest even, NaN stays NaN
-#pragma unroll
-            for (int k = 0; k < 4; k++) {
-                const f32x2_t pr = {f[2 * k], f[2 * k + 1]};
-                h[k] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pr, bf16x2_t_));
-            }
-            st16(reinterpret_cast<uint16_t *>(dst) + u * 8, make_uint4(h[0], h[1], h[2], h[3]));
+            int n;
+            const int64_t at = geom.at((uint32_t)u, 8, n);
+            if (n > 0) store8<DST>(dst, at, f, n);
         }
     }
 }
@@ -273,132 +229,156 @@ __global__ __launch_bounds__(256) void dequant_flat4_kernel(const uint8_t *__res
     }
 }
 
-// Axis 0 through LDS: the MX tensor is the cast of the transpose ([n_out][len] with the block axis
-// contiguous), the result is row-major [len][n_out].  A work-group takes 64 lines x 128 positions:
-// 16 lanes read one line's 128 codes side by side (coalesced), every lane decodes 8 of them, the
-// values go transposed into a [128][64] Float32 tile (pitch 65: reads below are conflict-free,
-// writes two-way), and the tile leaves row by row with 16-byte stores, adjacent lanes writing
-// adjacent 16 bytes, so that every store instruction fills whole 128-byte lines (a lane that owns
-// a longer run and stores it 16 bytes at a time leaves every line to several instructions, which
-// measured 60 instead of 40 us).  (One lane per 8 codes with strided 2-byte stores, the generic
-// kernel above, reads 8 bytes per lane from 64 different lines.)
+// Axis 0 through LDS: the MX tensor is the cast of the transpose ([n_out][plen] with the block axis
+// contiguous, plen = len rounded up to whole blocks), the result is row-major [len][n_out].  A work-group
+// takes 64 lines x 128 positions: 16 lanes read one line's 128 codes side by side (coalesced), every
+// lane decodes 8 of them, the values go transposed into a [128][64] Float32 tile (pitch 65: reads below
+// are conflict-free, writes two-way), and the tile leaves row by row with 16-byte stores, adjacent lanes
+// writing adjacent 16 bytes, so that every store instruction fills whole 128-byte lines (a lane that
+// owns a longer run and stores it 16 bytes at a time leaves every line to several instructions, which
+// measured 60 instead of 40 us).  Whole tiles take the form without bounds checks; blockIdx.z walks a
+// batch of tensors (128 tensors of 2048 x 128 bf16 <-> E4M3: cast and dequantize took 949 us with a launch
+// per tensor, 42 us with one each, 4.0 TB/s).  Remainders used to take a kernel with one lane per 8 codes
+// and 2-byte stores a result row apart.
 constexpr int DQT_O = 64, DQT_L = 128, DQT_PITCH = 65;
-template <int FMT, int DST>
+template <int FMT, int DST, bool WHOLE>
 __global__ __launch_bounds__(256) void dequant_tr_tile_kernel(const uint8_t *__restrict__ elems,
                                                               const uint8_t *__restrict__ scales, void *__restrict__ dst,
-                                                              int64_t n_out, int64_t len, int64_t ld)
+                                                              int64_t n_out, int64_t len, int64_t ld, Batch batch)
 {
     constexpr int w = Fmt<FMT>::bits;
     __shared__ float tile[DQT_L * DQT_PITCH];
+    elems += blockIdx.z * batch.elems;
+    scales += blockIdx.z * batch.scales;
+    dst = static_cast<char *>(dst) + blockIdx.z * batch.src * (DST == DT_F32 ? 4 : 2);
     const int t = threadIdx.x;
-    const int64_t tiles_o = n_out / DQT_O;
+    const int64_t tiles_o = (n_out + DQT_O - 1) / DQT_O;
     const int64_t O0 = (int64_t)(blockIdx.x % tiles_o) * DQT_O, L0 = (int64_t)(blockIdx.x / tiles_o) * DQT_L;
-    const int64_t units_per_row = len / 8;
+    const int64_t units_per_row = (len + BLOCK - 1) / BLOCK * (BLOCK / 8);
 #pragma unroll
     for (int p = 0; p < 4; p++) {
         const int o = 16 * p + (t >> 4), u = t & 15;
-        const int64_t unit = (O0 + o) * units_per_row + L0 / 8 + u;
-        const uint32_t s = scales[unit / 4];
         float f[8];
-        if (FMT != INT8 && s != SCALE_NAN) {
-            decode8_hw<FMT>(elems + unit * w, s, f);
-        } else {
-            uint32_t c[8];
-            load_codes8<FMT>(elems + unit * w, c);
+        if (WHOLE || (O0 + o < n_out && L0 / 8 + u < units_per_row)) {
+            const int64_t unit = (O0 + o) * units_per_row + L0 / 8 + u;
+            const uint32_t s = scales[unit / 4];
+            if (FMT != INT8 && s != SCALE_NAN) {
+                decode8_hw<FMT>(elems + unit * w, s, f);
+            } else {
+                uint32_t c[8];
+                load_codes8<FMT>(elems + unit * w, c);
 #pragma unroll
-            for (int i = 0; i < 8; i++) f[i] = decode_scaled<FMT>(c[i], s);
+                for (int i = 0; i < 8; i++) f[i] = decode_scaled<FMT>(c[i], s);
+            }
+#pragma unroll
+            for (int i = 0; i < 8; i++) tile[(8 * u + i) * DQT_PITCH + o] = f[i];
         }
-#pragma unroll
-        for (int i = 0; i < 8; i++) tile[(8 * u + i) * DQT_PITCH + o] = f[i];
     }
     __syncthreads();
-    if (DST == DT_F32) {
-        // a result row of the tile is 256 bytes = 16 lanes x 16 bytes; 16 rows per pass
+    // a result row of the tile is 64 values = 16 lanes x 16 bytes (Float32, 16 rows per pass) or 8 lanes
+    // (bf16, 32 rows per pass)
+    constexpr int PER = DST == DT_F32 ? 4 : 8, LPR = DQT_O / PER, RPP = 256 / LPR;
+    const int q = t % LPR;
+    const int64_t left = WHOLE ? PER : n_out - O0 - PER * q;
+    const int n = left >= PER ? PER : left > 0 ? (int)left : 0;
 #pragma unroll
-        for (int p = 0; p < DQT_L / 16; p++) {
-            const int row = 16 * p + (t >> 4), q = t & 15;
-            const float *src = tile + row * DQT_PITCH + 4 * q;
-            *reinterpret_cast<float4 *>(reinterpret_cast<float *>(dst) + (L0 + row) * ld + O0 + 4 * q) =
-                make_float4(src[0], src[1], src[2], src[3]);
-        }
-    } else {
-        // 128 bytes = 8 lanes x 16 bytes; 32 rows per pass
-#pragma unroll
-        for (int p = 0; p < DQT_L / 32; p++) {
-            const int row = 32 * p + (t >> 3), q = t & 7;
-            const float *src = tile + row * DQT_PITCH + 8 * q;
-            uint32_t h[4];
-#pragma unroll
-            for (int j = 0; j < 4; j++) {
-                const f32x2_t pr = {src[2 * j], src[2 * j + 1]};
-                h[j] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pr, bf16x2_t_));
+    for (int p = 0; p < DQT_L / RPP; p++) {
+        const int row = RPP * p + t / LPR;
+        if (!WHOLE && L0 + row >= len) break;
+        const float *src = tile + row * DQT_PITCH + PER * q;
+        const int64_t at = (L0 + row) * ld + O0 + PER * q;
+        if constexpr (DST == DT_F32) {
+            float *d = reinterpret_cast<float *>(dst) + at;
+            if (WHOLE || n == 4) {
+                *reinterpret_cast<float4 *>(d) = make_float4(src[0], src[1], src[2], src[3]);
+            } else {
+                for (int i = 0; i < n; i++) d[i] = src[i];
             }
-            st16(reinterpret_cast<uint16_t *>(dst) + (L0 + row) * ld + O0 + 8 * q, make_uint4(h[0], h[1], h[2], h[3]));
+        } else {
+            float f[8];
+#pragma unroll
+            for (int j = 0; j < 8; j++) f[j] = (WHOLE || j < n) ? src[j] : 0.f;
+            if (WHOLE || n == 8) store8<DST>(dst, at, f);
+            else if (n > 0) store8<DST>(dst, at, f, n);
         }
     }
 }
 
 template <int FMT, int DST>
 static hipError_t launch_t(const uint8_t *elems, const uint8_t *scales, int64_t rows, int64_t cols, int axis, void *dst,
-                           int64_t ld, hipStream_t st)
+                           int64_t ld, hipStream_t st, const Batch &batch)
 {
-    const int64_t n_out = axis == 1 ? rows : cols;
-    const int64_t len = axis == 1 ? cols : rows;
-    const int64_t plen = (len + BLOCK - 1) / BLOCK * BLOCK;
-    if (axis == 0 && n_out % DQT_O == 0 && len % DQT_L == 0 && (n_out / DQT_O) * (len / DQT_L) <= 0x7FFFFFFF) {
-        hipLaunchKernelGGL((dequant_tr_tile_kernel<FMT, DST>), dim3((unsigned)((n_out / DQT_O) * (len / DQT_L))), dim3(256), 0,
-                           st, elems, scales, dst, n_out, len, ld);
-        return hipGetLastError();
+    constexpr int w = Fmt<FMT>::bits;
+    constexpr int64_t esz = DST == DT_F32 ? 4 : 2;
+    if (axis == 0) {
+        const int64_t tiles = ((cols + DQT_O - 1) / DQT_O) * ((rows + DQT_L - 1) / DQT_L);
+        if (tiles > 0x7FFFFFFF) return hipErrorNotSupported;
+        for (int64_t i = 0; i < batch.n; i += 65535) {
+            const dim3 grid((unsigned)tiles, 1, (unsigned)(batch.n - i < 65535 ? batch.n - i : 65535));
+            const uint8_t *e = elems + i * batch.elems, *sc = scales + i * batch.scales;
+            void *d = static_cast<char *>(dst) + i * batch.src * esz;
+            if (cols % DQT_O == 0 && rows % DQT_L == 0)
+                hipLaunchKernelGGL((dequant_tr_tile_kernel<FMT, DST, true>), grid, dim3(256), 0, st, e, sc, d, cols, rows, ld, batch);
+            else
+                hipLaunchKernelGGL((dequant_tr_tile_kernel<FMT, DST, false>), grid, dim3(256), 0, st, e, sc, d, cols, rows, ld, batch);
+            const hipError_t err = hipGetLastError();
+            if (err != hipSuccess) return err;
+        }
+        return hipSuccess;
     }
-    if (axis == 1 && ld == len && plen == len) {
-        // dense rows of whole blocks: one flat run of units
-        const int64_t n_units = n_out * (len / 8);
-        if (DST == DT_F32 && Fmt<FMT>::bits == 8) {
-            if constexpr (Fmt<FMT>::bits == 8) {
-                const int64_t nq = n_units * 2, nbq = (nq + 256 * DQ_U - 1) / (256 * DQ_U);
-                if (nbq <= 0x7FFFFFFF) {
-                    hipLaunchKernelGGL((dequant_flat4_kernel<FMT>), dim3((unsigned)nbq), dim3(256), 0, st, elems, scales,
-                                       static_cast<float *>(dst), nq);
-                    return hipGetLastError();
-                }
+    // axis 1: the MX tensor is one run of batch.n * rows lines (a batch has dense inputs)
+    const int64_t upr = (cols + BLOCK - 1) / BLOCK * (BLOCK / 8), n_units = batch.n * rows * upr;
+    if (ld == cols && cols % BLOCK == 0 && (batch.n == 1 || batch.src == rows * ld)) {
+        if constexpr (DST == DT_F32 && w == 8) {
+            const int64_t nq = n_units * 2, nbq = (nq + 256 * DQ_U - 1) / (256 * DQ_U);
+            if (nbq <= 0x7FFFFFFF) {
+                hipLaunchKernelGGL((dequant_flat4_kernel<FMT>), dim3((unsigned)nbq), dim3(256), 0, st, elems, scales,
+                                   static_cast<float *>(dst), nq);
+                return hipGetLastError();
             }
         }
-        const int64_t nbf = (n_units + 256 * DQ_U - 1) / (256 * DQ_U);
-        if (nbf <= 0x7FFFFFFF) {
-            hipLaunchKernelGGL((dequant_flat_kernel<FMT, DST>), dim3((unsigned)nbf), dim3(256), 0, st, elems, scales, dst, n_units);
+        const int64_t nb = (n_units + 256 * DQ_U - 1) / (256 * DQ_U);
+        if (nb <= 0x7FFFFFFF) {
+            hipLaunchKernelGGL((dequant_row_kernel<FMT, DST, true>), dim3((unsigned)nb), dim3(256), 0, st, elems, scales, dst, n_units,
+                               RowGeom{});
             return hipGetLastError();
         }
     }
-    int64_t nb = (n_out * (plen / 8) + 255) / 256;
-    if (nb > 0x7FFFFFFF) nb = 0x7FFFFFFF;   // one unit per thread (a capped grid with a stride loop: Float32 output 20 % slower, bf16 3 % faster)
-    if (axis == 1)
-        hipLaunchKernelGGL((dequant_kernel<FMT, DST, false>), dim3((unsigned)nb), dim3(256), 0, st, elems, scales, dst,
-                           n_out, len, plen, ld);
-    else
-        hipLaunchKernelGGL((dequant_kernel<FMT, DST, true>), dim3((unsigned)nb), dim3(256), 0, st, elems, scales, dst,
-                           n_out, len, plen, ld);
-    return hipGetLastError();
+    // strided or ragged rows: units are numbered in 31 bits, so very large tensors go a run of rows at a time
+    const int64_t most = 0x7FFFFFFF / upr;
+    if (most < 1) return hipErrorNotSupported;
+    const bool once = batch.n * rows <= most;
+    for (int64_t i = 0; i < (once ? 1 : batch.n); i++)
+        for (int64_t r = 0; r < rows; r += once ? rows : most) {
+            const int64_t nr = once || rows - r < most ? rows - r : most, nz = once ? batch.n : 1, line = i * rows + r, n = nz * nr * upr;
+            hipLaunchKernelGGL((dequant_row_kernel<FMT, DST, false>), dim3((unsigned)((n + 256 * DQ_U - 1) / (256 * DQ_U))), dim3(256), 0, st,
+                               elems + line * upr * w, scales + line * (upr / 4), static_cast<char *>(dst) + (i * batch.src + r * ld) * esz, n,
+                               row_geom(nz, nr, cols, ld, nz > 1 ? batch.src : nr * ld, 8));
+            const hipError_t err = hipGetLastError();
+            if (err != hipSuccess) return err;
+        }
+    return hipSuccess;
 }
 
 template <int DST>
 static hipError_t launch_f(int fmt, const uint8_t *elems, const uint8_t *scales, int64_t rows, int64_t cols, int axis,
-                           void *dst, int64_t ld, hipStream_t st)
+                           void *dst, int64_t ld, hipStream_t st, const Batch &batch)
 {
     switch (fmt) {
-        case FP8_E4M3: return launch_t<FP8_E4M3, DST>(elems, scales, rows, cols, axis, dst, ld, st);
-        case FP8_E5M2: return launch_t<FP8_E5M2, DST>(elems, scales, rows, cols, axis, dst, ld, st);
-        case FP6_E3M2: return launch_t<FP6_E3M2, DST>(elems, scales, rows, cols, axis, dst, ld, st);
-        case FP6_E2M3: return launch_t<FP6_E2M3, DST>(elems, scales, rows, cols, axis, dst, ld, st);
-        case FP4_E2M1: return launch_t<FP4_E2M1, DST>(elems, scales, rows, cols, axis, dst, ld, st);
-        default:       return launch_t<INT8, DST>(elems, scales, rows, cols, axis, dst, ld, st);
+        case FP8_E4M3: return launch_t<FP8_E4M3, DST>(elems, scales, rows, cols, axis, dst, ld, st, batch);
+        case FP8_E5M2: return launch_t<FP8_E5M2, DST>(elems, scales, rows, cols, axis, dst, ld, st, batch);
+        case FP6_E3M2: return launch_t<FP6_E3M2, DST>(elems, scales, rows, cols, axis, dst, ld, st, batch);
+        case FP6_E2M3: return launch_t<FP6_E2M3, DST>(elems, scales, rows, cols, axis, dst, ld, st, batch);
+        case FP4_E2M1: return launch_t<FP4_E2M1, DST>(elems, scales, rows, cols, axis, dst, ld, st, batch);
+        default:       return launch_t<INT8, DST>(elems, scales, rows, cols, axis, dst, ld, st, batch);
     }
 }
 
 hipError_t launch_dequant(const uint8_t *elems, const uint8_t *scales, int fmt, int64_t rows, int64_t cols, int axis,
-                          void *dst, int dst_dt, int64_t ld, hipStream_t st)
+                          void *dst, int dst_dt, int64_t ld, hipStream_t st, const Batch &batch)
 {
-    return dst_dt == DT_F32 ? launch_f<DT_F32>(fmt, elems, scales, rows, cols, axis, dst, ld, st)
-                            : launch_f<DT_BF16>(fmt, elems, scales, rows, cols, axis, dst, ld, st);
+    return dst_dt == DT_F32 ? launch_f<DT_F32>(fmt, elems, scales, rows, cols, axis, dst, ld, st, batch)
+                            : launch_f<DT_BF16>(fmt, elems, scales, rows, cols, axis, dst, ld, st, batch);
 }
 
 }  // namespace mx

@@ -94,35 +94,25 @@ hipError_t launch_dequant_3d(const uint8_t *elems, const uint8_t *scales, int fm
     const int64_t dim[3] = {d0, d1, d2};
     const int64_t L = dim[axis], nblk = (L + BLOCK - 1) / BLOCK;
     const int w = fmt_bits(fmt);
-    const int64_t line_bytes = nblk * BLOCK * w / 8, esz = dst_dt == DT_F32 ? 4 : 2;
-    uint8_t *d8 = static_cast<uint8_t *>(dst);
+    const int64_t line_bytes = nblk * BLOCK * w / 8;
     if (keep_order && !(axis == 2 && d2 % BLOCK == 0))    // (whole blocks along the last axis: both layouts coincide)
         return launch_keep(fmt, elems, scales, dst, dst_dt, d0, d1, d2, axis, nblk, stride0, stride1, st);
-    if (axis == 2) {
+    Batch b;
+    if (axis == 2) {        // dense lines in, strided rows out
         if (stride0 == d1 * stride1) return launch_dequant(elems, scales, fmt, d0 * d1, d2, 1, dst, dst_dt, stride1, st);
-        for (int64_t i = 0; i < d0; i++) {
-            const hipError_t e = launch_dequant(elems + i * d1 * line_bytes, scales + i * d1 * nblk, fmt, d1, d2, 1,
-                                                d8 + i * stride0 * esz, dst_dt, stride1, st);
-            if (e != hipSuccess) return e;
-        }
-        return hipSuccess;
+        b.n = d0; b.src = stride0;
+        return launch_dequant(elems, scales, fmt, d1, d2, 1, dst, dst_dt, stride1, st, b);
     }
+    b.elems = d2 * line_bytes;
+    b.scales = d2 * nblk;
     if (axis == 1) {        // per i0 the transposed-axis dequantize of [d2] lines of length d1 into the [d1][d2] slice
-        for (int64_t i = 0; i < d0; i++) {
-            const hipError_t e = launch_dequant(elems + i * d2 * line_bytes, scales + i * d2 * nblk, fmt, d1, d2, 0,
-                                                d8 + i * stride0 * esz, dst_dt, stride1, st);
-            if (e != hipSuccess) return e;
-        }
-        return hipSuccess;
+        b.n = d0; b.src = stride0;
+        return launch_dequant(elems, scales, fmt, d1, d2, 0, dst, dst_dt, stride1, st, b);
     }
-    // axis 0: [d1 * d2] lines of length d0; one launch when the rows of the result are dense
+    // axis 0: [d1 * d2] lines of length d0; one matrix when the rows of the result are dense
     if (stride1 == d2) return launch_dequant(elems, scales, fmt, d0, d1 * d2, 0, dst, dst_dt, stride0, st);
-    for (int64_t i = 0; i < d1; i++) {
-        const hipError_t e = launch_dequant(elems + i * d2 * line_bytes, scales + i * d2 * nblk, fmt, d0, d2, 0,
-                                            d8 + i * stride1 * esz, dst_dt, stride0, st);
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+    b.n = d1; b.src = stride1;
+    return launch_dequant(elems, scales, fmt, d0, d2, 0, dst, dst_dt, stride0, st, b);
 }
 
 }  // namespace mx

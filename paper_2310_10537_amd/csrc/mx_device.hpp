@@ -219,6 +219,45 @@ __device__ __forceinline__ uint32_t group_max(uint32_t v)
     return v;
 }
 
+// ---------------------------------------------------------------------------
+// Division of n < 2^31 by a divisor that the host knows (multiply and shift): with l = ceil(log2 d)
+// and m = floor(2^32 (2^l - d) / d) + 1 the quotient is (umulhi(n, m) + n) >> l (Granlund and
+// Montgomery, PLDI 1994).  A 64-bit division costs a wave about 100 instructions.
+// ---------------------------------------------------------------------------
+struct FastDiv {
+    uint32_t d, m, l;
+    __device__ __forceinline__ uint32_t operator()(uint32_t n) const { return (__umulhi(n, m) + n) >> l; }
+};
+inline FastDiv fast_div(int64_t d)
+{
+    uint32_t l = 0;
+    while (((uint64_t)1 << l) < (uint64_t)d) l++;
+    return FastDiv{(uint32_t)d, (uint32_t)(((((uint64_t)1 << l) - (uint64_t)d) << 32) / (uint64_t)d + 1), l};
+}
+
+// The rows of a strided tensor for kernels that walk its elements in row-major order with the rows filled
+// up to whole blocks: row r = i0 * d1 + i1 starts at element i0 * stride0 + i1 * ld and holds cols elements;
+// units_per_row units of EPU elements each (the fill included).  n_units < 2^31.
+struct RowGeom {
+    FastDiv units_per_row, d1;
+    int64_t cols, ld, stride0;
+    uint32_t n_units;
+    // first element of unit u inside the tensor, and how many of its n elements lie inside the row
+    __device__ __forceinline__ int64_t at(uint32_t u, int epu, int &n) const
+    {
+        const uint32_t r = units_per_row(u), c = (u - r * units_per_row.d) * (uint32_t)epu;
+        const uint32_t i0 = d1(r), i1 = r - i0 * d1.d;
+        const int64_t left = cols - (int64_t)c;
+        n = left >= epu ? epu : left > 0 ? (int)left : 0;
+        return (int64_t)i0 * stride0 + (int64_t)i1 * ld + c;
+    }
+};
+inline RowGeom row_geom(int64_t batch, int64_t rows, int64_t cols, int64_t ld, int64_t stride0, int epu)
+{
+    const int64_t upr = (cols + BLOCK - 1) / BLOCK * (BLOCK / epu);
+    return RowGeom{fast_div(upr), fast_div(rows), cols, ld, stride0, (uint32_t)(batch * rows * upr)};
+}
+
 // 16-byte global load / store helpers
 __device__ __forceinline__ uint4 ld16(const void *p) { return *reinterpret_cast<const uint4 *>(p); }
 __device__ __forceinline__ void st16(void *p, uint4 v) { *reinterpret_cast<uint4 *>(p) = v; }

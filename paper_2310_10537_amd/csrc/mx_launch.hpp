@@ -7,9 +7,13 @@
 
 namespace mx {
 
-// seed: read by the stochastic rounding mode only
+// A batch of n tensors of one shape, src elements, elems bytes and scales bytes apart (one launch covers all)
+struct Batch { int64_t n = 1, src = 0, elems = 0, scales = 0; };
+
+// seed: read by the stochastic rounding mode only.  With a batch and axis 1 the outputs are dense
+// ([n * rows] lines one after the other).
 hipError_t launch_cast(const void *src, int src_dt, int64_t rows, int64_t cols, int64_t ld, int axis, int fmt, int rnd,
-                       uint8_t *elems, uint8_t *scales, hipStream_t st, uint64_t seed = 0);
+                       uint8_t *elems, uint8_t *scales, hipStream_t st, uint64_t seed = 0, const Batch &batch = Batch());
 
 // Algorithm 1 along axis 0, 1 or 2 of a 3-D tensor [d0][d1][d2] with element strides (stride0, stride1, 1);
 // keep_order = false: block axis moved last; true: codes in source order packed along d2
@@ -19,22 +23,19 @@ hipError_t launch_cast_3d(const void *src, int src_dt, int64_t d0, int64_t d1, i
 // bf16 sources and the two round-to-nearest modes only; hipErrorNotSupported when the shape is
 // outside what the fast kernels take
 hipError_t launch_cast_bf16_fast(const void *src, int64_t rows, int64_t cols, int64_t ld, int axis, int fmt, int rnd,
-                                 uint8_t *elems, uint8_t *scales, hipStream_t st);
+                                 uint8_t *elems, uint8_t *scales, hipStream_t st, const Batch &batch = Batch());
 
-// Float32 sources, axis 0, whole 128 x 64 tiles, the two round-to-nearest modes; else hipErrorNotSupported
-hipError_t launch_cast_col_f32_fast(const void *src, int64_t rows, int64_t cols, int64_t ld, int fmt, int rnd, uint8_t *elems,
-                                    uint8_t *scales, hipStream_t st);
-
-// Float32 sources, axis 1, dense rows of whole blocks, a whole number of 2048-element runs, round to nearest
-hipError_t launch_cast_row_f32_fast(const void *src, int64_t rows, int64_t cols, int64_t ld, int fmt, int rnd, uint8_t *elems,
-                                    uint8_t *scales, hipStream_t st);
+// the same for Float32 sources
+hipError_t launch_cast_f32_fast(const void *src, int64_t rows, int64_t cols, int64_t ld, int axis, int fmt, int rnd,
+                                uint8_t *elems, uint8_t *scales, hipStream_t st, const Batch &batch = Batch());
 
 // both axes in one pass over the source: (e1, s1) as launch_cast with axis 1, (e0, s0) with axis 0
 hipError_t launch_cast_dual(const void *src, int src_dt, int64_t rows, int64_t cols, int64_t ld, int fmt, int rnd,
                             uint8_t *e1, uint8_t *s1, uint8_t *e0, uint8_t *s0, hipStream_t st);
 
+// (batch: src is the distance of the results in elements)
 hipError_t launch_dequant(const uint8_t *elems, const uint8_t *scales, int fmt, int64_t rows, int64_t cols, int axis,
-                          void *dst, int dst_dt, int64_t ld, hipStream_t st);
+                          void *dst, int dst_dt, int64_t ld, hipStream_t st, const Batch &batch = Batch());
 
 // inverse of launch_cast_3d for both layouts; dst [d0][d1][d2] with element strides (stride0, stride1, 1)
 hipError_t launch_dequant_3d(const uint8_t *elems, const uint8_t *scales, int fmt, int64_t d0, int64_t d1, int64_t d2, int axis,

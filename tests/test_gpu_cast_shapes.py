@@ -1,0 +1,80 @@
+"""Casts and dequantize at the edges of their kernels' tiles: strided rows, partial last blocks, row and
+column remainders, batches of slices -- bit for bit against the reference."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_util import same_floats, to_dev, to_host
+from paper_2310_10537_amd import inputs
+
+pytestmark = pytest.mark.gpu
+NAMES = ("fp8_e4m3", "fp8_e5m2", "fp6_e3m2", "fp6_e2m3", "fp4_e2m1", "int8")
+
+
+@pytest.fixture(scope="module")
+def mx():
+    from paper_2310_10537_amd import binding
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    binding.lib()
+    return binding
+
+
+def source(rows, cols, dt, seed):
+    """A [rows, cols] array whose blocks cycle through the degenerate cases along rows, heavy tails elsewhere."""
+    x = inputs.student_t_f32((rows, cols), seed)
+    x[: rows // 2, : cols // 32 * 32] = inputs.adversarial_f32(max(rows // 2, 1), max(cols // 32 * 32, 32), seed)[: rows // 2, : cols // 32 * 32]
+    return x if dt == "f32" else inputs.f32_to_bf16_bits(x)
+
+
+def strided(a, pad):
+    """The array on the device as the left part of a wider tensor (rows start at multiples of 16 bytes)."""
+    t = to_dev(a)
+    step = 16 // t.element_size()
+    ld = -(-(a.shape[1] + pad) // step) * step
+    big = torch.full((a.shape[0], ld), 3.0e38, dtype=t.dtype, device="cuda")   # must never reach a block
+    big[:, : a.shape[1]] = t
+    return big[:, : a.shape[1]]
+
+
+# rows around the 128-row tile and the 32-row block, columns around the 64- and 128-column tiles and the 8-element load
+SHAPES = [(2, 1), (31, 7), (33, 65), (127, 63), (128, 64), (129, 129), (160, 200), (257, 72)]
+
+
+@pytest.mark.parametrize("fmt", range(6), ids=NAMES)
+@pytest.mark.parametrize("dt", ["bf16", "f32"])
+@pytest.mark.parametrize("axis", [1, 0])
+def test_cast_and_dequantize_at_tile_edges(mx, oracle, fmt, dt, axis):
+    for n, (rows, cols) in enumerate(SHAPES):
+        x = source(rows, cols, dt, seed=200 + n)
+        for rnd, pad in ((0, 0), (1, 40)):
+            e, s = mx.mx_quantize(strided(x, pad), axis, fmt, rnd)
+            e_ref, s_ref = oracle.quantize(x, axis, fmt, rnd)
+            assert np.array_equal(to_host(s), s_ref) and np.array_equal(to_host(e), e_ref), (rows, cols, rnd, pad)
+            for out_dt in (torch.float32, torch.bfloat16):
+                out = torch.full((rows, -(-(cols + pad) // 8) * 8), 7.0, dtype=out_dt, device="cuda")
+                mx.mx_dequantize(e, s, fmt, rows, cols, axis, out=out[:, :cols])
+                want = oracle.dequantize(e_ref, s_ref, fmt, rows, cols, axis, dst_dt=int(out_dt == torch.bfloat16))
+                assert same_floats(to_host(out[:, :cols]), want), (rows, cols, pad)
+                assert torch.all(out[:, cols:] == 7.0), (rows, cols)
+
+
+@pytest.mark.parametrize("fmt", [0, 3, 4, 5], ids=lambda f: NAMES[f])
+@pytest.mark.parametrize("dt", ["bf16", "f32"])
+@pytest.mark.parametrize("axis", [0, 1, 2])
+def test_batches_of_slices(mx, oracle, fmt, dt, axis):
+    """Whole-tile and ragged slices, dense and with padded strides, in one call."""
+    for shape in ((5, 128, 64), (3, 256, 128), (7, 45, 80), (2, 131, 96)):
+        x = source(shape[0] * shape[1], shape[2], dt, seed=300 + shape[1]).reshape(shape)
+        d = to_dev(x)
+        big = torch.full((shape[0] + 1, shape[1] + 3, shape[2] + 16), 3.0e38, dtype=d.dtype, device="cuda")
+        big[: shape[0], : shape[1], : shape[2]] = d
+        e_ref, s_ref = oracle.quantize_3d(x, axis, fmt, 0, False)
+        for t in (d, big[: shape[0], : shape[1], : shape[2]]):
+            e, s = mx.mx_quantize_3d(t, axis, fmt)
+            assert np.array_equal(to_host(s), s_ref) and np.array_equal(to_host(e), e_ref), (shape, t.stride())
+            back = torch.full_like(big, 7.0)
+            for y in (None, back[: shape[0], : shape[1], : shape[2]]):
+                y = mx.mx_dequantize_3d(e, s, fmt, shape, axis, dtype=d.dtype, out=y)
+                assert same_floats(to_host(y), oracle.dequantize_3d(e_ref, s_ref, fmt, shape, axis, False, dst_dt=int(dt == "bf16"))), shape
+            back[: shape[0], : shape[1], : shape[2]] = 7.0
+            assert torch.all(back == 7.0)
