@@ -228,6 +228,10 @@ hipError_t launch_cast(const void *src, int src_dt, int64_t rows, int64_t cols, 
         hipError_t e = launch_cast_f32_fast(src, rows, cols, ld, axis, fmt, rnd, elems, scales, st, batch);
         if (e != hipErrorNotSupported) return e;
     }
+    if (rnd == ROUND_STOCHASTIC && batch.n == 1) {   // (beyond 2^34 elements the generic kernels below draw the same numbers)
+        hipError_t e = launch_cast_sr(src, src_dt, rows, cols, ld, axis, fmt, seed, elems, scales, st);
+        if (e != hipErrorNotSupported) return e;
+    }
     return src_dt == DT_BF16 ? dispatch_fmt<DT_BF16>(fmt, rnd, seed, axis, src, rows, cols, ld, elems, scales, st, batch)
                              : dispatch_fmt<DT_F32>(fmt, rnd, seed, axis, src, rows, cols, ld, elems, scales, st, batch);
 }

@@ -78,3 +78,31 @@ def test_batches_of_slices(mx, oracle, fmt, dt, axis):
                 assert same_floats(to_host(y), oracle.dequantize_3d(e_ref, s_ref, fmt, shape, axis, False, dst_dt=int(dt == "bf16"))), shape
             back[: shape[0], : shape[1], : shape[2]] = 7.0
             assert torch.all(back == 7.0)
+
+
+@pytest.mark.parametrize("fmt", range(6), ids=NAMES)
+@pytest.mark.parametrize("dt", ["bf16", "f32"])
+@pytest.mark.parametrize("axis", [1, 0])
+def test_stochastic_cast_at_tile_edges(mx, oracle, fmt, dt, axis):
+    """Column counts on either side of a multiple of four (a Philox call serves four elements), degenerate blocks,
+    and values that reach from the block maximum to far below the smallest grid step."""
+    for n, (rows, cols) in enumerate(SHAPES + [(64, 130), (96, 127), (40, 256)]):
+        x = inputs.bf16_bits_to_f32(source(rows, cols, "bf16", seed=400 + n)) if dt == "bf16" else source(rows, cols, dt, seed=400 + n)
+        g = np.random.default_rng(500 + n)
+        x[rows // 2:] *= np.exp2(g.integers(-24, 1, x[rows // 2:].shape)).astype(np.float32)
+        x = inputs.f32_to_bf16_bits(x) if dt == "bf16" else x
+        for pad, seed in ((0, 77), (24, 2 ** 63 + 5)):
+            e, s = mx.mx_quantize_sr(strided(x, pad), axis, fmt, seed)
+            e_ref, s_ref = oracle.quantize(x, axis, fmt, oracle.ROUND_STOCHASTIC, seed=seed)
+            assert np.array_equal(to_host(s), s_ref) and np.array_equal(to_host(e), e_ref), (rows, cols, pad)
+
+
+def test_stochastic_cast_of_a_large_tensor(mx, oracle):
+    """2^24 elements and more: a lane takes a whole block."""
+    for shape, dt in (((4099, 4096), "bf16"), ((4096, 4102), "f32")):
+        x = source(*shape, dt, seed=600)
+        for fmt in (1, 2, 4, 5):
+            for axis in (1, 0):
+                e, s = mx.mx_quantize_sr(strided(x, 0), axis, fmt, 11)
+                e_ref, s_ref = oracle.quantize(x, axis, fmt, oracle.ROUND_STOCHASTIC, seed=11)
+                assert np.array_equal(to_host(s), s_ref) and np.array_equal(to_host(e), e_ref), (shape, fmt, axis)
