@@ -82,167 +82,102 @@ size_t gemm_q_workspace_bound(int64_t M, int64_t N, int64_t K, int fmtA, int fmt
 // ---------------------------------------------------------------------------
 // Direct kernel: operands go from global memory straight into MFMA registers.
 // Work-group = 4 waves, each wave one 32 x 32 output tile, K step 64.
-// Handles every shape (ragged M, N; K any multiple of 32).
+// Handles every shape (ragged M, N; K any multiple of 32, K = 0 and K > 2^23 included).
 // ---------------------------------------------------------------------------
-template <int FA, int FB, bool QA, int RND, int CDT>
+template <int FA, int FB, int CDT>
 __global__ __launch_bounds__(256) void gemm_direct_kernel(int64_t M, int64_t N, int64_t K,
                                                           const uint8_t *__restrict__ Ae, const uint8_t *__restrict__ As,
-                                                          const uint16_t *__restrict__ Abf, int64_t lda,
                                                           const uint8_t *__restrict__ Be, const uint8_t *__restrict__ Bs,
                                                           void *__restrict__ C, int64_t ldc)
 {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int64_t m0 = (int64_t)blockIdx.y * 64 + (wave >> 1) * 32;
     const int64_t n0 = (int64_t)blockIdx.x * 64 + (wave & 1) * 32;
-    direct_tile<FA, FB, QA, RND, CDT>(M, N, K, Ae, As, Abf, lda, Be, Bs, C, ldc, m0, n0, lane);
+    direct_tile<FA, FB, false, ROUND_RNE, CDT>(M, N, K, Ae, As, nullptr, 0, Be, Bs, C, ldc, m0, n0, lane);
 }
 
-// ---------------------------------------------------------------------------
-// Dispatch over (fmtA, fmtB, quantize-on-load, rounding, output type)
-// ---------------------------------------------------------------------------
 struct GemmArgs {
     int64_t M, N, K;
-    const uint8_t *Ae, *As;
-    const uint16_t *Abf;
-    int64_t lda;
-    const uint8_t *Be, *Bs;
+    const uint8_t *Ae, *As, *Be, *Bs;
     void *C;
     int64_t ldc;
     hipStream_t st;
 };
 
-template <int FA, int FB, bool QA, int RND, int CDT>
+template <int FA, int FB, int CDT>
 static hipError_t launch_direct(const GemmArgs &g)
 {
     dim3 grid((unsigned)((g.N + 63) / 64), (unsigned)((g.M + 63) / 64));
-    hipLaunchKernelGGL((gemm_direct_kernel<FA, FB, QA, RND, CDT>), grid, dim3(256), 0, g.st, g.M, g.N, g.K, g.Ae, g.As,
-                       g.Abf, g.lda, g.Be, g.Bs, g.C, g.ldc);
+    hipLaunchKernelGGL((gemm_direct_kernel<FA, FB, CDT>), grid, dim3(256), 0, g.st, g.M, g.N, g.K, g.Ae, g.As, g.Be, g.Bs, g.C, g.ldc);
     return hipGetLastError();
 }
 
-template <int FA, int FB>
-static hipError_t dispatch_mode(const GemmArgs &g, int rnd, int c_dt)
-{
-    if (g.Abf) {
-        if (rnd == ROUND_RNE)
-            return c_dt == DT_F32 ? launch_direct<FA, FB, true, ROUND_RNE, DT_F32>(g)
-                                  : launch_direct<FA, FB, true, ROUND_RNE, DT_BF16>(g);
-        return c_dt == DT_F32 ? launch_direct<FA, FB, true, ROUND_HALF_AWAY, DT_F32>(g)
-                              : launch_direct<FA, FB, true, ROUND_HALF_AWAY, DT_BF16>(g);
-    }
-    return c_dt == DT_F32 ? launch_direct<FA, FB, false, ROUND_RNE, DT_F32>(g)
-                          : launch_direct<FA, FB, false, ROUND_RNE, DT_BF16>(g);
-}
-
 template <int FA>
-static hipError_t dispatch_b(const GemmArgs &g, int fmtB, int rnd, int c_dt)
+static hipError_t dispatch_b(const GemmArgs &g, int fmtB, int c_dt)
 {
+#define MX_GO(FB) (c_dt == DT_F32 ? launch_direct<FA, FB, DT_F32>(g) : launch_direct<FA, FB, DT_BF16>(g))
     switch (fmtB) {
-        case FP8_E4M3: return dispatch_mode<FA, FP8_E4M3>(g, rnd, c_dt);
-        case FP8_E5M2: return dispatch_mode<FA, FP8_E5M2>(g, rnd, c_dt);
-        case FP6_E3M2: return dispatch_mode<FA, FP6_E3M2>(g, rnd, c_dt);
-        case FP6_E2M3: return dispatch_mode<FA, FP6_E2M3>(g, rnd, c_dt);
-        default:       return dispatch_mode<FA, FP4_E2M1>(g, rnd, c_dt);
+        case FP8_E4M3: return MX_GO(FP8_E4M3);
+        case FP8_E5M2: return MX_GO(FP8_E5M2);
+        case FP6_E3M2: return MX_GO(FP6_E3M2);
+        case FP6_E2M3: return MX_GO(FP6_E2M3);
+        default:       return MX_GO(FP4_E2M1);
     }
+#undef MX_GO
 }
 
-// Whether a problem goes to the kernel that shares the K range of 32 columns among eight waves
-// rather than to 256 x 256 tiles: few rows of A (a decoding step), shapes that are not whole tiles,
-// and so few tiles that most compute units would idle.  A tiled launch of fewer than 256 tiles
-// takes as long as its K loop, about 0.0095 us per element of K; the other kernel runs at 400
-// TFLOP/s on the whole chip (600 for long K).  Measured: 256 x 4096 x 4096 24 against 40 us, 256 x
-// 4096 x 11008 40 against 104 us, 512 x 4096 x 11008 77 against 105 us; but 512 x 4096 x 4096 44
-// against 42 us and 256 x 11008 x 4096 65 against 43 us.
-static bool shares_k_among_waves(int64_t M, int64_t N, int64_t K, int fmtA, int fmtB)
+// How a product of FP8 / FP6 / FP4 operands is computed; the choice depends on the shape and the formats only.
+enum Route {
+    SHARED_K,    // eight waves share the K range of 32 columns (mx_gemm_skinny.hip): few rows, or too few tiles to fill the chip
+    MID,         // 64 x 64 to 128 x 128 tiles (mx_gemm_mid.hpp): any shape
+    WHOLE,       // 256 x 256 tiles (mx_gemm_tile*.hpp), nothing left over
+    INTERIOR,    // 256 x 256 tiles over the largest interior they cover, MID for the L-shaped fringe
+    DIRECT       // K beyond 2^23
+};
+
+// Measured boundaries (E4M3 pairs unless said otherwise; us):
+//  - SHARED_K or MID.  Up to 32 rows the weight stream decides and the shared-K kernel reads it best; 33 to 64 rows: 64 x 1024 x 4096
+//    level, 64 x 4096 x 4096 16 against 11, 64 x 11008 x 4096 31 against 15.  Above 64 rows the shared-K kernel holds
+//    so many accumulators that one work-group fills a compute unit: 128 x 1024 x 4096 22 against 11, 256 x 4096 x 4096 25 against
+//    12 -- but a handful of tiles with a short K stays with it.
+//  - MID or 256 x 256 tiles.  2048^3 (64 whole tiles, one 128 x 128 tile per compute unit) 19 against 15, E2M1 15 against 12;
+//    2048 x 4096 x 4096 (128) 41 against 42, E3M2 x E2M1 36 against 40; 4096^3 (256) 61 against 85.
+//  - A problem with a fringe costs an extra launch or two that each leave most of the chip idle: 1000 x 4096 x 4096 60 against 26,
+//    5000 x 11008 x 4096 (817 whole tiles) 280 against 291.
+static Route route_of(int64_t M, int64_t N, int64_t K, int fmtA, int fmtB)
 {
-    if (!gemm_skinny_applies(M, N, K, fmtA, fmtB)) return false;
-    if (M <= 128 || !gemm_tiled_applies(M, N, K, fmtA, fmtB)) return true;
-    const int64_t tiles = (M / 256) * (N / 256);
-    return tiles < 32 || (tiles < 44 && K >= 8192);
+    if (!gemm_mid_applies(M, N, K, fmtA, fmtB)) return DIRECT;
+    const int64_t tiles64 = ((M + 63) / 64) * ((N + 63) / 64);
+    const bool shared = M <= 32 || (M <= 64 ? tiles64 < 64 : tiles64 < 24 && K < 4096);
+    if (shared && gemm_skinny_applies(M, N, K, fmtA, fmtB)) return SHARED_K;
+    const int64_t M0 = M & ~(int64_t)255, N0 = N & ~(int64_t)255, whole = (M0 / 256) * (N0 / 256);
+    if (M0 == M && N0 == N) return whole > 64 && gemm_tiled_applies(M, N, K, fmtA, fmtB) ? WHOLE : MID;
+    return whole > 192 && gemm_tiled_applies(M0, N0, K, fmtA, fmtB) ? INTERIOR : MID;
 }
 
 // whether the fused quantize-on-load tiled kernel beats cast + plain tiled kernel (256 x 256 tiles)
 static bool qa_fused_pays(int64_t M, int64_t N) { return N / 256 <= 2 && (M / 256) * (N / 256) >= 256; }
 
-// one problem, one kernel route
-static hipError_t launch_gemm_part(int64_t M, int64_t N, int64_t K, const uint8_t *A_elems, const uint8_t *A_scales,
-                                   const void *a_bf16, int64_t lda, int rnd, int fmtA, const uint8_t *B_elems,
-                                   const uint8_t *B_scales, int fmtB, void *C, int c_dt, int64_t ldc, hipStream_t st)
-{
-    if (fmtA == INT8 && fmtB == INT8) {
-        if (!a_bf16) return launch_gemm_int8(M, N, K, A_elems, A_scales, B_elems, B_scales, C, c_dt, ldc, st);
-        // quantize-on-load: cast A into a stream-ordered workspace first (the bytes mx_quantize writes)
-        const size_t eb = (size_t)M * (size_t)K, sb = eb / BLOCK;
-        if (eb == 0) return launch_gemm_int8(M, N, K, nullptr, nullptr, B_elems, B_scales, C, c_dt, ldc, st);
-        uint8_t *ws = nullptr;
-        hipError_t e = ws_acquire(eb + sb + 16, st, &ws);
-        if (e != hipSuccess) return e;
-        uint8_t *wss = ws + ((eb + 15) & ~(size_t)15);
-        e = launch_cast(a_bf16, DT_BF16, M, K, lda, 1, INT8, rnd, ws, wss, st);
-        if (e == hipSuccess) e = launch_gemm_int8(M, N, K, ws, wss, B_elems, B_scales, C, c_dt, ldc, st);
-        const hipError_t f = ws_release(ws, st);
-        return e != hipSuccess ? e : f;
-    }
-    // Quantize-on-load casts A into a workspace first (the bytes mx_quantize writes).
-    if (shares_k_among_waves(M, N, K, fmtA, fmtB)) {
-        if (!a_bf16) return launch_gemm_skinny(M, N, K, A_elems, A_scales, fmtA, B_elems, B_scales, fmtB, C, c_dt, ldc, st);
-        const size_t bits = fmtA <= FP8_E5M2 ? 8 : fmtA <= FP6_E2M3 ? 6 : 4;
-        const size_t eb = ((size_t)M * (size_t)K * bits / 8 + 15) & ~(size_t)15, sb = (size_t)M * (size_t)K / BLOCK;
-        uint8_t *ws = nullptr;
-        hipError_t e = ws_acquire(eb + sb, st, &ws);
-        if (e != hipSuccess) return e;
-        e = launch_cast(a_bf16, DT_BF16, M, K, lda, 1, fmtA, rnd, ws, ws + eb, st);
-        if (e == hipSuccess)
-            e = launch_gemm_skinny(M, N, K, ws, ws + eb, fmtA, B_elems, B_scales, fmtB, C, c_dt, ldc, st);
-        const hipError_t f = ws_release(ws, st);
-        return e != hipSuccess ? e : f;
-    }
-    // Quantize-on-load on whole tiles.  The fused kernel casts each A tile once per column of
-    // output tiles and reads it as bf16 that often, so it pays only for narrow outputs (measured:
-    // up to two tile columns), and only when there are enough tiles to fill the chip, since the
-    // stand-alone cast always runs on every compute unit.  Every other problem casts A once into
-    // a stream-ordered workspace (the same cast kernel, hence the same bytes, as mx_quantize)
-    // and runs the plain tiled kernel on it.
-    if (a_bf16 && gemm_tiled_applies(M, N, K, fmtA, fmtB) && !(gemm_tiled_fuses_cast(fmtA, fmtB) && qa_fused_pays(M, N))) {
-        const size_t bits = fmtA <= FP8_E5M2 ? 8 : fmtA <= FP6_E2M3 ? 6 : 4;
-        const size_t eb = (size_t)M * (size_t)K * bits / 8, sb = (size_t)M * (size_t)K / BLOCK;
-        uint8_t *ws = nullptr;
-        hipError_t e = ws_acquire(eb + sb, st, &ws);
-        if (e != hipSuccess) return e;
-        e = launch_cast_bf16_fast(a_bf16, M, K, lda, 1, fmtA, rnd, ws, ws + eb, st);
-        if (e == hipSuccess)
-            e = launch_gemm_tiled(M, N, K, ws, ws + eb, nullptr, 0, rnd, fmtA, B_elems, B_scales, fmtB, C, c_dt, ldc, st);
-        const hipError_t f = ws_release(ws, st);
-        return e != hipSuccess ? e : f;
-    }
-    {
-        hipError_t e = launch_gemm_tiled(M, N, K, A_elems, A_scales, a_bf16, lda, rnd, fmtA, B_elems, B_scales, fmtB, C,
-                                         c_dt, ldc, st);
-        if (e != hipErrorNotSupported) return e;
-    }
-    GemmArgs g{M, N, K, A_elems, A_scales, reinterpret_cast<const uint16_t *>(a_bf16), lda, B_elems, B_scales, C, ldc, st};
-    switch (fmtA) {
-        case FP8_E4M3: return dispatch_b<FP8_E4M3>(g, fmtB, rnd, c_dt);
-        case FP8_E5M2: return dispatch_b<FP8_E5M2>(g, fmtB, rnd, c_dt);
-        case FP6_E3M2: return dispatch_b<FP6_E3M2>(g, fmtB, rnd, c_dt);
-        case FP6_E2M3: return dispatch_b<FP6_E2M3>(g, fmtB, rnd, c_dt);
-        default:       return dispatch_b<FP4_E2M1>(g, fmtB, rnd, c_dt);
-    }
-}
+static size_t mx_bytes16(int64_t M, int64_t K, int fmt) { return ((size_t)M * (size_t)K * fmt_bits(fmt) / 8 + 15) & ~(size_t)15; }
 
-// A problem whose M or N is not a multiple of the 256 x 256 tile is cut into the largest interior
-// of whole tiles, which takes the tiled kernel, and an L-shaped fringe of fewer than 256 rows /
-// columns, which takes the kernel for shapes that are not whole tiles (or the direct kernel when
-// K is not a multiple of 128).  Every output entry is computed by exactly one launch; which one
+// A problem whose M or N is not a multiple of the 256 x 256 tile may be cut into the largest interior of whole tiles and an L-shaped
+// fringe of fewer than 256 rows / columns.  Every output entry is computed by exactly one launch; which one
 // depends on the shape only, so a result is reproducible, and quantize-on-load follows the same cut.
 hipError_t launch_gemm(int64_t M, int64_t N, int64_t K, const uint8_t *A_elems, const uint8_t *A_scales,
                        const void *a_bf16, int64_t lda, int rnd, int fmtA, const uint8_t *B_elems,
                        const uint8_t *B_scales, int fmtB, void *C, int c_dt, int64_t ldc, hipStream_t st)
 {
-    if (a_bf16 && rnd != ROUND_RNE && rnd != ROUND_HALF_AWAY && M * K > 0) {
-        // the in-kernel casts round to nearest only: any other mode casts A into a workspace first
-        const size_t bits = fmtA == FP4_E2M1 ? 4 : (fmtA == FP6_E3M2 || fmtA == FP6_E2M3) ? 6 : 8;
-        const size_t eb = ((size_t)M * (size_t)K * bits / 8 + 15) & ~(size_t)15, sb = (size_t)M * (size_t)K / BLOCK;
+    const bool int8 = fmtA == INT8 && fmtB == INT8;
+    const int64_t M0 = M & ~(int64_t)255, N0 = N & ~(int64_t)255;
+    const Route route = int8 ? DIRECT : route_of(M, N, K, fmtA, fmtB);
+    // Quantize-on-load.  The fused tiled kernel casts each A tile once per column of output tiles and reads it as bf16 that
+    // often, so it pays only for narrow outputs (measured: up to two tile columns), and only when there are enough tiles to
+    // fill the chip, since the stand-alone cast always runs on every compute unit.  Every other problem casts A once
+    // into a workspace (the same cast kernel, hence the same bytes, as mx_quantize) and runs the plain product on it.
+    const bool fused = a_bf16 && (rnd == ROUND_RNE || rnd == ROUND_HALF_AWAY) && (route == WHOLE || route == INTERIOR) &&
+                       gemm_tiled_fuses_cast(fmtA, fmtB) && qa_fused_pays(M0, N0);
+    if (a_bf16 && !fused && M > 0 && N > 0 && K > 0) {
+        const size_t eb = mx_bytes16(M, K, fmtA), sb = (size_t)M * (size_t)(K / BLOCK);
         uint8_t *ws = nullptr;
         hipError_t e = ws_acquire(eb + sb, st, &ws);
         if (e != hipSuccess) return e;
@@ -252,24 +187,35 @@ hipError_t launch_gemm(int64_t M, int64_t N, int64_t K, const uint8_t *A_elems, 
         const hipError_t f = ws_release(ws, st);
         return e != hipSuccess ? e : f;
     }
-    const int64_t M0 = M & ~(int64_t)255, N0 = N & ~(int64_t)255;
-    // small ragged problems: one launch of the kernel for such shapes instead of three
-    if (fmtA != INT8 && K % 128 == 0 && (M0 / 256) * (N0 / 256) < 32 && gemm_skinny_applies(M, N, K, fmtA, fmtB))
-        return launch_gemm_part(M, N, K, A_elems, A_scales, a_bf16, lda, rnd, fmtA, B_elems, B_scales, fmtB, C, c_dt, ldc, st);
-    if ((M0 == M && N0 == N) || M0 == 0 || N0 == 0 || fmtA == INT8 || !gemm_tiled_applies(M0, N0, K, fmtA, fmtB))
-        return launch_gemm_part(M, N, K, A_elems, A_scales, a_bf16, lda, rnd, fmtA, B_elems, B_scales, fmtB, C, c_dt, ldc, st);
-    const int64_t bitsA = fmtA <= FP8_E5M2 ? 8 : fmtA <= FP6_E2M3 ? 6 : 4, bitsB = fmtB <= FP8_E5M2 ? 8 : fmtB <= FP6_E2M3 ? 6 : 4;
-    const int64_t nkb = K / BLOCK, esz = c_dt == DT_F32 ? 4 : 2;
+    if (int8) return launch_gemm_int8(M, N, K, A_elems, A_scales, B_elems, B_scales, C, c_dt, ldc, st);
+    switch (route) {
+        case SHARED_K: return launch_gemm_skinny(M, N, K, A_elems, A_scales, fmtA, B_elems, B_scales, fmtB, C, c_dt, ldc, st);
+        case MID:      return launch_gemm_mid(M, N, K, A_elems, A_scales, fmtA, B_elems, B_scales, fmtB, C, c_dt, ldc, st);
+        case WHOLE:
+            return launch_gemm_tiled(M, N, K, A_elems, A_scales, a_bf16, lda, rnd, fmtA, B_elems, B_scales, fmtB, C, c_dt, ldc, st);
+        case DIRECT: {
+            const GemmArgs g{M, N, K, A_elems, A_scales, B_elems, B_scales, C, ldc, st};
+            switch (fmtA) {
+                case FP8_E4M3: return dispatch_b<FP8_E4M3>(g, fmtB, c_dt);
+                case FP8_E5M2: return dispatch_b<FP8_E5M2>(g, fmtB, c_dt);
+                case FP6_E3M2: return dispatch_b<FP6_E3M2>(g, fmtB, c_dt);
+                case FP6_E2M3: return dispatch_b<FP6_E2M3>(g, fmtB, c_dt);
+                default:       return dispatch_b<FP4_E2M1>(g, fmtB, c_dt);
+            }
+        }
+        default: break;
+    }
+    const int64_t bitsA = fmt_bits(fmtA), bitsB = fmt_bits(fmtB), nkb = K / BLOCK, esz = c_dt == DT_F32 ? 4 : 2;
     const uint8_t *a16 = static_cast<const uint8_t *>(a_bf16);
-    auto part = [&](int64_t r0, int64_t rows, int64_t c0, int64_t cols) {
-        return launch_gemm_part(rows, cols, K, A_elems ? A_elems + r0 * (K * bitsA / 8) : nullptr,
-                                A_scales ? A_scales + r0 * nkb : nullptr, a16 ? a16 + r0 * lda * 2 : nullptr, lda, rnd, fmtA,
-                                B_elems + c0 * (K * bitsB / 8), B_scales + c0 * nkb, fmtB,
-                                static_cast<uint8_t *>(C) + (r0 * ldc + c0) * esz, c_dt, ldc, st);
+    uint8_t *c8 = static_cast<uint8_t *>(C);
+    hipError_t e = launch_gemm_tiled(M0, N0, K, A_elems, A_scales, a_bf16, lda, rnd, fmtA, B_elems, B_scales, fmtB, C, c_dt, ldc, st);
+    auto fringe = [&](int64_t r0, int64_t rows, int64_t c0, int64_t cols) {
+        return launch_gemm(rows, cols, K, A_elems ? A_elems + r0 * (K * bitsA / 8) : nullptr, A_scales ? A_scales + r0 * nkb : nullptr,
+                           a16 ? a16 + r0 * lda * 2 : nullptr, lda, rnd, fmtA, B_elems + c0 * (K * bitsB / 8), B_scales + c0 * nkb, fmtB,
+                           c8 + (r0 * ldc + c0) * esz, c_dt, ldc, st);
     };
-    hipError_t e = part(0, M0, 0, N0);
-    if (e == hipSuccess && M > M0) e = part(M0, M - M0, 0, N);
-    if (e == hipSuccess && N > N0) e = part(0, M0, N0, N - N0);
+    if (e == hipSuccess && M > M0) e = fringe(M0, M - M0, 0, N);
+    if (e == hipSuccess && N > N0) e = fringe(0, M0, N0, N - N0);
     return e;
 }
 
@@ -279,8 +225,10 @@ hipError_t launch_gemm(int64_t M, int64_t N, int64_t K, const uint8_t *A_elems, 
 hipError_t launch_gemm_q(int64_t M, int64_t N, int64_t K, const uint8_t *Ae, const uint8_t *As, int fmtA, const uint8_t *Be,
                          const uint8_t *Bs, int fmtB, uint8_t *Ce, uint8_t *Cs, int fmtC, int rndC, hipStream_t st)
 {
-    // (only where mx_gemm runs the tiled kernel too: the two must see the same accumulators)
-    if (fmtA != INT8 && !shares_k_among_waves(M, N, K, fmtA, fmtB)) {
+    // The tiled kernel's accumulators are those of mx_gemm on every route but SHARED_K.  Below 32 tiles (44 with a long K) it would
+    // leave most of the chip idle for longer than writing and casting a Float32 C takes.
+    const int64_t tiles = (M / 256) * (N / 256);
+    if (fmtA != INT8 && tiles >= 32 && (tiles >= 44 || K < 8192) && route_of(M, N, K, fmtA, fmtB) != SHARED_K) {
         const hipError_t e = launch_gemm_tiled_mx(M, N, K, Ae, As, fmtA, Be, Bs, fmtB, Ce, Cs, fmtC, rndC, st);
         if (e != hipErrorNotSupported) return e;
     }
