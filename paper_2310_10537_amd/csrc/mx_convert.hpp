@@ -351,23 +351,11 @@ __device__ __forceinline__ void convert_f32_fast(const uint32_t (&v)[32], uint32
     }
 }
 
-// One block of 32 Float32 values in LDS, element i at src[i * stride] (stride 1: 16-byte aligned)
-// -> scale byte and packed codes.
-template <int FMT, int RND>
-__device__ __forceinline__ uint32_t quantize_block_lds(const uint32_t *src, int stride, uint32_t *packed)
+// One block of 32 Float32 values v, which at(i) reads again from LDS -> scale byte and packed codes.
+template <int FMT, int RND, typename At>
+__device__ __forceinline__ uint32_t quantize_block_f32(const uint32_t (&v)[32], At at, uint32_t *packed)
 {
     constexpr int w = Fmt<FMT>::bits;
-    uint32_t v[32];
-    if (stride == 1) {
-#pragma unroll
-        for (int i = 0; i < 8; i++) {
-            const uint4 d = *reinterpret_cast<const uint4 *>(src + 4 * i);
-            v[4 * i] = d.x; v[4 * i + 1] = d.y; v[4 * i + 2] = d.z; v[4 * i + 3] = d.w;
-        }
-    } else {
-#pragma unroll
-        for (int i = 0; i < 32; i++) v[i] = src[i * stride];
-    }
     uint32_t amax = 0, raw = 0;
 #pragma unroll
     for (int i = 0; i < 32; i++) {
@@ -388,7 +376,7 @@ __device__ __forceinline__ uint32_t quantize_block_lds(const uint32_t *src, int 
     if (Fmt<FMT>::elem_nan || s != SCALE_NAN) {
 #pragma unroll 1
         for (int it = 0; it < 32; it++) {
-            const uint32_t code = encode_elem<FMT, RND>(src[it * stride], s);
+            const uint32_t code = encode_elem<FMT, RND>(at(it), s);
 #pragma unroll
             for (int j = 0; j < w - 1; j++) o[j] = (o[j] >> w) | (o[j + 1] << (32 - w));
             o[w - 1] = (o[w - 1] >> w) | (code << (32 - w));
@@ -397,6 +385,24 @@ __device__ __forceinline__ uint32_t quantize_block_lds(const uint32_t *src, int 
 #pragma unroll
     for (int i = 0; i < w; i++) packed[i] = o[i];
     return s;
+}
+
+// The same for element i at src[i * stride] in LDS (stride 1: 16-byte aligned).
+template <int FMT, int RND>
+__device__ __forceinline__ uint32_t quantize_block_lds(const uint32_t *src, int stride, uint32_t *packed)
+{
+    uint32_t v[32];
+    if (stride == 1) {
+#pragma unroll
+        for (int i = 0; i < 8; i++) {
+            const uint4 d = *reinterpret_cast<const uint4 *>(src + 4 * i);
+            v[4 * i] = d.x; v[4 * i + 1] = d.y; v[4 * i + 2] = d.z; v[4 * i + 3] = d.w;
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < 32; i++) v[i] = src[i * stride];
+    }
+    return quantize_block_f32<FMT, RND>(v, [&](int i) { return src[i * stride]; }, packed);
 }
 
 }  // namespace mx

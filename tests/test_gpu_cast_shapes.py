@@ -106,3 +106,15 @@ def test_stochastic_cast_of_a_large_tensor(mx, oracle):
                 e, s = mx.mx_quantize_sr(strided(x, 0), axis, fmt, 11)
                 e_ref, s_ref = oracle.quantize(x, axis, fmt, oracle.ROUND_STOCHASTIC, seed=11)
                 assert np.array_equal(to_host(s), s_ref) and np.array_equal(to_host(e), e_ref), (shape, fmt, axis)
+
+
+# whole 128 x 64 tiles; one and two blocks; row and column remainders of a tile; a last group of strips that is not full
+@pytest.mark.parametrize("fmt", range(6), ids=NAMES)
+@pytest.mark.parametrize("dt", ["bf16", "f32"])
+def test_dual_cast_at_tile_edges(mx, oracle, fmt, dt):
+    for n, (rows, cols) in enumerate([(32, 32), (64, 32), (128, 64), (160, 96), (96, 288), (256, 1216), (384, 1120)]):
+        x = source(rows, cols, dt, seed=300 + n)
+        for rnd, pad in ((0, 0), (1, 40)):
+            for axis, (e, s) in zip((1, 0), mx.mx_quantize_dual(strided(x, pad), fmt, rnd)):
+                e_ref, s_ref = oracle.quantize(x, axis, fmt, rnd)
+                assert np.array_equal(to_host(s), s_ref) and np.array_equal(to_host(e), e_ref), (rows, cols, axis, rnd, pad)
