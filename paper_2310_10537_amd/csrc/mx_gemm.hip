@@ -158,6 +158,11 @@ static Route route_of(int64_t M, int64_t N, int64_t K, int fmtA, int fmtB)
 // whether the fused quantize-on-load tiled kernel beats cast + plain tiled kernel (256 x 256 tiles)
 static bool qa_fused_pays(int64_t M, int64_t N) { return N / 256 <= 2 && (M / 256) * (N / 256) >= 256; }
 
+// Whether the shared-K kernel casts few rows on load: every work-group casts its slice again (16 rows: a block a lane), mostly behind
+// the weight stream, against a launch and a stream-ordered workspace.  bf16 out, cast apart -> on load: 1 x 4096 x 4096 E4M3 27.9 ->
+// 9.1 us, 1 x 11008 x 4096 28.2 -> 11.7, 16 x 11008 x 4096 29.0 -> 13.7, 16 x 28672 x 8192 68.3 -> 63.4, E3M2 x E2M1 46.7 -> 41.9.
+static bool qa_few_rows_pays(int64_t M, int64_t K) { return M <= 16 && K % 128 == 0; }
+
 static size_t mx_bytes16(int64_t M, int64_t K, int fmt) { return ((size_t)M * (size_t)K * fmt_bits(fmt) / 8 + 15) & ~(size_t)15; }
 
 // A problem whose M or N is not a multiple of the 256 x 256 tile may be cut into the largest interior of whole tiles and an L-shaped
@@ -172,10 +177,13 @@ hipError_t launch_gemm(int64_t M, int64_t N, int64_t K, const uint8_t *A_elems, 
     const Route route = int8 ? DIRECT : route_of(M, N, K, fmtA, fmtB);
     // Quantize-on-load.  The fused tiled kernel casts each A tile once per column of output tiles and reads it as bf16 that
     // often, so it pays only for narrow outputs (measured: up to two tile columns), and only when there are enough tiles to
-    // fill the chip, since the stand-alone cast always runs on every compute unit.  Every other problem casts A once
+    // fill the chip, since the stand-alone cast always runs on every compute unit.  Up to 16 rows are cast by the
+    // shared-K kernel.  Every other problem casts A once
     // into a workspace (the same cast kernel, hence the same bytes, as mx_quantize) and runs the plain product on it.
     const bool fused = a_bf16 && (rnd == ROUND_RNE || rnd == ROUND_HALF_AWAY) && (route == WHOLE || route == INTERIOR) &&
                        gemm_tiled_fuses_cast(fmtA, fmtB) && qa_fused_pays(M0, N0);
+    if (a_bf16 && route == SHARED_K && qa_few_rows_pays(M, K) && (rnd == ROUND_RNE || rnd == ROUND_HALF_AWAY))
+        return launch_gemm_skinny_qa(M, N, K, a_bf16, lda, rnd, fmtA, B_elems, B_scales, fmtB, C, c_dt, ldc, st);
     if (a_bf16 && !fused && M > 0 && N > 0 && K > 0) {
         const size_t eb = mx_bytes16(M, K, fmtA), sb = (size_t)M * (size_t)(K / BLOCK);
         uint8_t *ws = nullptr;
