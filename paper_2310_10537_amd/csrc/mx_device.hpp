@@ -226,7 +226,7 @@ __device__ __forceinline__ uint32_t group_max(uint32_t v)
 // ---------------------------------------------------------------------------
 struct FastDiv {
     uint32_t d, m, l;
-    __device__ __forceinline__ uint32_t operator()(uint32_t n) const { return (__umulhi(n, m) + n) >> l; }
+    __host__ __device__ __forceinline__ uint32_t operator()(uint32_t n) const { return ((uint32_t)(((uint64_t)n * m) >> 32) + n) >> l; }
 };
 inline FastDiv fast_div(int64_t d)
 {
@@ -237,17 +237,17 @@ inline FastDiv fast_div(int64_t d)
 
 // The rows of a strided tensor for kernels that walk its elements in row-major order with the rows filled
 // up to whole blocks: row r = i0 * d1 + i1 starts at element i0 * stride0 + i1 * ld and holds cols elements;
-// units_per_row units of EPU elements each (the fill included).  n_units < 2^31.
+// units_per_row units of EPU elements each (the fill included).  n_units < 2^31, so a row may be longer than
+// 2^32 elements: positions inside a row are counted in 64 bits.
 struct RowGeom {
     FastDiv units_per_row, d1;
     int64_t cols, ld, stride0;
     uint32_t n_units;
     // first element of unit u inside the tensor, and how many of its n elements lie inside the row
-    __device__ __forceinline__ int64_t at(uint32_t u, int epu, int &n) const
+    __host__ __device__ __forceinline__ int64_t at(uint32_t u, int epu, int &n) const
     {
-        const uint32_t r = units_per_row(u), c = (u - r * units_per_row.d) * (uint32_t)epu;
-        const uint32_t i0 = d1(r), i1 = r - i0 * d1.d;
-        const int64_t left = cols - (int64_t)c;
+        const uint32_t r = units_per_row(u), i0 = d1(r), i1 = r - i0 * d1.d;
+        const int64_t c = (int64_t)(u - r * units_per_row.d) * epu, left = cols - c;
         n = left >= epu ? epu : left > 0 ? (int)left : 0;
         return (int64_t)i0 * stride0 + (int64_t)i1 * ld + c;
     }

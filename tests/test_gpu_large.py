@@ -192,3 +192,28 @@ def test_stochastic_counter_beyond_2_32(mx, oracle):
             sb, packed = block(piece[rr % PIECE_ROWS, c], rr * COLS + c)
             assert sh[c][rb] == sb, (c, rb)
             assert np.array_equal(eh[c][rb * 16:(rb + 1) * 16], packed), (c, rb)
+
+
+@pytest.mark.parametrize("dt", [torch.float32, torch.bfloat16], ids=["f32", "bf16"])
+def test_one_row_beyond_2_32_elements(mx, oracle, dt):
+    """A single row of 2^32 + 72 elements (a flattened tensor with a partial last block): the columns at its end, and at
+    its start, which an offset cut to 32 bits would read and write in their place."""
+    fmt, cols, t0 = 0, 2 ** 32 + 72, 2 ** 32 - 64
+    # rows of 4096 of one seeded piece, each scaled by its own power of two, so that no two places near the ends are alike
+    piece = inputs.gaussian_f32((1, 4096), seed=920) if dt == torch.float32 else inputs.gaussian_bf16((1, 4096), seed=920)
+    x = torch.empty((1, -(-cols // 4096) * 4096), dtype=dt, device="cuda")
+    x.view(-1, 4096)[:] = to_dev(piece)
+    x[0, :4096] *= 2
+    x[0, t0:] *= 4
+    x = x[:, :cols]
+    e, s = mx.mx_quantize(x, 1, fmt, RNE)
+    y = mx.mx_dequantize(e, s, fmt, 1, cols, 1, dtype=torch.bfloat16)
+    torch.cuda.synchronize()
+    for a, b in ((0, 256), (t0, cols)):
+        e_ref, s_ref = oracle.quantize(to_host(x[:, a:b]), 1, fmt, RNE)
+        assert np.array_equal(to_host(e[:, a:a + e_ref.shape[1]]), e_ref), (a, b)
+        assert np.array_equal(to_host(s[:, a // 32:a // 32 + s_ref.shape[1]]), s_ref), (a, b)
+        y_ref = oracle.dequantize(e_ref, s_ref, fmt, 1, b - a, 1, dst_dt=1)
+        assert same_floats(to_host(y[:, a:b]), y_ref), (a, b)
+    del x, e, s, y
+    torch.cuda.empty_cache()
