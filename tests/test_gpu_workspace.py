@@ -131,3 +131,34 @@ def test_epilogue_cast_ignores_the_workspace(mx):
     assert bits_equal(got[0], want[0]) and bits_equal(got[1], want[1])
     torch.cuda.synchronize()
     assert torch.all(ws == 0xA5)                              # C never existed at more than the format's width
+
+
+def test_graph_captured_without_torch_keeps_its_own_scratch(mx):
+    """A capture that torch's allocator knows nothing of: the graph's replays leave memory alone that torch has
+    handed out since, and give the eager result."""
+    import ctypes
+    with open("/proc/self/maps") as f:
+        hip = ctypes.CDLL(next(line.split()[-1] for line in f if "libamdhip64" in line))
+    M, N, K = 256, 512, 1024
+    a, _, gb = operands(mx, M, N, K, FP8, FP8, 350)
+    want = mx.mx_gemm_qa(a, FP8, 0, gb[0], gb[1], FP8)
+    out = torch.full_like(want, 7.0)
+    stream, graph, run = torch.cuda.Stream(), ctypes.c_void_p(), ctypes.c_void_p()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(stream):
+        h = ctypes.c_void_p(stream.cuda_stream)
+        mx.mx_gemm_qa(a, FP8, 0, gb[0], gb[1], FP8, out=out)                       # the stream's pool holds a block of that size
+        stream.synchronize()
+        assert hip.hipStreamBeginCapture(h, 2) == 0                                # relaxed
+        mx.mx_gemm_qa(a, FP8, 0, gb[0], gb[1], FP8, out=out)
+        assert hip.hipStreamEndCapture(h, ctypes.byref(graph)) == 0 and graph.value
+        assert hip.hipGraphInstantiate(ctypes.byref(run), graph, None, None, ctypes.c_size_t(0)) == 0
+        n = mx.mx_workspace_bytes("gemm_qa", M, N, K, FP8, FP8)
+        later = [torch.full((n,), 0xA5, dtype=torch.uint8, device="cuda") for _ in range(4)]
+        for _ in range(4):
+            out.fill_(7.0)
+            assert hip.hipGraphLaunch(run, h) == 0
+            stream.synchronize()
+            assert bits_equal(out, want) and all(bool((t == 0xA5).all()) for t in later)
+            assert bits_equal(mx.mx_gemm_qa(a, FP8, 0, gb[0], gb[1], FP8), want)   # eager work between the replays
+        assert hip.hipGraphExecDestroy(run) == 0 and hip.hipGraphDestroy(graph) == 0
