@@ -208,12 +208,14 @@ def _qa_workspace(M, N, K, fmtA, fmtB, device, stream):
     """Scratch memory of mx_gemm_qa from torch's caching allocator, or None for the library's own stream-ordered allocation.
     The tensor is dropped when the call returns, so it has to belong to the stream that the call runs on: torch's current one.
     A stream-ordered allocation and its release cost the host more than a small product takes: 1000 x 4096 x 4096 31.4 us a call
-    with them, 26.3 with this.  (Up to 16 rows are mostly cast without scratch memory.)  None too while the stream is being
+    with them, 26.3 with this.  None where the bound on the size says little about the need: up to 16 rows, mostly cast without
+    scratch memory; MXINT8, whose bound covers both operands (17 x 28672 x 8192: 735 MB against 140 KB); many rows and up to two
+    columns of 256 x 256 tiles, which FP8 pairs cast on load.  None too while the stream is being
     captured: a graph replays after this tensor has gone back to the allocator, the library's allocation belongs to the graph."""
     current = torch.cuda.current_stream()
     if M <= 16 or device != current.device or (stream is not None and stream.cuda_stream != current.cuda_stream):
         return None
-    if torch.cuda.is_current_stream_capturing():
+    if fmtA == INT8 or (N < 768 and (M // 256) * (N // 256) >= 256) or torch.cuda.is_current_stream_capturing():
         return None
     need = lib().mx_gemm_qa_workspace_bytes(M, N, K, fmtA, fmtB)
     try:
