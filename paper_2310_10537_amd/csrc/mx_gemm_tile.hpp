@@ -337,8 +337,7 @@ __global__ __launch_bounds__(256, 1) void gemm_tile_kernel(int64_t M, int64_t N,
         for (int i = 0; i < 16; i++) m = pk_absmax(m, d[i]);
         const uint32_t amax16 = pk_hmax(m);
         const uint32_t sbyte = scale_from_bf16_max<FA>(amax16);
-        // an all-zero block is safe with any scale: the converts keep (signed) zero
-        bad |= (uint32_t)(amax16 != 0 && !fast_ok(amax16, sbyte));
+        bad |= (uint32_t)!fast_ok(amax16, sbyte);
         // the converts clamp finite overflow to the largest normal only in saturate mode, and the
         // matrix instructions must not run in it (they would clamp NaN / Inf operands of B too)
         fp8_saturate_mode(true);

@@ -118,3 +118,28 @@ def test_dual_cast_at_tile_edges(mx, oracle, fmt, dt):
             for axis, (e, s) in zip((1, 0), mx.mx_quantize_dual(strided(x, pad), fmt, rnd)):
                 e_ref, s_ref = oracle.quantize(x, axis, fmt, rnd)
                 assert np.array_equal(to_host(s), s_ref) and np.array_equal(to_host(e), e_ref), (rows, cols, axis, rnd, pad)
+
+
+@pytest.mark.parametrize("fmt", range(6), ids=NAMES)
+@pytest.mark.parametrize("dt", ["bf16", "f32"])
+def test_blocks_of_zeros(mx, oracle, fmt, dt):
+    """Blocks of zeros of either sign beside blocks with values, along both axes, inside and at the edges of tiles: the
+    converts take them, and they come out as signed zeros under scale byte 0."""
+    for n, (rows, cols) in enumerate([(160, 200), (128, 256), (33, 1000), (96, 64)]):
+        x = inputs.student_t_f32((rows, cols), seed=700 + n)
+        x[:, (cols // 3) // 32 * 32:cols // 2] = 0
+        x[32:96] *= 0                                              # zeros that keep their signs
+        x[rows - 1, :40] = -0.0
+        x = x if dt == "f32" else inputs.f32_to_bf16_bits(x)
+        for axis in (1, 0):
+            for rnd in (0, 1, 2):
+                e, s = mx.mx_quantize(strided(x, 0), axis, fmt, rnd)
+                e_ref, s_ref = oracle.quantize(x, axis, fmt, rnd)
+                assert np.array_equal(to_host(s), s_ref) and np.array_equal(to_host(e), e_ref), (rows, cols, axis, rnd)
+            e, s = mx.mx_quantize_sr(strided(x, 0), axis, fmt, 9)
+            e_ref, s_ref = oracle.quantize(x, axis, fmt, oracle.ROUND_STOCHASTIC, seed=9)
+            assert np.array_equal(to_host(s), s_ref) and np.array_equal(to_host(e), e_ref), (rows, cols, axis)
+        if rows % 32 == 0 and cols % 32 == 0:
+            for axis, (e, s) in zip((1, 0), mx.mx_quantize_dual(strided(x, 0), fmt, 1)):
+                e_ref, s_ref = oracle.quantize(x, axis, fmt, 1)
+                assert np.array_equal(to_host(s), s_ref) and np.array_equal(to_host(e), e_ref), (rows, cols, axis)
