@@ -19,7 +19,8 @@
 //     the smallest normal only;
 //   * blocks with a non-finite value, a scale byte below 48 (above it a Float32 subnormal is less than
 //     2^-25 of a step, so F = 0 gives the zero the cast asks for) or a maximum next to the Float32 limit
-//     are redone with the integer encoder, one element at a time.
+//     are redone with the integer encoder, one element at a time -- but not blocks of zeros, which round to
+//     signed zeros under any scale: lanes outside the tensor hold them.
 // A lane owns NE elements, a whole block of a large tensor and half a block of a small one (with whole blocks a
 // small cast is one long chain per lane: 100 x 300 Float32 16 us along either axis, 8-10 us with halves; a large
 // one gains nothing from halves, and FP6, whose convert takes 32 elements at once, loses 10 %);
@@ -168,8 +169,8 @@ __device__ __forceinline__ uint32_t sr_block(V value, W words, B both, const uin
     }
     raw = both(raw);
     const uint32_t s = scale_byte<FMT>(Fmt<FMT>::elem_nan ? both(amax) : raw);
-    const bool fast = raw < SR_MAX_BITS && s >= SR_MIN_SCALE;
-    const uint32_t sq = fast ? s : SR_MIN_SCALE;          // (any scale: the block is redone below)
+    const bool fast = raw < SR_MAX_BITS && (s >= SR_MIN_SCALE || raw == 0);
+    const uint32_t sq = fast && raw ? s : SR_MIN_SCALE;   // (any scale: zeros, or the block is redone below)
     const float unit = sr_unit<FMT>(sq);
     f32x16_t lo = {}, hi = {};                            // FP6: elements 2i and 2i + 1 (the convert takes 32: zeros behind half a block)
 #pragma unroll
