@@ -241,8 +241,7 @@ __global__ __launch_bounds__(256) void dequant_flat4_kernel(const uint8_t *__res
 // owns a longer run and stores it 16 bytes at a time leaves every line to several instructions, which
 // measured 60 instead of 40 us).  Whole tiles take the form without bounds checks; blockIdx.z walks a
 // batch of tensors (128 tensors of 2048 x 128 bf16 <-> E4M3: cast and dequantize took 949 us with a launch
-// per tensor, 42 us with one each, 4.0 TB/s).  Remainders used to take a kernel with one lane per 8 codes
-// and 2-byte stores a result row apart.
+// per tensor, 42 us with one each, 4.0 TB/s).
 constexpr int DQT_O = 64, DQT_L = 128, DQT_PITCH = 65;
 template <int FMT, int DST, bool WHOLE>
 __global__ __launch_bounds__(256) void dequant_tr_tile_kernel(const uint8_t *__restrict__ elems,
@@ -307,6 +306,52 @@ __global__ __launch_bounds__(256) void dequant_tr_tile_kernel(const uint8_t *__r
     }
 }
 
+// Axis 0 without LDS: one lane per 8 codes of a line; adjacent lanes take adjacent lines, so that the stores of a wave coalesce
+// across it (2 or 4 bytes each).  Ahead of the tile kernel where a tile would be mostly empty or the tensor is small (see launch_t).
+template <int FMT, int DST>
+__global__ __launch_bounds__(256) void dequant_tr_kernel(const uint8_t *__restrict__ elems, const uint8_t *__restrict__ scales,
+                                                         void *__restrict__ dst, FastDiv n_out, int64_t len, int64_t ld,
+                                                         uint32_t n_units, Batch batch)
+{
+    constexpr int w = Fmt<FMT>::bits;
+    elems += blockIdx.z * batch.elems;
+    scales += blockIdx.z * batch.scales;
+    dst = static_cast<char *>(dst) + blockIdx.z * batch.src * (DST == DT_F32 ? 4 : 2);
+    const uint32_t u = blockIdx.x * 256 + threadIdx.x;
+    if (u >= n_units) return;
+    const uint32_t q = n_out(u), o = u - q * n_out.d;
+    const int64_t unit = o * ((len + BLOCK - 1) / BLOCK * (BLOCK / 8)) + q, l = (int64_t)q * 8;
+    const uint32_t s = scales[unit / 4];
+    float f[8];
+    if (FMT != INT8 && s != SCALE_NAN) {
+        decode8_hw<FMT>(elems + unit * w, s, f);
+    } else {
+        uint32_t c[8];
+        load_codes8<FMT>(elems + unit * w, c);
+#pragma unroll
+        for (int i = 0; i < 8; i++) f[i] = decode_scaled<FMT>(c[i], s);
+    }
+#pragma unroll
+    for (int i = 0; i < 8; i++) {
+        if (l + i >= len) break;
+        if (DST == DT_F32) reinterpret_cast<float *>(dst)[(l + i) * ld + o] = f[i];
+        else reinterpret_cast<uint16_t *>(dst)[(l + i) * ld + o] = (uint16_t)f32_to_bf16_bits(f[i]);
+    }
+}
+
+// Which tensors of remainders go through the tile kernel (whole tiles always do, and what the other cannot number in 31 bits): both
+// dimensions fill most of a tile and there are enough of them.  Without LDS / tiles, us, Float32: 31 x 270600 E4M3 10.6 / 16.9,
+// 90 x 93200 E3M2 9.0 / 12.0, 200 x 41944 E4M3 15.1 / 11.6; lines of few columns, 699057 x 12 E4M3 10 / 16, 174759 x 48 11 / 10.6,
+// 86487 x 97 16 / 13; and 2^21 elements, 257 x 8160 4.3 / 4.7.  A second tile that is nearly empty, 130 x 129048: E2M1 15.5 / 21.9, E3M2
+// 18.8 / 23.2, but 129 x 65024 E4M3 21 / 12.6 (a line of whole 128-byte lines of codes and a bit suits the reads without LDS badly).
+static bool tr_tiles_pay(int64_t n, int64_t rows, int64_t cols, int w)
+{
+    const int64_t lines = (rows + DQT_L - 1) / DQT_L * DQT_L;
+    if (cols % DQT_O == 0 && rows % DQT_L == 0) return true;
+    if (cols * ((rows + 7) / 8) > 0x7FFFFFFF) return true;
+    return rows >= DQT_L && cols >= 96 && n * rows * cols >= ((int64_t)1 << 22) && (w == 8 || rows * 5 >= lines * 3);
+}
+
 template <int FMT, int DST>
 static hipError_t launch_t(const uint8_t *elems, const uint8_t *scales, int64_t rows, int64_t cols, int axis, void *dst,
                            int64_t ld, hipStream_t st, const Batch &batch)
@@ -315,12 +360,18 @@ static hipError_t launch_t(const uint8_t *elems, const uint8_t *scales, int64_t 
     constexpr int64_t esz = DST == DT_F32 ? 4 : 2;
     if (axis == 0) {
         const int64_t tiles = ((cols + DQT_O - 1) / DQT_O) * ((rows + DQT_L - 1) / DQT_L);
-        if (tiles > 0x7FFFFFFF) return hipErrorNotSupported;
+        const bool tiled = tr_tiles_pay(batch.n, rows, cols, w);
+        if (tiled && tiles > 0x7FFFFFFF) return hipErrorNotSupported;
+        const int64_t n_units = cols * ((rows + 7) / 8);
         for (int64_t i = 0; i < batch.n; i += 65535) {
-            const dim3 grid((unsigned)tiles, 1, (unsigned)(batch.n - i < 65535 ? batch.n - i : 65535));
+            const dim3 grid((unsigned)(tiled ? tiles : (n_units + 255) / 256), 1,
+                            (unsigned)(batch.n - i < 65535 ? batch.n - i : 65535));
             const uint8_t *e = elems + i * batch.elems, *sc = scales + i * batch.scales;
             void *d = static_cast<char *>(dst) + i * batch.src * esz;
-            if (cols % DQT_O == 0 && rows % DQT_L == 0)
+            if (!tiled)
+                hipLaunchKernelGGL((dequant_tr_kernel<FMT, DST>), grid, dim3(256), 0, st, e, sc, d, fast_div(cols), rows, ld,
+                                   (uint32_t)n_units, batch);
+            else if (cols % DQT_O == 0 && rows % DQT_L == 0)
                 hipLaunchKernelGGL((dequant_tr_tile_kernel<FMT, DST, true>), grid, dim3(256), 0, st, e, sc, d, cols, rows, ld, batch);
             else
                 hipLaunchKernelGGL((dequant_tr_tile_kernel<FMT, DST, false>), grid, dim3(256), 0, st, e, sc, d, cols, rows, ld, batch);
