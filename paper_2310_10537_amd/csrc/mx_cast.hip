@@ -212,23 +212,37 @@ static hipError_t dispatch_fmt(int fmt, int rnd, uint64_t seed, int axis, const 
     }
 }
 
+// Whether a cast along axis 0 leaves most of each 128-row tile empty, so that one lane per block without LDS is faster (one lane per
+// block / tiles, us).  Float32, E4M3: 3 x 2796200 75 / 106, 15 x 559240 21 / 26, 31 x 270600 14 / 15, but 31 x 67648 6 / 5.4 and
+// 24 x 21840 4 / 3.6.  Stochastic: 3 x 2796200 Float32 150 / 322, 31 x 270600 bf16 33 / 35, 31 x 67648 bf16 13 / 12,
+// 12 x 43688 bf16 9 / 8.  (bf16, to nearest: tiles throughout, 3 x 2796200 77 / 69.)  A work-group without tiles covers 256
+// columns: narrower matrices of a batch would leave its lanes idle.
+static bool few_rows_of_a_tile(int src_dt, int rnd, int64_t n, int64_t rows, int64_t cols)
+{
+    const int64_t size = n * rows * cols;
+    if (cols < 256) return false;
+    if (rnd == ROUND_STOCHASTIC) return rows <= 10 || (rows <= BLOCK && size >= ((int64_t)1 << 20));
+    return src_dt == DT_F32 && (rows <= 6 || (rows <= BLOCK && size >= ((int64_t)1 << (rows <= 24 ? 20 : 22))));
+}
+
 hipError_t launch_cast(const void *src, int src_dt, int64_t rows, int64_t cols, int64_t ld, int axis, int fmt, int rnd,
                        uint8_t *elems, uint8_t *scales, hipStream_t st, uint64_t seed, const Batch &batch)
 {
     // The fast kernels store scale bytes 4 and 16 at a time; a scale array that starts at an odd
     // address (a slice of a larger output, see launch_cast_3d) takes the generic kernels, which
     // store them one by one.
+    const bool tiles = axis == 1 || !few_rows_of_a_tile(src_dt, rnd, batch.n, rows, cols);
     const bool scales_aligned = (reinterpret_cast<uintptr_t>(scales) & 15u) == 0;
     // the kernels built on the hardware converts round to nearest only
     if (scales_aligned && src_dt == DT_BF16 && (rnd == ROUND_RNE || rnd == ROUND_HALF_AWAY)) {
         hipError_t e = launch_cast_bf16_fast(src, rows, cols, ld, axis, fmt, rnd, elems, scales, st, batch);
         if (e != hipErrorNotSupported) return e;
     }
-    if (scales_aligned && src_dt == DT_F32 && (rnd == ROUND_RNE || rnd == ROUND_HALF_AWAY)) {
+    if (tiles && scales_aligned && src_dt == DT_F32 && (rnd == ROUND_RNE || rnd == ROUND_HALF_AWAY)) {
         hipError_t e = launch_cast_f32_fast(src, rows, cols, ld, axis, fmt, rnd, elems, scales, st, batch);
         if (e != hipErrorNotSupported) return e;
     }
-    if (rnd == ROUND_STOCHASTIC && batch.n == 1) {   // (beyond 2^34 elements the generic kernels below draw the same numbers)
+    if (tiles && rnd == ROUND_STOCHASTIC && batch.n == 1) {   // (beyond 2^34 elements the generic kernels below draw the same numbers)
         hipError_t e = launch_cast_sr(src, src_dt, rows, cols, ld, axis, fmt, seed, elems, scales, st);
         if (e != hipErrorNotSupported) return e;
     }

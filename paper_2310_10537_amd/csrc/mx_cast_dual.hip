@@ -309,11 +309,13 @@ static hipError_t launch_dual_fmt(int rnd, const void *src, int src_dt, int64_t 
                             : launch_dual_r<FMT, ROUND_HALF_AWAY>(src, src_dt, rows, cols, ld, e1, s1, e0, s0, st);
 }
 
-// One pass for both axes; two ordinary casts (same bytes) for the rounding modes without hardware converts.
+// One pass for both axes; two ordinary casts (same bytes) for the rounding modes without hardware converts, and for 32 long rows of
+// Float32 to 8 bits, which fill a quarter of a tile (32 x 582272 E5M2: one pass 43 us, two casts 38).
 hipError_t launch_cast_dual(const void *src, int src_dt, int64_t rows, int64_t cols, int64_t ld, int fmt, int rnd,
                             uint8_t *e1, uint8_t *s1, uint8_t *e0, uint8_t *s0, hipStream_t st)
 {
-    if (rnd == ROUND_RNE || rnd == ROUND_HALF_AWAY) {
+    const bool quarter = src_dt == DT_F32 && fmt_bits(fmt) == 8 && rows == BLOCK && cols >= ((int64_t)1 << 17);
+    if (!quarter && (rnd == ROUND_RNE || rnd == ROUND_HALF_AWAY)) {
         hipError_t e;
         switch (fmt) {
             case FP8_E4M3: e = launch_dual_fmt<FP8_E4M3>(rnd, src, src_dt, rows, cols, ld, e1, s1, e0, s0, st); break;
