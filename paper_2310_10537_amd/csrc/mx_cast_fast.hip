@@ -490,20 +490,26 @@ __global__ __launch_bounds__(256) void cast_row_f32_kernel(const float *__restri
     scales[blk0 + lane] = (uint8_t)s;                  // 64 consecutive bytes per wave
 }
 
-// A row kernel numbers its units in 31 bits: slices of a batch, then runs of rows, go to one launch each
-// (multiples of 16 lines, so that the scale bytes of a run stay 16-byte aligned).  go(batch, rows, src, lines
-// before it); hipErrorNotSupported where a single run of 16 rows is too long.
+// Dense rows of whole blocks, slices one after the other: one run of elements, counted in 64 bits
+static bool one_run(const Batch &b, int64_t rows, int64_t cols, int64_t ld)
+{
+    return ld == cols && cols % BLOCK == 0 && (b.n == 1 || b.src == rows * ld);
+}
+
+// Other rows: their units are numbered in 31 bits, so slices of a batch, then runs of rows, go to one launch each (of 16 lines or
+// blocks at a time, so that the scale bytes of a run stay 16-byte aligned).  go(batch, rows, src, lines before it);
+// hipErrorNotSupported where such a run is too long.
 template <typename F>
 static hipError_t for_rows(const Batch &b, int64_t rows, int64_t cols, int64_t ld, int epu, int src_bytes, const void *src, F go)
 {
-    const int64_t upr = (cols + BLOCK - 1) / BLOCK * (BLOCK / epu), most = 0x7FFFFFFF / upr;
+    const int64_t nblk = (cols + BLOCK - 1) / BLOCK, most = 0x7FFFFFFF / (nblk * (BLOCK / epu));
     const char *p = static_cast<const char *>(src);
     if (b.n * rows <= most) return go(b.n, rows, p, (int64_t)0);
-    if (most < 16 || (b.n > 1 && rows % 16)) return hipErrorNotSupported;
+    const int64_t run = nblk % 16 == 0 ? most : most & ~(int64_t)15;
+    if (run < 1 || (b.n > 1 && rows * nblk % 16)) return hipErrorNotSupported;
     for (int64_t i = 0; i < b.n; i++)
-        for (int64_t r = 0; r < rows; r += most & ~(int64_t)15) {
-            const int64_t n = rows - r < (most & ~(int64_t)15) ? rows - r : (most & ~(int64_t)15);
-            const hipError_t e = go((int64_t)1, n, p + (i * b.src + r * ld) * src_bytes, i * rows + r);
+        for (int64_t r = 0; r < rows; r += run) {
+            const hipError_t e = go((int64_t)1, rows - r < run ? rows - r : run, p + (i * b.src + r * ld) * src_bytes, i * rows + r);
             if (e != hipSuccess) return e;
         }
     return hipSuccess;
@@ -514,15 +520,19 @@ static hipError_t launch_row_f32_r(const void *src, int64_t rows, int64_t cols, 
                                    const Batch &batch)
 {
     const int64_t nblk = (cols + BLOCK - 1) / BLOCK;
+    auto wgs_of = [](int64_t waves) { return (waves + 3) / 4; };
+    const int64_t all = batch.n * rows * nblk;
+    if (one_run(batch, rows, cols, ld) && all % 64 == 0 && wgs_of(all / 64) <= 0x7FFFFFFF) {
+        hipLaunchKernelGGL((cast_row_f32_kernel<FMT, RND, true>), dim3((unsigned)wgs_of(all / 64)), dim3(256), 0, st,
+                           static_cast<const float *>(src), RowGeom{}, elems, scales, all / 64);
+        return hipGetLastError();
+    }
     return for_rows(batch, rows, cols, ld, 4, 4, src, [&](int64_t nb, int64_t nr, const char *p, int64_t line0) {
-        const int64_t blocks = nb * nr * nblk, n_waves = (blocks + 63) / 64, wgs = (n_waves + 3) / 4;
+        const int64_t n_waves = (nb * nr * nblk + 63) / 64;
         const RowGeom geom = row_geom(nb, nr, cols, ld, nb > 1 ? batch.src : nr * ld, 4);
-        uint8_t *e = elems + line0 * nblk * (BLOCK * Fmt<FMT>::bits / 8), *sc = scales + line0 * nblk;
-        const float *s = reinterpret_cast<const float *>(p);
-        if (ld == cols && cols % BLOCK == 0 && (nb == 1 || batch.src == nr * ld) && blocks % 64 == 0)
-            hipLaunchKernelGGL((cast_row_f32_kernel<FMT, RND, true>), dim3((unsigned)wgs), dim3(256), 0, st, s, geom, e, sc, n_waves);
-        else
-            hipLaunchKernelGGL((cast_row_f32_kernel<FMT, RND, false>), dim3((unsigned)wgs), dim3(256), 0, st, s, geom, e, sc, n_waves);
+        hipLaunchKernelGGL((cast_row_f32_kernel<FMT, RND, false>), dim3((unsigned)wgs_of(n_waves)), dim3(256), 0, st,
+                           reinterpret_cast<const float *>(p), geom, elems + line0 * nblk * (BLOCK * Fmt<FMT>::bits / 8),
+                           scales + line0 * nblk, n_waves);
         return hipGetLastError();
     });
 }
@@ -557,18 +567,23 @@ static hipError_t launch_fast_t(const void *src, int64_t rows, int64_t cols, int
 {
     if (axis == 1) {
         const int64_t pcols = (cols + BLOCK - 1) / BLOCK * BLOCK;
-        return for_rows(batch, rows, cols, ld, 8, 2, src, [&](int64_t nb, int64_t nr, const char *q, int64_t line0) {
-            const int64_t n = nb * nr * pcols, wgs = (n + 4 * ROW_WAVE_ELEMS - 1) / (4 * ROW_WAVE_ELEMS);
-            const RowGeom geom = row_geom(nb, nr, cols, ld, nb > 1 ? batch.src : nr * ld, 8);
-            uint8_t *e = elems + line0 * (pcols * Fmt<FMT>::bits / 8), *sc = scales + line0 * (pcols / BLOCK);
-            const uint16_t *p = reinterpret_cast<const uint16_t *>(q);
-            const bool flat = ld == cols && pcols == cols && (nb == 1 || batch.src == nr * ld);
-            if (flat && n % (4 * ROW_WAVE_ELEMS) == 0)
-                hipLaunchKernelGGL((cast_row_bf16_kernel<FMT, RND, true, true>), dim3((unsigned)wgs), dim3(256), 0, st, p, geom, e, sc, n);
-            else if (flat)
-                hipLaunchKernelGGL((cast_row_bf16_kernel<FMT, RND, true>), dim3((unsigned)wgs), dim3(256), 0, st, p, geom, e, sc, n);
+        auto wgs_of = [](int64_t n) { return (n + 4 * ROW_WAVE_ELEMS - 1) / (4 * ROW_WAVE_ELEMS); };
+        const int64_t all = batch.n * rows * pcols;
+        if (one_run(batch, rows, cols, ld) && wgs_of(all) <= 0x7FFFFFFF) {
+            const uint16_t *p = static_cast<const uint16_t *>(src);
+            const dim3 grid((unsigned)wgs_of(all));
+            if (all % (4 * ROW_WAVE_ELEMS) == 0)
+                hipLaunchKernelGGL((cast_row_bf16_kernel<FMT, RND, true, true>), grid, dim3(256), 0, st, p, RowGeom{}, elems, scales, all);
             else
-                hipLaunchKernelGGL((cast_row_bf16_kernel<FMT, RND, false>), dim3((unsigned)wgs), dim3(256), 0, st, p, geom, e, sc, n);
+                hipLaunchKernelGGL((cast_row_bf16_kernel<FMT, RND, true>), grid, dim3(256), 0, st, p, RowGeom{}, elems, scales, all);
+            return hipGetLastError();
+        }
+        return for_rows(batch, rows, cols, ld, 8, 2, src, [&](int64_t nb, int64_t nr, const char *q, int64_t line0) {
+            const int64_t n = nb * nr * pcols;
+            const RowGeom geom = row_geom(nb, nr, cols, ld, nb > 1 ? batch.src : nr * ld, 8);
+            hipLaunchKernelGGL((cast_row_bf16_kernel<FMT, RND, false>), dim3((unsigned)wgs_of(n)), dim3(256), 0, st,
+                               reinterpret_cast<const uint16_t *>(q), geom, elems + line0 * (pcols * Fmt<FMT>::bits / 8),
+                               scales + line0 * (pcols / BLOCK), n);
             return hipGetLastError();
         });
     }
