@@ -31,7 +31,8 @@ __global__ __launch_bounds__(256) void cast_row_kernel(const void *__restrict__ 
     constexpr int ND = EPL * w / 32;
     const int64_t stride = (int64_t)gridDim.x * 256;
     const int64_t units_per_row = pcols / EPL;
-    const bool flat = (ld == cols && cols == pcols && stride0 == rows * ld);
+    const bool even = stride0 == rows * ld;         // rows one pitch apart throughout: no second division
+    const bool flat = even && ld == cols && cols == pcols;
 
     for (int64_t u = (int64_t)blockIdx.x * 256 + threadIdx.x; u < n_units; u += stride) {
         int64_t off;     // element offset of this lane's first element in the source
@@ -40,8 +41,9 @@ __global__ __launch_bounds__(256) void cast_row_kernel(const void *__restrict__ 
         if (flat) {
             off = e0 = u * EPL;
         } else {
-            const int64_t r = u / units_per_row, c0 = (u - r * units_per_row) * EPL, i0 = r / rows;
-            off = i0 * stride0 + (r - i0 * rows) * ld + c0;
+            const int64_t r = u / units_per_row, c0 = (u - r * units_per_row) * EPL;
+            off = r * ld + c0;
+            if (!even) off += r / rows * (stride0 - rows * ld);
             e0 = r * cols + c0;
             n_valid = cols - c0 >= EPL ? EPL : cols - c0 > 0 ? (int)(cols - c0) : 0;
         }
