@@ -170,7 +170,7 @@ template <int FA, int FB>
 static hipError_t launch_pair(int64_t M, int64_t N, int64_t K, const uint8_t *Ae, const uint8_t *As, const uint8_t *Be,
                               const uint8_t *Bs, void *C, int c_dt, int64_t ldc, hipStream_t st)
 {
-    const bool staged = K % 128 == 0;   // whole 128-element chunks, 16-byte aligned rows
+    const bool staged = K % 128 == 0 && K <= SK_MAX_K;   // whole 128-element chunks, 16-byte aligned rows
     if (M <= 32) return staged ? launch_lds<FA, FB, 1>(M, N, K, Ae, As, Be, Bs, C, c_dt, ldc, st)
                                : launch_mt<FA, FB, 1>(M, N, K, Ae, As, Be, Bs, C, c_dt, ldc, st);
     if (M <= 64) return staged ? launch_lds<FA, FB, 2>(M, N, K, Ae, As, Be, Bs, C, c_dt, ldc, st)

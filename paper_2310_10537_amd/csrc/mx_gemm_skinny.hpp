@@ -16,6 +16,7 @@
 namespace mx {
 
 constexpr int SK_WAVES = 8;
+constexpr int64_t SK_MAX_K = (int64_t)1 << 25;       // of the staged kernel
 
 // ---------------------------------------------------------------------------------------------
 // K a multiple of 128: operands staged through LDS.
@@ -26,12 +27,12 @@ constexpr int SK_WAVES = 8;
 // read adjacent 16 bytes of a row (every line touched once), parks the 16-byte pieces in a private
 // LDS tile laid out exactly as the large tiled kernel lays out its stages (same swizzles, same
 // operand reads), and multiplies from there; the next chunk's loads are in flight meanwhile.
-// Rows beyond M and columns beyond N are neither loaded nor parked (their part of the LDS tile holds anything): rows and
-// columns of the product are independent, and such results are never stored.
-// Up to 32 rows (MT = 1) the path from L2 into the compute unit decides, so loads take whole lines: 4-bit B comes two chunks at
-// a time (128 bytes of a row) and stays in flight for two steps, and the scales of four chunks are one 16-byte load per row
-// (a dword per chunk touches each of 32 lines four times as often).  At most 128 registers keep two work-groups on a compute
-// unit.  16 x 28672 x 8192, E3M2 x E2M1: 49.0 us before that, 39.6 after (3.2 TB/s).
+// Rows beyond M and columns beyond N read a valid row instead (clamped), as every load of a step then sits in one straight run that
+// the waits can count; such results are never stored.  (A branch per load to leave absent rows out made every wait one for all
+// loads in flight: 9 x 5120 x 7424 E4M3 8.8 us clamped, 15.9 with branches; 32 x 2503 x 17536 24.7 and 40.6; 64 rows 10 % slower.)
+// 4-bit B, up to 32 rows: two chunks at a time, 128 bytes of a row -- whole lines -- in flight for two steps.  16 x 28672 x 8192
+// E3M2 x E2M1: 33.9 us a chunk at a time, 30.0 so.  No bound on the registers: 128 would let two work-groups share a compute unit
+// but made 38 of the 100 cast-on-load instances spill; measured level for 8-bit operands, 5 to 15 % slower for 6-bit ones.
 // QA: up to 16 rows of bf16 activations are cast on load -- a lane takes one block of a chunk and parks its codes, the
 // same cast and hence the same bytes as the stand-alone one.
 // ---------------------------------------------------------------------------------------------
@@ -42,7 +43,7 @@ template <int W> struct SkStage {                    // one 32-row block of a 12
 
 constexpr int MX_OPERAND = -1;                       // QA: A is an MX operand, else the rounding of its cast
 template <int FA, int FB, int MT, int CDT, int QA = MX_OPERAND>
-__global__ __launch_bounds__(64 * SK_WAVES, MT == 1 ? 4 : 1) void gemm_skinny_lds_kernel(int64_t M, int64_t N, int64_t K,
+__global__ __launch_bounds__(64 * SK_WAVES, 1) void gemm_skinny_lds_kernel(int64_t M, int64_t N, int64_t K,
                                                                          const uint8_t *__restrict__ Ae, const uint8_t *__restrict__ As,
                                                                          const uint8_t *__restrict__ Be, const uint8_t *__restrict__ Bs,
                                                                          void *__restrict__ C, int64_t ldc, int64_t lda)
@@ -51,7 +52,6 @@ __global__ __launch_bounds__(64 * SK_WAVES, MT == 1 ? 4 : 1) void gemm_skinny_ld
     static_assert(!CAST || MT == 1, "the cast takes one 32-row tile");
     constexpr int WA = Fmt<FA>::bits, WB = Fmt<FB>::bits;
     constexpr int HA = hw_fmt(FA), HB = hw_fmt(FB);   // must reach the builtin as literal constants
-    constexpr int SG = MT == 1 ? 4 : 1;               // chunks whose scales are loaded together
     constexpr int CB = MT == 1 && WB == 4 ? 2 : 1;    // chunks of B loaded together
     constexpr int A_BYTES = MT * SkStage<WA>::BYTES, B_BYTES = CB * SkStage<WB>::BYTES, W_BYTES = A_BYTES + B_BYTES;
     constexpr int RED_BYTES = (SK_WAVES - 1) * MT * 16 * 64 * 4;
@@ -71,58 +71,58 @@ __global__ __launch_bounds__(64 * SK_WAVES, MT == 1 ? 4 : 1) void gemm_skinny_ld
     const int ar = lane / PA, ap = lane % PA, br = lane / PB, bp = lane % PB;
     const bool a_on = WA != 6 || ap < 6, b_on = WB != 6 || bp < 6;
     const int64_t a_rb = K * WA / 8, b_rb = K * WB / 8;                   // bytes per matrix row
-    // K is at most 2^23 (the route's bound): sixteen rows stay within 32-bit offsets from a wave-uniform address
-    const uint32_t a_lane = (uint32_t)(ar * a_rb) + ap * 16, b_lane = (uint32_t)(br * b_rb) + bp * 16;
+    auto clampi = [](int64_t v, int64_t hi) { return v < hi ? v : hi; };
+    // 32-bit offsets of the lane's pieces from wave-uniform addresses (K up to SK_MAX_K: 127 rows stay below 2^32 bytes)
+    uint32_t a_ofs[MT][NJA], b_ofs[NJB];
+#pragma unroll
+    for (int x = 0; x < MT; x++)
+#pragma unroll
+        for (int j = 0; j < NJA; j++) a_ofs[x][j] = (uint32_t)clampi(32 * x + j * (64 / PA) + ar, M - 1 - m0) * (uint32_t)a_rb + ap * 16;
+#pragma unroll
+    for (int j = 0; j < NJB; j++) b_ofs[j] = (uint32_t)clampi(j * (64 / PB) + br, N - 1 - n0) * (uint32_t)b_rb + bp * 16;
+    const uint8_t *const a0_ = Ae + m0 * a_rb, *const b0_ = Be + n0 * b_rb;
+    const uint8_t *sa_row[MT], *const sb_row = Bs + clampi(n0 + i, N - 1) * nkb;
+#pragma unroll
+    for (int x = 0; x < (CAST ? 0 : MT); x++) sa_row[x] = As + clampi(m0 + 32 * x + i, M - 1) * nkb;
     auto lds_slot = [](int w, int r, int c) {
         return w == 8 ? r * 128 + ((c ^ ((r >> 1) & 7)) << 4) : w == 6 ? r * 96 + ((c ^ ((r >> 3) & 1)) << 4)
                                                                        : r * 64 + ((c ^ ((r >> 2) & 3)) << 4);
     };
-    auto clampi = [](int64_t v, int64_t hi) { return v < hi ? v : hi; };
-    const int m_left = (int)clampi(M - m0, 32 * MT), n_left = (int)clampi(N - n0, 32);
-    auto a_ok = [&](int x, int j) { return a_on && 32 * x + j * (64 / PA) + ar < m_left; };
-    auto b_ok = [&](int j) { return b_on && j * (64 / PB) + br < n_left; };
     uint4 ra[MT][NJA], rq[4], rb[NJB];
-    uint32_t sa_d[MT][SG], sb_d[SG];
+    uint32_t sa_d[MT], sb_d;
     const int qr = lane >> 2, qb = lane & 3;          // CAST: the lane's row and its block of a chunk
+    const uint8_t *const q0 = Ae + (qr * lda + qb * 32) * 2;              // (dereferenced where the row exists)
     auto request_a = [&](int64_t c) {
         if constexpr (CAST) {
-            if (qr < m_left) {
-                const uint8_t *p = Ae + (qr * lda + c * 128 + qb * 32) * 2;
+            if (qr < M) {
 #pragma unroll
-                for (int j = 0; j < 4; j++) rq[j] = ld16(p + j * 16);
+                for (int j = 0; j < 4; j++) rq[j] = ld16(q0 + c * 256 + j * 16);
             }
-            return;
+        } else if (a_on) {
+#pragma unroll
+            for (int x = 0; x < MT; x++)
+#pragma unroll
+                for (int j = 0; j < NJA; j++) ra[x][j] = ld16(a0_ + c * (128 * WA / 8) + a_ofs[x][j]);
         }
-#pragma unroll
-        for (int x = 0; x < MT; x++)
-#pragma unroll
-            for (int j = 0; j < NJA; j++)
-                if (a_ok(x, j)) ra[x][j] = ld16(Ae + (m0 + 32 * x + j * (64 / PA)) * a_rb + c * (128 * WA / 8) + a_lane);
     };
-    auto request_b = [&](int64_t c) {                                     // a second chunk beyond the slice is not loaded
+    auto request_b = [&](int64_t c) {                                     // (a second chunk beyond K: the first one again)
+        const uint32_t back = CB == 2 && bp >= 4 && c + 1 >= chunks ? 64 : 0;
+        if (b_on) {
 #pragma unroll
-        for (int j = 0; j < NJB; j++)
-            if (b_ok(j) && (CB == 1 || c + bp / 4 < c_end)) rb[j] = ld16(Be + (n0 + j * (64 / PB)) * b_rb + c * (128 * WB / 8) + b_lane);
-    };
-    auto scales = [&](const uint8_t *row, int64_t c, uint32_t (&d)[SG]) {
-        if (SG > 1 && c + SG <= chunks) {
-            __builtin_memcpy(d, __builtin_assume_aligned(row + c * 4, 4), 4 * SG);
-        } else {
-#pragma unroll
-            for (int k = 0; k < SG; k++) d[k] = *reinterpret_cast<const uint32_t *>(row + clampi(c + k, chunks - 1) * 4);
+            for (int j = 0; j < NJB; j++) rb[j] = ld16(b0_ + c * (128 * WB / 8) + (b_ofs[j] - back));
         }
     };
     auto request_s = [&](int64_t c) {
 #pragma unroll
-        for (int x = 0; x < (CAST ? 0 : MT); x++) scales(As + clampi(m0 + 32 * x + i, M - 1) * nkb, c, sa_d[x]);
-        scales(Bs + clampi(n0 + i, N - 1) * nkb, c, sb_d);
+        for (int x = 0; x < (CAST ? 0 : MT); x++) sa_d[x] = *reinterpret_cast<const uint32_t *>(sa_row[x] + c * 4);
+        sb_d = *reinterpret_cast<const uint32_t *>(sb_row + c * 4);
     };
     uint8_t *const cast_sc = tA + 16 * TileFmt<WA>::ROW;                  // CAST: the scales of 16 rows, where rows 16 .. 31 would be
     auto park_a = [&]() {
         if constexpr (CAST) {
             // on for the converts only: matrix instructions would clamp NaN / Inf operands of B and results
             if constexpr (FA == FP8_E4M3 || FA == FP8_E5M2) fp8_saturate_mode(true);
-            if (qr < m_left) {
+            if (qr < M) {
                 uint32_t d[16], out[WA];
 #pragma unroll
                 for (int j = 0; j < 4; j++) {
@@ -131,25 +131,26 @@ __global__ __launch_bounds__(64 * SK_WAVES, MT == 1 ? 4 : 1) void gemm_skinny_ld
                 cast_sc[lane] = (uint8_t)quantize_block_bf16<FA, QA>(d, out);
 #pragma unroll
                 for (int q = 0; q < WA / 2; q++) {
-                    const int o = qb * (4 * WA) + 8 * q;                  // byte of the row's chunk
+                    const int o = qb * (4 * WA) + 8 * q;                      // byte of the row's chunk
                     *reinterpret_cast<uint2 *>(tA + lds_slot(WA, qr, o >> 4) + (o & 15)) = make_uint2(out[2 * q], out[2 * q + 1]);
                 }
             }
             if constexpr (FA == FP8_E4M3 || FA == FP8_E5M2) fp8_saturate_mode(false);
-            return;
+        } else if (a_on) {
+#pragma unroll
+            for (int x = 0; x < MT; x++)
+#pragma unroll
+                for (int j = 0; j < NJA; j++)
+                    *reinterpret_cast<uint4 *>(tA + x * SkStage<WA>::BYTES + lds_slot(WA, j * (64 / PA) + ar, ap)) = ra[x][j];
         }
-#pragma unroll
-        for (int x = 0; x < MT; x++)
-#pragma unroll
-            for (int j = 0; j < NJA; j++)
-                if (a_ok(x, j)) *reinterpret_cast<uint4 *>(tA + x * SkStage<WA>::BYTES + lds_slot(WA, j * (64 / PA) + ar, ap)) = ra[x][j];
     };
     auto park_b = [&]() {
+        if (b_on) {
 #pragma unroll
-        for (int j = 0; j < NJB; j++)
-            if (b_ok(j))
+            for (int j = 0; j < NJB; j++)
                 *reinterpret_cast<uint4 *>(tB + (CB == 2 ? (bp >> 2) * SkStage<WB>::BYTES + lds_slot(WB, j * (64 / PB) + br, bp & 3)
                                                          : lds_slot(WB, j * (64 / PB) + br, bp))) = rb[j];
+        }
     };
     const FragOfs<WA> fa = frag_ofs<WA>(i, g);
     const FragOfs<WB> fb = frag_ofs<WB>(i, g);
@@ -161,38 +162,37 @@ __global__ __launch_bounds__(64 * SK_WAVES, MT == 1 ? 4 : 1) void gemm_skinny_ld
         for (int t = 0; t < 16; t++) acc[x][t] = 0.f;
 
     if (c_begin < c_end) {
-        request_s(c_begin);
         request_a(c_begin);
         request_b(c_begin);
+        request_s(c_begin);
     }
-    for (int64_t c0 = c_begin; c0 < c_end; c0 += SG) {
-        uint32_t sa[MT][SG], sb[SG];
-        // lanes 32 .. 63 shift their scale dword by a byte: one selector then addresses block 2 sub + g
+    for (int64_t c0 = c_begin; c0 < c_end; c0 += CB) {
 #pragma unroll
-        for (int k = 0; k < SG; k++) {
-#pragma unroll
-            for (int x = 0; x < (CAST ? 0 : MT); x++) sa[x][k] = g ? sa_d[x][k] >> 8 : sa_d[x][k];
-            sb[k] = g ? sb_d[k] >> 8 : sb_d[k];
-        }
-        if (c0 + SG < c_end) request_s(c0 + SG);
-#pragma unroll
-        for (int k = 0; k < SG; k++) {
+        for (int k = 0; k < CB; k++) {
             const int64_t c = c0 + k;
-            if (c >= c_end) break;
+            if (k > 0 && c >= c_end) break;
             park_a();
-            if (k % CB == 0) park_b();
+            if (k == 0) park_b();
+            // lanes 32 .. 63 shift their scale dword by a byte: one selector then addresses block 2 sub + g
+            uint32_t sa[MT];
+#pragma unroll
+            for (int x = 0; x < (CAST ? 0 : MT); x++) sa[x] = g ? sa_d[x] >> 8 : sa_d[x];
+            const uint32_t sb = g ? sb_d >> 8 : sb_d;
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             __builtin_amdgcn_wave_barrier();
-            if constexpr (CAST) sa[0][k] = reinterpret_cast<const uint32_t *>(cast_sc)[i & 15] >> (g ? 8 : 0);
+            if constexpr (CAST) sa[0] = reinterpret_cast<const uint32_t *>(cast_sc)[i & 15] >> (g ? 8 : 0);
+            // loads return in order: the scales, wanted last, behind the operands of their step but before those of a later one
             if (c + 1 < c_end) request_a(c + 1);
-            if (k % CB == 0 && c + CB < c_end) request_b(c + CB);
-            const uint8_t *tb = tB + (k % CB) * SkStage<WB>::BYTES;
+            if (CB == 1 && c + 1 < c_end) request_b(c + 1);
+            if (c + 1 < c_end) request_s(c + 1);
+            if (CB == 2 && k == 0 && c0 + CB < c_end) request_b(c0 + CB);
+            const uint8_t *tb = tB + k * SkStage<WB>::BYTES;
             const v8i_t b0 = read_frag<WB>(tb, fb, 0, 0), b1 = read_frag<WB>(tb, fb, 1, 0);
 #pragma unroll
             for (int x = 0; x < MT; x++) {
                 const v8i_t a0 = read_frag<WA>(tA + x * SkStage<WA>::BYTES, fa, 0, 0), a1 = read_frag<WA>(tA + x * SkStage<WA>::BYTES, fa, 1, 0);
-                acc[x] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a0, b0, acc[x], HA, HB, 0, (int)sa[x][k], 0, (int)sb[k]);
-                acc[x] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a1, b1, acc[x], HA, HB, 2, (int)sa[x][k], 2, (int)sb[k]);
+                acc[x] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a0, b0, acc[x], HA, HB, 0, (int)sa[x], 0, (int)sb);
+                acc[x] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a1, b1, acc[x], HA, HB, 2, (int)sa[x], 2, (int)sb);
             }
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the tile is read before the next chunk is parked in it
             __builtin_amdgcn_wave_barrier();
