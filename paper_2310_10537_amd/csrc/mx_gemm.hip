@@ -132,9 +132,11 @@ enum Route {
     MID,         // 64 x 64 to 128 x 128 tiles (mx_gemm_mid.hpp): any shape
     WHOLE,       // 256 x 256 tiles (mx_gemm_tile*.hpp), nothing left over
     INTERIOR,    // 256 x 256 tiles over the largest interior they cover, MID for the L-shaped fringe
-    DIRECT       // K beyond 2^23
+    DIRECT       // what none of the others takes: K = 0; K beyond 2^23 and no multiple of 128, more than 128 rows
 };
 
+// Beyond the MID kernel's sizes (K over 2^23, over 2^24 tiles of 64 x 64): up to 128 rows SHARED_K, then 256 x 256 tiles, then
+// SHARED_K in groups of 128 rows.  A long K needs the waves: the direct kernel walks all of it with one wave per 32 x 32 tile.
 // Measured boundaries (E4M3 pairs unless said otherwise; us):
 //  - SHARED_K or MID.  Up to 32 rows the weight stream decides and the shared-K kernel reads it best; 33 to 64 rows: 64 x 1024 x 4096
 //    level, 64 x 4096 x 4096 16 against 11, 64 x 11008 x 4096 31 against 15.  Above 64 rows the shared-K kernel holds
@@ -146,11 +148,17 @@ enum Route {
 //    5000 x 11008 x 4096 (817 whole tiles) 280 against 291.
 static Route route_of(int64_t M, int64_t N, int64_t K, int fmtA, int fmtB)
 {
-    if (!gemm_mid_applies(M, N, K, fmtA, fmtB)) return DIRECT;
+    const int64_t M0 = M & ~(int64_t)255, N0 = N & ~(int64_t)255;
+    const bool shared_ok = gemm_skinny_applies(M, N, K, fmtA, fmtB);
+    if (!gemm_mid_applies(M, N, K, fmtA, fmtB)) {
+        if (shared_ok && M <= 128) return SHARED_K;
+        if (gemm_tiled_applies(M0, N0, K, fmtA, fmtB)) return M0 == M && N0 == N ? WHOLE : INTERIOR;
+        return shared_ok ? SHARED_K : DIRECT;
+    }
     const int64_t tiles64 = ((M + 63) / 64) * ((N + 63) / 64);
     const bool shared = M <= 32 || (M <= 64 ? tiles64 < 64 : tiles64 < 24 && K < 4096);
-    if (shared && gemm_skinny_applies(M, N, K, fmtA, fmtB)) return SHARED_K;
-    const int64_t M0 = M & ~(int64_t)255, N0 = N & ~(int64_t)255, whole = (M0 / 256) * (N0 / 256);
+    if (shared && shared_ok) return SHARED_K;
+    const int64_t whole = (M0 / 256) * (N0 / 256);
     if (M0 == M && N0 == N) return whole > 64 && gemm_tiled_applies(M, N, K, fmtA, fmtB) ? WHOLE : MID;
     return whole > 192 && gemm_tiled_applies(M0, N0, K, fmtA, fmtB) ? INTERIOR : MID;
 }

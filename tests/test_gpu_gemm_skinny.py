@@ -60,3 +60,21 @@ def test_cast_on_load_of_nan_and_infinity(mx, fa, fb):
             got = mx.mx_gemm_qa(x, fa, rnd, *b, fb, dtype=torch.float32)
             assert torch.equal(got.isnan(), want.isnan()) and not got[0, 64:].isnan().any()
             assert torch.equal(torch.nan_to_num(got, 1.0, 2.0, 3.0), torch.nan_to_num(want, 1.0, 2.0, 3.0))
+
+
+@pytest.mark.parametrize("M,N,K", [(2, 33, 2 ** 23 + 128), (130, 40, 2 ** 23 + 256), (3, 33, 2 ** 25 + 128)], ids=lambda v: str(v))
+def test_k_beyond_2_23(mx, M, N, K):
+    """Long K, where each wave walks an eighth: the end of the range of the other kernels, and of the staged form's 32-bit offsets."""
+    g = torch.Generator(device="cuda").manual_seed(M)
+
+    def operand(rows):
+        e = torch.randint(0, 256, (rows, K // 2), dtype=torch.uint8, device="cuda", generator=g)
+        s = torch.randint(120, 130, (rows, K // 32), dtype=torch.uint8, device="cuda", generator=g)
+        return e, s
+
+    A, B = operand(M), operand(N)
+    C = mx.mx_gemm(*A, 4, *B, 4, K)
+    a, b = (mx.mx_dequantize(*t, 4, r, K, 1).double() for t, r in ((A, M), (B, N)))
+    want, scale = a @ b.T, a.abs() @ b.abs().T
+    # Float32 sums of exact products: K / 64 additions in eight chains, errors of either sign
+    assert bool(((C.double() - want).abs() <= scale * 2.0 ** -24 * (K / 512) ** 0.5 * 4).all())

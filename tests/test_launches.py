@@ -30,3 +30,25 @@ def test_long_dense_rows_are_one_run(trace):
         # padded rows: a few launches of the same kernel
         (status, seen), = trace([quantize(20, 1 << 30, (1 << 30) + 8, dt)])
         assert status == 0 and 2 <= len(seen) <= 3 and set(names(seen)) == {kernel}, dt
+
+
+def gemm(M, N, K, fa=0, fb=0, dt=F32):
+    return "mx_gemm", (M, N, K, P, P, fa, P, P, fb, P, dt, N, 0)
+
+
+def kernel_of(trace, *args, **kw):
+    (status, seen), = trace([gemm(*args, **kw)])
+    assert status == 0
+    return names(seen)
+
+
+def test_gemm_beyond_the_sizes_of_the_small_tiles(trace):
+    long_k = (1 << 23) + 128
+    staged, plain = "gemm_skinny_lds_kernel", "gemm_skinny_kernel"
+    assert kernel_of(trace, 1, 64, long_k) == kernel_of(trace, 128, 64, long_k) == kernel_of(trace, 300, 64, long_k) == [staged]
+    assert kernel_of(trace, 16, 64, (1 << 25) + 128) == kernel_of(trace, 300, 64, 1 << 26) == [plain]     # 32-bit offsets end
+    assert kernel_of(trace, 100, 64, (1 << 23) + 32) == [plain]
+    assert kernel_of(trace, 300, 64, (1 << 23) + 32) == ["gemm_direct_kernel"]
+    # more than 2^36 entries of C: 256 x 256 tiles as far as those go, in 2^24 of them
+    assert all("tile" in k for k in kernel_of(trace, 1 << 19, 1 << 19, 1024, dt=BF16))
+    assert kernel_of(trace, (1 << 20) + 256, 1 << 20, 1024) == [staged]
