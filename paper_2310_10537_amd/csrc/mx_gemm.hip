@@ -132,12 +132,17 @@ enum Route {
     MID,         // 64 x 64 to 128 x 128 tiles (mx_gemm_mid.hpp): any shape
     WHOLE,       // 256 x 256 tiles (mx_gemm_tile*.hpp), nothing left over
     INTERIOR,    // 256 x 256 tiles over the largest interior they cover, MID for the L-shaped fringe
-    DIRECT       // what none of the others takes: K = 0; K beyond 2^23 and no multiple of 128, more than 128 rows
+    DIRECT       // short K, and what none of the others takes: K = 0; K beyond 2^23 and no multiple of 128, more than 128 rows
 };
 
 // Beyond the MID kernel's sizes (K over 2^23, over 2^24 tiles of 64 x 64): up to 128 rows SHARED_K, then 256 x 256 tiles, then
 // SHARED_K in groups of 128 rows.  A long K needs the waves: the direct kernel walks all of it with one wave per 32 x 32 tile.
 // Measured boundaries (E4M3 pairs unless said otherwise; us):
+//  - DIRECT for short K, more than 64 rows: a tile's load, wait, multiply and store take their time however few steps lie between.
+//    MID / DIRECT: 593 x 7040 x 64 10.6 / 5.9, 8192 x 8192 x 64 64 / 43, 1536 x 8704 x 128 19 / 19 and E3M2 20 / 12,
+//    8192 x 8192 x 128 61 / 77 and E3M2 61 / 50, 8192 x 8192 x 192 81 / 73, 1536 x 8704 x 256 21 / 31. Narrow operands load less per step, and
+//    the line moves on: E3M2 593 x 7040 x 384 13 / 12, 4096 x 1536 x 384 14 / 16; E4M3 x E2M1 1000 x 1000 x 256 5.3 / 5, 593 x 7040
+//    level, 1536 x 8704 21 / 26; a partial last step, E4M3 768 x 2560 x 288 7.0 / 6.0, with E2M1 593 x 7040 x 288 10.5 / 9.0.
 //  - SHARED_K or MID.  Up to 32 rows the weight stream decides and the shared-K kernel reads it best; 33 to 64 rows: 64 x 1024 x 4096
 //    level, 64 x 4096 x 4096 16 against 11, 64 x 11008 x 4096 31 against 15.  Above 64 rows the shared-K kernel holds
 //    so many accumulators that one work-group fills a compute unit: 128 x 1024 x 4096 22 against 11, 256 x 4096 x 4096 25 against
@@ -146,6 +151,15 @@ enum Route {
 //    2048 x 4096 x 4096 (128) 41 against 42, E3M2 x E2M1 36 against 40; 4096^3 (256) 61 against 85.
 //  - A problem with a fringe costs an extra launch or two that each leave most of the chip idle: 1000 x 4096 x 4096 60 against 26,
 //    5000 x 11008 x 4096 (817 whole tiles) 280 against 291.
+static bool direct_pays(int64_t M, int64_t N, int64_t K, int fmtA, int fmtB)
+{
+    if (M <= 64 || (M + 63) / 64 > 65535) return false;                     // (the direct kernel's grid)
+    const int narrow = (fmt_bits(fmtA) < 8) + (fmt_bits(fmtB) < 8);
+    if (K < 256) return !(narrow == 0 && K == 128 && M * N > ((int64_t)1 << 24));
+    const bool tail = K % 128 != 0;                                          // one more, partial step in the MID kernel
+    return K < 512 && M * N * K <= (narrow == 2 ? (int64_t)1 << 31 : narrow == 1 ? (int64_t)(tail ? 3 : 1) << 29 : (int64_t)(tail ? 5 : 0) << 27);
+}
+
 static Route route_of(int64_t M, int64_t N, int64_t K, int fmtA, int fmtB)
 {
     const int64_t M0 = M & ~(int64_t)255, N0 = N & ~(int64_t)255;
@@ -158,6 +172,7 @@ static Route route_of(int64_t M, int64_t N, int64_t K, int fmtA, int fmtB)
     const int64_t tiles64 = ((M + 63) / 64) * ((N + 63) / 64);
     const bool shared = M <= 32 || (M <= 64 ? tiles64 < 64 : tiles64 < 24 && K < 4096);
     if (shared && shared_ok) return SHARED_K;
+    if (direct_pays(M, N, K, fmtA, fmtB)) return DIRECT;
     const int64_t whole = (M0 / 256) * (N0 / 256);
     if (M0 == M && N0 == N) return whole > 64 && gemm_tiled_applies(M, N, K, fmtA, fmtB) ? WHOLE : MID;
     return whole > 192 && gemm_tiled_applies(M0, N0, K, fmtA, fmtB) ? INTERIOR : MID;

@@ -52,3 +52,18 @@ def test_gemm_beyond_the_sizes_of_the_small_tiles(trace):
     # more than 2^36 entries of C: 256 x 256 tiles as far as those go, in 2^24 of them
     assert all("tile" in k for k in kernel_of(trace, 1 << 19, 1 << 19, 1024, dt=BF16))
     assert kernel_of(trace, (1 << 20) + 256, 1 << 20, 1024) == [staged]
+
+
+def test_gemm_of_short_k(trace):
+    direct, mid = ["gemm_direct_kernel"], ["gemm_mid_kernel"]
+    E4M3, E3M2, E2M1 = 0, 2, 4
+    for K in (32, 96, 224):
+        assert kernel_of(trace, 593, 7040, K) == kernel_of(trace, 8192, 8192, K, E3M2, E2M1) == direct, K
+    assert kernel_of(trace, 4096, 4096, 128) == kernel_of(trace, 8192, 8192, 128, E4M3, E2M1) == direct
+    assert kernel_of(trace, 8192, 8192, 128) == mid                               # 8-bit pairs, many tiles
+    assert kernel_of(trace, 593, 7040, 384, E3M2, E2M1) == direct and kernel_of(trace, 4096, 1536, 384, E3M2, E2M1) == mid
+    assert kernel_of(trace, 1000, 1000, 256, E4M3, E2M1) == direct and kernel_of(trace, 593, 7040, 256, E4M3, E2M1) == mid
+    assert kernel_of(trace, 1000, 1000, 256) == kernel_of(trace, 593, 1000, 512, E2M1, E2M1) == mid
+    assert kernel_of(trace, 768, 2560, 288) == direct and kernel_of(trace, 768, 2560, 352) == mid
+    assert kernel_of(trace, 593, 7040, 288, E4M3, E2M1) == direct and kernel_of(trace, 593, 7040, 416, E4M3, E2M1) == mid
+    assert kernel_of(trace, 1 << 23, 64, 64) == mid                               # more rows than the direct grid holds
