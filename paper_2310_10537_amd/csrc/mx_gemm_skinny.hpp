@@ -80,10 +80,29 @@ __global__ __launch_bounds__(64 * SK_WAVES, 1) void gemm_skinny_lds_kernel(int64
         for (int j = 0; j < NJA; j++) a_ofs[x][j] = (uint32_t)clampi(32 * x + j * (64 / PA) + ar, M - 1 - m0) * (uint32_t)a_rb + ap * 16;
 #pragma unroll
     for (int j = 0; j < NJB; j++) b_ofs[j] = (uint32_t)clampi(j * (64 / PB) + br, N - 1 - n0) * (uint32_t)b_rb + bp * 16;
-    const uint8_t *const a0_ = Ae + m0 * a_rb, *const b0_ = Be + n0 * b_rb;
-    const uint8_t *sa_row[MT], *const sb_row = Bs + clampi(n0 + i, N - 1) * nkb;
+    uint32_t sa_ofs[MT];
+    const uint32_t sb_ofs = (uint32_t)clampi(i, N - 1 - n0) * (uint32_t)nkb;
 #pragma unroll
-    for (int x = 0; x < (CAST ? 0 : MT); x++) sa_row[x] = As + clampi(m0 + 32 * x + i, M - 1) * nkb;
+    for (int x = 0; x < MT; x++) sa_ofs[x] = (uint32_t)clampi(32 * x + i, M - 1 - m0) * (uint32_t)nkb;
+    // A wave-uniform address and a 32-bit offset per lane, kept apart up to the load (the empty asm statements hide them from the
+    // loop optimiser): it would carry a 64-bit address per load instead -- with 128 rows 50 vector registers, and 8-bit operands spill
+    // (512 x 128 x 3456 E4M3 21.7 us, 16.5 so).  Up to 32 rows there is room for them, and one add less per load measured 5-10 % faster.
+    typedef const __attribute__((address_space(1))) uint8_t *global_ptr;
+    auto scalar = [](const uint8_t *p) {
+        global_ptr g = (global_ptr)p;
+        if constexpr (MT > 1) asm volatile("" : "+s"(g));
+        return g;
+    };
+    auto piece = [](global_ptr p, uint32_t o) {           // 16 bytes
+        if constexpr (MT > 1) asm volatile("" : "+v"(o));
+        typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+        const u32x4 v = *(const __attribute__((address_space(1))) u32x4 *)(p + o);
+        return make_uint4(v.x, v.y, v.z, v.w);
+    };
+    auto dword = [](global_ptr p, uint32_t o) {
+        if constexpr (MT > 1) asm volatile("" : "+v"(o));
+        return *(const __attribute__((address_space(1))) uint32_t *)(p + o);
+    };
     auto lds_slot = [](int w, int r, int c) {
         return w == 8 ? r * 128 + ((c ^ ((r >> 1) & 7)) << 4) : w == 6 ? r * 96 + ((c ^ ((r >> 3) & 1)) << 4)
                                                                        : r * 64 + ((c ^ ((r >> 2) & 3)) << 4);
@@ -98,24 +117,31 @@ __global__ __launch_bounds__(64 * SK_WAVES, 1) void gemm_skinny_lds_kernel(int64
 #pragma unroll
                 for (int j = 0; j < 4; j++) rq[j] = ld16(q0 + c * 256 + j * 16);
             }
-        } else if (a_on) {
+        } else {
+            const global_ptr p = scalar(Ae + m0 * a_rb + c * (128 * WA / 8));
+            if (a_on) {
 #pragma unroll
-            for (int x = 0; x < MT; x++)
+                for (int x = 0; x < MT; x++)
 #pragma unroll
-                for (int j = 0; j < NJA; j++) ra[x][j] = ld16(a0_ + c * (128 * WA / 8) + a_ofs[x][j]);
+                    for (int j = 0; j < NJA; j++) ra[x][j] = piece(p, a_ofs[x][j]);
+            }
         }
     };
     auto request_b = [&](int64_t c) {                                     // (a second chunk beyond K: the first one again)
+        const global_ptr p = scalar(Be + n0 * b_rb + c * (128 * WB / 8));
         const uint32_t back = CB == 2 && bp >= 4 && c + 1 >= chunks ? 64 : 0;
         if (b_on) {
 #pragma unroll
-            for (int j = 0; j < NJB; j++) rb[j] = ld16(b0_ + c * (128 * WB / 8) + (b_ofs[j] - back));
+            for (int j = 0; j < NJB; j++) rb[j] = piece(p, b_ofs[j] - back);
         }
     };
     auto request_s = [&](int64_t c) {
+        if constexpr (!CAST) {
+            const global_ptr p = scalar(As + m0 * nkb + c * 4);
 #pragma unroll
-        for (int x = 0; x < (CAST ? 0 : MT); x++) sa_d[x] = *reinterpret_cast<const uint32_t *>(sa_row[x] + c * 4);
-        sb_d = *reinterpret_cast<const uint32_t *>(sb_row + c * 4);
+            for (int x = 0; x < MT; x++) sa_d[x] = dword(p, sa_ofs[x]);
+        }
+        sb_d = dword(scalar(Bs + n0 * nkb + c * 4), sb_ofs);
     };
     uint8_t *const cast_sc = tA + 16 * TileFmt<WA>::ROW;                  // CAST: the scales of 16 rows, where rows 16 .. 31 would be
     auto park_a = [&]() {
