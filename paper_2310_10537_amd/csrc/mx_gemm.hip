@@ -186,6 +186,22 @@ static bool qa_fused_pays(int64_t M, int64_t N) { return N / 256 <= 2 && (M / 25
 // 9.1 us, 1 x 11008 x 4096 28.2 -> 11.7, 16 x 11008 x 4096 29.0 -> 13.7, 16 x 28672 x 8192 68.3 -> 63.4, E3M2 x E2M1 46.7 -> 41.9.
 static bool qa_few_rows_pays(int64_t M, int64_t K) { return M <= 16 && K % 128 == 0; }
 
+// Whether A can do without scratch memory where the few-rows kernel does not cast it: more than 128 rows with K below 512 or no multiple
+// of 128, round to nearest.  Such problems are cast in registers when that is faster, and when scratch memory is refused.
+static bool qa_in_registers(int64_t M, int64_t K, int rnd)
+{
+    return M > 128 && (M + 63) / 64 <= 65535 && (K % 128 != 0 || K < 512) && (rnd == ROUND_RNE || rnd == ROUND_HALF_AWAY);
+}
+
+// The cast in registers takes about 4 + K (0.018 + 0.024 w) us, w = M N / 2^20 waves of a SIMD (at least one): 300 x 500 x 160 9.8,
+// 768 x 2560 x 288 21, 1000 x 4096 x 128 19, 4096 x 1536 x 96 24 (E4M3; a seventh less below 8 bits).  Cast and product apart take
+// about 9 us when these times are short, and 21 with a stream-ordered allocation and its release.
+static bool qa_in_registers_pays(int64_t M, int64_t N, int64_t K, int fmtA, bool own_scratch)
+{
+    const int64_t w16 = M * N >> 16;                                        // sixteenths of w
+    return K * (18 + 24 * (w16 > 16 ? w16 : 16) / 16) < (own_scratch ? 4000 : fmt_bits(fmtA) < 8 ? 20000 : 17000);
+}
+
 static size_t mx_bytes16(int64_t M, int64_t K, int fmt) { return ((size_t)M * (size_t)K * fmt_bits(fmt) / 8 + 15) & ~(size_t)15; }
 
 // A problem whose M or N is not a multiple of the 256 x 256 tile may be cut into the largest interior of whole tiles and an L-shaped
@@ -201,17 +217,20 @@ hipError_t launch_gemm(int64_t M, int64_t N, int64_t K, const uint8_t *A_elems, 
     // Quantize-on-load.  The fused tiled kernel casts each A tile once per column of output tiles and reads it as bf16 that
     // often, so it pays only for narrow outputs (measured: up to two tile columns), and only when there are enough tiles to
     // fill the chip, since the stand-alone cast always runs on every compute unit.  Up to 16 rows are cast by the
-    // shared-K kernel.  Every other problem casts A once
+    // shared-K kernel, a short K in registers by the direct one.  Every other problem casts A once
     // into a workspace (the same cast kernel, hence the same bytes, as mx_quantize) and runs the plain product on it.
     const bool fused = a_bf16 && (rnd == ROUND_RNE || rnd == ROUND_HALF_AWAY) && (route == WHOLE || route == INTERIOR) &&
                        gemm_tiled_fuses_cast(fmtA, fmtB) && qa_fused_pays(M0, N0);
     if (a_bf16 && route == SHARED_K && qa_few_rows_pays(M, K) && (rnd == ROUND_RNE || rnd == ROUND_HALF_AWAY))
         return launch_gemm_skinny_qa(M, N, K, a_bf16, lda, rnd, fmtA, B_elems, B_scales, fmtB, C, c_dt, ldc, st);
     if (a_bf16 && !fused && M > 0 && N > 0 && K > 0) {
+        const bool registers = !int8 && qa_in_registers(M, K, rnd);
+        auto in_registers = [&]() { return launch_gemm_direct_qa(M, N, K, a_bf16, lda, rnd, fmtA, B_elems, B_scales, fmtB, C, c_dt, ldc, st); };
+        if (registers && qa_in_registers_pays(M, N, K, fmtA, g_ws.active)) return in_registers();
         const size_t eb = mx_bytes16(M, K, fmtA), sb = (size_t)M * (size_t)(K / BLOCK);
         uint8_t *ws = nullptr;
         hipError_t e = ws_acquire(eb + sb, st, &ws);
-        if (e != hipSuccess) return e;
+        if (e != hipSuccess) return registers ? in_registers() : e;
         e = launch_cast(a_bf16, DT_BF16, M, K, lda, 1, fmtA, rnd, ws, ws + eb, st);
         if (e == hipSuccess)
             e = launch_gemm(M, N, K, ws, ws + eb, nullptr, 0, ROUND_RNE, fmtA, B_elems, B_scales, fmtB, C, c_dt, ldc, st);

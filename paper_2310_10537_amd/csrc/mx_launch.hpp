@@ -90,6 +90,10 @@ bool gemm_mid_applies(int64_t M, int64_t N, int64_t K, int fmtA, int fmtB);
 hipError_t launch_gemm_mid(int64_t M, int64_t N, int64_t K, const uint8_t *Ae, const uint8_t *As, int fmtA, const uint8_t *Be,
                            const uint8_t *Bs, int fmtB, void *C, int c_dt, int64_t ldc, hipStream_t st);
 
+// bf16 A cast in registers, no scratch memory: any M up to 64 * 65535, any N and K, round to nearest
+hipError_t launch_gemm_direct_qa(int64_t M, int64_t N, int64_t K, const void *a_bf16, int64_t lda, int rnd, int fmtA, const uint8_t *Be,
+                                 const uint8_t *Bs, int fmtB, void *C, int c_dt, int64_t ldc, hipStream_t st);
+
 // At most 128 rows of A: eight waves per 32 columns of C share the K range (FP8 / FP6 / FP4 operands)
 hipError_t launch_gemm_skinny_qa(int64_t M, int64_t N, int64_t K, const void *a_bf16, int64_t lda, int rnd, int fmtA, const uint8_t *Be,
                                  const uint8_t *Bs, int fmtB, void *C, int c_dt, int64_t ldc, hipStream_t st);   // M <= 16, K % 128 == 0

@@ -92,7 +92,7 @@ def trace(runtime, calls):
             if name == "alloc":
                 seen.append(("alloc", int(numbers[0])))
                 continue
-            head = name.split("(")[0].removeprefix("void ").split("<", 1)
+            head = name.replace("(anonymous namespace)::", "").split("(")[0].removeprefix("void ").split("<", 1)
             args = tuple(a.strip() for a in head[1].rstrip(">").split(",")) if len(head) > 1 else ()
             g = tuple(int(v) for v in numbers)
             seen.append((head[0].split("::")[-1], args, g[:3], g[3]))

@@ -46,3 +46,26 @@ def test_matches_model(mx, oracle, M, N, K, fa, fb):
         mx.mx_gemm(dev[0], dev[1], fa, dev[2], dev[3], fb, K, out=buf[:, :N])
         assert torch.equal(buf[:, :N], Cd.to(dt)), (dt, pad)
         assert pad == 0 or bool((buf[:, N:] == 7.0).all())
+
+
+# one and two blocks of K, partial steps, fewer and more than a tile's rows and columns; a long odd K whose scratch is refused
+@pytest.mark.parametrize("fa,fb", [(0, 0), (1, 3), (2, 4), (3, 2), (4, 1)], ids=lambda v: str(v))
+def test_cast_in_registers(mx, fa, fb):
+    """Short K of many rows is cast without scratch memory: the same bits as the cast and the product apart."""
+    for M, N, K in ((129, 65, 32), (300, 500, 96), (257, 64, 160), (700, 130, 128)):
+        x = inputs.student_t_bf16((M, K), seed=M + fa)
+        x[0, :32] = 0
+        x[M - 1, K - 32:] = 0x0003                                 # a block of subnormals
+        x[1, 3], x[2, K - 1] = 0x7F80, 0x7FC1                      # infinity, NaN
+        a = torch.full((M, K + 24), 3.0e38, dtype=torch.bfloat16, device="cuda")[:, :K]
+        a.copy_(to_dev(x))
+        b = mx.mx_quantize(to_dev(inputs.gaussian_f32((N, K), seed=N + fb, std=0.02)), 1, fb)
+        for rnd in (0, 1):
+            ma = mx.mx_quantize(a, 1, fa, rnd)
+            for dt in (torch.float32, torch.bfloat16):
+                want = mx.mx_gemm(*ma, fa, *b, fb, K, dtype=dt)
+                buf = torch.full((M, N + 9), 7.0, dtype=dt, device="cuda")
+                mx.mx_gemm_qa_ws(a, fa, rnd, *b, fb, None, out=buf[:, :N])
+                got = buf[:, :N]
+                assert torch.equal(got.isnan(), want.isnan()) and torch.equal(got.nan_to_num(1.0, 2.0, 3.0), want.nan_to_num(1.0, 2.0, 3.0))
+                assert bool((buf[:, N:] == 7.0).all()), (M, N, K)

@@ -67,3 +67,36 @@ def test_gemm_of_short_k(trace):
     assert kernel_of(trace, 768, 2560, 288) == direct and kernel_of(trace, 768, 2560, 352) == mid
     assert kernel_of(trace, 593, 7040, 288, E4M3, E2M1) == direct and kernel_of(trace, 593, 7040, 416, E4M3, E2M1) == mid
     assert kernel_of(trace, 1 << 23, 64, 64) == mid                               # more rows than the direct grid holds
+
+
+def gemm_qa(M, N, K, fa=0, fb=0, rnd=0):
+    return "mx_gemm_qa", (M, N, K, P, K, fa, rnd, P, P, fb, P, BF16, N, 0)
+
+
+def test_cast_on_load_of_short_k_in_registers(trace):
+    kernel = "gemm_direct_qa_kernel"
+    for M, N, K in ((300, 500, 160), (768, 2560, 256), (1000, 4096, 128), (129, 64, 288)):
+        (status, seen), = trace([gemm_qa(M, N, K)])
+        assert status == 0 and names(seen) == [kernel], (M, N, K)
+    for M, N, K in ((300, 500, 512), (1000, 4096, 160), (4096, 1536, 256), (300, 500, 544), (128, 500, 96)):
+        (status, seen), = trace([gemm_qa(M, N, K)])
+        assert status == 0 and names(seen)[0] == "alloc" and kernel not in names(seen), (M, N, K)
+    # scratch memory of the caller costs nothing: the line lies lower
+    ws = 1 << 30
+    for K, registers in ((64, True), (160, False)):
+        call = "mx_gemm_qa_ws", (300, 500, K, P, K, 0, 0, P, P, 0, P, BF16, 500, P, ws, 0)
+        (status, seen), = trace([call])
+        assert status == 0 and "alloc" not in names(seen) and (kernel in names(seen)) == registers, K
+
+
+def test_cast_on_load_when_scratch_is_refused(trace):
+    """What never needed scratch memory does not fail without it; what always did still says so."""
+    for M, N, K in ((300, 500, 4128), (1000, 4096, 160), (129, 64, 32), (5000, 64, 480)):
+        for rnd in (0, 1):
+            (status, seen), = trace([gemm_qa(M, N, K, rnd=rnd)], refuse=1)
+            assert status == 0 and names(seen) == ["gemm_direct_qa_kernel"], (M, N, K)
+    for call in (gemm_qa(300, 500, 4096), gemm_qa(128, 500, 4128), gemm_qa(300, 500, 4128, rnd=2), gemm_qa(300, 500, 4128, 5, 5)):
+        (status, seen), = trace([call], refuse=1)
+        assert status == 8 and seen == [], call
+    (status, seen), = trace([gemm_qa(16, 500, 4096)], refuse=1)
+    assert status == 0 and names(seen) == ["gemm_skinny_lds_kernel"]
