@@ -133,15 +133,16 @@ def test_shapes(mx, oracle, shape):
 @pytest.mark.parametrize("shape,dt", [  # few tiles: the kernel that shares the K range among eight waves, rows in groups of 128
                                       ((512, 256, 384), torch.float32), ((256, 768, 128), torch.bfloat16),
                                       ((256, 512, 1536), torch.float32), ((512, 256, 512), torch.bfloat16),
-                                      # at least 32 tiles: the LDS-tiled kernel.  8, 16 and 32 tile rows: the XCD-banded
-                                      # tile orders (sub-bands of 1, 2, 4 rows), and a tile count that is no multiple of 8
+                                      # 32 tiles of 256 x 256 and more: tiles up to 128 x 128.  8, 16 and 32 rows of them and more: the XCD-banded
+                                      # tile orders, and a tile count that is no multiple of 8
                                       ((2048, 1280, 512), torch.float32), ((4096, 512, 512), torch.bfloat16),
                                       ((8192, 256, 512), torch.float32), ((1792, 1280, 1536), torch.bfloat16),
                                       # K = 5, 6, 7 and 9 steps of 128: a partial last scale group of 1, 2, 3 and 1 steps
                                       ((1024, 2048, 640), torch.float32), ((2048, 1024, 768), torch.bfloat16),
                                       ((1024, 2048, 896), torch.float32), ((2048, 1024, 1152), torch.float32)])
 def test_tiled_kernel_full_tiles(mx, oracle, fa, fb, shape, dt):
-    """Shapes made of whole 256 x 256 x 128 tiles; blocks get very different scales so that a scale
+    """Shapes made of whole 256 x 256 x 128 tiles, up to 64 of them: the kernel with 64 x 64 to 128 x 128 tiles, or the one that shares
+    K among eight waves (more tiles: test_gpu_gemm_tiles.py).  Blocks get very different scales so that a scale
     byte read for the wrong row, block or K step shows up."""
     M, N, K = shape
     rng = np.random.default_rng(M + N + fa)
@@ -158,7 +159,7 @@ def test_tiled_kernel_full_tiles(mx, oracle, fa, fb, shape, dt):
 @pytest.mark.parametrize("shape,dt", [((1024, 2048, 1536), torch.float32), ((2048, 1024, 512), torch.bfloat16),
                                       ((1024, 2048, 896), torch.float32), ((256, 512, 640), torch.float32)])
 def test_tiled_kernel_all_format_pairs(mx, oracle, fa, fb, shape, dt):
-    """Every FP8 / FP6 / FP4 pair on whole tiles: each element width has its own LDS layout and
+    """Every FP8 / FP6 / FP4 pair on shapes of up to 64 tiles of 256 x 256 (more: test_gpu_gemm_tiles.py): each element width has its own LDS layout and
     direct-load shape, so every (row, K block) must come back from the right slot.  Per-block
     scales differ widely, and the exactly representable pairs are held to the plain 1e-5 bound."""
     M, N, K = shape
@@ -176,7 +177,7 @@ def test_tiled_kernel_all_format_pairs(mx, oracle, fa, fb, shape, dt):
 def test_tiled_kernel_one_hot_rows(mx, oracle, fa, fb, M, N, K):
     """A is one-hot per row (element k = m mod K is 1.0, scale byte 127): C[m][n] must reproduce
     B[n][m mod K] exactly, which pins the K position of every element of every LDS slot
-    (32 tiles: the LDS-tiled kernel; 2 tiles: the kernel that shares K among eight waves)."""
+    (2048 x 1024: the kernel with tiles up to 128 x 128; 512 x 256: the one that shares K among eight waves)."""
     a = np.zeros((M, K), np.float32)
     a[np.arange(M), np.arange(M) % K] = 1.0
     b = inputs.gaussian_f32((N, K), seed=95, std=1.0)
@@ -461,7 +462,7 @@ def test_config5_sampled(mx, oracle, rnd):
 def test_tiled_kernel_output_leading_dimension(mx, oracle, dt, pad):
     """C as a view with a leading dimension (the header allows any ldc >= N): the padding columns
     must stay untouched."""
-    M, N, K = (2048, 1024, 512) if pad == 2 else (256, 512, 512)      # the LDS-tiled kernel / the shared-K kernel
+    M, N, K = (2048, 1024, 512) if pad == 2 else (256, 512, 512)      # tiles up to 128 x 128 / the shared-K kernel
     a = inputs.gaussian_f32((M, K), seed=120)
     b = inputs.gaussian_f32((N, K), seed=121, std=0.02)
     ea, sa = oracle.quantize(a, 1, 0)
@@ -692,10 +693,8 @@ def test_int8_gemm_full_size_sampled(mx, oracle):
                                    (2048, 1030, 640), (2050, 1024, 544)])
 @pytest.mark.parametrize("fa,fb", [(0, 0), (2, 4)], ids=["e4m3xe4m3", "e3m2xe2m1"])
 def test_ragged_shapes_with_a_tiled_interior(mx, oracle, shape, fa, fb):
-    """M or N not a multiple of 256.  With an interior of at least 32 whole tiles that interior goes
-    to the tiled kernel and the L-shaped fringe to the kernel for other shapes (to the direct kernel
-    when K is not a multiple of 128); smaller problems are one launch of the latter.  Also with A
-    cast on load."""
+    """M or N not a multiple of 256: one launch of the kernel with tiles up to 128 x 128, K = 544 with a partial last step.  (An
+    interior of more than 192 whole tiles goes to the 256 x 256 tiles: test_gpu_gemm_tiles.py.)  Also with A cast on load."""
     M, N, K = shape
     a = inputs.student_t_bf16((M, K), seed=140)
     b = inputs.gaussian_f32((N, K), seed=141, std=0.02)
@@ -911,11 +910,12 @@ def test_mfma_stream_probe_counts_its_instructions(mx, fmt):
     assert int(clk.max()) < 16 * iters * 64 * 20
 
 
-@pytest.mark.parametrize("fa,fb,shape", [(0, 0, (1280, 15360, 512)), (2, 4, (2560, 7680, 640)), (4, 1, (1024, 2048, 1024))],
-                         ids=["e4m3_300_tiles", "e3m2xe2m1_300_tiles", "e2m1xe5m2_32_tiles"])
+@pytest.mark.parametrize("fa,fb,shape", [(0, 0, (1280, 15360, 512)), (2, 4, (2560, 7680, 640)), (4, 1, (1024, 2048, 1024)),
+                                            (4, 1, (2560, 2048, 1024))],
+                         ids=["e4m3_300_tiles", "e3m2xe2m1_300_tiles", "e2m1xe5m2_32_tiles", "e2m1xe5m2_80_tiles"])
 def test_whole_and_half_width_tiles_give_the_same_bits(mx, oracle, fa, fb, shape):
     """Problems whose last round of 256 x 256 tiles is at most half full run their last tile columns as
-    256 x 128 tiles, and problems of at most 128 tiles run on those alone.  An entry's K chain does not
+    256 x 128 tiles, and problems of 65 to 128 tiles run on those alone (smaller ones on tiles up to 128 x 128).  An entry's K chain does not
     depend on the tile it lies in: the same columns computed inside a problem of another size (150 or 160
     tiles: whole tiles only) have the same bits, and sampled entries match the reference."""
     M, N, K = shape
@@ -929,7 +929,7 @@ def test_whole_and_half_width_tiles_give_the_same_bits(mx, oracle, fa, fb, shape
             part = mx.mx_gemm(ga[0], ga[1], fa, gb[0][lo:hi].contiguous(), gb[1][lo:hi].contiguous(), fb, K)
             assert torch.equal(part.view(torch.int32), C[:, lo:hi].contiguous().view(torch.int32)), (lo, hi)
     else:
-        # 32 tiles run as 64 half-width tiles; five copies of B side by side are 160 whole tiles
+        # 80 tiles run as 160 half-width tiles, 32 as 128 of 128 x 128; five copies of B side by side are 400 or 160 whole tiles
         big = mx.mx_gemm(ga[0], ga[1], fa, gb[0].repeat(5, 1), gb[1].repeat(5, 1), fb, K)
         for r in range(5):
             assert torch.equal(big[:, r * N:(r + 1) * N].contiguous().view(torch.int32), C.view(torch.int32)), r

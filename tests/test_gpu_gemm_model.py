@@ -133,7 +133,7 @@ def quantized_operands(oracle, M, N, K, fa, fb, seed, wide):
 @pytest.mark.parametrize("fa,fb", [(0, 0), (1, 0), (2, 4), (2, 2), (4, 4), (0, 3)], ids=lambda v: str(v))
 @pytest.mark.parametrize("wide", [False, True], ids=["gauss", "student_t"])
 def test_tiled_kernel_matches_model(mx, oracle, fa, fb, wide):
-    """32 whole 256 x 256 tiles, K = 640 (five K steps of the tiled kernel, a partial scale
+    """2048 x 1024, 128 tiles of 128 x 128, and K = 640 (five K steps, a partial scale
     group): 8192 sampled entries plus the corners of the first and last tile, bit for bit."""
     M, N, K = 2048, 1024, 640
     ea, sa, eb, sb = quantized_operands(oracle, M, N, K, fa, fb, 300 + 10 * fa + fb, wide)

@@ -100,3 +100,21 @@ def test_cast_on_load_when_scratch_is_refused(trace):
         assert status == 8 and seen == [], call
     (status, seen), = trace([gemm_qa(16, 500, 4096)], refuse=1)
     assert status == 0 and names(seen) == ["gemm_skinny_lds_kernel"]
+
+
+def test_shapes_of_the_tile_tests_reach_their_kernels(trace):
+    """tests/test_gpu_gemm_tiles.py on half-width and whole tiles, on an interior with a fringe, and cast on load by the tiles."""
+    pytest.importorskip("torch")
+    import test_gpu_gemm_tiles as t
+    wide = ("gemm_tile_kernel", "gemm_tile16_kernel", "gemm_tile8_kernel")
+    cases = [(shapes, half, shape, fa, fb) for shapes, half in ((t.HALF, True), (t.WHOLE, False), (t.INTERIOR, False))
+             for shape in shapes for fa in range(5) for fb in range(5)]
+    for (shapes, half, shape, fa, fb), (status, seen) in zip(cases, trace([gemm(*shape, fa, fb) for _, _, shape, fa, fb in cases])):
+        name, args = seen[0][:2]
+        assert status == 0 and name in wide, (shape, fa, fb)
+        assert (name == "gemm_tile8_kernel" and args[-1] == "4") == half, (shape, fa, fb)           # four waves: half-width tiles
+        assert len(seen) == (1 if shapes is not t.INTERIOR else 1 + (shape[0] % 256 > 0) + (shape[1] % 256 > 0)), shape
+    M, N, K = t.NARROW
+    (status, seen), = trace([gemm_qa(M, N, K)])
+    assert status == 0 and seen[0][0] == "gemm_tile_kernel" and seen[0][1][3] == "true"       # casts on load
+    assert names(seen)[1:] == ["alloc", "cast_row_bf16_kernel", "gemm_skinny_lds_kernel"]     # the last 32 rows

@@ -38,7 +38,7 @@ def pair(mx, M, N, K, fa, fb, rnd, dt, seed):
 
 @pytest.mark.parametrize("fa,fb,rnd", [(0, 0, 0), (2, 4, 1), (4, 1, 2)], ids=["e4m3", "e3m2xe2m1_away", "e2m1xe5m2_trunc"])
 def test_two_calls_in_a_row_second_smaller(mx, fa, fb, rnd):
-    # tiled route (32 whole tiles), then a smaller ragged problem on the shared-K / direct kernels
+    # 128 x 128 tiles, then a smaller ragged problem and one row
     pair(mx, 2048, 1024, 1024, fa, fb, rnd, torch.bfloat16, 900)
     pair(mx, 200, 136, 288, fa, fb, rnd, torch.float32, 902)
     pair(mx, 1, 64, 32, fa, fb, rnd, torch.float32, 904)
