@@ -30,9 +30,12 @@ constexpr int64_t SK_MAX_K = (int64_t)1 << 25;       // of the staged kernel
 // Rows beyond M and columns beyond N read a valid row instead (clamped), as every load of a step then sits in one straight run that
 // the waits can count; such results are never stored.  (A branch per load to leave absent rows out made every wait one for all
 // loads in flight: 9 x 5120 x 7424 E4M3 8.8 us clamped, 15.9 with branches; 32 x 2503 x 17536 24.7 and 40.6; 64 rows 10 % slower.)
-// 4-bit B, up to 32 rows: two chunks at a time, 128 bytes of a row -- whole lines -- in flight for two steps.  16 x 28672 x 8192
-// E3M2 x E2M1: 33.9 us a chunk at a time, 30.0 so.  No bound on the registers: 128 would let two work-groups share a compute unit
-// but made 38 of the 100 cast-on-load instances spill; measured level for 8-bit operands, 5 to 15 % slower for 6-bit ones.
+// Up to 8 rows (FEW) one load brings all of A: 1 x 28672 x 8192 E4M3 x E2M1 29.7 us with the loads of 32 rows, 26.7 without.
+// 4-bit B, up to 32 rows: two chunks at a time, 128 bytes of a row -- whole lines -- in flight for two steps; and the scales of four
+// chunks in one 16-byte load per row, which waits in LDS for its chunks: a dword per chunk touches each line four times as often, in
+// a cache that B streams through.  16 x 28672 x 8192 E3M2 x E2M1, weights from HBM: a chunk and a dword at a time 49.8 us, two
+// chunks 43.0, with the groups 36.4.
+// No bound on the registers: 128 would always let two work-groups share a compute unit, but made 38 of the 100 cast-on-load instances spill.
 // QA: up to 16 rows of bf16 activations are cast on load -- a lane takes one block of a chunk and parks its codes, the
 // same cast and hence the same bytes as the stand-alone one.
 // ---------------------------------------------------------------------------------------------
@@ -42,18 +45,20 @@ template <int W> struct SkStage {                    // one 32-row block of a 12
 };
 
 constexpr int MX_OPERAND = -1;                       // QA: A is an MX operand, else the rounding of its cast
-template <int FA, int FB, int MT, int CDT, int QA = MX_OPERAND>
+// FEW: at most 8 rows (16 of 4 bits), what one wave-wide load of A brings
+template <int FA, int FB, int MT, int CDT, int QA = MX_OPERAND, bool FEW = false>
 __global__ __launch_bounds__(64 * SK_WAVES, 1) void gemm_skinny_lds_kernel(int64_t M, int64_t N, int64_t K,
                                                                          const uint8_t *__restrict__ Ae, const uint8_t *__restrict__ As,
                                                                          const uint8_t *__restrict__ Be, const uint8_t *__restrict__ Bs,
                                                                          void *__restrict__ C, int64_t ldc, int64_t lda)
 {
     constexpr bool CAST = QA != MX_OPERAND;          // A: bf16 [M][lda], at most 16 rows
-    static_assert(!CAST || MT == 1, "the cast takes one 32-row tile");
+    static_assert((!CAST && !FEW) || MT == 1, "one 32-row tile");
     constexpr int WA = Fmt<FA>::bits, WB = Fmt<FB>::bits;
     constexpr int HA = hw_fmt(FA), HB = hw_fmt(FB);   // must reach the builtin as literal constants
     constexpr int CB = MT == 1 && WB == 4 ? 2 : 1;    // chunks of B loaded together
-    constexpr int A_BYTES = MT * SkStage<WA>::BYTES, B_BYTES = CB * SkStage<WB>::BYTES, W_BYTES = A_BYTES + B_BYTES;
+    constexpr bool GROUPS = CB == 2;                  // scales of four chunks in one load, by way of LDS
+    constexpr int A_BYTES = MT * SkStage<WA>::BYTES, B_BYTES = CB * SkStage<WB>::BYTES, W_BYTES = A_BYTES + B_BYTES + (GROUPS ? 1024 : 0);
     constexpr int RED_BYTES = (SK_WAVES - 1) * MT * 16 * 64 * 4;
     constexpr int LDS_BYTES = SK_WAVES * W_BYTES > RED_BYTES ? SK_WAVES * W_BYTES : RED_BYTES;
     __shared__ __attribute__((aligned(16))) uint8_t lds[LDS_BYTES];
@@ -67,7 +72,7 @@ __global__ __launch_bounds__(64 * SK_WAVES, 1) void gemm_skinny_lds_kernel(int64
 
     // ---- staging: lane -> (row l / P, 16-byte piece l % P) of a wave-wide load; P pieces per row chunk
     constexpr int PA = WA == 4 ? 4 : 8, PB = WB == 4 ? 4 * CB : 8;       // (6-bit: pieces 6 and 7 stay idle)
-    constexpr int NJA = SkStage<WA>::NJ, NJB = CB * SkStage<WB>::NJ;
+    constexpr int NJA = FEW ? 1 : SkStage<WA>::NJ, NJB = CB * SkStage<WB>::NJ;
     const int ar = lane / PA, ap = lane % PA, br = lane / PB, bp = lane % PB;
     const bool a_on = WA != 6 || ap < 6, b_on = WB != 6 || bp < 6;
     const int64_t a_rb = K * WA / 8, b_rb = K * WB / 8;                   // bytes per matrix row
@@ -135,6 +140,16 @@ __global__ __launch_bounds__(64 * SK_WAVES, 1) void gemm_skinny_lds_kernel(int64
             for (int j = 0; j < NJB; j++) rb[j] = piece(p, b_ofs[j] - back);
         }
     };
+    // GROUPS: lanes 0 .. 31 fetch the scale bytes of rows of A, lanes 32 .. 63 of B (CAST: all of B); the last group of a row is
+    // its last 16 bytes and sits further back in the slot
+    uint8_t *const tS = tB + B_BYTES;
+    const uint8_t *const srow = g == 0 && !CAST ? As + (m0 + clampi(i, M - 1 - m0)) * nkb : Bs + (n0 + clampi(i, N - 1 - n0)) * nkb;
+    uint4 sg = make_uint4(0, 0, 0, 0);
+    auto group_at = [&](int64_t c) { return c + 4 <= chunks ? c : chunks >= 4 ? chunks - 4 : c; };
+    auto request_g = [&](int64_t c) {
+        if (chunks >= 4) __builtin_memcpy(&sg, __builtin_assume_aligned(srow + group_at(c) * 4, 4), 16);
+        else sg.x = *reinterpret_cast<const uint32_t *>(srow + c * 4);             // fewer than four chunks: one per wave
+    };
     auto request_s = [&](int64_t c) {
         if constexpr (!CAST) {
             const global_ptr p = scalar(As + m0 * nkb + c * 4);
@@ -188,29 +203,48 @@ __global__ __launch_bounds__(64 * SK_WAVES, 1) void gemm_skinny_lds_kernel(int64
         for (int t = 0; t < 16; t++) acc[x][t] = 0.f;
 
     if (c_begin < c_end) {
+        if constexpr (GROUPS) request_g(c_begin);
         request_a(c_begin);
         request_b(c_begin);
-        request_s(c_begin);
+        if constexpr (!GROUPS) request_s(c_begin);
     }
+    int pos = 0;                                      // GROUPS: the chunk's dword in its group's slot
     for (int64_t c0 = c_begin; c0 < c_end; c0 += CB) {
+        if constexpr (GROUPS) {
+            if (((c0 - c_begin) & 3) == 0) {
+                *reinterpret_cast<uint4 *>(tS + lane * 16) = sg;
+                pos = (int)(c0 - group_at(c0));
+                if (c0 + 4 < c_end) request_g(c0 + 4);
+            }
+        }
 #pragma unroll
         for (int k = 0; k < CB; k++) {
             const int64_t c = c0 + k;
             if (k > 0 && c >= c_end) break;
             park_a();
             if (k == 0) park_b();
-            // lanes 32 .. 63 shift their scale dword by a byte: one selector then addresses block 2 sub + g
-            uint32_t sa[MT];
+            uint32_t sa[MT], sb;
+            if constexpr (!GROUPS) {
 #pragma unroll
-            for (int x = 0; x < (CAST ? 0 : MT); x++) sa[x] = g ? sa_d[x] >> 8 : sa_d[x];
-            const uint32_t sb = g ? sb_d >> 8 : sb_d;
+                for (int x = 0; x < (CAST ? 0 : MT); x++) sa[x] = sa_d[x];
+                sb = sb_d;
+            }
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             __builtin_amdgcn_wave_barrier();
-            if constexpr (CAST) sa[0] = reinterpret_cast<const uint32_t *>(cast_sc)[i & 15] >> (g ? 8 : 0);
-            // loads return in order: the scales, wanted last, behind the operands of their step but before those of a later one
+            if constexpr (GROUPS) {
+                if constexpr (!CAST) sa[0] = *reinterpret_cast<const uint32_t *>(tS + i * 16 + pos * 4);
+                sb = *reinterpret_cast<const uint32_t *>(tS + 512 + i * 16 + pos * 4);
+                pos++;
+            }
+            if constexpr (CAST) sa[0] = reinterpret_cast<const uint32_t *>(cast_sc)[i & 15];
+            // lanes 32 .. 63 shift their scale dword by a byte: one selector then addresses block 2 sub + g
+            sb = g ? sb >> 8 : sb;
+#pragma unroll
+            for (int x = 0; x < MT; x++) sa[x] = g ? sa[x] >> 8 : sa[x];
+            // loads return in order: the scales, wanted last, behind the operands of their step
             if (c + 1 < c_end) request_a(c + 1);
             if (CB == 1 && c + 1 < c_end) request_b(c + 1);
-            if (c + 1 < c_end) request_s(c + 1);
+            if (!GROUPS && c + 1 < c_end) request_s(c + 1);
             if (CB == 2 && k == 0 && c0 + CB < c_end) request_b(c0 + CB);
             const uint8_t *tb = tB + k * SkStage<WB>::BYTES;
             const v8i_t b0 = read_frag<WB>(tb, fb, 0, 0), b1 = read_frag<WB>(tb, fb, 1, 0);
