@@ -150,7 +150,7 @@ enum Route {
 //  - MID or 256 x 256 tiles.  2048^3 (64 whole tiles, one 128 x 128 tile per compute unit) 19 against 15, E2M1 15 against 12;
 //    2048 x 4096 x 4096 (128) 41 against 42, E3M2 x E2M1 36 against 40; 4096^3 (256) 61 against 85.
 //  - A problem with a fringe costs an extra launch or two that each leave most of the chip idle: 1000 x 4096 x 4096 60 against 26,
-//    5000 x 11008 x 4096 (817 whole tiles) 280 against 291.
+//    5000 x 11008 x 4096 (817 whole tiles) 280 against 291; the line in between: interior_pays.
 static bool direct_pays(int64_t M, int64_t N, int64_t K, int fmtA, int fmtB)
 {
     if (M <= 64 || (M + 63) / 64 > 65535) return false;                     // (the direct kernel's grid)
@@ -158,6 +158,22 @@ static bool direct_pays(int64_t M, int64_t N, int64_t K, int fmtA, int fmtB)
     if (K < 256) return !(narrow == 0 && K == 128 && M * N > ((int64_t)1 << 24));
     const bool tail = K % 128 != 0;                                          // one more, partial step in the MID kernel
     return K < 512 && M * N * K <= (narrow == 2 ? (int64_t)1 << 31 : narrow == 1 ? (int64_t)(tail ? 3 : 1) << 29 : (int64_t)(tail ? 5 : 0) << 27);
+}
+
+// Whether an interior of 129 to 192 whole tiles with a fringe goes to 256 x 256 tiles: one or two more launches against a K loop that
+// runs at two thirds of the rate or less, so the longer K the better, and the sooner the narrower the operands of both sides.
+// MID / INTERIOR, us: fringe on one side, 3100 x 3072 x 4096 E4M3 59 / 54, E3M2 58 / 46, E3M2 x E2M1 49 / 39, E4M3 x E2M1 47 / 51; K = 2048
+// 33 / 34, 33 / 28, 28 / 25; E3M2 K = 1024 22 / 20; on both sides, 3340 x 3340 x 4096 65 / 62, 69 / 59, 53 / 52, 49 / 62, K = 8192 122 / 110,
+// 129 / 104, 97 / 91, 92 / 107.  Interiors of 100 tiles: MID is ahead (2600 x 2560 x 4096 E4M3 34 / 43) but for 6-bit pairs (40 / 40; K = 8192 76 / 69).
+static bool interior_pays(int64_t M, int64_t N, int64_t K, int64_t whole, int fmtA, int fmtB)
+{
+    if (whole > 192) return true;
+    const int a = fmt_bits(fmtA), b = fmt_bits(fmtB);
+    const bool both = M % 256 != 0 && N % 256 != 0;
+    if (a + b == 12 && a != b) return !both && whole > 184 && K >= 4096;      // 8 x 4 bits
+    if (whole <= (a + b == 12 && !both && K >= 4096 ? 96 : 128)) return false;
+    if (both) return K >= (a + b == 12 || a + b == 10 ? 4096 : 6144);
+    return K >= (a + b == 16 ? 4096 : a + b == 12 ? 1024 : 2048);
 }
 
 static Route route_of(int64_t M, int64_t N, int64_t K, int fmtA, int fmtB)
@@ -175,7 +191,7 @@ static Route route_of(int64_t M, int64_t N, int64_t K, int fmtA, int fmtB)
     if (direct_pays(M, N, K, fmtA, fmtB)) return DIRECT;
     const int64_t whole = (M0 / 256) * (N0 / 256);
     if (M0 == M && N0 == N) return whole > 64 && gemm_tiled_applies(M, N, K, fmtA, fmtB) ? WHOLE : MID;
-    return whole > 192 && gemm_tiled_applies(M0, N0, K, fmtA, fmtB) ? INTERIOR : MID;
+    return interior_pays(M, N, K, whole, fmtA, fmtB) && gemm_tiled_applies(M0, N0, K, fmtA, fmtB) ? INTERIOR : MID;
 }
 
 // whether the fused quantize-on-load tiled kernel beats cast + plain tiled kernel (256 x 256 tiles)

@@ -118,3 +118,15 @@ def test_shapes_of_the_tile_tests_reach_their_kernels(trace):
     (status, seen), = trace([gemm_qa(M, N, K)])
     assert status == 0 and seen[0][0] == "gemm_tile_kernel" and seen[0][1][3] == "true"       # casts on load
     assert names(seen)[1:] == ["alloc", "cast_row_bf16_kernel", "gemm_skinny_lds_kernel"]     # the last 32 rows
+
+
+def test_interior_of_129_to_192_tiles(trace):
+    E4M3, E3M2, E2M1 = 0, 2, 4
+    one, two = (3100, 3072), (3340, 3340)                                          # 144 and 169 whole tiles
+    for (M, N), K, fa, fb, interior in ((one, 4096, E4M3, E4M3, True), (one, 2048, E4M3, E4M3, False), (one, 1024, E3M2, E3M2, True),
+                                        (one, 2048, E3M2, E2M1, True), (one, 4096, E4M3, E2M1, False), ((3100, 4096), 4096, E4M3, E2M1, True),
+                                        (two, 4096, E4M3, E4M3, False), (two, 8192, E4M3, E4M3, True), (two, 4096, E3M2, E2M1, True),
+                                        (two, 2048, E3M2, E3M2, False), (two, 8192, E2M1, E4M3, False), ((2600, 2560), 8192, E2M1, E2M1, False),
+                                        ((2600, 2560), 4096, E3M2, E3M2, True)):
+        (status, seen), = trace([gemm(M, N, K, fa, fb)])
+        assert status == 0 and (seen[0][0] != "gemm_mid_kernel") == interior, (M, N, K, fa, fb)
