@@ -230,17 +230,13 @@ static bool few_rows_of_a_tile(int src_dt, int rnd, int64_t n, int64_t rows, int
 hipError_t launch_cast(const void *src, int src_dt, int64_t rows, int64_t cols, int64_t ld, int axis, int fmt, int rnd,
                        uint8_t *elems, uint8_t *scales, hipStream_t st, uint64_t seed, const Batch &batch)
 {
-    // The fast kernels store scale bytes 4 and 16 at a time; a scale array that starts at an odd
-    // address (a slice of a larger output, see launch_cast_3d) takes the generic kernels, which
-    // store them one by one.
     const bool tiles = axis == 1 || !few_rows_of_a_tile(src_dt, rnd, batch.n, rows, cols);
-    const bool scales_aligned = (reinterpret_cast<uintptr_t>(scales) & 15u) == 0;
     // the kernels built on the hardware converts round to nearest only
-    if (scales_aligned && src_dt == DT_BF16 && (rnd == ROUND_RNE || rnd == ROUND_HALF_AWAY)) {
+    if (src_dt == DT_BF16 && (rnd == ROUND_RNE || rnd == ROUND_HALF_AWAY)) {
         hipError_t e = launch_cast_bf16_fast(src, rows, cols, ld, axis, fmt, rnd, elems, scales, st, batch);
         if (e != hipErrorNotSupported) return e;
     }
-    if (tiles && scales_aligned && src_dt == DT_F32 && (rnd == ROUND_RNE || rnd == ROUND_HALF_AWAY)) {
+    if (tiles && src_dt == DT_F32 && (rnd == ROUND_RNE || rnd == ROUND_HALF_AWAY)) {
         hipError_t e = launch_cast_f32_fast(src, rows, cols, ld, axis, fmt, rnd, elems, scales, st, batch);
         if (e != hipErrorNotSupported) return e;
     }

@@ -294,8 +294,8 @@ static hipError_t launch_mid_t(const TileArgs &a)
     return hipGetLastError();
 }
 
-// The tile: the largest of 64 x 64, 64 x 128 and 128 x 128 that still gives no compute unit two tiles while another has
-// none -- a smaller one re-reads the operands more often, a larger one leaves compute units idle.  E4M3 pairs, 64 x 64 / 64 x 128 /
+// The tile: the smallest of 64 x 64, 64 x 128 and 128 x 128 whose tiles all run at once, one per compute unit -- a smaller one takes a
+// second round and re-reads the operands more often, a larger one leaves compute units idle; 128 x 128 where none does.  E4M3 pairs, 64 x 64 / 64 x 128 /
 // 128 x 128: 256 x 4096 x 4096 11.6 / 15.1 / 19.8 us, 512 x 4096 x 4096 19.5 / 16.6 / 20.8, 129 x 11008 x 4096 30.6 / 32.6 / 24.2,
 // 1000 x 4096 x 4096 37.3 / 29.5 / 25.8.  Three stages (four for the smallest tile) keep the loads ahead of one work-group per compute
 // unit; with more tiles than compute units two resident work-groups hide more than a third stage does, so a pair whose
