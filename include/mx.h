@@ -231,12 +231,14 @@ int mx_dequantize(const void *elems, const uint8_t *scales, mx_format_t fmt,
  * largest product, which is exact for FP6 E2M3 / FP4 E2M1 operands and loses at
  * most 14 * 2^-14 of each run's largest product otherwise.
  * Which kernel runs depends on the shape and the formats only, never on the
- * data or on timing, so a result is reproducible.  Problems with at most 128
- * rows of A, problems that are not made of whole 256 x 256 tiles (K a multiple
- * of 128) and problems of fewer than 32 such tiles split K over the eight waves
- * of a work-group and add the eight partial sums in a fixed order: a different
- * Float32 rounding than the K order of the LDS-tiled kernel, which takes the
- * large problems.
+ * data or on timing, so a result is reproducible.  Most problems add the
+ * products of an entry in the order of K: whole 256 x 256 tiles (K a multiple of
+ * 128), smaller tiles for every other size, and one wave per 32 x 32 entries for
+ * a short K, all with the same bits.  Problems of few rows (up to 32; up to 64
+ * where N is small), small ones (fewer than 24 tiles of 64 x 64, K below 4096)
+ * and those with K beyond 2^23 split K over the eight waves of a work-group
+ * instead and add the eight partial sums in a fixed order: a different Float32
+ * rounding.
  * C is row-major [M][N] of type c_dt with leading dimension ldc >= N (elements;
  * any value, a multiple of 16 bytes is fastest); the C pointer is 16-byte
  * aligned; bf16 output is the Float32 accumulator rounded to nearest even.
@@ -262,17 +264,19 @@ int mx_gemm(int64_t M, int64_t N, int64_t K,
  * elements, a multiple of 8) and cast to fmtA with rounding rnd while it is
  * loaded.  The result is bit-identical to mx_quantize(A, axis 1) followed by
  * mx_gemm.
- * Three routes serve it, chosen by shape.  Problems made of whole 256 x 256
- * output tiles with FP8 / FP6 / FP4 formats and K a multiple of 128 (at least
- * 512) run the LDS-tiled kernel: with 8-bit formats, at most two tile columns
- * and at least 256 tiles the cast happens inside its K loop (one launch, no
- * scratch); otherwise A is first cast into scratch memory of
- * M*K*(bits/8 + 1/32) bytes (MX_INT8 takes the same route, and large MX_INT8
- * products take scratch of their own, see mx_gemm).  Problems that mx_gemm
- * gives to its kernel for few rows / few tiles / ragged shapes cast A into
- * scratch as well; what remains (K not a multiple of 128) casts in registers
- * in the direct kernel.  The in-kernel casts round to nearest:
- * MX_ROUND_TOWARD_ZERO always casts into scratch first; MX_ROUND_STOCHASTIC is
+ * The routes, chosen by shape:
+ *   - up to 16 rows with K a multiple of 128 that mx_gemm gives to its kernel for
+ *     few rows: cast by that kernel (no scratch);
+ *   - 8-bit formats on whole 256 x 256 tiles, at most two columns and at least 256
+ *     of them: cast in the K loop of the tiled kernel (no scratch; a fringe of rows
+ *     or columns beside the tiles is a product of its own and may need some);
+ *   - more than 128 rows and a K below 512 or no multiple of 128: cast in registers
+ *     (no scratch) where that is faster, otherwise as the rest; and in registers
+ *     too when scratch memory is refused, so such a call never fails for want of it;
+ *   - the rest: A is cast into scratch memory of M*K*(bits/8 + 1/32) bytes first
+ *     (MX_INT8 too, whose large products take scratch of their own, see mx_gemm).
+ * The casts without scratch round to nearest: MX_ROUND_TOWARD_ZERO always casts
+ * into scratch first; MX_ROUND_STOCHASTIC is
  * MX_ERR_ENUM.  Where the scratch comes from, and what happens when there is
  * none, is stated under "Scratch memory of the GEMM entry points" below.
  */
@@ -285,8 +289,7 @@ int mx_gemm_qa(int64_t M, int64_t N, int64_t K,
  * Scratch memory of the GEMM entry points.  Some routes need device scratch:
  *   mx_gemm     MX_INT8 problems of at least 96 whole 256 x 256 tiles (the two
  *               E2M3 halves of both operands);
- *   mx_gemm_qa  every route that casts A ahead of the product (all but the
- *               narrow-output fused kernel and the direct kernel);
+ *   mx_gemm_qa  every route that casts A ahead of the product (see there);
  *   mx_gemm_q   every route that does not cast in the tiled kernel's epilogue
  *               (a Float32 C).
  * mx_gemm / mx_gemm_qa / mx_gemm_q take it from the device's default memory
@@ -298,9 +301,9 @@ int mx_gemm_qa(int64_t M, int64_t N, int64_t K,
  * With a non-NULL workspace the library allocates nothing at all; a workspace
  * smaller than the bound is MX_ERR_WORKSPACE and nothing is launched.
  * workspace = NULL makes a _ws form behave exactly like the plain one.
- * In either form a request that cannot be met is an error (MX_ERR_WORKSPACE);
- * no route falls back to a slower kernel on its account.  Results are
- * bit-identical between the two forms.
+ * In either form a request that cannot be met is an error (MX_ERR_WORKSPACE),
+ * except where mx_gemm_qa can cast in registers instead (see there).  Results
+ * are bit-identical between the two forms.
  */
 size_t mx_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, mx_format_t fmtA, mx_format_t fmtB);
 size_t mx_gemm_qa_workspace_bytes(int64_t M, int64_t N, int64_t K, mx_format_t fmtA, mx_format_t fmtB);
