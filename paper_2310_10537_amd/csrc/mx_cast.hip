@@ -217,22 +217,30 @@ static hipError_t dispatch_fmt(int fmt, int rnd, uint64_t seed, int axis, const 
 // Whether a cast along axis 0 leaves most of each 128-row tile empty, so that one lane per block without LDS is faster (one lane per
 // block / tiles, us).  Float32, E4M3: 3 x 2796200 75 / 106, 15 x 559240 21 / 26, 31 x 270600 14 / 15, but 31 x 67648 6 / 5.4 and
 // 24 x 21840 4 / 3.6.  Stochastic: 3 x 2796200 Float32 150 / 322, 31 x 270600 bf16 33 / 35, 31 x 67648 bf16 13 / 12,
-// 12 x 43688 bf16 9 / 8.  (bf16, to nearest: tiles throughout, 3 x 2796200 77 / 69.)  A work-group without tiles covers 256
+// 12 x 43688 bf16 9 / 8.  bf16 to nearest, E4M3: tiles throughout, 4 x 2097152 59 / 53; INT8 with ties away 25 / 38, 16 x 131072 7 / 7.3 but
+// 12 x 87376 7 / 6.3, ties to even 4 x 2097152 52 / 61; E2M3 with ties away 46 / 53, E2M1 45 / 53, but 8 x 131072 6 / 5.4.  A work-group without tiles covers 256
 // columns: narrower matrices of a batch would leave its lanes idle.
-static bool few_rows_of_a_tile(int src_dt, int rnd, int64_t n, int64_t rows, int64_t cols)
+static bool few_rows_of_a_tile(int src_dt, int fmt, int rnd, int64_t n, int64_t rows, int64_t cols)
 {
     const int64_t size = n * rows * cols;
     if (cols < 256) return false;
     if (rnd == ROUND_STOCHASTIC) return rows <= 10 || (rows <= BLOCK && size >= ((int64_t)1 << 20));
-    return src_dt == DT_F32 && (rows <= 6 || (rows <= BLOCK && size >= ((int64_t)1 << (rows <= 24 ? 20 : 22))));
+    if (src_dt == DT_BF16) {
+        const bool away = rnd == ROUND_HALF_AWAY, large = size >= 2000000;
+        int64_t most = 0;
+        if (fmt == INT8) most = away && large ? 16 : away || large ? 8 : 6;
+        else if (fmt_bits(fmt) < 8 && away) most = large ? 8 : 6;
+        return most && (rows <= (fmt == INT8 && away ? 4 : 2) || (rows <= most && size >= 1000000));
+    }
+    return rows <= 6 || (rows <= BLOCK && size >= ((int64_t)1 << (rows <= 24 ? 20 : 22)));
 }
 
 hipError_t launch_cast(const void *src, int src_dt, int64_t rows, int64_t cols, int64_t ld, int axis, int fmt, int rnd,
                        uint8_t *elems, uint8_t *scales, hipStream_t st, uint64_t seed, const Batch &batch)
 {
-    const bool tiles = axis == 1 || !few_rows_of_a_tile(src_dt, rnd, batch.n, rows, cols);
+    const bool tiles = axis == 1 || !few_rows_of_a_tile(src_dt, fmt, rnd, batch.n, rows, cols);
     // the kernels built on the hardware converts round to nearest only
-    if (src_dt == DT_BF16 && (rnd == ROUND_RNE || rnd == ROUND_HALF_AWAY)) {
+    if (tiles && src_dt == DT_BF16 && (rnd == ROUND_RNE || rnd == ROUND_HALF_AWAY)) {
         hipError_t e = launch_cast_bf16_fast(src, rows, cols, ld, axis, fmt, rnd, elems, scales, st, batch);
         if (e != hipErrorNotSupported) return e;
     }

@@ -130,3 +130,18 @@ def test_interior_of_129_to_192_tiles(trace):
                                         ((2600, 2560), 4096, E3M2, E3M2, True)):
         (status, seen), = trace([gemm(M, N, K, fa, fb)])
         assert status == 0 and (seen[0][0] != "gemm_mid_kernel") == interior, (M, N, K, fa, fb)
+
+
+def test_casts_of_few_rows_along_axis_0(trace):
+    simple, away = "cast_col_simple_kernel", 1
+    for rows, cols, dt, fmt, rnd, few in ((6, 400, F32, 0, 0, True), (24, 65536, F32, 4, 0, True), (24, 30000, F32, 4, 0, False),
+                                          (32, 262144, F32, 2, away, True), (32, 65536, F32, 2, 0, False), (33, 262144, F32, 2, 0, False),
+                                          (4, 1 << 21, BF16, 0, 0, False), (4, 1 << 21, BF16, 0, away, False), (4, 1 << 21, BF16, 5, 0, True),
+                                          (16, 131072, BF16, 5, away, True), (12, 87376, BF16, 5, away, False), (12, 1 << 19, BF16, 5, 0, False),
+                                          (6, 1 << 19, BF16, 3, away, True), (6, 1 << 19, BF16, 3, 0, False), (8, 1 << 17, BF16, 2, away, False), (8, 1 << 19, BF16, 4, away, True),
+                                          (4, 248, F32, 0, 0, False)):
+        (status, seen), = trace([quantize(rows, cols, cols, dt, 0, fmt, rnd)])
+        assert status == 0 and len(seen) == 1 and (seen[0][0] == simple) == few, (rows, cols, dt, fmt, rnd)
+    for rows, cols, few in ((10, 4096, True), (12, 65536, False), (12, 87384, True), (32, 32768, True), (33, 32768, False)):
+        (status, seen), = trace([("mx_quantize_sr", (P, BF16, rows, cols, cols, 0, 0, 7, P, P, 0))])
+        assert status == 0 and len(seen) == 1 and (seen[0][0] == simple) == few, (rows, cols)
