@@ -165,12 +165,15 @@ static bool direct_pays(int64_t M, int64_t N, int64_t K, int fmtA, int fmtB)
 // MID / INTERIOR, us: fringe on one side, 3100 x 3072 x 4096 E4M3 59 / 54, E3M2 58 / 46, E3M2 x E2M1 49 / 39, E4M3 x E2M1 47 / 51; K = 2048
 // 33 / 34, 33 / 28, 28 / 25; E3M2 K = 1024 22 / 20; on both sides, 3340 x 3340 x 4096 65 / 62, 69 / 59, 53 / 52, 49 / 62, K = 8192 122 / 110,
 // 129 / 104, 97 / 91, 92 / 107.  Interiors of 100 tiles: MID is ahead (2600 x 2560 x 4096 E4M3 34 / 43) but for 6-bit pairs (40 / 40; K = 8192 76 / 69).
+// A very long K moves the line further: 1568 x 3584 (84 tiles) x 8192 E3M2 79 / 66, E2M1 x E3M2 68 / 54, x 16384 E2M1 92 / 83, E5M2 x E2M3 x 24960
+// 147 / 139.
 static bool interior_pays(int64_t M, int64_t N, int64_t K, int64_t whole, int fmtA, int fmtB)
 {
     if (whole > 192) return true;
     const int a = fmt_bits(fmtA), b = fmt_bits(fmtB);
     const bool both = M % 256 != 0 && N % 256 != 0;
     if (a + b == 12 && a != b) return !both && whole > 184 && K >= 4096;      // 8 x 4 bits
+    if (whole > 72 && !both && a < 8 && b < 8 && (K >= 16384 || (K >= 8192 && b == 6))) return true;
     if (whole <= (a + b == 12 && !both && K >= 4096 ? 96 : 128)) return false;
     if (both) return K >= (a + b == 12 || a + b == 10 ? 4096 : 6144);
     return K >= (a + b == 16 ? 4096 : a + b == 12 ? 1024 : 2048);

@@ -127,7 +127,9 @@ def test_interior_of_129_to_192_tiles(trace):
                                         (one, 2048, E3M2, E2M1, True), (one, 4096, E4M3, E2M1, False), ((3100, 4096), 4096, E4M3, E2M1, True),
                                         (two, 4096, E4M3, E4M3, False), (two, 8192, E4M3, E4M3, True), (two, 4096, E3M2, E2M1, True),
                                         (two, 2048, E3M2, E3M2, False), (two, 8192, E2M1, E4M3, False), ((2600, 2560), 8192, E2M1, E2M1, False),
-                                        ((2600, 2560), 4096, E3M2, E3M2, True)):
+                                        ((2600, 2560), 4096, E3M2, E3M2, True), ((1568, 3584), 8192, E3M2, E3M2, True),
+                                        ((1568, 3584), 8192, E2M1, E2M1, False), ((1568, 3584), 16384, E2M1, E2M1, True),
+                                        ((1568, 3584), 16384, E4M3, E4M3, False)):
         (status, seen), = trace([gemm(M, N, K, fa, fb)])
         assert status == 0 and (seen[0][0] != "gemm_mid_kernel") == interior, (M, N, K, fa, fb)
 
