@@ -4,7 +4,7 @@
 // load (which drops with the switching activity of the operands: the power limit) and the clocks
 // one K step takes (against 2048 / 1024 clocks of matrix instructions for 8-bit / narrower pairs).
 #include "mx_gemm_tile8.hpp"
-#include "mx_gemm_tile16.hpp"
+#include "mx_gemm_tile16n.hpp"
 
 #include "../../include/mx.h"
 
@@ -33,7 +33,11 @@ hipError_t probe8(int64_t M, int64_t N, int64_t K, const uint8_t *Ae, const uint
 {
     const int tiles_m = (int)(M / TM), tiles_n = (int)(N / TN);
     const Raster rast = choose_raster(tiles_m, tiles_n, Fmt<FA>::bits, Fmt<FB>::bits);
-    hipLaunchKernelGGL((gemm_tile8_kernel<FA, FB, DT_BF16, true>), dim3(raster_grid(rast, tiles_m, tiles_n)), dim3(512), 0, st, M, N, K, Ae,
+    if (gemm_tiled16n_pays(M, N, K, FA, FB))        // as mx_gemm picks them
+        hipLaunchKernelGGL((narrow::gemm_tile16_kernel<FA, FB, DT_BF16, true>), dim3(raster_grid(rast, tiles_m, tiles_n)), dim3(256), 0, st, M, N,
+                           K, Ae, As, Be, Bs, C, ldc, tiles_m, tiles_n, rast, probe);
+    else
+        hipLaunchKernelGGL((gemm_tile8_kernel<FA, FB, DT_BF16, true>), dim3(raster_grid(rast, tiles_m, tiles_n)), dim3(512), 0, st, M, N, K, Ae,
                        As, Be, Bs, C, ldc, tiles_m, tiles_n, rast, probe);
     return hipGetLastError();
 }

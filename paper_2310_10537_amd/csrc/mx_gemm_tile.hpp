@@ -633,6 +633,10 @@ hipError_t launch_gemm_tiled16_a8(const TileArgs &a, int fmtA, int fmtB);
 // the eight-wave form of the kernel (plain operands, Float32 / bf16 output), same split
 hipError_t launch_gemm_tiled8_a6(const TileArgs &a, int fmtA, int fmtB);
 hipError_t launch_gemm_tiled8_a4(const TileArgs &a, int fmtA, int fmtB);
+// pairs of narrow formats, one of them 6-bit, on the 16 x 16 x 128 instruction (mx_gemm_tile16n.hpp), and which problems take it
+hipError_t launch_gemm_tiled16n_a6(const TileArgs &a, int fmtA, int fmtB);
+hipError_t launch_gemm_tiled16n_a4(const TileArgs &a, int fmtA, int fmtB);
+bool gemm_tiled16n_pays(int64_t M, int64_t N, int64_t K, int fmtA, int fmtB);
 // the half-width form (256 x 128 tiles, four waves), plain operands, Float32 / bf16 output, every pair
 hipError_t launch_gemm_tiledh_a8(const TileArgs &a, int fmtA, int fmtB);
 hipError_t launch_gemm_tiledh_a6(const TileArgs &a, int fmtA, int fmtB);

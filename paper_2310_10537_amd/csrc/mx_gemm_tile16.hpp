@@ -47,6 +47,80 @@ __device__ __forceinline__ void mfma16(v4f_t &acc, const v8i_t &op1, const v8i_t
                  : "v"(op1), "v"(op2), "v"(s1), "v"(s2), "n"(H1), "n"(H2));
 }
 
+// Behind the last matrix instruction.
+__device__ __forceinline__ void acc_settle(v4f_t (&acc)[8][8])
+{
+    // The compiler does not know that the assembly above is matrix instructions, so it leaves no wait
+    // states between the last of them (8 passes) and the first read of an accumulator register.  The
+    // waits are written here, and every accumulator passes through a statement behind them (volatile
+    // statements keep their order), so that no read of one can move in front.
+#define MX_ACC_ROW(X)                                                                                                  \
+    "+a"(acc[X][0]), "+a"(acc[X][1]), "+a"(acc[X][2]), "+a"(acc[X][3]), "+a"(acc[X][4]), "+a"(acc[X][5]), "+a"(acc[X][6]), "+a"(acc[X][7])
+    asm volatile("s_nop 15\n\ts_nop 15" : MX_ACC_ROW(0), MX_ACC_ROW(1));
+    asm volatile("" : MX_ACC_ROW(2), MX_ACC_ROW(3));
+    asm volatile("" : MX_ACC_ROW(4), MX_ACC_ROW(5));
+    asm volatile("" : MX_ACC_ROW(6), MX_ACC_ROW(7));
+#undef MX_ACC_ROW
+}
+
+// The wave's 128 x 128 accumulators to C, whose entry (row0, col0) is the first.
+template <int CDT>
+__device__ __forceinline__ void store_tile16(const v4f_t (&acc)[8][8], void *__restrict__ C, int64_t ldc, int64_t row0, int64_t col0, int i, int q)
+{
+    // ---- epilogue: lane (i, q), register t of instruction tile (x, y) -> C[16x + i][16y + 4q + t]: four
+    // consecutive columns per lane, stored 16 bytes at a time where the row pitch keeps them aligned.  bf16
+    // output uses the hardware's packed Float32 -> bf16 convert: round to nearest even, a NaN stays a NaN.
+    typedef float f32x2_t __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2_t_ __attribute__((ext_vector_type(2)));
+    auto pack2 = [](float lo, float hi) {
+        const f32x2_t v = {lo, hi};
+        return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t_));
+    };
+    const int64_t r0 = row0 + i, c0 = col0 + 4 * q;
+    if constexpr (CDT == DT_F32) {
+        if ((ldc & 3) == 0) {
+#pragma unroll
+            for (int x = 0; x < 8; x++)
+#pragma unroll
+                for (int y = 0; y < 8; y++)
+                    *reinterpret_cast<float4 *>(reinterpret_cast<float *>(C) + (r0 + x * 16) * ldc + c0 + y * 16) =
+                        make_float4(acc[x][y][0], acc[x][y][1], acc[x][y][2], acc[x][y][3]);
+        } else {
+#pragma unroll
+            for (int x = 0; x < 8; x++)
+#pragma unroll
+                for (int y = 0; y < 8; y++) {
+                    float *o = reinterpret_cast<float *>(C) + (r0 + x * 16) * ldc + c0 + y * 16;
+                    o[0] = acc[x][y][0]; o[1] = acc[x][y][1]; o[2] = acc[x][y][2]; o[3] = acc[x][y][3];
+                }
+        }
+    } else if ((ldc & 7) == 0) {
+        // Four bf16 are 8 bytes per lane and 32 bytes per row and instruction.  Lanes q and q ^ 1 hold
+        // neighbouring column groups of the same rows, so they trade: the even one hands over its four
+        // columns of tile y + 1 and takes the odd one's of tile y (the row swap of the lane-permute unit
+        // does exactly this exchange between 16-lane rows), and each stores 8 consecutive columns, 16
+        // bytes -- 64 contiguous bytes per row and instruction, half as many instructions.
+        const int64_t c1 = col0 + 16 * (q & 1) + 4 * (q & 2);
+#pragma unroll
+        for (int x = 0; x < 8; x++)
+#pragma unroll
+            for (int y = 0; y < 8; y += 2) {
+                const auto lo = __builtin_amdgcn_permlane16_swap(pack2(acc[x][y][0], acc[x][y][1]), pack2(acc[x][y + 1][0], acc[x][y + 1][1]), false, false);
+                const auto hi = __builtin_amdgcn_permlane16_swap(pack2(acc[x][y][2], acc[x][y][3]), pack2(acc[x][y + 1][2], acc[x][y + 1][3]), false, false);
+                *reinterpret_cast<uint4 *>(reinterpret_cast<uint16_t *>(C) + (r0 + x * 16) * ldc + c1 + y * 16) = make_uint4(lo[0], hi[0], lo[1], hi[1]);
+            }
+    } else {
+#pragma unroll
+        for (int x = 0; x < 8; x++)
+#pragma unroll
+            for (int y = 0; y < 8; y++) {
+                const uint32_t p0 = pack2(acc[x][y][0], acc[x][y][1]), p1 = pack2(acc[x][y][2], acc[x][y][3]);
+                uint16_t *o = reinterpret_cast<uint16_t *>(C) + (r0 + x * 16) * ldc + c0 + y * 16;
+                o[0] = (uint16_t)p0; o[1] = (uint16_t)(p0 >> 16); o[2] = (uint16_t)p1; o[3] = (uint16_t)(p1 >> 16);
+            }
+    }
+}
+
 template <int FA, int FB, int CDT, bool PROBE = false>
 __global__ __launch_bounds__(256, 1) void gemm_tile16_kernel(int64_t M, int64_t N, int64_t K,
                                                               const uint8_t *__restrict__ Ae, const uint8_t *__restrict__ As,
@@ -268,17 +342,7 @@ __global__ __launch_bounds__(256, 1) void gemm_tile16_kernel(int64_t M, int64_t 
 #undef MX_QUAD_READ
 #undef MX_MF
 #undef MX_FENCE
-    // The compiler does not know that the assembly above is matrix instructions, so it leaves no wait
-    // states between the last of them (8 passes) and the first read of an accumulator register.  The
-    // waits are written here, and every accumulator passes through a statement behind them (volatile
-    // statements keep their order), so that no read of one can move in front.
-#define MX_ACC_ROW(X)                                                                                                  \
-    "+a"(acc[X][0]), "+a"(acc[X][1]), "+a"(acc[X][2]), "+a"(acc[X][3]), "+a"(acc[X][4]), "+a"(acc[X][5]), "+a"(acc[X][6]), "+a"(acc[X][7])
-    asm volatile("s_nop 15\n\ts_nop 15" : MX_ACC_ROW(0), MX_ACC_ROW(1));
-    asm volatile("" : MX_ACC_ROW(2), MX_ACC_ROW(3));
-    asm volatile("" : MX_ACC_ROW(4), MX_ACC_ROW(5));
-    asm volatile("" : MX_ACC_ROW(6), MX_ACC_ROW(7));
-#undef MX_ACC_ROW
+    acc_settle(acc);
     if constexpr (PROBE) {
         if (threadIdx.x == 0) {
             probe[2 * blockIdx.x] = __builtin_readcyclecounter() - probe_c0;
@@ -286,58 +350,7 @@ __global__ __launch_bounds__(256, 1) void gemm_tile16_kernel(int64_t M, int64_t 
         }
     }
 
-    // ---- epilogue: lane (i, q), register t of instruction tile (x, y) -> C[16x + i][16y + 4q + t]: four
-    // consecutive columns per lane, stored 16 bytes at a time where the row pitch keeps them aligned.  bf16
-    // output uses the hardware's packed Float32 -> bf16 convert: round to nearest even, a NaN stays a NaN.
-    typedef float f32x2_t __attribute__((ext_vector_type(2)));
-    typedef __bf16 bf16x2_t_ __attribute__((ext_vector_type(2)));
-    auto pack2 = [](float lo, float hi) {
-        const f32x2_t v = {lo, hi};
-        return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t_));
-    };
-    const int64_t r0 = m0 + wm * 128 + i, c0 = n0 + wn * 128 + 4 * q;
-    if constexpr (CDT == DT_F32) {
-        if ((ldc & 3) == 0) {
-#pragma unroll
-            for (int x = 0; x < 8; x++)
-#pragma unroll
-                for (int y = 0; y < 8; y++)
-                    *reinterpret_cast<float4 *>(reinterpret_cast<float *>(C) + (r0 + x * 16) * ldc + c0 + y * 16) =
-                        make_float4(acc[x][y][0], acc[x][y][1], acc[x][y][2], acc[x][y][3]);
-        } else {
-#pragma unroll
-            for (int x = 0; x < 8; x++)
-#pragma unroll
-                for (int y = 0; y < 8; y++) {
-                    float *o = reinterpret_cast<float *>(C) + (r0 + x * 16) * ldc + c0 + y * 16;
-                    o[0] = acc[x][y][0]; o[1] = acc[x][y][1]; o[2] = acc[x][y][2]; o[3] = acc[x][y][3];
-                }
-        }
-    } else if ((ldc & 7) == 0) {
-        // Four bf16 are 8 bytes per lane and 32 bytes per row and instruction.  Lanes q and q ^ 1 hold
-        // neighbouring column groups of the same rows, so they trade: the even one hands over its four
-        // columns of tile y + 1 and takes the odd one's of tile y (the row swap of the lane-permute unit
-        // does exactly this exchange between 16-lane rows), and each stores 8 consecutive columns, 16
-        // bytes -- 64 contiguous bytes per row and instruction, half as many instructions.
-        const int64_t c1 = n0 + wn * 128 + 16 * (q & 1) + 4 * (q & 2);
-#pragma unroll
-        for (int x = 0; x < 8; x++)
-#pragma unroll
-            for (int y = 0; y < 8; y += 2) {
-                const auto lo = __builtin_amdgcn_permlane16_swap(pack2(acc[x][y][0], acc[x][y][1]), pack2(acc[x][y + 1][0], acc[x][y + 1][1]), false, false);
-                const auto hi = __builtin_amdgcn_permlane16_swap(pack2(acc[x][y][2], acc[x][y][3]), pack2(acc[x][y + 1][2], acc[x][y + 1][3]), false, false);
-                *reinterpret_cast<uint4 *>(reinterpret_cast<uint16_t *>(C) + (r0 + x * 16) * ldc + c1 + y * 16) = make_uint4(lo[0], hi[0], lo[1], hi[1]);
-            }
-    } else {
-#pragma unroll
-        for (int x = 0; x < 8; x++)
-#pragma unroll
-            for (int y = 0; y < 8; y++) {
-                const uint32_t p0 = pack2(acc[x][y][0], acc[x][y][1]), p1 = pack2(acc[x][y][2], acc[x][y][3]);
-                uint16_t *o = reinterpret_cast<uint16_t *>(C) + (r0 + x * 16) * ldc + c0 + y * 16;
-                o[0] = (uint16_t)p0; o[1] = (uint16_t)(p0 >> 16); o[2] = (uint16_t)p1; o[3] = (uint16_t)(p1 >> 16);
-            }
-    }
+    store_tile16<CDT>(acc, C, ldc, m0 + wm * 128, n0 + wn * 128, i, q);
     // The last steps requested stages beyond the end of K (clamped to the last one: harmless, branch-free);
     // those direct loads must have landed before this work-group's LDS is handed to another one.  The
     // epilogue above does not touch LDS, so the wait stands here, behind the stores, where it costs nothing.

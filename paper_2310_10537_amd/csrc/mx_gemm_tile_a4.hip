@@ -15,11 +15,29 @@ bool gemm_tiled_applies(int64_t M, int64_t N, int64_t K, int fmtA, int fmtB)
 
 bool gemm_tiled_fuses_cast(int fmtA, int fmtB) { return fmtA <= FP8_E5M2 && fmtB <= FP8_E5M2; }
 
+// Pairs of 6- and 4-bit formats with at least one 6-bit operand: the kernel of mx_gemm_tile16n.hpp needs 10 % less time per K step on a
+// full chip (it costs less energy and fetches every cache line once), but 2 us more per tile in front of and behind its loop, and with
+// one wave per SIMD it falls behind when the chip is partly idle and the clock high.  us, eight waves of 128 x 64 / this kernel (the
+// mixed pairs differ by 5 % from box to box, so their line lies where all are ahead):
+// E3M2 16384 x 2048 x K = 2048 51.9 / 53.2, 4096 92.6 / 87.0, 8192 178 / 162; 2048 x 8192 x 4096 51.7 / 47.8; 224 tiles x 3072 36.2 / 36.2 to
+// 38.2, x 4096 95 %; E3M2 x E2M1 8192^2 x 3072 level to 136 / 144, 4096 x 8192 x 4096 94 to 102 %, 6144 93 %, 4096 x 28672 x 8192 578 / 517 to 591 /
+// 554; 192 tiles x 4096 101 and 102 %, x 8192 96 and 97 %; 176 tiles x 8192 98 and 104 %.  4-bit pairs gain 4 % at most (K >= 8192) and
+// lose up to 20 % on one round of 135 tiles: they stay.
+bool gemm_tiled16n_pays(int64_t M, int64_t N, int64_t K, int fmtA, int fmtB)
+{
+    const bool six_a = fmtA == FP6_E3M2 || fmtA == FP6_E2M3, six_b = fmtB == FP6_E3M2 || fmtB == FP6_E2M3;
+    if (!(six_a && (six_b || fmtB == FP4_E2M1)) && !(fmtA == FP4_E2M1 && six_b)) return false;
+    return K % (4 * TK) == 0 && K >= (six_a && six_b ? 4096 : 6144) && (M / TM) * (N / TN) >= 224;
+}
+
 // whole 256 x 256 tiles: four waves, on the 16 x 16 x 128 instruction for plain pairs of 8-bit formats with
-// K >= 1024 (mx_gemm_tile16.hpp: its scale bytes travel in groups of eight K steps), or eight waves for pairs without an 8-bit operand (mx_gemm_tile8.hpp)
+// K >= 1024 (mx_gemm_tile16.hpp: its scale bytes travel in groups of eight K steps) and for pairs with a 6-bit and no 8-bit operand where
+// that pays, or eight waves for the other pairs without an 8-bit operand (mx_gemm_tile8.hpp)
 static hipError_t launch_whole(const TileArgs &a, int fmtA, int fmtB)
 {
     if (!a.Abf && fmtA <= FP8_E5M2 && fmtB <= FP8_E5M2 && a.K >= 1024) return launch_gemm_tiled16_a8(a, fmtA, fmtB);
+    if (!a.Abf && gemm_tiled16n_pays(a.M, a.N, a.K, fmtA, fmtB))
+        return fmtA <= FP6_E2M3 ? launch_gemm_tiled16n_a6(a, fmtA, fmtB) : launch_gemm_tiled16n_a4(a, fmtA, fmtB);
     if (!a.Abf && fmtA >= FP6_E3M2 && fmtB >= FP6_E3M2)
         return fmtA <= FP6_E2M3 ? launch_gemm_tiled8_a6(a, fmtA, fmtB) : launch_gemm_tiled8_a4(a, fmtA, fmtB);
     switch (fmtA) {
