@@ -357,7 +357,7 @@ def other_configs(n, samples, extras):
                 out[f"decode_gemm_{M}x{N}x{K}_{name}"] = {"avg_us": round(1e3 * ms, 2), "weights_GBps": round(N * K * (1 + 1 / 32) / ms / 1e6, 1)}
         del w, Be, Bs
 
-        # MXINT8 on the projection shape of config 3 (each element split into two E2M3 halves, tiled kernel at depth 4K)
+        # MXINT8 on the projection shape of config 3 (elements times scales as bf16 values, bf16 tiles)
         M, K, N = 8192, 4096, 4096
         a = to_dev_bf16(inputs.gaussian_bf16((M, K), seed=2))
         w = torch.from_numpy(inputs.gaussian_f32((K, N), seed=102, std=0.02)).cuda()

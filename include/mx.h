@@ -245,11 +245,13 @@ int mx_dequantize(const void *elems, const uint8_t *scales, mx_format_t fmt,
  * fmtA / fmtB may differ, except that MX_INT8 pairs only with MX_INT8 (anything
  * else is MX_ERR_UNSUPPORTED).  That pair runs the integer matrix instruction
  * block by block -- every block sum is an exact integer -- and adds the scaled
- * block sums in Float32; problems of at least 96 whole 256 x 256 tiles (64 when
- * K < 1024) instead split every element exactly into two FP6 E2M3 halves (scratch
- * memory of (M + N) * K * 3.125 bytes, see "Scratch memory of the GEMM entry
- * points" below) and run one E2M3 product of depth 4K, whose products are exact in
- * the block-scaled instruction; few rows (M <= 128, K >= 256) and mid-size
+ * block sums in Float32; larger problems (whole 256 x 256 tiles, at least 96 or 64
+ * when K < 1024; more than 128 rows and 768 tiles of 64 x 32, or 2^31 products for
+ * a K below 1024 or no multiple of 128) instead write the elements times their
+ * scales as bf16 numbers, which hold them exactly, to scratch memory (less than
+ * (M + N) * K * 3.125 bytes, see "Scratch memory of the GEMM entry points" below)
+ * and run a bf16 product with Float32 sums, recomputed block by block where
+ * the scales leave the range of these types; few rows (M <= 128, K >= 256) and mid-size
  * problems with a long K let eight waves share the K range of each 32-column
  * tile and add their partial tiles in a fixed order.  All routes differ from
  * the exact sum only by Float32 accumulation rounding.
@@ -287,8 +289,9 @@ int mx_gemm_qa(int64_t M, int64_t N, int64_t K,
 
 /*
  * Scratch memory of the GEMM entry points.  Some routes need device scratch:
- *   mx_gemm     MX_INT8 problems of at least 96 whole 256 x 256 tiles (the two
- *               E2M3 halves of both operands);
+ *   mx_gemm     larger MX_INT8 problems (the bf16 values of both operands; see
+ *               there).  Without scratch memory those of whole 256 x 256 tiles
+ *               fail and the others take a slower kernel;
  *   mx_gemm_qa  every route that casts A ahead of the product (see there);
  *   mx_gemm_q   every route that does not cast in the tiled kernel's epilogue
  *               (a Float32 C).

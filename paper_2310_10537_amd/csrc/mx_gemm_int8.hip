@@ -12,18 +12,14 @@
 // A scale of a block is needed per output row, i.e. per result register: the 32 row bytes
 // go through a wave-private LDS line and come back as the sixteen dwords a lane needs.
 //
-// Whole 256 x 256 tiles take a faster, equally exact route through the block-scaled
-// instruction.  An MXINT8 element q / 64 (q the two's-complement code) is split as
-//   q / 64 = sign(q) (H + L * 2^-3),   H = (|q| >> 3) / 8  in {0, ..., 2},   L = (|q| & 7) / 8  in {0, ..., 0.875},
-// and both halves, each with the sign of q so that nothing cancels, are FP6 E2M3 numbers
-// (code = sign bit and the integer |q| >> 3, resp. |q| & 7), with the factor 2^-3 moved into
-// the block scale (byte s - 3).  Then
-//   a b = Ha Hb + Ha Lb' + La' Hb + La' Lb'        (primed = with the lowered scale),
-// which is ONE E2M3 x E2M3 product of depth 4K: every source block b becomes the four blocks
-// [Ha, Ha, La, La] of A' and [Hb, Lb, Hb, Lb] of B'.  E2M3 products are exact in the
-// instruction and the LDS-tiled kernel does the rest.  A scale byte below 3 cannot be lowered:
-// the split kernel then raises a flag, and the direct kernel -- launched after the tiled one,
-// leaving at once when the flag is clear -- recomputes the whole product.
+// Larger products take a faster, equally exact route: an element times its block's scale, q 2^(s - 133), is a bf16 number (q has
+// eight significant bits at most), the product of two such numbers is exact in Float32, and so C is the plain bf16 product of the
+// scaled elements on the bf16 matrix instruction (mx_gemm_bf16.hip), Float32 sums as everywhere.  That holds while the values and
+// their products stay within the exponents of bf16 and Float32; int8_widen_kernel notes the range of the scales, and the direct
+// kernel's tiles -- launched after the product, left at once as a rule -- recompute C when it does not.  (The 8-bit integer
+// instruction is twice as fast as the bf16 one, but every block's sums have to be scaled by the vector pipe: 48 instructions for
+// 32 clocks of it.  Splitting q into two E2M3 halves, four products on the block-scaled instruction at four times the bf16 rate, moves
+// three bytes an element instead of two for the same matrix work: 8192 x 4096 x 4096 348 us where this takes 226.)
 #include "mx_device.hpp"
 #include "mx_launch.hpp"
 
@@ -78,65 +74,108 @@ __device__ __forceinline__ void i8_accumulate(float (&acc)[16], const v16i_t &p,
     wave_lds_sync8();   // the line is rewritten for the next block
 }
 
-// Clears the split route's flag word.  A kernel rather than a memset node, so that a caller who captures the
-// stream into a graph replays an ordinary launch.
-__global__ void int8_clear_flag_kernel(uint32_t *flag) { *flag = 0u; }
+// ---------------------------------------------------------------------------------------------
+// MXINT8 -> bf16.  A block's elements times its scale are q 2^(s - 133), |q| <= 128: exact in bf16 (eight significant bits) for
+// scale bytes from 7 to 253.  The products of such values are exact in Float32 as long as sA + sB >= 140 (no product of less than
+// 2^-126) and finite for sA + sB <= 378.  Each work-group leaves the least and the largest scale byte of its elements other than zero
+// (NaN scales: 0 and 255, which no partner satisfies) in a word of its own; gemm_int8_repair_kernel, launched behind the product on few
+// work-groups, looks at all of them and recomputes C when the ranges of A and B do not fit together.
+// Bound by memory: 3 bytes an element, 16-byte stores.
+// ---------------------------------------------------------------------------------------------
+constexpr int WIDEN_PER = 4;                                   // pieces of eight elements per lane
+constexpr int WIDEN_ELEMS = 256 * 8 * WIDEN_PER;               // elements per work-group
 
-// MXINT8 [R][K] -> FP6 E2M3 [R][4K]: one lane per source block.  B_SIDE picks the block order.
-template <bool B_SIDE>
-__global__ __launch_bounds__(256) void int8_split_kernel(const uint8_t *__restrict__ elems, const uint8_t *__restrict__ scales,
-                                                         int64_t n_blocks, uint8_t *__restrict__ e6, uint8_t *__restrict__ s6,
-                                                         uint32_t *__restrict__ flag)
+__global__ __launch_bounds__(256) void int8_widen_kernel(const uint8_t *__restrict__ Ae, const uint8_t *__restrict__ As, int64_t a_elems,
+                                                         const uint8_t *__restrict__ Be, const uint8_t *__restrict__ Bs, int64_t b_elems,
+                                                         uint16_t *__restrict__ Aw, uint16_t *__restrict__ Bw, uint32_t *__restrict__ range,
+                                                         unsigned a_groups)
 {
-    const int64_t b = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (b >= n_blocks) return;
-    const uint4 q0 = ld16(elems + b * 32), q1 = ld16(elems + b * 32 + 16);
-    const uint32_t dw[8] = {q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, q1.z, q1.w};
-    uint32_t hi[32], lo[32];
+    __shared__ uint32_t part[4];
+    const bool isb = blockIdx.x >= a_groups;
+    const uint8_t *e = isb ? Be : Ae, *sc = isb ? Bs : As;
+    uint16_t *w = isb ? Bw : Aw;
+    const int64_t n = isb ? b_elems : a_elems, base = (int64_t)(blockIdx.x - (isb ? a_groups : 0)) * WIDEN_ELEMS + threadIdx.x * 8;
+    uint2 q[WIDEN_PER];
+    uint32_t s[WIDEN_PER];
 #pragma unroll
-    for (int i = 0; i < 32; i++) {
-        const int q = (int)(int8_t)(dw[i >> 2] >> (8 * (i & 3)));
-        const uint32_t m = (uint32_t)(q < 0 ? -q : q), sg = q < 0 ? 32u : 0u;   // m <= 128
-        const uint32_t h = m >> 3, l = m & 7;       // E2M3 codes of h / 8 (<= 2.0) and l / 8: the magnitude bits ARE the code
-        hi[i] = h ? (sg | h) : 0u;
-        lo[i] = l ? (sg | l) : 0u;
+    for (int k = 0; k < WIDEN_PER; k++) {
+        const int64_t at = base + k * 2048;
+        q[k] = make_uint2(0, 0);
+        s[k] = 127;
+        if (at < n) {
+            q[k] = *reinterpret_cast<const uint2 *>(e + at);
+            s[k] = sc[at >> 5];
+        }
     }
-    uint32_t ph[6], pl[6];
-    pack_codes<FP6_E2M3, 32>(hi, ph);
-    pack_codes<FP6_E2M3, 32>(lo, pl);
-    const uint32_t s = scales[b];
-    uint32_t sl = s == SCALE_NAN ? SCALE_NAN : s - 3;
-    if (s < 3) { sl = 0; *flag = 1u; }              // cannot lower the scale: the caller's exact pass takes over
-    uint4 *o = reinterpret_cast<uint4 *>(e6 + b * 96);
-    const uint4 H0 = make_uint4(ph[0], ph[1], ph[2], ph[3]), H1 = make_uint4(ph[4], ph[5], 0, 0);
-    const uint4 L0 = make_uint4(pl[0], pl[1], pl[2], pl[3]), L1 = make_uint4(pl[4], pl[5], 0, 0);
-    // four blocks of 24 bytes: A side H H L L, B side H L H L
-    const uint4 b0a = H0, b0b = H1;
-    const uint4 b1a = B_SIDE ? L0 : H0, b1b = B_SIDE ? L1 : H1;
-    const uint4 b2a = B_SIDE ? H0 : L0, b2b = B_SIDE ? H1 : L1;
-    const uint4 b3a = L0, b3b = L1;
-    o[0] = b0a;                                                         // bytes  0..15
-    o[1] = make_uint4(b0b.x, b0b.y, b1a.x, b1a.y);                      //       16..31
-    o[2] = make_uint4(b1a.z, b1a.w, b1b.x, b1b.y);                      //       32..47
-    o[3] = b2a;                                                         //       48..63
-    o[4] = make_uint4(b2b.x, b2b.y, b3a.x, b3a.y);                      //       64..79
-    o[5] = make_uint4(b3a.z, b3a.w, b3b.x, b3b.y);                      //       80..95
-    const uint32_t s1 = B_SIDE ? sl : s, s2 = B_SIDE ? s : sl;
-    *reinterpret_cast<uint32_t *>(s6 + b * 4) = s | (s1 << 8) | (s2 << 16) | (sl << 24);
+    uint32_t lo = 255, hi = 0;
+#pragma unroll
+    for (int k = 0; k < WIDEN_PER; k++) {
+        const bool any = (q[k].x | q[k].y) != 0, fits = s[k] >= 7 && s[k] <= 253;
+        if (any && fits) { lo = lo < s[k] ? lo : s[k]; hi = hi > s[k] ? hi : s[k]; }
+        if ((any && !fits) || s[k] == SCALE_NAN) { lo = 0; hi = 255; }
+        const float f = __uint_as_float(fits ? (s[k] - 6u) << 23 : 0u);
+        uint32_t d[4];
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            const int dw = (int)(i < 2 ? q[k].x : q[k].y), sh = 16 * (i & 1);
+            const uint32_t v0 = __float_as_uint((float)((dw << (24 - sh)) >> 24) * f), v1 = __float_as_uint((float)((dw << (16 - sh)) >> 24) * f);
+            d[i] = __builtin_amdgcn_perm(v1, v0, 0x07060302);
+        }
+        const int64_t at = base + k * 2048;
+        if (at < n) st16(reinterpret_cast<uint8_t *>(w + at), make_uint4(d[0], d[1], d[2], d[3]));
+    }
+    // 255 - lo and hi in one maximum each half-word
+    uint32_t m = (255 - lo) << 16 | hi;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t t = (uint32_t)__shfl_xor((int)m, o);
+        m = ((m >> 16) > (t >> 16) ? m & 0xffff0000u : t & 0xffff0000u) | ((m & 0xffff) > (t & 0xffff) ? m & 0xffff : t & 0xffff);
+    }
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = m;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int k = 1; k < 4; k++) {
+            const uint32_t t = part[k];
+            m = ((m >> 16) > (t >> 16) ? m & 0xffff0000u : t & 0xffff0000u) | ((m & 0xffff) > (t & 0xffff) ? m & 0xffff : t & 0xffff);
+        }
+        range[blockIdx.x] = m;
+    }
 }
 
-template <int CDT>
-__global__ __launch_bounds__(256) void gemm_int8_kernel(int64_t M, int64_t N, int64_t K, const uint8_t *__restrict__ Ae,
-                                                        const uint8_t *__restrict__ As, const uint8_t *__restrict__ Be,
-                                                        const uint8_t *__restrict__ Bs, void *__restrict__ C, int64_t ldc,
-                                                        const uint32_t *__restrict__ run_if)
+// What int8_widen_kernel left: whether the ranges of the scales of A and B allow the product of the bf16 values.  (range: n_a words
+// of A's work-groups, then n_b of B's.)  Every thread of the work-group gets the answer.
+__device__ __forceinline__ bool widened_product_holds(const uint32_t *__restrict__ range, unsigned n_a, unsigned n_b)
 {
-    if (run_if && *run_if == 0) return;   // exact pass behind the split route: nothing to repair
-    __shared__ __attribute__((aligned(16))) uint32_t lds_all[4 * 32];
+    __shared__ uint32_t worst[4];                              // 255 - least and largest of A, of B
+    if (threadIdx.x < 4) worst[threadIdx.x] = 0;
+    __syncthreads();
+    uint32_t m[4] = {0, 0, 0, 0};
+    for (unsigned k = threadIdx.x; k < n_a + n_b; k += blockDim.x) {
+        const uint32_t r = range[k], a = r >> 16, b = r & 0xffff;
+        const int o = k < n_a ? 0 : 2;
+        m[o] = m[o] > a ? m[o] : a;
+        m[o + 1] = m[o + 1] > b ? m[o + 1] : b;
+    }
+#pragma unroll
+    for (int k = 0; k < 4; k++)
+        if (m[k]) atomicMax(&worst[k], m[k]);
+    __syncthreads();
+    const int lo_a = 255 - (int)worst[0], hi_a = (int)worst[1], lo_b = 255 - (int)worst[2], hi_b = (int)worst[3];
+    if (lo_a == 0 || lo_b == 0) return false;                  // a scale of its own out of range
+    return hi_a == 0 || hi_b == 0 /* zeros only */ || (lo_a + lo_b >= 140 && hi_a + hi_b <= 378);
+}
+
+// One tile of 64 x 64
+template <int CDT>
+__device__ __forceinline__ void int8_tile(int64_t M, int64_t N, int64_t K, const uint8_t *__restrict__ Ae, const uint8_t *__restrict__ As,
+                                          const uint8_t *__restrict__ Be, const uint8_t *__restrict__ Bs, void *__restrict__ C, int64_t ldc,
+                                          int64_t tile_m, int64_t tile_n, uint32_t *lds_all)
+{
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     uint32_t *lds = lds_all + wave * 32;
-    const int64_t m0 = (int64_t)blockIdx.y * 64 + (wave >> 1) * 32;
-    const int64_t n0 = (int64_t)blockIdx.x * 64 + (wave & 1) * 32;
+    const int64_t m0 = tile_m * 64 + (wave >> 1) * 32;
+    const int64_t n0 = tile_n * 64 + (wave & 1) * 32;
     const int i = lane & 31, g = lane >> 5;
     const int64_t nkb = K / BLOCK;
     const int64_t row = m0 + i, col = n0 + i;
@@ -168,6 +207,29 @@ __global__ __launch_bounds__(256) void gemm_int8_kernel(int64_t M, int64_t N, in
             else reinterpret_cast<uint16_t *>(C)[r * ldc + col] = (uint16_t)f32_to_bf16_bits(acc[t]);
         }
     }
+}
+
+template <int CDT>
+__global__ __launch_bounds__(256) void gemm_int8_kernel(int64_t M, int64_t N, int64_t K, const uint8_t *__restrict__ Ae,
+                                                        const uint8_t *__restrict__ As, const uint8_t *__restrict__ Be,
+                                                        const uint8_t *__restrict__ Bs, void *__restrict__ C, int64_t ldc)
+{
+    __shared__ __attribute__((aligned(16))) uint32_t lds_all[4 * 32];
+    int8_tile<CDT>(M, N, K, Ae, As, Be, Bs, C, ldc, blockIdx.y, blockIdx.x, lds_all);
+}
+
+// Behind the product of the bf16 values, on few work-groups: nothing to repair, as a rule
+template <int CDT>
+__global__ __launch_bounds__(256) void gemm_int8_repair_kernel(int64_t M, int64_t N, int64_t K, const uint8_t *__restrict__ Ae,
+                                                               const uint8_t *__restrict__ As, const uint8_t *__restrict__ Be,
+                                                               const uint8_t *__restrict__ Bs, void *__restrict__ C, int64_t ldc,
+                                                               const uint32_t *__restrict__ range, unsigned n_a, unsigned n_b)
+{
+    if (widened_product_holds(range, n_a, n_b)) return;
+    __shared__ __attribute__((aligned(16))) uint32_t lds_all[4 * 32];
+    const int64_t tiles_n = (N + 63) / 64, tiles = tiles_n * ((M + 63) / 64);
+    for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x)
+        int8_tile<CDT>(M, N, K, Ae, As, Be, Bs, C, ldc, tile / tiles_n, tile % tiles_n, lds_all);
 }
 
 // Few rows of A (a decoding step): the kernel above gives such a problem N / 32 waves that each walk
@@ -405,55 +467,83 @@ static hipError_t launch_int8_lds(int64_t M, int64_t N, int64_t K, const uint8_t
 }
 
 static hipError_t launch_int8_direct(int64_t M, int64_t N, int64_t K, const uint8_t *Ae, const uint8_t *As, const uint8_t *Be,
-                                     const uint8_t *Bs, void *C, int c_dt, int64_t ldc, const uint32_t *run_if, hipStream_t st)
+                                     const uint8_t *Bs, void *C, int c_dt, int64_t ldc, hipStream_t st)
 {
     const dim3 grid((unsigned)((N + 63) / 64), (unsigned)((M + 63) / 64));
-    if (c_dt == DT_F32) hipLaunchKernelGGL((gemm_int8_kernel<DT_F32>), grid, dim3(256), 0, st, M, N, K, Ae, As, Be, Bs, C, ldc, run_if);
-    else hipLaunchKernelGGL((gemm_int8_kernel<DT_BF16>), grid, dim3(256), 0, st, M, N, K, Ae, As, Be, Bs, C, ldc, run_if);
+    if (c_dt == DT_F32) hipLaunchKernelGGL((gemm_int8_kernel<DT_F32>), grid, dim3(256), 0, st, M, N, K, Ae, As, Be, Bs, C, ldc);
+    else hipLaunchKernelGGL((gemm_int8_kernel<DT_BF16>), grid, dim3(256), 0, st, M, N, K, Ae, As, Be, Bs, C, ldc);
     return hipGetLastError();
+}
+
+static hipError_t launch_int8_repair(int64_t M, int64_t N, int64_t K, const uint8_t *Ae, const uint8_t *As, const uint8_t *Be,
+                                     const uint8_t *Bs, void *C, int c_dt, int64_t ldc, const uint32_t *range, unsigned n_a, unsigned n_b,
+                                     hipStream_t st)
+{
+    const int64_t tiles = ((N + 63) / 64) * ((M + 63) / 64);
+    const dim3 grid((unsigned)(tiles < 512 ? tiles : 512));
+    if (c_dt == DT_F32)
+        hipLaunchKernelGGL((gemm_int8_repair_kernel<DT_F32>), grid, dim3(256), 0, st, M, N, K, Ae, As, Be, Bs, C, ldc, range, n_a, n_b);
+    else
+        hipLaunchKernelGGL((gemm_int8_repair_kernel<DT_BF16>), grid, dim3(256), 0, st, M, N, K, Ae, As, Be, Bs, C, ldc, range, n_a, n_b);
+    return hipGetLastError();
+}
+
+// C from the bf16 values of the blocks, in scratch memory; *refused when there is none to be had
+static hipError_t launch_int8_widened(int64_t M, int64_t N, int64_t K, const uint8_t *Ae, const uint8_t *As, const uint8_t *Be,
+                                      const uint8_t *Bs, void *C, int c_dt, int64_t ldc, hipStream_t st, bool *refused)
+{
+    const int64_t na = M * K, nb = N * K;
+    const unsigned ga = (unsigned)((na + WIDEN_ELEMS - 1) / WIDEN_ELEMS), gb = (unsigned)((nb + WIDEN_ELEMS - 1) / WIDEN_ELEMS);
+    const size_t range_bytes = ((size_t)(ga + gb) * 4 + 255) & ~(size_t)255, a_bytes = ((size_t)na * 2 + 255) & ~(size_t)255;
+    uint8_t *ws = nullptr;
+    hipError_t e = ws_acquire(range_bytes + a_bytes + (size_t)nb * 2, st, &ws);
+    *refused = e != hipSuccess;
+    if (*refused) return e;
+    uint32_t *range = reinterpret_cast<uint32_t *>(ws);
+    uint16_t *Aw = reinterpret_cast<uint16_t *>(ws + range_bytes), *Bw = reinterpret_cast<uint16_t *>(ws + range_bytes + a_bytes);
+    hipLaunchKernelGGL(int8_widen_kernel, dim3(ga + gb), dim3(256), 0, st, Ae, As, na, Be, Bs, nb, Aw, Bw, range, ga);
+    e = hipGetLastError();
+    if (e == hipSuccess) e = launch_gemm_bf16(M, N, K, Aw, Bw, C, c_dt, ldc, st);
+    if (e == hipSuccess) e = launch_int8_repair(M, N, K, Ae, As, Be, Bs, C, c_dt, ldc, range, ga, gb, st);
+    const hipError_t f = ws_release(ws, st);
+    return e != hipSuccess ? e : f;
+}
+
+// Whole 256 x 256 tiles that fill much of the chip: scratch memory has always been part of their product
+static bool int8_whole_tiles(int64_t M, int64_t N, int64_t K)
+{
+    const int64_t tiles = (M / 256) * (N / 256);
+    return M % 256 == 0 && N % 256 == 0 && K >= 128 && (tiles >= 96 || (tiles >= 64 && K < 1024));
+}
+
+// Whether the bf16 values are worth their making (3 bytes an element, at 4 TB/s) and two more launches.  us, the kernel that took the
+// problem before / bf16 values in a stream-ordered workspace, which costs the host 10 to 20 us (less with the caller's):
+//  - the staged kernel runs its 64 x 32 tiles in rounds of 256, 5.4 + 2.85 K / 1024 us each.  Two rounds: 256 x 4096 x 4096 34 / 44, 1000 x
+//    1000 x 8192 56 / 51; four: 1000 x 2048 x 1024 33 / 29, 512 x 4096 x 4096 67 / 49; more: 256 x 11008 x 4096 99 / 75, 1000 x 4096 x 4096
+//    134 / 61, 2048^3 88 / 44.  Few rows read the weights twice where they read them once: 128 x 11008 x 4096 52 / 71.
+//  - the direct kernel (short or odd K): 256 x 11008 x 512 (2^30 products) 20 / 31, 1000 x 4096 x 512 (2^31) 26 / 29, 8192 x 1000 x 512 48 / 35.
+static bool int8_widened_pays(int64_t M, int64_t N, int64_t K)
+{
+    if (M <= 128) return false;
+    if (K % 128 == 0 && K >= 1024) return ((M + 63) / 64) * ((N + 31) / 32) > 768;
+    return K >= 64 && M * N >= ((int64_t)1 << 31) / K;
 }
 
 hipError_t launch_gemm_int8(int64_t M, int64_t N, int64_t K, const uint8_t *Ae, const uint8_t *As, const uint8_t *Be,
                             const uint8_t *Bs, void *C, int c_dt, int64_t ldc, hipStream_t st)
 {
-    // Four routes, picked by measurement (same box, bf16 output; TOP/s = 2 M N K / time):
-    //  - the split route: whole 256 x 256 tiles and a depth the tiled kernel takes (4K a multiple of 128, >= 512).
-    //    It wins once the tiles fill most of the chip: 4096^3 505 TOP/s, 8192 x 4096 x 4096 631, 2048 x 8192 x 1024
-    //    363, 4096 x 4096 x 512 272 -- against 250, 257, 136, 74 for the staged kernel;
-    //  - the LDS-staged shared-K kernel (K a multiple of 128): about 230 TOP/s when K is long, falling with K
-    //    (each tile's eight partial sums cost the same whatever K is): 512 x 4096 x 4096 77 us against the
-    //    direct kernel's 128, 256 x 11008 x 4096 112 against 189, 1000 x 1000 x 1024 19 against 25; with 64 tiles
-    //    and a long K it is ahead of the split route too (2048^3 95 against 116 us, 1024 x 4096 x 4096 146 against
-    //    196; level at 2048 x 2048 x 512), and few rows (decoding) are 1.2-1.7 times faster than unstaged;
+    // Routes, picked by measurement (bf16 output; TOP/s = 2 M N K / time):
+    //  - the product of the bf16 values (int8_widened_pays): 8192 x 4096 x 4096 1220 TOP/s, 4096^3 1070, 1000 x 4096 x 4096 550;
+    //  - the LDS-staged shared-K kernel (K a multiple of 128): about 250 TOP/s when K is long, falling with K (each tile's eight
+    //    partial sums cost the same whatever K is): 256 x 4096 x 4096 34 us, 1000 x 1000 x 1024 18;
     //  - the unstaged shared-K kernel for few rows or few tiles when K is not a multiple of 128;
     //  - the direct kernel for everything else (short K, odd shapes): 80-170 TOP/s.
-    const int64_t tiles256 = (M / 256) * (N / 256);
-    const bool split = M > 0 && N > 0 && K >= 128 && (tiles256 >= 96 || (tiles256 >= 64 && K < 1024)) &&
-                       gemm_tiled_applies(M, N, 4 * K, FP6_E2M3, FP6_E2M3);
-    if (split) {
-        const size_t nba = (size_t)M * (size_t)(K / BLOCK), nbb = (size_t)N * (size_t)(K / BLOCK);
-        const size_t off_ea = 256, off_eb = off_ea + nba * 96, off_sa = off_eb + nbb * 96, off_sb = off_sa + nba * 4;
-        uint8_t *ws = nullptr;
-        hipError_t e = ws_acquire(off_sb + nbb * 4, st, &ws);
-        if (e != hipSuccess) return e;
-        {
-            uint32_t *flag = reinterpret_cast<uint32_t *>(ws);
-            hipLaunchKernelGGL(int8_clear_flag_kernel, dim3(1), dim3(1), 0, st, flag);
-            e = hipGetLastError();
-            if (e == hipSuccess) {
-                hipLaunchKernelGGL((int8_split_kernel<false>), dim3((unsigned)((nba + 255) / 256)), dim3(256), 0, st, Ae, As,
-                                   (int64_t)nba, ws + off_ea, ws + off_sa, flag);
-                hipLaunchKernelGGL((int8_split_kernel<true>), dim3((unsigned)((nbb + 255) / 256)), dim3(256), 0, st, Be, Bs,
-                                   (int64_t)nbb, ws + off_eb, ws + off_sb, flag);
-                e = hipGetLastError();
-            }
-            if (e == hipSuccess)
-                e = launch_gemm_tiled(M, N, 4 * K, ws + off_ea, ws + off_sa, nullptr, 0, ROUND_RNE, FP6_E2M3, ws + off_eb,
-                                      ws + off_sb, FP6_E2M3, C, c_dt, ldc, st);
-            if (e == hipSuccess) e = launch_int8_direct(M, N, K, Ae, As, Be, Bs, C, c_dt, ldc, flag, st);
-            const hipError_t f = ws_release(ws, st);
-            return e != hipSuccess ? e : f;
-        }
+    // (by shape alone, with or without a caller's workspace: the same product gives the same bits through every entry point)
+    const bool whole = int8_whole_tiles(M, N, K);
+    if (gemm_bf16_applies(M, N, K) && (whole || int8_widened_pays(M, N, K))) {
+        bool refused;
+        const hipError_t e = launch_int8_widened(M, N, K, Ae, As, Be, Bs, C, c_dt, ldc, st, &refused);
+        if (!refused || whole) return e;
     }
     if (M > 0 && N > 0 && K % 128 == 0 && (M <= 128 ? K >= 8 * BLOCK : K >= 1024) && (M + 63) / 64 <= 65535)
         return M <= 8    ? launch_int8_lds<1, 1>(M, N, K, Ae, As, Be, Bs, C, c_dt, ldc, st)
@@ -472,7 +562,7 @@ hipError_t launch_gemm_int8(int64_t M, int64_t N, int64_t K, const uint8_t *Ae, 
             hipLaunchKernelGGL((gemm_int8_shared_k_kernel<DT_BF16>), grid, dim3(64 * I8_WAVES), 0, st, M, N, K, Ae, As, Be, Bs, C, ldc);
         return hipGetLastError();
     }
-    return launch_int8_direct(M, N, K, Ae, As, Be, Bs, C, c_dt, ldc, nullptr, st);
+    return launch_int8_direct(M, N, K, Ae, As, Be, Bs, C, c_dt, ldc, st);
 }
 
 }  // namespace mx

@@ -51,6 +51,9 @@ __global__ __launch_bounds__(256, 2) void gemm_mid_kernel(int M, int N, int64_t 
 {
     constexpr int WA = Fmt<FA>::bits, WB = Fmt<FB>::bits;
     constexpr int HA = hw_fmt(FA), HB = hw_fmt(FB);   // must reach the builtin as literal constants
+    // FA = FB = INT8: bf16 operands without scales, K counts the bytes of a row (64 elements a step), and the two 16-byte chunks of a
+    // lane are the operands of two 32 x 32 x 16 bf16 instructions; everything else is the same
+    constexpr bool BF = FA == INT8 && FB == INT8;
     constexpr int BM = 64 * MB, BN = 64 * NB;
     // wave-wide direct loads (1 KB) per wave and operand; a 6-bit tile of 64 rows (6 KB) is padded to 8 KB
     constexpr int NJA = (BM * TileFmt<WA>::ROW + 4095) / 4096, NJB = (BN * TileFmt<WB>::ROW + 4095) / 4096, NJ = NJA + NJB;
@@ -116,6 +119,7 @@ __global__ __launch_bounds__(256, 2) void gemm_mid_kernel(int M, int N, int64_t 
     if (seg < MB) srow = As + (int64_t)(m0 + seg * 64 + lane < M ? m0 + seg * 64 + lane : M - 1) * nkb;
     else srow = Bs + (int64_t)(n0 + (seg - MB) * 64 + lane < N ? n0 + (seg - MB) * 64 + lane : N - 1) * nkb;
     auto stage_scales = [&](int G) {
+        if constexpr (BF) return;
         if (direct_scales) {
             const uint32_t l = scl0 + (G & 1) * SG_BYTES + seg * 1024;
             const uint8_t *p = srow + (4 * G + 4 <= steps ? 16 * G : 4 * steps - 16);
@@ -126,9 +130,10 @@ __global__ __launch_bounds__(256, 2) void gemm_mid_kernel(int M, int N, int64_t 
             *reinterpret_cast<uint4 *>(scl + (G & 1) * SG_BYTES + seg * 1024 + lane * 16) = make_uint4(d[0], d[1], d[2], d[3]);
         }
     };
-    uint32_t sa[MB], sb[NB];
+    uint32_t sa[MB] = {}, sb[NB] = {};
     // scale dwords of step t; lanes 32 .. 63 shift theirs by a byte: one selector then addresses block 2 sub + g
     auto read_scales = [&](int t) {
+        if constexpr (BF) return;
         t = t < steps ? t : steps - 1;
         const int pos = direct_scales && (t | 3) >= steps ? t - steps + 4 : t & 3;
         const uint8_t *s = scl + ((t >> 2) & 1) * SG_BYTES + pos * 4;
@@ -156,8 +161,18 @@ __global__ __launch_bounds__(256, 2) void gemm_mid_kernel(int M, int N, int64_t 
         for (int y = 0; y < NB; y++) b[y] = read_frag<WB>(buf + A_BYTES, fb, sub, y);
     };
     // B goes first: a lane ends up with groups of four consecutive columns of one row of C
+    auto mid_bf16 = [](const v8i_t &b, const v8i_t &a, v16f_t c) __attribute__((always_inline)) {
+        typedef __bf16 bf16x8_t_ __attribute__((ext_vector_type(8)));
+        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t_, __builtin_shufflevector(b, b, 0, 1, 2, 3)),
+                                                    __builtin_bit_cast(bf16x8_t_, __builtin_shufflevector(a, a, 0, 1, 2, 3)), c, 0, 0, 0);
+        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t_, __builtin_shufflevector(b, b, 4, 5, 6, 7)),
+                                                       __builtin_bit_cast(bf16x8_t_, __builtin_shufflevector(a, a, 4, 5, 6, 7)), c, 0, 0, 0);
+    };
 #define MX_MID_MFMA(SUB, A_, B_, X, Y)                                                                                              \
-    acc[X][Y] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(B_[Y], A_[X], acc[X][Y], HB, HA, 2 * SUB, (int)sb[Y], 2 * SUB, (int)sa[X])
+    do {                                                                                                                            \
+        if constexpr (BF) acc[X][Y] = mid_bf16(B_[Y], A_[X], acc[X][Y]);                                                            \
+        else acc[X][Y] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(B_[Y], A_[X], acc[X][Y], HB, HA, 2 * SUB, (int)sb[Y], 2 * SUB, (int)sa[X]); \
+    } while (0)
 
     stage_scales(0);
     if (T > 0) {

@@ -45,12 +45,12 @@ hipError_t launch_dequant(const uint8_t *elems, const uint8_t *scales, int fmt, 
 hipError_t launch_dequant_3d(const uint8_t *elems, const uint8_t *scales, int fmt, int64_t d0, int64_t d1, int64_t d2, int axis,
                              bool keep_order, void *dst, int dst_dt, int64_t stride0, int64_t stride1, hipStream_t st);
 
-// Scratch memory of the GEMM routes that need it (the MX form of a bf16 operand, the two E2M3 halves of
+// Scratch memory of the GEMM routes that need it (the MX form of a bf16 operand, the bf16 values of
 // MXINT8 operands, a Float32 C that is cast afterwards).  Inside a WorkspaceScope -- opened by the
 // entry points that take a caller-owned workspace -- ws_acquire carves 256-byte aligned pieces off
 // that workspace (hipErrorOutOfMemory when it is too small); outside one it takes the piece from
 // the device's memory pool in stream order.  ws_release returns the piece (last acquired first).
-// A refused request is an error of the call; no route falls back to another kernel because of it.
+// A refused request is an error of the call, but for problems that other kernels take without scratch memory.
 struct WorkspaceScope {
     WorkspaceScope(void *p, size_t bytes);
     ~WorkspaceScope();
@@ -72,6 +72,10 @@ hipError_t launch_gemm(int64_t M, int64_t N, int64_t K, const uint8_t *A_elems, 
 // MXINT8 x MXINT8: integer matrix instruction per block, Float32 accumulation of the scaled block sums
 hipError_t launch_gemm_int8(int64_t M, int64_t N, int64_t K, const uint8_t *Ae, const uint8_t *As, const uint8_t *Be,
                             const uint8_t *Bs, void *C, int c_dt, int64_t ldc, hipStream_t st);
+
+// C = A B^T for bf16 operands [M][K], [N][K], 16-byte aligned
+bool gemm_bf16_applies(int64_t M, int64_t N, int64_t K);
+hipError_t launch_gemm_bf16(int64_t M, int64_t N, int64_t K, const void *A, const void *B, void *C, int c_dt, int64_t ldc, hipStream_t st);
 
 // true when the LDS-tiled kernel takes the problem: FP8 / FP6 / FP4 operands, whole 256 x 256
 // tiles, K a multiple of 128 and at least 512

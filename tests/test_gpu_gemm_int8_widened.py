@@ -1,0 +1,114 @@
+"""MXINT8 products on the bf16 values of their blocks (more than 128 rows and many tiles or products): ragged sizes, partial K steps, whole
+tiles with a remainder, scale bytes at the ends of what bf16 and Float32 hold and beyond them."""
+import pytest
+
+import launches
+
+INT8 = 5
+
+
+def test_routes(tmp_path):
+    rt = launches.build(str(tmp_path))
+    P = 1 << 20
+
+    def kernels(M, N, K, ws=True, refuse=0):
+        call = ("mx_gemm_ws", (M, N, K, P, P, INT8, P, P, INT8, P, 1, N, P, 1 << 40, 0)) if ws else \
+            ("mx_gemm", (M, N, K, P, P, INT8, P, P, INT8, P, 1, N, 0))
+        (status, seen), = launches.trace(rt, [call + (refuse,)])
+        return status, [k[0] for k in seen]
+    wide, mid, check = "gemm_tile16_kernel", "gemm_mid_kernel", "gemm_int8_repair_kernel"
+    assert kernels(8192, 4096, 4096) == (0, ["int8_widen_kernel", wide, check])
+    assert kernels(4096, 4352, 512) == (0, ["int8_widen_kernel", wide, mid, check])             # 272 tiles: 16 of 17 columns, the rest in small tiles
+    assert kernels(4100, 4352, 512) == (0, ["int8_widen_kernel", wide, mid, mid, check])
+    assert kernels(1000, 4096, 4096) == kernels(4096, 4096, 544)[:1] + (["int8_widen_kernel", mid, check],)
+    assert kernels(4096, 4096, 4064)[1] == ["int8_widen_kernel", mid, check]                    # half a K step at the end: no whole tiles
+    for M, N, K in ((128, 11008, 4096), (256, 4096, 4096), (1000, 1000, 4096)):
+        assert kernels(M, N, K) == (0, ["gemm_int8_lds_kernel"])
+    assert kernels(256, 11008, 512) == kernels(300, 300, 96) == (0, ["gemm_int8_kernel"])
+    for M, N, K in ((8192, 4096, 4096), (1000, 1600, 4096)):                                    # by shape, wherever the scratch comes from
+        assert kernels(M, N, K, ws=False)[1] == ["alloc"] + kernels(M, N, K)[1]
+    # refused scratch memory: an error where it always was one, the kernels without it elsewhere
+    assert kernels(8192, 4096, 4096, ws=False, refuse=1)[0] != 0
+    assert kernels(8000, 4000, 4096, ws=False, refuse=1) == (0, ["gemm_int8_lds_kernel"])
+
+
+def test_scratch_of_the_binding(monkeypatch):
+    """From torch's allocator on the current stream, outside a capture, for the sizes whose route uses it."""
+    import types
+
+    import torch
+    from paper_2310_10537_amd import binding
+    cpu, capturing = torch.device("cpu"), [False]
+    current = types.SimpleNamespace(device=cpu, cuda_stream=11)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: current)
+    monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: capturing[0])
+    monkeypatch.setattr(torch, "empty", lambda n, dtype, device: n)                            # (gigabytes otherwise)
+
+    def size(M, N, K, stream=None):
+        return binding._int8_workspace(M, N, K, cpu, stream)
+    assert size(8192, 4096, 4096) == binding.mx_workspace_bytes("gemm", 8192, 4096, 4096, INT8, INT8)
+    assert size(1000, 1600, 4096) is not None and size(1000, 4096, 512) is not None and size(2048, 2048, 512) is not None
+    for shape in ((128, 28672, 8192), (256, 4096, 4096), (300, 300, 96)):
+        assert size(*shape) is None
+    assert size(8192, 4096, 4096, types.SimpleNamespace(cuda_stream=12)) is None
+    capturing[0] = True
+    assert size(8192, 4096, 4096) is None
+
+
+def operand(torch, g, rows, K, lo, hi):
+    q = torch.randint(-128, 128, (rows, K), generator=g, device="cuda", dtype=torch.int32)
+    s = torch.randint(lo, hi + 1, (rows, K // 32), generator=g, device="cuda", dtype=torch.int32)
+    q[0, :32], s[0, 0] = 0, 0                                     # zeros: their scale does not count
+    q[1, 32:64], s[1, 1] = -128, hi
+    q[2, :] = 127
+    return q.to(torch.int8), s.to(torch.uint8)
+
+
+SHAPES = [(129, 12320, 4096), (1000, 2050, 1024), (515, 4103, 2080), (4100, 4360, 544), (4096, 4352, 576), (2304, 3840, 96)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("ranges", [((120, 134), (120, 134)), ((7, 20), (133, 160)), ((180, 253), (60, 125)),            # held by bf16
+                                    ((6, 20), (133, 160)), ((60, 79), (60, 79)), ((200, 254), (60, 120)), ((180, 200), (180, 200))])
+def test_against_float64(shape, ranges):
+    import torch
+    from paper_2310_10537_amd import binding as mx
+    M, N, K = shape
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M + N + K)
+    (qa, sa), (qb, sb) = operand(torch, g, M, K, *ranges[0]), operand(torch, g, N, K, *ranges[1])
+    C = mx.mx_gemm(qa.view(torch.uint8), sa, INT8, qb.view(torch.uint8), sb, INT8, K)
+    rows = torch.cat([torch.arange(3), torch.randint(0, M, (29,), generator=torch.Generator().manual_seed(1)), torch.tensor([M - 1])]).cuda()
+
+    def value(q, s):
+        return q.double() * torch.exp2(s.double() - 133).repeat_interleave(32, dim=1)
+    a, b = value(qa[rows], sa[rows]), value(qb, sb)
+    ref, mag = a @ b.T, a.abs() @ b.abs().T
+    got = C[rows].double()
+    big = torch.finfo(torch.float32).max
+    inside = mag < big / 4                                        # beyond: a sum of Float32 numbers overflows on the way, or not
+    # every block sum is exact or a few roundings of 2^-24 of the running sum, K / 16 steps of the instruction at most; below, the
+    # spacing of Float32's denormal numbers once per block
+    tol = mag * (K / 16 * 2.0 ** -24) + K / 32 * 2.0 ** -149
+    assert bool(((got - ref).abs() <= tol)[inside].all()), float(((got - ref).abs() / mag.clamp_min(1e-300))[inside].max())
+    assert bool((~torch.isfinite(got) | (got.abs() > big / 1e6))[ref.abs() > big * 2].all())
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("zeros", [False, True])
+def test_nan_scales(zeros):
+    import torch
+    from paper_2310_10537_amd import binding as mx
+    M, N, K = 1000, 2050, 1024
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    (qa, sa), (qb, sb) = operand(torch, g, M, K, 120, 130), operand(torch, g, N, K, 120, 130)
+    sa[700, 3] = 255
+    sb[2049, 31] = 255
+    if zeros:
+        qa[700, 96:128] = 0
+        qb[2049, 992:] = 0
+    C = mx.mx_gemm(qa.view(torch.uint8), sa, INT8, qb.view(torch.uint8), sb, INT8, K)
+    nan = torch.isnan(C)
+    assert bool(nan[700].all()) and bool(nan[:, 2049].all()) and int(nan.sum()) == M + N - 1
