@@ -154,15 +154,15 @@ static hipError_t launch_mt(int64_t M, int64_t N, int64_t K, const uint8_t *Ae, 
     return hipGetLastError();
 }
 
-template <int FA, int FB, int MT, bool FEW = false>
+template <int FA, int FB, int MT, int ROWS = 32 * MT>
 static hipError_t launch_lds(int64_t M, int64_t N, int64_t K, const uint8_t *Ae, const uint8_t *As, const uint8_t *Be,
                              const uint8_t *Bs, void *C, int c_dt, int64_t ldc, hipStream_t st)
 {
     const dim3 grid((unsigned)((N + 31) / 32), (unsigned)((M + 32 * MT - 1) / (32 * MT)));
     if (c_dt == DT_F32)
-        hipLaunchKernelGGL((gemm_skinny_lds_kernel<FA, FB, MT, DT_F32, MX_OPERAND, FEW>), grid, dim3(64 * SK_WAVES), 0, st, M, N, K, Ae, As, Be, Bs, C, ldc, (int64_t)0);
+        hipLaunchKernelGGL((gemm_skinny_lds_kernel<FA, FB, MT, DT_F32, MX_OPERAND, ROWS>), grid, dim3(64 * SK_WAVES), 0, st, M, N, K, Ae, As, Be, Bs, C, ldc, (int64_t)0);
     else
-        hipLaunchKernelGGL((gemm_skinny_lds_kernel<FA, FB, MT, DT_BF16, MX_OPERAND, FEW>), grid, dim3(64 * SK_WAVES), 0, st, M, N, K, Ae, As, Be, Bs, C, ldc, (int64_t)0);
+        hipLaunchKernelGGL((gemm_skinny_lds_kernel<FA, FB, MT, DT_BF16, MX_OPERAND, ROWS>), grid, dim3(64 * SK_WAVES), 0, st, M, N, K, Ae, As, Be, Bs, C, ldc, (int64_t)0);
     return hipGetLastError();
 }
 
@@ -171,7 +171,9 @@ static hipError_t launch_pair(int64_t M, int64_t N, int64_t K, const uint8_t *Ae
                               const uint8_t *Bs, void *C, int c_dt, int64_t ldc, hipStream_t st)
 {
     const bool staged = K % 128 == 0 && K <= SK_MAX_K;   // whole 128-element chunks, 16-byte aligned rows
-    if (staged && M <= (Fmt<FA>::bits == 4 ? 16 : 8)) return launch_lds<FA, FB, 1, true>(M, N, K, Ae, As, Be, Bs, C, c_dt, ldc, st);
+    // the loads of A that its rows need: 8 or 16 rows of one 32-row tile (figures at the kernel)
+    if (staged && M <= 8) return launch_lds<FA, FB, 1, 8>(M, N, K, Ae, As, Be, Bs, C, c_dt, ldc, st);
+    if (staged && M <= 16) return launch_lds<FA, FB, 1, 16>(M, N, K, Ae, As, Be, Bs, C, c_dt, ldc, st);
     if (M <= 32) return staged ? launch_lds<FA, FB, 1>(M, N, K, Ae, As, Be, Bs, C, c_dt, ldc, st)
                                : launch_mt<FA, FB, 1>(M, N, K, Ae, As, Be, Bs, C, c_dt, ldc, st);
     if (M <= 64) return staged ? launch_lds<FA, FB, 2>(M, N, K, Ae, As, Be, Bs, C, c_dt, ldc, st)

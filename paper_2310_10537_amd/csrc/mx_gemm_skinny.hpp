@@ -30,7 +30,12 @@ constexpr int64_t SK_MAX_K = (int64_t)1 << 25;       // of the staged kernel
 // Rows beyond M and columns beyond N read a valid row instead (clamped), as every load of a step then sits in one straight run that
 // the waits can count; such results are never stored.  (A branch per load to leave absent rows out made every wait one for all
 // loads in flight: 9 x 5120 x 7424 E4M3 8.8 us clamped, 15.9 with branches; 32 x 2503 x 17536 24.7 and 40.6; 64 rows 10 % slower.)
-// Up to 8 rows (FEW) one load brings all of A: 1 x 28672 x 8192 E4M3 x E2M1 29.7 us with the loads of 32 rows, 26.7 without.
+// Up to 8 or 16 rows A has loads of its own.  The load path takes its time by the line touched, 2.6 to 3.2 clocks each, whole or
+// not: with the loads of 32 rows A's pieces of a chunk were 48 such lines against 16 of 4-bit weights.  Against those two chunks of A go
+// together as well (PAIR_A): whole lines of 4- and 8-bit rows, two lines instead of three of 6-bit ones, and one wait instead of two.
+// 16 x 28672 x 8192 E3M2 x E2M1 36.2 us with the loads of 32 rows, 31.8 so (4 TB/s of weights); 16 x 4096 x 14336 12.2 / 10.1; 12 x 4096 x 4096
+// E4M3 pairs 6.5 / 6.1; 1 x 16128 x 8192 E4M3 x E2M1, 8 rows in both, 13.7 / 13.2 from the pairs alone.  The second chunk's 16 rows take the
+// tile's place of rows 16 .. 31, so 17 rows and more go a chunk at a time.
 // 4-bit B, up to 32 rows: two chunks at a time, 128 bytes of a row -- whole lines -- in flight for two steps; and the scales of four
 // chunks in one 16-byte load per row, which waits in LDS for its chunks: a dword per chunk touches each line four times as often, in
 // a cache that B streams through.  16 x 28672 x 8192 E3M2 x E2M1, weights from HBM: a chunk and a dword at a time 49.8 us, two
@@ -45,18 +50,19 @@ template <int W> struct SkStage {                    // one 32-row block of a 12
 };
 
 constexpr int MX_OPERAND = -1;                       // QA: A is an MX operand, else the rounding of its cast
-// FEW: at most 8 rows (16 of 4 bits), what one wave-wide load of A brings
-template <int FA, int FB, int MT, int CDT, int QA = MX_OPERAND, bool FEW = false>
+// ROWS: the most rows an MX operand A has, 8, 16 or 32 * MT
+template <int FA, int FB, int MT, int CDT, int QA = MX_OPERAND, int ROWS = 32 * MT>
 __global__ __launch_bounds__(64 * SK_WAVES, 1) void gemm_skinny_lds_kernel(int64_t M, int64_t N, int64_t K,
                                                                          const uint8_t *__restrict__ Ae, const uint8_t *__restrict__ As,
                                                                          const uint8_t *__restrict__ Be, const uint8_t *__restrict__ Bs,
                                                                          void *__restrict__ C, int64_t ldc, int64_t lda)
 {
     constexpr bool CAST = QA != MX_OPERAND;          // A: bf16 [M][lda], at most 16 rows
-    static_assert((!CAST && !FEW) || MT == 1, "one 32-row tile");
+    static_assert(MT == 1 || (!CAST && ROWS == 32 * MT), "one 32-row tile");
     constexpr int WA = Fmt<FA>::bits, WB = Fmt<FB>::bits;
     constexpr int HA = hw_fmt(FA), HB = hw_fmt(FB);   // must reach the builtin as literal constants
     constexpr int CB = MT == 1 && WB == 4 ? 2 : 1;    // chunks of B loaded together
+    constexpr bool PAIR_A = CB == 2 && ROWS <= 16 && !CAST;     // two chunks of A loaded together
     constexpr bool GROUPS = CB == 2;                  // scales of four chunks in one load, by way of LDS
     constexpr int A_BYTES = MT * SkStage<WA>::BYTES, B_BYTES = CB * SkStage<WB>::BYTES, W_BYTES = A_BYTES + B_BYTES + (GROUPS ? 1024 : 0);
     constexpr int RED_BYTES = (SK_WAVES - 1) * MT * 16 * 64 * 4;
@@ -71,10 +77,11 @@ __global__ __launch_bounds__(64 * SK_WAVES, 1) void gemm_skinny_lds_kernel(int64
     uint8_t *tA = lds + wave * W_BYTES, *tB = tA + A_BYTES;
 
     // ---- staging: lane -> (row l / P, 16-byte piece l % P) of a wave-wide load; P pieces per row chunk
-    constexpr int PA = WA == 4 ? 4 : 8, PB = WB == 4 ? 4 * CB : 8;       // (6-bit: pieces 6 and 7 stay idle)
-    constexpr int NJA = FEW ? 1 : SkStage<WA>::NJ, NJB = CB * SkStage<WB>::NJ;
+    // PAIR_A: the P = 2 WA pieces of both chunks in a row, a run of 64 after the other; the second chunk's tile stands where rows 16 .. 31 would be
+    constexpr int PA = PAIR_A ? 2 * WA : WA == 4 ? 4 : 8, PB = WB == 4 ? 4 * CB : 8;       // (6-bit: pieces 6 and 7 stay idle)
+    constexpr int NJA = ((ROWS < 32 ? ROWS : 32) * PA + 63) / 64, NJB = CB * SkStage<WB>::NJ;
     const int ar = lane / PA, ap = lane % PA, br = lane / PB, bp = lane % PB;
-    const bool a_on = WA != 6 || ap < 6, b_on = WB != 6 || bp < 6;
+    const bool a_on = PAIR_A || WA != 6 || ap < 6, b_on = WB != 6 || bp < 6;
     const int64_t a_rb = K * WA / 8, b_rb = K * WB / 8;                   // bytes per matrix row
     auto clampi = [](int64_t v, int64_t hi) { return v < hi ? v : hi; };
     // 32-bit offsets of the lane's pieces from wave-uniform addresses (K up to SK_MAX_K: 127 rows stay below 2^32 bytes)
@@ -82,7 +89,10 @@ __global__ __launch_bounds__(64 * SK_WAVES, 1) void gemm_skinny_lds_kernel(int64
 #pragma unroll
     for (int x = 0; x < MT; x++)
 #pragma unroll
-        for (int j = 0; j < NJA; j++) a_ofs[x][j] = (uint32_t)clampi(32 * x + j * (64 / PA) + ar, M - 1 - m0) * (uint32_t)a_rb + ap * 16;
+        for (int j = 0; j < NJA; j++) {
+            const int n = j * 64 + lane, r = PAIR_A ? n / PA : j * (64 / PA) + ar, p = PAIR_A ? n % PA : ap;
+            a_ofs[x][j] = (uint32_t)clampi(32 * x + r, M - 1 - m0) * (uint32_t)a_rb + p * 16;
+        }
 #pragma unroll
     for (int j = 0; j < NJB; j++) b_ofs[j] = (uint32_t)clampi(j * (64 / PB) + br, N - 1 - n0) * (uint32_t)b_rb + bp * 16;
     uint32_t sa_ofs[MT];
@@ -128,7 +138,10 @@ __global__ __launch_bounds__(64 * SK_WAVES, 1) void gemm_skinny_lds_kernel(int64
 #pragma unroll
                 for (int x = 0; x < MT; x++)
 #pragma unroll
-                    for (int j = 0; j < NJA; j++) ra[x][j] = piece(p, a_ofs[x][j]);
+                    for (int j = 0; j < NJA; j++) {           // (a second chunk beyond K: the first one again)
+                        const uint32_t back = PAIR_A && c + 1 >= chunks && (j * 64 + lane) % PA >= WA ? 16 * WA : 0;
+                        ra[x][j] = piece(p, a_ofs[x][j] - back);
+                    }
             }
         }
     };
@@ -177,6 +190,13 @@ __global__ __launch_bounds__(64 * SK_WAVES, 1) void gemm_skinny_lds_kernel(int64
                 }
             }
             if constexpr (FA == FP8_E4M3 || FA == FP8_E5M2) fp8_saturate_mode(false);
+        } else if constexpr (PAIR_A) {
+#pragma unroll
+            for (int j = 0; j < NJA; j++) {
+                const int n = j * 64 + lane, r = n / PA, p = n % PA;
+                if (ROWS * PA % 64 == 0 || n < ROWS * PA)
+                    *reinterpret_cast<uint4 *>(tA + (p >= WA ? A_BYTES / 2 + lds_slot(WA, r, p - WA) : lds_slot(WA, r, p))) = ra[0][j];
+            }
         } else if (a_on) {
 #pragma unroll
             for (int x = 0; x < MT; x++)
@@ -221,7 +241,7 @@ __global__ __launch_bounds__(64 * SK_WAVES, 1) void gemm_skinny_lds_kernel(int64
         for (int k = 0; k < CB; k++) {
             const int64_t c = c0 + k;
             if (k > 0 && c >= c_end) break;
-            park_a();
+            if (!PAIR_A || k == 0) park_a();
             if (k == 0) park_b();
             uint32_t sa[MT], sb;
             if constexpr (!GROUPS) {
@@ -242,15 +262,16 @@ __global__ __launch_bounds__(64 * SK_WAVES, 1) void gemm_skinny_lds_kernel(int64
 #pragma unroll
             for (int x = 0; x < MT; x++) sa[x] = g ? sa[x] >> 8 : sa[x];
             // loads return in order: the scales, wanted last, behind the operands of their step
-            if (c + 1 < c_end) request_a(c + 1);
+            if (!PAIR_A && c + 1 < c_end) request_a(c + 1);
+            if (PAIR_A && k == 0 && c0 + CB < c_end) request_a(c0 + CB);
             if (CB == 1 && c + 1 < c_end) request_b(c + 1);
             if (!GROUPS && c + 1 < c_end) request_s(c + 1);
             if (CB == 2 && k == 0 && c0 + CB < c_end) request_b(c0 + CB);
-            const uint8_t *tb = tB + k * SkStage<WB>::BYTES;
+            const uint8_t *tb = tB + k * SkStage<WB>::BYTES, *ta = tA + (PAIR_A ? k * (A_BYTES / 2) : 0);
             const v8i_t b0 = read_frag<WB>(tb, fb, 0, 0), b1 = read_frag<WB>(tb, fb, 1, 0);
 #pragma unroll
             for (int x = 0; x < MT; x++) {
-                const v8i_t a0 = read_frag<WA>(tA + x * SkStage<WA>::BYTES, fa, 0, 0), a1 = read_frag<WA>(tA + x * SkStage<WA>::BYTES, fa, 1, 0);
+                const v8i_t a0 = read_frag<WA>(ta + x * SkStage<WA>::BYTES, fa, 0, 0), a1 = read_frag<WA>(ta + x * SkStage<WA>::BYTES, fa, 1, 0);
                 acc[x] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a0, b0, acc[x], HA, HB, 0, (int)sa[x], 0, (int)sb);
                 acc[x] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a1, b1, acc[x], HA, HB, 2, (int)sa[x], 2, (int)sb);
             }
