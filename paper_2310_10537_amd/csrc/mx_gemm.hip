@@ -12,8 +12,9 @@
 //   scales: lane l supplies the E8M0 byte of row/column i, K block g (byte 0 of
 //     the scale register with op_sel 0), whatever the element width;
 //   result: lane l, register t holds C[8*(t/4) + 4*g + t%4][i].
-// The 32x32x64 form is used for every format pair: it runs 6- and 4-bit pairs
-// at twice the 8-bit rate, which the 16x16x128 form does not.
+// The kernel in this file uses the 32x32x64 form for every format pair.  Both forms run
+// 6- and 4-bit pairs at twice the 8-bit rate and return the same bits; the 16x16x128 form, which
+// needs less energy, is in the kernels for large products (mx_gemm_tile16.hpp, mx_gemm_tile16n.hpp).
 #include "mx_gemm_frag.hpp"
 #include "mx_launch.hpp"
 
