@@ -19,7 +19,7 @@
 // kernel's tiles -- launched after the product, left at once as a rule -- recompute C when it does not.  (The 8-bit integer
 // instruction is twice as fast as the bf16 one, but every block's sums have to be scaled by the vector pipe: 48 instructions for
 // 32 clocks of it.  Splitting q into two E2M3 halves, four products on the block-scaled instruction at four times the bf16 rate, moves
-// three bytes an element instead of two for the same matrix work: 8192 x 4096 x 4096 348 us where this takes 226.)
+// three bytes an element instead of two for the same matrix work: 8192 x 4096 x 4096 348 us where this takes 215.)
 #include "mx_device.hpp"
 #include "mx_launch.hpp"
 
@@ -144,24 +144,44 @@ __global__ __launch_bounds__(256) void int8_widen_kernel(const uint8_t *__restri
 }
 
 // What int8_widen_kernel left: whether the ranges of the scales of A and B allow the product of the bf16 values.  (range: n_a words
-// of A's work-groups, then n_b of B's.)  Every thread of the work-group gets the answer.
+// of A's work-groups, then n_b of B's.)  Every thread of the work-group (256) gets the answer.  Bound by the latency of its loads: eight
+// in flight, where one after the other took 16.9 us over the 6144 words of 8192 x 4096 x 4096 (4.6 us so).
 __device__ __forceinline__ bool widened_product_holds(const uint32_t *__restrict__ range, unsigned n_a, unsigned n_b)
 {
-    __shared__ uint32_t worst[4];                              // 255 - least and largest of A, of B
-    if (threadIdx.x < 4) worst[threadIdx.x] = 0;
-    __syncthreads();
-    uint32_t m[4] = {0, 0, 0, 0};
-    for (unsigned k = threadIdx.x; k < n_a + n_b; k += blockDim.x) {
-        const uint32_t r = range[k], a = r >> 16, b = r & 0xffff;
-        const int o = k < n_a ? 0 : 2;
-        m[o] = m[o] > a ? m[o] : a;
-        m[o + 1] = m[o + 1] > b ? m[o + 1] : b;
+    typedef uint16_t u16x2_t __attribute__((ext_vector_type(2)));
+    __shared__ uint32_t part[2][4];
+    constexpr unsigned AHEAD = 8;
+    const unsigned n = n_a + n_b;
+    const u16x2_t none = {0, 0};
+    u16x2_t wa = none, wb = none;                              // {largest, 255 - least} of A, of B
+    for (unsigned k0 = threadIdx.x; k0 < n; k0 += AHEAD * 256) {
+        uint32_t r[AHEAD];
+#pragma unroll
+        for (unsigned j = 0; j < AHEAD; j++) r[j] = range[k0 + j * 256 < n ? k0 + j * 256 : n - 1];     // (beyond the end: B's last word again)
+#pragma unroll
+        for (unsigned j = 0; j < AHEAD; j++) {
+            const u16x2_t v = __builtin_bit_cast(u16x2_t, r[j]);
+            const bool of_a = k0 + j * 256 < n_a;
+            wa = __builtin_elementwise_max(wa, of_a ? v : none);
+            wb = __builtin_elementwise_max(wb, of_a ? none : v);
+        }
     }
 #pragma unroll
-    for (int k = 0; k < 4; k++)
-        if (m[k]) atomicMax(&worst[k], m[k]);
+    for (int o = 1; o < 64; o <<= 1) {
+        wa = __builtin_elementwise_max(wa, __builtin_bit_cast(u16x2_t, __shfl_xor(__builtin_bit_cast(int, wa), o)));
+        wb = __builtin_elementwise_max(wb, __builtin_bit_cast(u16x2_t, __shfl_xor(__builtin_bit_cast(int, wb), o)));
+    }
+    if ((threadIdx.x & 63) == 0) {
+        part[0][threadIdx.x >> 6] = __builtin_bit_cast(uint32_t, wa);
+        part[1][threadIdx.x >> 6] = __builtin_bit_cast(uint32_t, wb);
+    }
     __syncthreads();
-    const int lo_a = 255 - (int)worst[0], hi_a = (int)worst[1], lo_b = 255 - (int)worst[2], hi_b = (int)worst[3];
+#pragma unroll
+    for (int k = 0; k < 4; k++) {
+        wa = __builtin_elementwise_max(wa, __builtin_bit_cast(u16x2_t, part[0][k]));
+        wb = __builtin_elementwise_max(wb, __builtin_bit_cast(u16x2_t, part[1][k]));
+    }
+    const int lo_a = 255 - (int)wa[1], hi_a = (int)wa[0], lo_b = 255 - (int)wb[1], hi_b = (int)wb[0];
     if (lo_a == 0 || lo_b == 0) return false;                  // a scale of its own out of range
     return hi_a == 0 || hi_b == 0 /* zeros only */ || (lo_a + lo_b >= 140 && hi_a + hi_b <= 378);
 }
@@ -533,7 +553,7 @@ hipError_t launch_gemm_int8(int64_t M, int64_t N, int64_t K, const uint8_t *Ae, 
                             const uint8_t *Bs, void *C, int c_dt, int64_t ldc, hipStream_t st)
 {
     // Routes, picked by measurement (bf16 output; TOP/s = 2 M N K / time):
-    //  - the product of the bf16 values (int8_widened_pays): 8192 x 4096 x 4096 1220 TOP/s, 4096^3 1070, 1000 x 4096 x 4096 550;
+    //  - the product of the bf16 values (int8_widened_pays): 8192 x 4096 x 4096 1280 TOP/s, 4096^3 1070 and more, 1000 x 4096 x 4096 550;
     //  - the LDS-staged shared-K kernel (K a multiple of 128): about 250 TOP/s when K is long, falling with K (each tile's eight
     //    partial sums cost the same whatever K is): 256 x 4096 x 4096 34 us, 1000 x 1000 x 1024 18;
     //  - the unstaged shared-K kernel for few rows or few tiles when K is not a multiple of 128;
