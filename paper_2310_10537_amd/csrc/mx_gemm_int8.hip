@@ -553,7 +553,7 @@ hipError_t launch_gemm_int8(int64_t M, int64_t N, int64_t K, const uint8_t *Ae, 
                             const uint8_t *Bs, void *C, int c_dt, int64_t ldc, hipStream_t st)
 {
     // Routes, picked by measurement (bf16 output; TOP/s = 2 M N K / time):
-    //  - the product of the bf16 values (int8_widened_pays): 8192 x 4096 x 4096 1280 TOP/s, 4096^3 1070 and more, 1000 x 4096 x 4096 550;
+    //  - the product of the bf16 values (int8_widened_pays): 8192 x 4096 x 4096 1280 TOP/s, 4096^3 over 1070, 1000 x 4096 x 4096 over 550;
     //  - the LDS-staged shared-K kernel (K a multiple of 128): about 250 TOP/s when K is long, falling with K (each tile's eight
     //    partial sums cost the same whatever K is): 256 x 4096 x 4096 34 us, 1000 x 1000 x 1024 18;
     //  - the unstaged shared-K kernel for few rows or few tiles when K is not a multiple of 128;
