@@ -510,7 +510,7 @@ static hipError_t launch_int8_repair(int64_t M, int64_t N, int64_t K, const uint
 
 // C from the bf16 values of the blocks, in scratch memory; *refused when there is none to be had
 static hipError_t launch_int8_widened(int64_t M, int64_t N, int64_t K, const uint8_t *Ae, const uint8_t *As, const uint8_t *Be,
-                                      const uint8_t *Bs, void *C, int c_dt, int64_t ldc, hipStream_t st, bool *refused)
+                                      const uint8_t *Bs, void *C, int c_dt, int64_t ldc, bool whole, hipStream_t st, bool *refused)
 {
     const int64_t na = M * K, nb = N * K;
     const unsigned ga = (unsigned)((na + WIDEN_ELEMS - 1) / WIDEN_ELEMS), gb = (unsigned)((nb + WIDEN_ELEMS - 1) / WIDEN_ELEMS);
@@ -523,7 +523,7 @@ static hipError_t launch_int8_widened(int64_t M, int64_t N, int64_t K, const uin
     uint16_t *Aw = reinterpret_cast<uint16_t *>(ws + range_bytes), *Bw = reinterpret_cast<uint16_t *>(ws + range_bytes + a_bytes);
     hipLaunchKernelGGL(int8_widen_kernel, dim3(ga + gb), dim3(256), 0, st, Ae, As, na, Be, Bs, nb, Aw, Bw, range, ga);
     e = hipGetLastError();
-    if (e == hipSuccess) e = launch_gemm_bf16(M, N, K, Aw, Bw, C, c_dt, ldc, st);
+    if (e == hipSuccess) e = launch_gemm_bf16(M, N, K, Aw, Bw, C, c_dt, ldc, !whole, st);
     if (e == hipSuccess) e = launch_int8_repair(M, N, K, Ae, As, Be, Bs, C, c_dt, ldc, range, ga, gb, st);
     const hipError_t f = ws_release(ws, st);
     return e != hipSuccess ? e : f;
@@ -562,7 +562,7 @@ hipError_t launch_gemm_int8(int64_t M, int64_t N, int64_t K, const uint8_t *Ae, 
     const bool whole = int8_whole_tiles(M, N, K);
     if (gemm_bf16_applies(M, N, K) && (whole || int8_widened_pays(M, N, K))) {
         bool refused;
-        const hipError_t e = launch_int8_widened(M, N, K, Ae, As, Be, Bs, C, c_dt, ldc, st, &refused);
+        const hipError_t e = launch_int8_widened(M, N, K, Ae, As, Be, Bs, C, c_dt, ldc, whole, st, &refused);
         if (!refused || whole) return e;
     }
     if (M > 0 && N > 0 && K % 128 == 0 && (M <= 128 ? K >= 8 * BLOCK : K >= 1024) && (M + 63) / 64 <= 65535)

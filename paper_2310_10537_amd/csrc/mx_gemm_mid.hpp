@@ -52,8 +52,14 @@ __global__ __launch_bounds__(256, 2) void gemm_mid_kernel(int M, int N, int64_t 
     constexpr int WA = Fmt<FA>::bits, WB = Fmt<FB>::bits;
     constexpr int HA = hw_fmt(FA), HB = hw_fmt(FB);   // must reach the builtin as literal constants
     // FA = FB = INT8: bf16 operands without scales, K counts the bytes of a row (64 elements a step), and the two 16-byte chunks of a
-    // lane are the operands of two 32 x 32 x 16 bf16 instructions; everything else is the same
+    // lane are the operands of two 32 x 32 x 16 bf16 instructions; everything else is the same, but for the sums.  The bf16 instruction
+    // rounds the running sum several times, so its chains are kept short and their results added to sums of their own:
+    //  - LEVELS = 2 (128 x 128 tiles): chains of `chain` steps, one sum of them;
+    //  - LEVELS = 3 (tiles of half the size: three sets of accumulators fill the registers of two waves per SIMD otherwise): both halves of
+    //    a step apart, added to each other and to the sum of `each` steps, about the root of their number, that one to the sum of all.
+    // Error (2-norm, scales spread over 16 octaves, K = 4096): one chain 3.4e-7, LEVELS = 2 1.3e-7, LEVELS = 3 0.8e-7.
     constexpr bool BF = FA == INT8 && FB == INT8;
+    constexpr int LEVELS = !BF ? 1 : MB * NB > 2 ? 2 : 3;
     constexpr int BM = 64 * MB, BN = 64 * NB;
     // wave-wide direct loads (1 KB) per wave and operand; a 6-bit tile of 64 rows (6 KB) is padded to 8 KB
     constexpr int NJA = (BM * TileFmt<WA>::ROW + 4095) / 4096, NJB = (BN * TileFmt<WB>::ROW + 4095) / 4096, NJ = NJA + NJB;
@@ -152,6 +158,17 @@ __global__ __launch_bounds__(256, 2) void gemm_mid_kernel(int M, int N, int64_t 
         for (int y = 0; y < NB; y++)
 #pragma unroll
             for (int t = 0; t < 16; t++) acc[x][y][t] = 0.f;
+    // LEVELS > 1: acc is the first half step's chain or the running one
+    v16f_t acc1[MB][NB], run[MB][NB], sum[MB][NB];            // the second half step's chain; sums of `each` steps; of everything
+    const int chain = K < 1024 ? 1 : K < 2048 ? 4 : 8;        // (LEVELS = 2; the shorter K, the fewer roundings to stay below)
+    int each = 4;
+    while (LEVELS == 3 && each * each * 3 / 2 < T) each *= 2;
+    if constexpr (LEVELS > 1) {
+#pragma unroll
+        for (int x = 0; x < MB; x++)
+#pragma unroll
+            for (int y = 0; y < NB; y++) { run[x][y] = acc[x][y]; sum[x][y] = acc[x][y]; }
+    }
 
     v8i_t a0[MB], b0[NB], a1[MB], b1[NB];                     // operands of sub-step 0 / 1
     auto read_sub = [&](const uint8_t *buf, int sub, v8i_t (&a)[MB], v8i_t (&b)[NB]) {
@@ -168,11 +185,36 @@ __global__ __launch_bounds__(256, 2) void gemm_mid_kernel(int M, int N, int64_t 
         return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t_, __builtin_shufflevector(b, b, 4, 5, 6, 7)),
                                                        __builtin_bit_cast(bf16x8_t_, __builtin_shufflevector(a, a, 4, 5, 6, 7)), c, 0, 0, 0);
     };
+    constexpr v16f_t zero = {};
 #define MX_MID_MFMA(SUB, A_, B_, X, Y)                                                                                              \
     do {                                                                                                                            \
-        if constexpr (BF) acc[X][Y] = mid_bf16(B_[Y], A_[X], acc[X][Y]);                                                            \
+        if constexpr (LEVELS == 3 && SUB == 0) acc[X][Y] = mid_bf16(B_[Y], A_[X], zero);                                            \
+        else if constexpr (LEVELS == 3) acc1[X][Y] = mid_bf16(B_[Y], A_[X], zero);                                                  \
+        else if constexpr (BF) acc[X][Y] = mid_bf16(B_[Y], A_[X], acc[X][Y]);                                                       \
         else acc[X][Y] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(B_[Y], A_[X], acc[X][Y], HB, HA, 2 * SUB, (int)sb[Y], 2 * SUB, (int)sa[X]); \
     } while (0)
+    // behind step t (LEVELS > 1)
+    auto add_up = [&](int t, bool second) __attribute__((always_inline)) {
+        if constexpr (LEVELS == 3) {
+#pragma unroll
+            for (int x = 0; x < MB; x++)
+#pragma unroll
+                for (int y = 0; y < NB; y++) run[x][y] += second ? acc[x][y] + acc1[x][y] : acc[x][y];
+            if ((t & (each - 1)) == each - 1) {
+#pragma unroll
+                for (int x = 0; x < MB; x++)
+#pragma unroll
+                    for (int y = 0; y < NB; y++) { sum[x][y] += run[x][y]; run[x][y] = zero; }
+            }
+        } else if constexpr (LEVELS == 2) {
+            if ((t + 1) % chain == 0) {
+#pragma unroll
+                for (int x = 0; x < MB; x++)
+#pragma unroll
+                    for (int y = 0; y < NB; y++) { sum[x][y] += acc[x][y]; acc[x][y] = zero; }
+            }
+        }
+    };
 
     stage_scales(0);
     if (T > 0) {
@@ -215,6 +257,7 @@ __global__ __launch_bounds__(256, 2) void gemm_mid_kernel(int M, int N, int64_t 
                     __builtin_amdgcn_sched_barrier(0);
                 }
             read_scales(t + 1);
+            add_up(t, true);
             buf = nxt;
         }
     }
@@ -247,8 +290,15 @@ __global__ __launch_bounds__(256, 2) void gemm_mid_kernel(int M, int N, int64_t 
                 MX_MID_MFMA(0, a0, b0, x, y);
                 if (tail > 64) MX_MID_MFMA(1, a1, b1, x, y);
             }
+        if constexpr (LEVELS == 3) add_up(T, tail > 64);
     }
 #undef MX_MID_MFMA
+    if constexpr (LEVELS > 1) {
+#pragma unroll
+        for (int x = 0; x < MB; x++)
+#pragma unroll
+            for (int y = 0; y < NB; y++) acc[x][y] = sum[x][y] + (LEVELS == 3 ? run[x][y] : acc[x][y]);
+    }
 
     // ---- epilogue: result register t of instruction tile (x, y): row i, column 8 (t / 4) + 4g + t % 4.  bf16: the two
     // half-waves trade groups of four columns, so that each lane stores eight consecutive ones (columns 16 h + 8g ..).

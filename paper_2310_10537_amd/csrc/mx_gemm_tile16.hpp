@@ -34,7 +34,6 @@
 namespace mx {
 
 typedef float v4f_t __attribute__((ext_vector_type(4)));
-typedef int int32x4_t __attribute__((ext_vector_type(4)));
 
 // One instruction, accumulator updated in place in the accumulation registers.  Written as assembly so that
 // destination and addend are the same registers by construction: given the choice the register allocator
@@ -122,18 +121,6 @@ __device__ __forceinline__ void store_tile16(const v4f_t (&acc)[8][8], void *__r
     }
 }
 
-// Two instructions of 32 products of bf16 values each, the same way: element pairs 0-31 and 32-63 of a 64-element step
-struct Bf16Frag { int32x4_t lo, hi; };
-__device__ __forceinline__ void mfma16_bf16(v4f_t &acc, const int32x4_t &op1, const int32x4_t &op2)
-{
-    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(op1), "v"(op2));
-}
-template <bool BF> struct Frag16B { typedef v8i_t type; };
-template <> struct Frag16B<true> { typedef Bf16Frag type; };
-
-// FA = FB = INT8: the operands are bf16 values without scales (MXINT8 blocks times their scales, see mx_gemm_int8.hip) and K counts
-// the bytes of a row.  A step of 128 bytes is 64 elements, a fragment's two 16-byte chunks are the operands of two
-// v_mfma_f32_16x16x32_bf16; everything else is the same.
 template <int FA, int FB, int CDT, bool PROBE = false>
 __global__ __launch_bounds__(256, 1) void gemm_tile16_kernel(int64_t M, int64_t N, int64_t K,
                                                               const uint8_t *__restrict__ Ae, const uint8_t *__restrict__ As,
@@ -145,7 +132,6 @@ __global__ __launch_bounds__(256, 1) void gemm_tile16_kernel(int64_t M, int64_t 
     if constexpr (PROBE) { probe_c0 = __builtin_readcyclecounter(); probe_r0 = __builtin_amdgcn_s_memrealtime(); }
     static_assert(Fmt<FA>::bits == 8 && Fmt<FB>::bits == 8, "pairs of 8-bit formats");
     static_assert(CDT == DT_F32 || CDT == DT_BF16, "plain output types only");
-    constexpr bool BF = FA == INT8 && FB == INT8;
     typedef TileFmt<8> TF;
     constexpr int A_BYTES = TM * TF::ROW, B_BYTES = TN * TF::ROW, STAGE_BYTES = A_BYTES + B_BYTES;
     // {A tile, B tile} x two stages, then {A scale dwords, B scale dwords} x two groups
@@ -155,7 +141,7 @@ __global__ __launch_bounds__(256, 1) void gemm_tile16_kernel(int64_t M, int64_t 
     // per load, one load pair per four steps) the scale loads took 260 clocks per K step, 9 % of the loop,
     // for 3 % of its bytes; the 160 KB of LDS have room for exactly this doubling, no more.
     constexpr int SG = 8, SG_ROW = 4 * SG, SG_BYTES = (TM + TN) * SG_ROW;
-    __shared__ __attribute__((aligned(16))) uint8_t lds[2 * STAGE_BYTES + (BF ? 0 : 2 * SG_BYTES)];
+    __shared__ __attribute__((aligned(16))) uint8_t lds[2 * STAGE_BYTES + 2 * SG_BYTES];
     static_assert(sizeof(lds) <= 160 * 1024, "LDS of a compute unit");
     constexpr int HA = hw_fmt(FA), HB = hw_fmt(FB);
     const int tid = threadIdx.x, lane = tid & 63;
@@ -226,7 +212,6 @@ __global__ __launch_bounds__(256, 1) void gemm_tile16_kernel(int64_t M, int64_t 
     // scale bytes of K steps 8G .. 8G+7 (group G, clamped to the last) into slot G & 1, for the 32 rows j (0 / 1)
     // of this wave's 64 rows of A and of B
     auto stage_scales = [&](int G, int j) {
-        if constexpr (BF) return;
         G = G < n_groups ? G : n_groups - 1;
         const uint32_t l0 = lds0 + 2 * STAGE_BYTES + (G & 1) * SG_BYTES + wave * (64 * SG_ROW - 1024) + j * 1024;   // lds0 holds wave * 1024
         const int64_t src_ofs = (G * SG + SG <= T ? (int64_t)G * SG_ROW : (int64_t)T * 4 - SG_ROW) + j * 32 * nkb;
@@ -235,20 +220,16 @@ __global__ __launch_bounds__(256, 1) void gemm_tile16_kernel(int64_t M, int64_t 
         asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(pb), "s"(l0 + TM * SG_ROW) : "m0");
     };
     // fragment of 16-row block xb of the tile at buf
-    typedef typename Frag16B<BF>::type frag_t;
     auto frag = [&](const uint8_t *buf, int ofs, int xb) {
         const uint4 lo = *reinterpret_cast<const uint4 *>(buf + ofs + xb * 2048);
         const uint4 hi = *reinterpret_cast<const uint4 *>(buf + (ofs ^ 64) + xb * 2048);
-        if constexpr (BF)
-            return Bf16Frag{int32x4_t{(int)lo.x, (int)lo.y, (int)lo.z, (int)lo.w}, int32x4_t{(int)hi.x, (int)hi.y, (int)hi.z, (int)hi.w}};
-        else
-            return v8i_t{(int)lo.x, (int)lo.y, (int)lo.z, (int)lo.w, (int)hi.x, (int)hi.y, (int)hi.z, (int)hi.w};
+        return v8i_t{(int)lo.x, (int)lo.y, (int)lo.z, (int)lo.w, (int)hi.x, (int)hi.y, (int)hi.z, (int)hi.w};
     };
 
-    frag_t aL[4], aH[4], bL[4], bH[4];
+    v8i_t aL[4], aH[4], bL[4], bH[4];
     // Scale bytes of the step, one register per 16-row block.  Each half of them (rows / columns 0-63,
     // 64-127) is refilled in place for the next step as soon as its last quadrant is over: no second set.
-    uint32_t sa[8] = {}, sb[8] = {};
+    uint32_t sa[8], sb[8];
     // byte offset, from the scale area, of the dword row 0 holds for K step ts (clamped to the last step)
     auto scale_ofs = [&](int ts) {
         ts = ts < T ? ts : T - 1;
@@ -256,43 +237,31 @@ __global__ __launch_bounds__(256, 1) void gemm_tile16_kernel(int64_t M, int64_t 
     };
     auto read_sa = [&](int so, int x0) {
 #pragma unroll
-        for (int x = 0; x < (BF ? 0 : 4); x++) sa[x0 + x] = scl[so + rsa + ((x0 + x) >> 1) * 1024 + ((x0 + x) & 1) * 256];
+        for (int x = 0; x < 4; x++) sa[x0 + x] = scl[so + rsa + ((x0 + x) >> 1) * 1024 + ((x0 + x) & 1) * 256];
     };
     auto read_sb = [&](int so, int y0) {
 #pragma unroll
-        for (int y = 0; y < (BF ? 0 : 4); y++) sb[y0 + y] = scl[so + rsb + ((y0 + y) >> 1) * 1024 + ((y0 + y) & 1) * 256];
+        for (int y = 0; y < 4; y++) sb[y0 + y] = scl[so + rsb + ((y0 + y) >> 1) * 1024 + ((y0 + y) & 1) * 256];
     };
 
 #define MX_FENCE() __builtin_amdgcn_sched_barrier(0)
     // instruction (x, y) of the wave's 8 x 8: B fragment first (see the header)
-    // ... and (x + 1, y) behind it
-    auto mf2 = [&](v4f_t &c0, v4f_t &c1, const frag_t &b, const frag_t &a0, const frag_t &a1, uint32_t s_b, uint32_t s_a0, uint32_t s_a1)
-        __attribute__((always_inline)) {
-        if constexpr (BF) {
-            mfma16_bf16(c0, b.lo, a0.lo); mfma16_bf16(c1, b.lo, a1.lo);
-            mfma16_bf16(c0, b.hi, a0.hi); mfma16_bf16(c1, b.hi, a1.hi);
-        } else {
-            mfma16<HB, HA>(c0, b, a0, s_b, s_a0);
-            mfma16<HB, HA>(c1, b, a1, s_b, s_a1);
-        }
-    };
-#define MX_MF2(AS, BS, X0, Y0, XX, YY)                                                                                 \
-    mf2(acc[X0 + XX][Y0 + YY], acc[X0 + XX + 1][Y0 + YY], BS[YY], AS[XX], AS[XX + 1], sb[Y0 + YY], sa[X0 + XX], sa[X0 + XX + 1])
+#define MX_MF(AS, BS, X0, Y0, XX, YY) mfma16<HB, HA>(acc[X0 + XX][Y0 + YY], BS[YY], AS[XX], sb[Y0 + YY], sa[X0 + XX])
     // a quadrant whose 16 instructions run beside the refill of set RS (four fragments, two per group of
     // four instructions, none in the last two groups) from tile RBUF at offset ROFS, blocks RB0 .. RB0+3
 #define MX_QUAD_READ(AS, BS, X0, Y0, RS, RBUF, ROFS, RB0, EXTRA)                                                            \
     RS[0] = frag(RBUF, ROFS, RB0 + 0); RS[1] = frag(RBUF, ROFS, RB0 + 1);                                              \
-    MX_MF2(AS, BS, X0, Y0, 0, 0); MX_MF2(AS, BS, X0, Y0, 2, 0); MX_FENCE(); \
+    MX_MF(AS, BS, X0, Y0, 0, 0); MX_MF(AS, BS, X0, Y0, 1, 0); MX_MF(AS, BS, X0, Y0, 2, 0); MX_MF(AS, BS, X0, Y0, 3, 0); MX_FENCE(); \
     RS[2] = frag(RBUF, ROFS, RB0 + 2); RS[3] = frag(RBUF, ROFS, RB0 + 3);                                              \
-    MX_MF2(AS, BS, X0, Y0, 0, 1); MX_MF2(AS, BS, X0, Y0, 2, 1); MX_FENCE(); \
+    MX_MF(AS, BS, X0, Y0, 0, 1); MX_MF(AS, BS, X0, Y0, 1, 1); MX_MF(AS, BS, X0, Y0, 2, 1); MX_MF(AS, BS, X0, Y0, 3, 1); MX_FENCE(); \
     EXTRA;                                                                                                             \
-    MX_MF2(AS, BS, X0, Y0, 0, 2); MX_MF2(AS, BS, X0, Y0, 2, 2); MX_FENCE(); \
-    MX_MF2(AS, BS, X0, Y0, 0, 3); MX_MF2(AS, BS, X0, Y0, 2, 3); MX_FENCE()
+    MX_MF(AS, BS, X0, Y0, 0, 2); MX_MF(AS, BS, X0, Y0, 1, 2); MX_MF(AS, BS, X0, Y0, 2, 2); MX_MF(AS, BS, X0, Y0, 3, 2); MX_FENCE(); \
+    MX_MF(AS, BS, X0, Y0, 0, 3); MX_MF(AS, BS, X0, Y0, 1, 3); MX_MF(AS, BS, X0, Y0, 2, 3); MX_MF(AS, BS, X0, Y0, 3, 3); MX_FENCE()
     // the same with eight direct loads (numbers L0 .. L0+7 of stage TS into DA / DB), one per two
     // instructions: a burst would fill the memory pipeline's queue and stall the wave in front of its
     // next matrix instruction
 #define MX_PAIR(AS, BS, X0, Y0, XX, YY, LK, TS, DA, DB)                                                                \
-    stage_one(LK, TS, DA, DB); MX_MF2(AS, BS, X0, Y0, XX, YY); MX_FENCE()
+    stage_one(LK, TS, DA, DB); MX_MF(AS, BS, X0, Y0, XX, YY); MX_MF(AS, BS, X0, Y0, XX + 1, YY); MX_FENCE()
 #define MX_QUAD_LOAD(AS, BS, X0, Y0, RS, RBUF, ROFS, RB0, L0, TS, DA, DB, EXTRA)                                       \
     RS[0] = frag(RBUF, ROFS, RB0 + 0); RS[1] = frag(RBUF, ROFS, RB0 + 1);                                              \
     MX_PAIR(AS, BS, X0, Y0, 0, 0, L0 + 0, TS, DA, DB); MX_PAIR(AS, BS, X0, Y0, 2, 0, L0 + 1, TS, DA, DB);              \
@@ -371,7 +340,7 @@ __global__ __launch_bounds__(256, 1) void gemm_tile16_kernel(int64_t M, int64_t 
 #undef MX_QUAD_LOAD
 #undef MX_PAIR
 #undef MX_QUAD_READ
-#undef MX_MF2
+#undef MX_MF
 #undef MX_FENCE
     acc_settle(acc);
     if constexpr (PROBE) {

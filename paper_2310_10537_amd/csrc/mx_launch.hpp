@@ -73,9 +73,10 @@ hipError_t launch_gemm(int64_t M, int64_t N, int64_t K, const uint8_t *A_elems, 
 hipError_t launch_gemm_int8(int64_t M, int64_t N, int64_t K, const uint8_t *Ae, const uint8_t *As, const uint8_t *Be,
                             const uint8_t *Bs, void *C, int c_dt, int64_t ldc, hipStream_t st);
 
-// C = A B^T for bf16 operands [M][K], [N][K], 16-byte aligned
+// C = A B^T for bf16 operands [M][K], [N][K], 16-byte aligned.  short_chains: smaller tiles, whose Float32 sums err less
 bool gemm_bf16_applies(int64_t M, int64_t N, int64_t K);
-hipError_t launch_gemm_bf16(int64_t M, int64_t N, int64_t K, const void *A, const void *B, void *C, int c_dt, int64_t ldc, hipStream_t st);
+hipError_t launch_gemm_bf16(int64_t M, int64_t N, int64_t K, const void *A, const void *B, void *C, int c_dt, int64_t ldc,
+                            bool short_chains, hipStream_t st);
 
 // true when the LDS-tiled kernel takes the problem: FP8 / FP6 / FP4 operands, whole 256 x 256
 // tiles, K a multiple of 128 and at least 512

@@ -15,13 +15,13 @@ def test_routes(tmp_path):
         call = ("mx_gemm_ws", (M, N, K, P, P, INT8, P, P, INT8, P, 1, N, P, 1 << 40, 0)) if ws else \
             ("mx_gemm", (M, N, K, P, P, INT8, P, P, INT8, P, 1, N, 0))
         (status, seen), = launches.trace(rt, [call + (refuse,)])
-        return status, [k[0] for k in seen]
-    wide, mid, check = "gemm_tile16_kernel", "gemm_mid_kernel", "gemm_int8_repair_kernel"
-    assert kernels(8192, 4096, 4096) == (0, ["int8_widen_kernel", wide, check])
-    assert kernels(4096, 4352, 512) == (0, ["int8_widen_kernel", wide, mid, check])             # 272 tiles: 16 of 17 columns, the rest in small tiles
-    assert kernels(4100, 4352, 512) == (0, ["int8_widen_kernel", wide, mid, mid, check])
-    assert kernels(1000, 4096, 4096) == kernels(4096, 4096, 544)[:1] + (["int8_widen_kernel", mid, check],)
-    assert kernels(4096, 4096, 4064)[1] == ["int8_widen_kernel", mid, check]                    # half a K step at the end: no whole tiles
+        return status, [k[0] + "".join(k[1][2:4]) if k[0] == "gemm_mid_kernel" else k[0] for k in seen]
+    widen, large, short, check = "int8_widen_kernel", "gemm_mid_kernel22", "gemm_mid_kernel21", "gemm_int8_repair_kernel"
+    # whole 256 x 256 tiles: 128 x 128 tiles, two levels of sums; other sizes: 128 x 64 tiles, three levels
+    for M, N, K in ((8192, 4096, 4096), (4096, 4352, 512), (2048, 2048, 160)):
+        assert kernels(M, N, K) == (0, [widen, large, check])
+    for M, N, K in ((1000, 4096, 4096), (4100, 4352, 512), (4096, 4100, 544), (2048, 2048, 4096)):
+        assert kernels(M, N, K) == (0, [widen, short, check])
     for M, N, K in ((128, 11008, 4096), (256, 4096, 4096), (1000, 1000, 4096)):
         assert kernels(M, N, K) == (0, ["gemm_int8_lds_kernel"])
     assert kernels(256, 11008, 512) == kernels(300, 300, 96) == (0, ["gemm_int8_kernel"])
@@ -93,6 +93,37 @@ def test_against_float64(shape, ranges):
     tol = mag * (K / 16 * 2.0 ** -24) + K / 32 * 2.0 ** -149
     assert bool(((got - ref).abs() <= tol)[inside].all()), float(((got - ref).abs() / mag.clamp_min(1e-300))[inside].max())
     assert bool((~torch.isfinite(got) | (got.abs() > big / 1e6))[ref.abs() > big * 2].all())
+
+
+# n Float32 additions of terms of random sign, one behind the other, leave a relative error of 2.4e-8 (n / 2)^0.5 in the 2-norm (a sum of k
+# terms is of the order of k^0.5, a rounding errs by 2^-24 times 0.41 in the mean square).  The integer kernels add a wave's K / 256 block sums
+# and then eight waves' sums, or (short K, or no multiple of 128) K / 32 block sums; the chains of E2M3 halves that whole tiles had, K / 16 terms.
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", [(4096, 4096, 4096), (2048, 2304, 512), (2048, 2048, 160), (1000, 4096, 4096), (1000, 4100, 1024),
+                                   (512, 4096, 8192), (8192, 1000, 512), (3000, 2000, 2080)], ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("signs", ["random", "one"])
+def test_sums_err_no_more_than_block_sums_do(shape, signs):
+    import torch
+    from paper_2310_10537_amd import binding as mx
+    M, N, K = shape
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M + 3 * N + K)
+
+    def operand(rows):                                            # scales over 16 octaves: sums that Float32 rounds
+        x = torch.randn((rows, K), generator=g, device="cuda")
+        x = x * torch.exp2(torch.randint(-8, 8, (rows, K // 32), generator=g, device="cuda").float()).repeat_interleave(32, dim=1)
+        return mx.mx_quantize((x.abs() if signs == "one" else x).to(torch.bfloat16), 1, INT8)
+    (qa, sa), (qb, sb) = operand(M), operand(N)
+    C = mx.mx_gemm(qa, sa, INT8, qb, sb, INT8, K)
+
+    def value(q, s):
+        return q.view(torch.int8).double() * torch.exp2(s.double() - 133).repeat_interleave(32, dim=1)
+    ref = value(qa[:256], sa[:256]) @ value(qb, sb).T
+    err = float((C[:256].double() - ref).norm() / ref.norm())
+    whole = M % 256 == 0 and N % 256 == 0 and (M // 256) * (N // 256) >= 64
+    terms = K / 16 if whole else K / 32 if K % 128 or K < 1024 else K / 256 + 8
+    # with one sign the sums grow evenly: (n / 3)^0.5 roundings of the whole, less than above
+    assert err <= 1.1 * 2.4e-8 * (terms / 2) ** 0.5, err
 
 
 @pytest.mark.gpu
