@@ -230,8 +230,9 @@ int mx_dequantize(const void *elems, const uint8_t *scales, mx_format_t fmt,
  * run of 8 consecutive K products in fixed point with 14 bits below the run's
  * largest product, which is exact for FP6 E2M3 / FP4 E2M1 operands and loses at
  * most 14 * 2^-14 of each run's largest product otherwise.
- * Which kernel runs depends on the shape and the formats only, never on the
- * data or on timing, so a result is reproducible.  Most problems add the
+ * Which kernel runs depends on the shape and the formats only, never on
+ * timing or (MXINT8 near the end of Float32's range apart, see below) on the data,
+ * so a result is reproducible.  Most problems add the
  * products of an entry in the order of K: whole 256 x 256 tiles (K a multiple of
  * 128), smaller tiles for every other size, and one wave per 32 x 32 entries for
  * a short K, all with the same bits.  Problems of few rows (up to 32; up to 64
@@ -250,8 +251,10 @@ int mx_dequantize(const void *elems, const uint8_t *scales, mx_format_t fmt,
  * a K below 1024 or no multiple of 128) instead write the elements times their
  * scales as bf16 numbers, which hold them exactly, to scratch memory (less than
  * (M + N) * K * 3.125 bytes, see "Scratch memory of the GEMM entry points" below)
- * and run a bf16 product with Float32 sums, recomputed block by block where
- * the scales leave the range of these types; few rows (M <= 128, K >= 256) and mid-size
+ * and run a bf16 product with Float32 sums; 64 x 64 tiles of C whose scale bytes
+ * are so large that a sum could overflow (two bytes that add up to more than
+ * 379 - log2 K: products beyond 2^(127 - log2 K)) are recomputed block by block,
+ * the one place where data has a say in how an entry is computed; few rows (M <= 128, K >= 256) and mid-size
  * problems with a long K let eight waves share the K range of each 32-column
  * tile and add their partial tiles in a fixed order.  All routes differ from
  * the exact sum only by Float32 accumulation rounding.

@@ -14,9 +14,9 @@
 //
 // Larger products take a faster, equally exact route: an element times its block's scale, q 2^(s - 133), is a bf16 number (q has
 // eight significant bits at most), the product of two such numbers is exact in Float32, and so C is the plain bf16 product of the
-// scaled elements on the bf16 matrix instruction (mx_gemm_bf16.hip), Float32 sums as everywhere.  That holds while the values and
-// their products stay within the exponents of bf16 and Float32; int8_widen_kernel notes the range of the scales, and the direct
-// kernel's tiles -- launched after the product, left at once as a rule -- recompute C when it does not.  (The 8-bit integer
+// scaled elements on the bf16 matrix instruction (mx_gemm_bf16.hip), Float32 sums as everywhere.  That holds while no sum can leave
+// the range of Float32; int8_widen_kernel notes the largest scales, and the direct kernel's tiles -- launched after the product, left at
+// once as a rule -- recompute the parts of C where it does not.  (The 8-bit integer
 // instruction is twice as fast as the bf16 one, but every block's sums have to be scaled by the vector pipe: 48 instructions for
 // 32 clocks of it.  Splitting q into two E2M3 halves, four products on the block-scaled instruction at four times the bf16 rate, moves
 // three bytes an element instead of two for the same matrix work: 8192 x 4096 x 4096 348 us where this takes 215.)
@@ -75,15 +75,34 @@ __device__ __forceinline__ void i8_accumulate(float (&acc)[16], const v16i_t &p,
 }
 
 // ---------------------------------------------------------------------------------------------
-// MXINT8 -> bf16.  A block's elements times its scale are q 2^(s - 133), |q| <= 128: exact in bf16 (eight significant bits) for
-// scale bytes from 7 to 253.  The products of such values are exact in Float32 as long as sA + sB >= 140 (no product of less than
-// 2^-126) and finite for sA + sB <= 378.  Each work-group leaves the least and the largest scale byte of its elements other than zero
-// (NaN scales: 0 and 255, which no partner satisfies) in a word of its own; gemm_int8_repair_kernel, launched behind the product on few
-// work-groups, looks at all of them and recomputes C when the ranges of A and B do not fit together.
+// MXINT8 -> bf16.  A block's elements times its scale are q 2^(s - 133), |q| <= 128: exact in bf16, which holds eight significant
+// bits down to 2^-126 and whole multiples of 2^-133 below (the matrix instruction takes and returns such numbers as they are).  Only
+// -128 2^(254 - 133) = -2^128 has no bf16 value; a NaN scale makes its block's values NaN.  Products and sums below 2^-126 are as exact
+// as Float32 is there.  At the other end a sum of K products must stay finite whatever its signs, as a block's sum does in
+// integers: |product| <= 2^(sA + sB - 252), so sA + sB + log2 K <= 379.  Each work-group leaves the largest scale byte of its elements
+// other than zero in a word of its own (OUT_OF_RANGE: a value without a bf16 form); gemm_int8_repair_kernel, launched behind the product on
+// few work-groups, looks at all of them and recomputes the 64 x 64 tiles whose rows and columns do not fit together.
 // Bound by memory: 3 bytes an element, 16-byte stores.
 // ---------------------------------------------------------------------------------------------
 constexpr int WIDEN_PER = 4;                                   // pieces of eight elements per lane
 constexpr int WIDEN_ELEMS = 256 * 8 * WIDEN_PER;               // elements per work-group
+constexpr uint32_t OUT_OF_RANGE = 1000;
+
+// the largest of the work-group's (256 threads) values, for all of them
+__device__ __forceinline__ uint32_t group_max(uint32_t m, uint32_t *part)
+{
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t t = (uint32_t)__shfl_xor((int)m, o);
+        m = m > t ? m : t;
+    }
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = m;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 4; k++) m = m > part[k] ? m : part[k];
+    return m;
+}
 
 __global__ __launch_bounds__(256) void int8_widen_kernel(const uint8_t *__restrict__ Ae, const uint8_t *__restrict__ As, int64_t a_elems,
                                                          const uint8_t *__restrict__ Be, const uint8_t *__restrict__ Bs, int64_t b_elems,
@@ -107,83 +126,43 @@ __global__ __launch_bounds__(256) void int8_widen_kernel(const uint8_t *__restri
             s[k] = sc[at >> 5];
         }
     }
-    uint32_t lo = 255, hi = 0;
+    uint32_t hi = 0;
 #pragma unroll
     for (int k = 0; k < WIDEN_PER; k++) {
-        const bool any = (q[k].x | q[k].y) != 0, fits = s[k] >= 7 && s[k] <= 253;
-        if (any && fits) { lo = lo < s[k] ? lo : s[k]; hi = hi > s[k] ? hi : s[k]; }
-        if ((any && !fits) || s[k] == SCALE_NAN) { lo = 0; hi = 255; }
-        const float f = __uint_as_float(fits ? (s[k] - 6u) << 23 : 0u);
-        uint32_t d[4];
+        const float f = __uint_as_float(s[k] == SCALE_NAN ? 0x7FC00000u : s[k] >= 7 ? (s[k] - 6u) << 23 : 0x00400000u >> (6u - s[k]));
+        uint32_t d[4], most = 0;
 #pragma unroll
         for (int i = 0; i < 4; i++) {
             const int dw = (int)(i < 2 ? q[k].x : q[k].y), sh = 16 * (i & 1);
             const uint32_t v0 = __float_as_uint((float)((dw << (24 - sh)) >> 24) * f), v1 = __float_as_uint((float)((dw << (16 - sh)) >> 24) * f);
             d[i] = __builtin_amdgcn_perm(v1, v0, 0x07060302);
+            most = most > v0 ? most : v0;
+            most = most > v1 ? most : v1;
         }
+        // (-2^128 is -Inf, the largest of all values but NaN by their bits)
+        const uint32_t top = s[k] == SCALE_NAN ? 0 : most == 0xFF800000u ? OUT_OF_RANGE : (q[k].x | q[k].y) != 0 ? s[k] : 0;
+        hi = hi > top ? hi : top;
         const int64_t at = base + k * 2048;
         if (at < n) st16(reinterpret_cast<uint8_t *>(w + at), make_uint4(d[0], d[1], d[2], d[3]));
     }
-    // 255 - lo and hi in one maximum each half-word
-    uint32_t m = (255 - lo) << 16 | hi;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t t = (uint32_t)__shfl_xor((int)m, o);
-        m = ((m >> 16) > (t >> 16) ? m & 0xffff0000u : t & 0xffff0000u) | ((m & 0xffff) > (t & 0xffff) ? m & 0xffff : t & 0xffff);
-    }
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = m;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-#pragma unroll
-        for (int k = 1; k < 4; k++) {
-            const uint32_t t = part[k];
-            m = ((m >> 16) > (t >> 16) ? m & 0xffff0000u : t & 0xffff0000u) | ((m & 0xffff) > (t & 0xffff) ? m & 0xffff : t & 0xffff);
-        }
-        range[blockIdx.x] = m;
-    }
+    hi = group_max(hi, part);
+    if (threadIdx.x == 0) range[blockIdx.x] = hi;
 }
 
-// What int8_widen_kernel left: whether the ranges of the scales of A and B allow the product of the bf16 values.  (range: n_a words
-// of A's work-groups, then n_b of B's.)  Every thread of the work-group (256) gets the answer.  Bound by the latency of its loads: eight
-// in flight, where one after the other took 16.9 us over the 6144 words of 8192 x 4096 x 4096 (4.6 us so).
-__device__ __forceinline__ bool widened_product_holds(const uint32_t *__restrict__ range, unsigned n_a, unsigned n_b)
+// The largest of the words [first, last] of what int8_widen_kernel left, for every thread of the work-group (256).  Bound by the
+// latency of its loads: eight in flight, where one after the other took 16.9 us over the 6144 words of 8192 x 4096 x 4096 (4.6 us so).
+__device__ __forceinline__ uint32_t largest_scale(const uint32_t *__restrict__ range, unsigned first, unsigned last, uint32_t *part)
 {
-    typedef uint16_t u16x2_t __attribute__((ext_vector_type(2)));
-    __shared__ uint32_t part[2][4];
     constexpr unsigned AHEAD = 8;
-    const unsigned n = n_a + n_b;
-    const u16x2_t none = {0, 0};
-    u16x2_t wa = none, wb = none;                              // {largest, 255 - least} of A, of B
-    for (unsigned k0 = threadIdx.x; k0 < n; k0 += AHEAD * 256) {
+    uint32_t m = 0;
+    for (unsigned k0 = first + threadIdx.x; k0 <= last; k0 += AHEAD * 256) {
         uint32_t r[AHEAD];
 #pragma unroll
-        for (unsigned j = 0; j < AHEAD; j++) r[j] = range[k0 + j * 256 < n ? k0 + j * 256 : n - 1];     // (beyond the end: B's last word again)
+        for (unsigned j = 0; j < AHEAD; j++) r[j] = range[k0 + j * 256 <= last ? k0 + j * 256 : last];    // (beyond the end: the last word again)
 #pragma unroll
-        for (unsigned j = 0; j < AHEAD; j++) {
-            const u16x2_t v = __builtin_bit_cast(u16x2_t, r[j]);
-            const bool of_a = k0 + j * 256 < n_a;
-            wa = __builtin_elementwise_max(wa, of_a ? v : none);
-            wb = __builtin_elementwise_max(wb, of_a ? none : v);
-        }
+        for (unsigned j = 0; j < AHEAD; j++) m = m > r[j] ? m : r[j];
     }
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        wa = __builtin_elementwise_max(wa, __builtin_bit_cast(u16x2_t, __shfl_xor(__builtin_bit_cast(int, wa), o)));
-        wb = __builtin_elementwise_max(wb, __builtin_bit_cast(u16x2_t, __shfl_xor(__builtin_bit_cast(int, wb), o)));
-    }
-    if ((threadIdx.x & 63) == 0) {
-        part[0][threadIdx.x >> 6] = __builtin_bit_cast(uint32_t, wa);
-        part[1][threadIdx.x >> 6] = __builtin_bit_cast(uint32_t, wb);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < 4; k++) {
-        wa = __builtin_elementwise_max(wa, __builtin_bit_cast(u16x2_t, part[0][k]));
-        wb = __builtin_elementwise_max(wb, __builtin_bit_cast(u16x2_t, part[1][k]));
-    }
-    const int lo_a = 255 - (int)wa[1], hi_a = (int)wa[0], lo_b = 255 - (int)wb[1], hi_b = (int)wb[0];
-    if (lo_a == 0 || lo_b == 0) return false;                  // a scale of its own out of range
-    return hi_a == 0 || hi_b == 0 /* zeros only */ || (lo_a + lo_b >= 140 && hi_a + hi_b <= 378);
+    return group_max(m, part);
 }
 
 // One tile of 64 x 64
@@ -238,18 +217,26 @@ __global__ __launch_bounds__(256) void gemm_int8_kernel(int64_t M, int64_t N, in
     int8_tile<CDT>(M, N, K, Ae, As, Be, Bs, C, ldc, blockIdx.y, blockIdx.x, lds_all);
 }
 
-// Behind the product of the bf16 values, on few work-groups: nothing to repair, as a rule
+// Behind the product of the bf16 values, on few work-groups: nothing to repair, as a rule.  limit: the largest sum of two scale bytes
+// that the product allows.  A tile's words are those of the work-groups that widened its rows or columns, neighbours among them.
 template <int CDT>
 __global__ __launch_bounds__(256) void gemm_int8_repair_kernel(int64_t M, int64_t N, int64_t K, const uint8_t *__restrict__ Ae,
                                                                const uint8_t *__restrict__ As, const uint8_t *__restrict__ Be,
                                                                const uint8_t *__restrict__ Bs, void *__restrict__ C, int64_t ldc,
-                                                               const uint32_t *__restrict__ range, unsigned n_a, unsigned n_b)
+                                                               const uint32_t *__restrict__ range, unsigned n_a, unsigned n_b, unsigned limit)
 {
-    if (widened_product_holds(range, n_a, n_b)) return;
+    __shared__ uint32_t part[4];
+    if (largest_scale(range, 0, n_a - 1, part) + largest_scale(range + n_a, 0, n_b - 1, part) <= limit) return;
     __shared__ __attribute__((aligned(16))) uint32_t lds_all[4 * 32];
     const int64_t tiles_n = (N + 63) / 64, tiles = tiles_n * ((M + 63) / 64);
-    for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x)
-        int8_tile<CDT>(M, N, K, Ae, As, Be, Bs, C, ldc, tile / tiles_n, tile % tiles_n, lds_all);
+    auto strip = [&](const uint32_t *words, int64_t t, int64_t rows) {
+        const int64_t end = 64 * t + 64 < rows ? 64 * t + 64 : rows;
+        return largest_scale(words, (unsigned)(64 * t * K / WIDEN_ELEMS), (unsigned)((end * K - 1) / WIDEN_ELEMS), part);
+    };
+    for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+        const int64_t tm = tile / tiles_n, tn = tile % tiles_n;
+        if (strip(range, tm, M) + strip(range + n_a, tn, N) > limit) int8_tile<CDT>(M, N, K, Ae, As, Be, Bs, C, ldc, tm, tn, lds_all);
+    }
 }
 
 // Few rows of A (a decoding step): the kernel above gives such a problem N / 32 waves that each walk
@@ -501,10 +488,12 @@ static hipError_t launch_int8_repair(int64_t M, int64_t N, int64_t K, const uint
 {
     const int64_t tiles = ((N + 63) / 64) * ((M + 63) / 64);
     const dim3 grid((unsigned)(tiles < 512 ? tiles : 512));
+    unsigned limit = 379;                                      // see int8_widen_kernel
+    for (int64_t k = 1; k < K; k *= 2) limit--;
     if (c_dt == DT_F32)
-        hipLaunchKernelGGL((gemm_int8_repair_kernel<DT_F32>), grid, dim3(256), 0, st, M, N, K, Ae, As, Be, Bs, C, ldc, range, n_a, n_b);
+        hipLaunchKernelGGL((gemm_int8_repair_kernel<DT_F32>), grid, dim3(256), 0, st, M, N, K, Ae, As, Be, Bs, C, ldc, range, n_a, n_b, limit);
     else
-        hipLaunchKernelGGL((gemm_int8_repair_kernel<DT_BF16>), grid, dim3(256), 0, st, M, N, K, Ae, As, Be, Bs, C, ldc, range, n_a, n_b);
+        hipLaunchKernelGGL((gemm_int8_repair_kernel<DT_BF16>), grid, dim3(256), 0, st, M, N, K, Ae, As, Be, Bs, C, ldc, range, n_a, n_b, limit);
     return hipGetLastError();
 }
 

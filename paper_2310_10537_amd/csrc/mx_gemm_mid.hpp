@@ -56,7 +56,8 @@ __global__ __launch_bounds__(256, 2) void gemm_mid_kernel(int M, int N, int64_t 
     // rounds the running sum several times, so its chains are kept short and their results added to sums of their own:
     //  - LEVELS = 2 (128 x 128 tiles): chains of `chain` steps, one sum of them;
     //  - LEVELS = 3 (tiles of half the size: three sets of accumulators fill the registers of two waves per SIMD otherwise): both halves of
-    //    a step apart, added to each other and to the sum of `each` steps, about the root of their number, that one to the sum of all.
+    //    a step -- an MXINT8 block each, whose sum is exact -- apart, added to each other and to the sum of `each` steps, about the root of
+    //    their number, that one to the sum of all.
     // Error (2-norm, scales spread over 16 octaves, K = 4096): one chain 3.4e-7, LEVELS = 2 1.3e-7, LEVELS = 3 0.8e-7.
     constexpr bool BF = FA == INT8 && FB == INT8;
     constexpr int LEVELS = !BF ? 1 : MB * NB > 2 ? 2 : 3;

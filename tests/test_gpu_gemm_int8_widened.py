@@ -70,7 +70,8 @@ SHAPES = [(129, 12320, 4096), (1000, 2050, 1024), (515, 4103, 2080), (4100, 4360
 @pytest.mark.gpu
 @pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
 @pytest.mark.parametrize("ranges", [((120, 134), (120, 134)), ((7, 20), (133, 160)), ((180, 253), (60, 125)),            # held by bf16
-                                    ((6, 20), (133, 160)), ((60, 79), (60, 79)), ((200, 254), (60, 120)), ((180, 200), (180, 200))])
+                                    ((6, 20), (133, 160)), ((60, 79), (60, 79)), ((200, 254), (60, 120)), ((180, 200), (180, 200)),
+                                    ((0, 12), (120, 160))])
 def test_against_float64(shape, ranges):
     import torch
     from paper_2310_10537_amd import binding as mx
@@ -143,3 +144,72 @@ def test_nan_scales(zeros):
     C = mx.mx_gemm(qa.view(torch.uint8), sa, INT8, qb.view(torch.uint8), sb, INT8, K)
     nan = torch.isnan(C)
     assert bool(nan[700].all()) and bool(nan[:, 2049].all()) and int(nan.sum()) == M + N - 1
+
+
+def spread(torch, g, rows, K, lo=120, hi=136):
+    q = torch.randint(-127, 128, (rows, K), generator=g, device="cuda", dtype=torch.int32).to(torch.int8)
+    return q, torch.randint(lo, hi, (rows, K // 32), generator=g, device="cuda", dtype=torch.int32).to(torch.uint8)
+
+
+TWO = [(1000, 4100, 1024), (4096, 4096, 512)]                     # three levels of sums, two
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", TWO, ids=lambda s: "x".join(map(str, s)))
+def test_a_block_out_of_the_ordinary_leaves_the_other_rows_alone(shape):
+    """A NaN scale, scales near 0, at the largest value of a block and at the end of Float32's range: the entries of rows and columns in
+    other 64 x 64 tiles keep their bits."""
+    import torch
+    from paper_2310_10537_amd import binding as mx
+    M, N, K = shape
+    g = torch.Generator(device="cuda")
+    g.manual_seed(K)
+    (qa, sa), (qb, sb) = spread(torch, g, M, K), spread(torch, g, N, K)
+
+    def product():
+        return mx.mx_gemm(qa.view(torch.uint8), sa, INT8, qb.view(torch.uint8), sb, INT8, K)
+
+    def value(q, s):
+        return q.double() * torch.exp2(s.double() - 133).repeat_interleave(32, dim=-1)
+    plain, c = product(), slice(3900, 4096)
+    for scale, q in ((255, 1), (0, 3), (3, -128), (6, 127), (253, 1), (254, -128)):
+        sa[130, 5], qa[130, 160:192] = scale, q
+        sb[4000, 5] = 60                                          # (with the largest ones a product below 2^127)
+        got = product()
+        keep = torch.ones((M, N), dtype=torch.bool, device="cuda")
+        keep[130], keep[:, 4000] = False, False
+        if scale in (253, 254):                                   # recomputed: the tiles of rows 128 .. 191
+            keep[128:192] = False
+        assert torch.equal(got[keep], plain[keep]), scale
+        if scale == 255:
+            assert bool(torch.isnan(got[130]).all()) and int(torch.isnan(got).sum()) == N
+            continue
+        x, y = value(qa[130], sa[130]), value(qb[c], sb[c])
+        ref, mag = y @ x, y.abs() @ x.abs()
+        inside = ref.abs() < 2.0 ** 127
+        assert bool(((got[130, c].double() - ref).abs() <= mag * K * 2.0 ** -24)[inside].all()), scale
+        assert bool((torch.isinf(got[130, c]) | (got[130, c].abs() > 2.0 ** 126))[~inside].all()), scale
+        assert scale < 253 or bool(inside[100])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape,total", [(TWO[0], 366), (TWO[0], 378), (TWO[0], 379), (TWO[1], 378), (TWO[1], 379)], ids=str)
+def test_sums_that_cancel_inside_a_block(shape, total):
+    """Sixteen products of 2^14 times the scales of one sign, then sixteen of the other: the block's sum is zero, and so it stays
+    where the sum of half of them is beyond Float32 (or, in sums of one block at a time, so large that it would wipe out the others)."""
+    import torch
+    from paper_2310_10537_amd import binding as mx
+    M, N, K = shape
+    g = torch.Generator(device="cuda")
+    g.manual_seed(total)
+    (qa, sa), (qb, sb) = spread(torch, g, M, K), spread(torch, g, N, K)
+
+    def product():
+        return mx.mx_gemm(qa.view(torch.uint8), sa, INT8, qb.view(torch.uint8), sb, INT8, K)[200:232, 300:340]
+    qa[200:232, 64:96], qb[300:340, 64:96] = 0, 0
+    without = product()
+    qa[200:232, 64:80], qa[200:232, 80:96], qb[300:340, 64:96] = 127, -127, 127
+    sa[200:232, 2], sb[300:340, 2] = total - 185, 185
+    got = product()
+    tol = float(without.square().mean().sqrt()) * 100 * K * 2.0 ** -24       # (the other blocks' sums in another order of magnitude at most)
+    assert bool(torch.isfinite(got).all()) and float((got - without).abs().max()) <= tol
