@@ -247,10 +247,10 @@ int mx_dequantize(const void *elems, const uint8_t *scales, mx_format_t fmt,
  * else is MX_ERR_UNSUPPORTED).  That pair runs the integer matrix instruction
  * block by block -- every block sum is an exact integer -- and adds the scaled
  * block sums in Float32; larger problems (whole 256 x 256 tiles, at least 96 or 64
- * when K < 1024; more than 128 rows and 768 tiles of 64 x 32, or 2^31 products for
- * a K below 1024 or no multiple of 128) instead write the elements times their
- * scales as bf16 numbers, which hold them exactly, to scratch memory (less than
- * (M + N) * K * 3.125 bytes, see "Scratch memory of the GEMM entry points" below)
+ * when K < 1024; other sizes of more than 128 rows that the integer kernels take
+ * about 100 us for, see mx_gemm_workspace_bytes) instead write the elements times
+ * their scales as bf16 numbers, which hold them exactly, to scratch memory
+ * ((M + N) * K * 2 bytes and some, see "Scratch memory of the GEMM entry points" below)
  * and run a bf16 product with Float32 sums; 64 x 64 tiles of C whose scale bytes
  * are so large that a sum could overflow (two bytes that add up to more than
  * 379 - log2 K: products beyond 2^(127 - log2 K)) are recomputed block by block,
@@ -293,8 +293,7 @@ int mx_gemm_qa(int64_t M, int64_t N, int64_t K,
 /*
  * Scratch memory of the GEMM entry points.  Some routes need device scratch:
  *   mx_gemm     larger MX_INT8 problems (the bf16 values of both operands; see
- *               there).  Without scratch memory those of whole 256 x 256 tiles
- *               fail and the others take a slower kernel;
+ *               there);
  *   mx_gemm_qa  every route that casts A ahead of the product (see there);
  *   mx_gemm_q   every route that does not cast in the tiled kernel's epilogue
  *               (a Float32 C).
@@ -308,8 +307,11 @@ int mx_gemm_qa(int64_t M, int64_t N, int64_t K,
  * smaller than the bound is MX_ERR_WORKSPACE and nothing is launched.
  * workspace = NULL makes a _ws form behave exactly like the plain one.
  * In either form a request that cannot be met is an error (MX_ERR_WORKSPACE),
- * except where mx_gemm_qa can cast in registers instead (see there).  Results
- * are bit-identical between the two forms.
+ * with two exceptions: where mx_gemm_qa can cast in registers instead (see there),
+ * and where the memory pool has no room for an MX_INT8 product of other sizes than
+ * whole 256 x 256 tiles, which then runs on the integer kernels (a different Float32
+ * rounding).  Otherwise results are bit-identical between the two forms.  A call
+ * captured into a graph without a workspace puts the allocation into the graph.
  */
 size_t mx_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, mx_format_t fmtA, mx_format_t fmtB);
 size_t mx_gemm_qa_workspace_bytes(int64_t M, int64_t N, int64_t K, mx_format_t fmtA, mx_format_t fmtB);

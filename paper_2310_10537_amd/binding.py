@@ -183,7 +183,7 @@ def mx_gemm(A_elems, A_scales, fmtA, B_elems, B_scales, fmtB, K, dtype=torch.flo
     if out is None:
         out = torch.empty((M, N), dtype=dtype, device=A_elems.device)
     ldc = out.stride(0) if M > 1 else N
-    ws = _int8_workspace(M, N, K, A_elems.device, stream) if fmtA == INT8 and fmtB == INT8 else None
+    ws = _int8_workspace("gemm", M, N, K, A_elems.device, stream) if fmtA == INT8 and fmtB == INT8 else None
     if ws is not None:
         _check(lib().mx_gemm_ws(M, N, K, A_elems.data_ptr(), A_scales.data_ptr(), fmtA, B_elems.data_ptr(), B_scales.data_ptr(), fmtB,
                                 out.data_ptr(), _dt(out), ldc, ws.data_ptr(), ws.numel(), _stream(stream)))
@@ -204,24 +204,24 @@ def mx_gemm_q(A_elems, A_scales, fmtA, B_elems, B_scales, fmtB, K, fmtC, rnd=ROU
     if out is None:
         out = (torch.empty((M, nblk * BLOCK * w // 8), dtype=torch.uint8, device=A_elems.device),
                torch.empty((M, nblk), dtype=torch.uint8, device=A_elems.device))
-    _check(lib().mx_gemm_q(M, N, K, A_elems.data_ptr(), A_scales.data_ptr(), fmtA, B_elems.data_ptr(), B_scales.data_ptr(),
-                           fmtB, fmtC, rnd, out[0].data_ptr(), out[1].data_ptr(), _stream(stream)))
+    ws = _int8_workspace("gemm_q", M, N, K, A_elems.device, stream) if fmtA == INT8 and fmtB == INT8 else None
+    wp, wb = _ws_args(ws)
+    _check(lib().mx_gemm_q_ws(M, N, K, A_elems.data_ptr(), A_scales.data_ptr(), fmtA, B_elems.data_ptr(), B_scales.data_ptr(),
+                              fmtB, fmtC, rnd, out[0].data_ptr(), out[1].data_ptr(), wp, wb, _stream(stream)))
     return out
 
 
-def _int8_workspace(M, N, K, device, stream):
-    """The same for an MXINT8 product, where its size lets the library use scratch memory (the bf16 values of both operands; more than
-    128 rows, and many tiles or many products).  Besides the host's time, the library's stream-ordered allocation goes back to the
-    driver whenever the device is waited for: 8192 x 4096 x 4096 took 400 us among others and 520 alone."""
-    many = -(-M // 64) * -(-N // 32) > 768 if K % 128 == 0 and K >= 1024 else M * N * K >= 1 << 31
-    if M <= 128 or not (many or (M // 256) * (N // 256) >= 64):
+def _int8_workspace(kind, M, N, K, device, stream):
+    """Scratch memory of an MXINT8 product (kind "gemm", or "gemm_q" with its Float32 C) from torch's caching allocator, where the
+    product's shape makes the library use any; None for the library's own stream-ordered allocation, which costs the host time and goes
+    back to the driver whenever the device is waited for.  As for mx_gemm_qa, torch's current stream only, and none while it is captured."""
+    if M <= 128 or not lib().mx_gemm_workspace_bytes(M, N, K, INT8, INT8):
         return None
     current = torch.cuda.current_stream()
     if device != current.device or (stream is not None and stream.cuda_stream != current.cuda_stream) or torch.cuda.is_current_stream_capturing():
         return None
-    need = lib().mx_gemm_workspace_bytes(M, N, K, INT8, INT8)
     try:
-        return torch.empty(need, dtype=torch.uint8, device=device) if need else None
+        return torch.empty(mx_workspace_bytes(kind, M, N, K, INT8, INT8), dtype=torch.uint8, device=device)
     except torch.cuda.OutOfMemoryError:
         return None
 
@@ -230,14 +230,16 @@ def _qa_workspace(M, N, K, fmtA, fmtB, device, stream):
     """Scratch memory of mx_gemm_qa from torch's caching allocator, or None for the library's own stream-ordered allocation.
     The tensor is dropped when the call returns, so it has to belong to the stream that the call runs on: torch's current one.
     A stream-ordered allocation and its release cost the host more than a small product takes: 1000 x 4096 x 4096 31.4 us a call
-    with them, 26.3 with this.  None where the bound on the size says little about the need: up to 16 rows, mostly cast without
-    scratch memory; MXINT8, whose bound covers both operands (17 x 28672 x 8192: 735 MB against 140 KB); many rows and up to two
-    columns of 256 x 256 tiles, which FP8 pairs cast on load.  None too while the stream is being
+    with them, 26.3 with this.  None where the bound on the size says little about the need, or the product itself
+    does without: up to 16 rows, mostly cast without scratch memory; MXINT8 products that take none beside the cast of A; many rows and
+    up to two columns of 256 x 256 tiles, which FP8 pairs cast on load.  None too while the stream is being
     captured: a graph replays after this tensor has gone back to the allocator, the library's allocation belongs to the graph."""
     current = torch.cuda.current_stream()
     if M <= 16 or device != current.device or (stream is not None and stream.cuda_stream != current.cuda_stream):
         return None
-    if fmtA == INT8 or (N < 768 and (M // 256) * (N // 256) >= 256) or torch.cuda.is_current_stream_capturing():
+    if (N < 768 and (M // 256) * (N // 256) >= 256 and fmtA != INT8) or torch.cuda.is_current_stream_capturing():
+        return None
+    if fmtA == INT8 and not lib().mx_gemm_workspace_bytes(M, N, K, fmtA, fmtB):
         return None
     need = lib().mx_gemm_qa_workspace_bytes(M, N, K, fmtA, fmtB)
     try:

@@ -64,8 +64,7 @@ static size_t cast_ws_bytes(int64_t M, int64_t K, int fmtA)
 
 size_t gemm_workspace_bound(int64_t M, int64_t N, int64_t K, int fmtA, int fmtB)
 {
-    if (fmtA != INT8 || fmtB != INT8 || M <= 0 || N <= 0 || K <= 0) return 0;
-    return up256(256 + (size_t)(M + N) * (size_t)(K / BLOCK) * 100);      // (the bf16 values of both operands take two thirds of it)
+    return fmtA == INT8 && fmtB == INT8 ? gemm_int8_workspace(M, N, K) : 0;
 }
 
 size_t gemm_qa_workspace_bound(int64_t M, int64_t N, int64_t K, int fmtA, int fmtB)

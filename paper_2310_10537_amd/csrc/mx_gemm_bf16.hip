@@ -12,7 +12,7 @@ namespace mx {
 
 bool gemm_bf16_applies(int64_t M, int64_t N, int64_t K)
 {
-    return M > 0 && N > 0 && K > 0 && K % BLOCK == 0 && K <= (1 << 22) /* 32-bit byte offsets inside a tile */ && M <= (1 << 30) &&
+    return M > 0 && N > 0 && K > 0 && K % BLOCK == 0 && K <= (1 << 21) /* 32-bit byte offsets inside a tile */ && M <= (1 << 30) &&
            N <= (1 << 30) && ((M + 63) / 64) * ((N + 63) / 64) <= (1 << 24);
 }
 

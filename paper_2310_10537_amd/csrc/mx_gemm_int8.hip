@@ -497,26 +497,20 @@ static hipError_t launch_int8_repair(int64_t M, int64_t N, int64_t K, const uint
     return hipGetLastError();
 }
 
-// C from the bf16 values of the blocks, in scratch memory; *refused when there is none to be had
-static hipError_t launch_int8_widened(int64_t M, int64_t N, int64_t K, const uint8_t *Ae, const uint8_t *As, const uint8_t *Be,
-                                      const uint8_t *Bs, void *C, int c_dt, int64_t ldc, bool whole, hipStream_t st, bool *refused)
-{
-    const int64_t na = M * K, nb = N * K;
-    const unsigned ga = (unsigned)((na + WIDEN_ELEMS - 1) / WIDEN_ELEMS), gb = (unsigned)((nb + WIDEN_ELEMS - 1) / WIDEN_ELEMS);
-    const size_t range_bytes = ((size_t)(ga + gb) * 4 + 255) & ~(size_t)255, a_bytes = ((size_t)na * 2 + 255) & ~(size_t)255;
-    uint8_t *ws = nullptr;
-    hipError_t e = ws_acquire(range_bytes + a_bytes + (size_t)nb * 2, st, &ws);
-    *refused = e != hipSuccess;
-    if (*refused) return e;
-    uint32_t *range = reinterpret_cast<uint32_t *>(ws);
-    uint16_t *Aw = reinterpret_cast<uint16_t *>(ws + range_bytes), *Bw = reinterpret_cast<uint16_t *>(ws + range_bytes + a_bytes);
-    hipLaunchKernelGGL(int8_widen_kernel, dim3(ga + gb), dim3(256), 0, st, Ae, As, na, Be, Bs, nb, Aw, Bw, range, ga);
-    e = hipGetLastError();
-    if (e == hipSuccess) e = launch_gemm_bf16(M, N, K, Aw, Bw, C, c_dt, ldc, !whole, st);
-    if (e == hipSuccess) e = launch_int8_repair(M, N, K, Ae, As, Be, Bs, C, c_dt, ldc, range, ga, gb, st);
-    const hipError_t f = ws_release(ws, st);
-    return e != hipSuccess ? e : f;
-}
+// Scratch memory of launch_int8_widened: a word per work-group of int8_widen_kernel, then the values of A and of B
+struct Widened {
+    unsigned groups_a, groups_b;
+    size_t a_at, b_at, bytes;
+    Widened(int64_t M, int64_t N, int64_t K)
+    {
+        auto up256 = [](size_t n) { return (n + 255) & ~(size_t)255; };
+        groups_a = (unsigned)((M * K + WIDEN_ELEMS - 1) / WIDEN_ELEMS);
+        groups_b = (unsigned)((N * K + WIDEN_ELEMS - 1) / WIDEN_ELEMS);
+        a_at = up256(((size_t)groups_a + groups_b) * 4);
+        b_at = a_at + up256((size_t)M * (size_t)K * 2);
+        bytes = up256(b_at + (size_t)N * (size_t)K * 2);
+    }
+};
 
 // Whole 256 x 256 tiles that fill much of the chip: scratch memory has always been part of their product
 static bool int8_whole_tiles(int64_t M, int64_t N, int64_t K)
@@ -525,17 +519,47 @@ static bool int8_whole_tiles(int64_t M, int64_t N, int64_t K)
     return M % 256 == 0 && N % 256 == 0 && K >= 128 && (tiles >= 96 || (tiles >= 64 && K < 1024));
 }
 
-// Whether the bf16 values are worth their making (3 bytes an element, at 4 TB/s) and two more launches.  us, the kernel that took the
-// problem before / bf16 values in a stream-ordered workspace, which costs the host 10 to 20 us (less with the caller's):
-//  - the staged kernel runs its 64 x 32 tiles in rounds of 256, 5.4 + 2.85 K / 1024 us each.  Two rounds: 256 x 4096 x 4096 34 / 44, 1000 x
-//    1000 x 8192 56 / 51; four: 1000 x 2048 x 1024 33 / 29, 512 x 4096 x 4096 67 / 49; more: 256 x 11008 x 4096 99 / 75, 1000 x 4096 x 4096
-//    134 / 61, 2048^3 88 / 44.  Few rows read the weights twice where they read them once: 128 x 11008 x 4096 52 / 71.
-//  - the direct kernel (short or odd K): 256 x 11008 x 512 (2^30 products) 20 / 31, 1000 x 4096 x 512 (2^31) 26 / 29, 8192 x 1000 x 512 48 / 35.
+// Whether the bf16 values are worth their making for other sizes, which have kernels without scratch memory.  Widening takes 3 bytes an
+// element at 4 TB/s and two more launches; and where the library allocates by itself, the memory goes back to the driver whenever
+// the device is waited for, so that a call that is waited for takes 30 to 40 us more, and up to 250 from 64 MB on.  The lines lie where a call
+// is not slower even so, one allocation in many apart.  us, the kernels without scratch / with the caller's scratch / allocated by the library and waited for
+// (in brackets the first of them waited for):
+//  - the staged kernel runs its 64 x 32 tiles in rounds of 256, 5.4 + 2.85 K / 1024 us each: 748 x 2432 x 1408 43 / 25 / 65 (55), 353 x 4618 x 4608
+//    78 / 53 / 96 (89), 669 x 7461 x 1024 90 / 53 / 89 (100), 936 x 8448 x 2176 205 / 77 / 125 (218); beyond 64 MB 6690 x 801 x 7168 293 / 156 / 334
+//    (298), 1719 x 9664 x 7168 792 / 373 / 466 (804).  Up to 128 rows it reads the weights once, the values are read twice and written.
+//  - the direct kernel (short or odd K) takes some 24 us for 2^31 products: 4806 x 1099 x 896 66 / 46 / 84 (77), 2847 x 2112 x 1248 87 / 47 /
+//    91 (98), 2908 x 4992 x 896 133 / 62 / 106 (142).  Short K is C's write, in rows whose ends are no whole 16 bytes above all:
+//    3121 x 6304 x 512 121 / 55 / 96 (131), 1744 x 9463 x 512 103 / 89 / 131 (113); 5680 x 9728 x 320 155 / 92 / 128 (167), 7333 x 1948 x 256 46 / 64 / 105
+//    (58), 5251 x 4911 x 96 30 / 101 / 116 (43).
 static bool int8_widened_pays(int64_t M, int64_t N, int64_t K)
 {
     if (M <= 128) return false;
-    if (K % 128 == 0 && K >= 1024) return ((M + 63) / 64) * ((N + 31) / 32) > 768;
-    return K >= 64 && M * N >= ((int64_t)1 << 31) / K;
+    const bool staged = K % 128 == 0 && K >= 1024;
+    const int64_t without = staged ? (((M + 63) / 64) * ((N + 31) / 32) + 255) / 256 * (5400 + K * 2783 / 1000) / 1000      // us
+                                   : M * N * K / (((int64_t)1 << 31) / 24);
+    const int64_t least = Widened(M, N, K).bytes >= (size_t)64 << 20 ? 450 : K >= 1024 || (K >= 512 && N % 8 == 0) ? 100 : 190;
+    return K >= 256 && without >= least;
+}
+
+static bool int8_widened(int64_t M, int64_t N, int64_t K)
+{
+    return gemm_bf16_applies(M, N, K) && (int8_whole_tiles(M, N, K) || int8_widened_pays(M, N, K));
+}
+
+size_t gemm_int8_workspace(int64_t M, int64_t N, int64_t K) { return int8_widened(M, N, K) ? Widened(M, N, K).bytes : 0; }
+
+// C from the bf16 values of the blocks, in scratch memory (ws: Widened::bytes)
+static hipError_t launch_int8_widened(int64_t M, int64_t N, int64_t K, const uint8_t *Ae, const uint8_t *As, const uint8_t *Be,
+                                      const uint8_t *Bs, void *C, int c_dt, int64_t ldc, uint8_t *ws, hipStream_t st)
+{
+    const Widened at(M, N, K);
+    uint32_t *range = reinterpret_cast<uint32_t *>(ws);
+    uint16_t *Aw = reinterpret_cast<uint16_t *>(ws + at.a_at), *Bw = reinterpret_cast<uint16_t *>(ws + at.b_at);
+    hipLaunchKernelGGL(int8_widen_kernel, dim3(at.groups_a + at.groups_b), dim3(256), 0, st, Ae, As, M * K, Be, Bs, N * K, Aw, Bw, range, at.groups_a);
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess) e = launch_gemm_bf16(M, N, K, Aw, Bw, C, c_dt, ldc, !int8_whole_tiles(M, N, K), st);
+    if (e == hipSuccess) e = launch_int8_repair(M, N, K, Ae, As, Be, Bs, C, c_dt, ldc, range, at.groups_a, at.groups_b, st);
+    return e;
 }
 
 hipError_t launch_gemm_int8(int64_t M, int64_t N, int64_t K, const uint8_t *Ae, const uint8_t *As, const uint8_t *Be,
@@ -547,12 +571,18 @@ hipError_t launch_gemm_int8(int64_t M, int64_t N, int64_t K, const uint8_t *Ae, 
     //    partial sums cost the same whatever K is): 256 x 4096 x 4096 34 us, 1000 x 1000 x 1024 18;
     //  - the unstaged shared-K kernel for few rows or few tiles when K is not a multiple of 128;
     //  - the direct kernel for everything else (short K, odd shapes): 80-170 TOP/s.
-    // (by shape alone, with or without a caller's workspace: the same product gives the same bits through every entry point)
-    const bool whole = int8_whole_tiles(M, N, K);
-    if (gemm_bf16_applies(M, N, K) && (whole || int8_widened_pays(M, N, K))) {
-        bool refused;
-        const hipError_t e = launch_int8_widened(M, N, K, Ae, As, Be, Bs, C, c_dt, ldc, whole, st, &refused);
-        if (!refused || whole) return e;
+    // By shape alone, with or without a caller's workspace: the same product gives the same bits through every entry point.  Only
+    // where the memory pool has none, sizes other than whole tiles, which need no scratch elsewhere, take the kernel without (other
+    // sums of the same blocks).
+    if (int8_widened(M, N, K)) {
+        uint8_t *ws = nullptr;
+        hipError_t e = ws_acquire(Widened(M, N, K).bytes, st, &ws);
+        if (e == hipSuccess) {
+            e = launch_int8_widened(M, N, K, Ae, As, Be, Bs, C, c_dt, ldc, ws, st);
+            const hipError_t f = ws_release(ws, st);
+            return e != hipSuccess ? e : f;
+        }
+        if (e != hipErrorOutOfMemory || int8_whole_tiles(M, N, K)) return e;
     }
     if (M > 0 && N > 0 && K % 128 == 0 && (M <= 128 ? K >= 8 * BLOCK : K >= 1024) && (M + 63) / 64 <= 65535)
         return M <= 8    ? launch_int8_lds<1, 1>(M, N, K, Ae, As, Be, Bs, C, c_dt, ldc, st)

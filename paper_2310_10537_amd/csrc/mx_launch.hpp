@@ -50,7 +50,8 @@ hipError_t launch_dequant_3d(const uint8_t *elems, const uint8_t *scales, int fm
 // entry points that take a caller-owned workspace -- ws_acquire carves 256-byte aligned pieces off
 // that workspace (hipErrorOutOfMemory when it is too small); outside one it takes the piece from
 // the device's memory pool in stream order.  ws_release returns the piece (last acquired first).
-// A refused request is an error of the call, but for problems that other kernels take without scratch memory.
+// A refused request is an error of the call, but for problems that other kernels take without scratch memory (mx_gemm_qa in registers,
+// MXINT8 products of other sizes than whole tiles).
 struct WorkspaceScope {
     WorkspaceScope(void *p, size_t bytes);
     ~WorkspaceScope();
@@ -69,7 +70,9 @@ hipError_t launch_gemm(int64_t M, int64_t N, int64_t K, const uint8_t *A_elems, 
                        const void *a_bf16, int64_t lda, int rnd, int fmtA, const uint8_t *B_elems,
                        const uint8_t *B_scales, int fmtB, void *C, int c_dt, int64_t ldc, hipStream_t st);
 
-// MXINT8 x MXINT8: integer matrix instruction per block, Float32 accumulation of the scaled block sums
+// MXINT8 x MXINT8: integer matrix instruction per block, Float32 accumulation of the scaled block sums; or, with scratch memory of
+// gemm_int8_workspace bytes (0: such a shape takes none), the bf16 values of the blocks
+size_t gemm_int8_workspace(int64_t M, int64_t N, int64_t K);
 hipError_t launch_gemm_int8(int64_t M, int64_t N, int64_t K, const uint8_t *Ae, const uint8_t *As, const uint8_t *Be,
                             const uint8_t *Bs, void *C, int c_dt, int64_t ldc, hipStream_t st);
 

@@ -1,5 +1,5 @@
-"""MXINT8 products on the bf16 values of their blocks (more than 128 rows and many tiles or products): ragged sizes, partial K steps, whole
-tiles with a remainder, scale bytes at the ends of what bf16 and Float32 hold and beyond them."""
+"""MXINT8 products on the bf16 values of their blocks (whole tiles, and other sizes that the integer kernels take long for): routes and
+scratch memory, ragged sizes, partial K steps, scale bytes at the ends of what bf16 and Float32 hold, the error of the sums."""
 import pytest
 
 import launches
@@ -17,19 +17,38 @@ def test_routes(tmp_path):
         (status, seen), = launches.trace(rt, [call + (refuse,)])
         return status, [k[0] + "".join(k[1][2:4]) if k[0] == "gemm_mid_kernel" else k[0] for k in seen]
     widen, large, short, check = "int8_widen_kernel", "gemm_mid_kernel22", "gemm_mid_kernel21", "gemm_int8_repair_kernel"
+    staged, direct = "gemm_int8_lds_kernel", "gemm_int8_kernel"
     # whole 256 x 256 tiles: 128 x 128 tiles, two levels of sums; other sizes: 128 x 64 tiles, three levels
     for M, N, K in ((8192, 4096, 4096), (4096, 4352, 512), (2048, 2048, 160)):
         assert kernels(M, N, K) == (0, [widen, large, check])
-    for M, N, K in ((1000, 4096, 4096), (4100, 4352, 512), (4096, 4100, 544), (2048, 2048, 4096)):
+    for M, N, K in ((1000, 4096, 4096), (4100, 4352, 512), (8000, 6000, 416), (2048, 2048, 4096), (2847, 2624, 1248)):
         assert kernels(M, N, K) == (0, [widen, short, check])
-    for M, N, K in ((128, 11008, 4096), (256, 4096, 4096), (1000, 1000, 4096)):
-        assert kernels(M, N, K) == (0, ["gemm_int8_lds_kernel"])
-    assert kernels(256, 11008, 512) == kernels(300, 300, 96) == (0, ["gemm_int8_kernel"])
-    for M, N, K in ((8192, 4096, 4096), (1000, 1600, 4096)):                                    # by shape, wherever the scratch comes from
-        assert kernels(M, N, K, ws=False)[1] == ["alloc"] + kernels(M, N, K)[1]
+    # ... where the kernels without scratch memory take long: five rounds and six of the staged one at K = 4096, scratch beyond 64 MB
+    for M, N, K in ((128, 11008, 4096), (256, 4096, 4096), (1000, 1000, 4096), (748, 2432, 1408), (2048, 2048, 2048), (576, 4096, 4096), (6690, 801, 7168)):
+        assert kernels(M, N, K) == (0, [staged])
+    for M, N, K in ((256, 11008, 512), (300, 300, 96), (2847, 2112, 1248), (4806, 1099, 896), (1744, 9463, 512), (5251, 4911, 96), (8192, 8191, 224)):
+        assert kernels(M, N, K) == (0, [direct])
+    assert kernels(768, 3392, 4096) == (0, [staged]) and kernels(768, 3424, 4096) == (0, [widen, short, check])
+    for M, N, K in ((8192, 4096, 4096), (1000, 4096, 4096)):                                    # by shape, wherever the scratch comes from
+        assert kernels(M, N, K, ws=False)[1][1:] == kernels(M, N, K)[1]
     # refused scratch memory: an error where it always was one, the kernels without it elsewhere
     assert kernels(8192, 4096, 4096, ws=False, refuse=1)[0] != 0
-    assert kernels(8000, 4000, 4096, ws=False, refuse=1) == (0, ["gemm_int8_lds_kernel"])
+    assert kernels(8000, 4000, 4096, ws=False, refuse=1) == (0, [staged])
+    # K beyond 2^21 has never taken any
+    assert kernels(2048, 2048, (1 << 21) + 32, ws=False, refuse=1) == (0, [direct])
+
+
+def test_scratch_is_what_the_library_says(tmp_path):
+    """The one allocation of a call is the bound that mx_gemm_workspace_bytes gives, and there is none where it gives 0."""
+    from paper_2310_10537_amd import binding
+    rt = launches.build(str(tmp_path))
+    P = 1 << 20
+    shapes = [(8192, 4096, 4096), (1000, 4096, 4096), (1001, 4099, 2080), (2304, 2816, 160), (300, 300, 96), (748, 2432, 1408), (128, 28672, 8192)]
+    calls = [("mx_gemm", (M, N, K, P, P, INT8, P, P, INT8, P, 1, N, 0), 0) for M, N, K in shapes]
+    for (M, N, K), (status, seen) in zip(shapes, launches.trace(rt, calls)):
+        need = binding.mx_workspace_bytes("gemm", M, N, K, INT8, INT8)
+        taken = [k[1] for k in seen if k[0] == "alloc"]
+        assert status == 0 and taken == ([need] if need else []), (M, N, K)
 
 
 def test_scratch_of_the_binding(monkeypatch):
@@ -44,15 +63,30 @@ def test_scratch_of_the_binding(monkeypatch):
     monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: capturing[0])
     monkeypatch.setattr(torch, "empty", lambda n, dtype, device: n)                            # (gigabytes otherwise)
 
-    def size(M, N, K, stream=None):
-        return binding._int8_workspace(M, N, K, cpu, stream)
+    def size(M, N, K, stream=None, kind="gemm"):
+        return binding._int8_workspace(kind, M, N, K, cpu, stream)
     assert size(8192, 4096, 4096) == binding.mx_workspace_bytes("gemm", 8192, 4096, 4096, INT8, INT8)
-    assert size(1000, 1600, 4096) is not None and size(1030, 4096, 512) is not None and size(2048, 2048, 512) is not None
-    for shape in ((128, 28672, 8192), (256, 4096, 4096), (300, 300, 96)):
+    assert size(1000, 4096, 4096, kind="gemm_q") == binding.mx_workspace_bytes("gemm_q", 1000, 4096, 4096, INT8, INT8)
+    assert size(4100, 4352, 512) is not None and size(2048, 2048, 512) is not None
+    for shape in ((128, 28672, 8192), (256, 4096, 4096), (300, 300, 96), (2100, 2100, 512)):     # (64 tiles in the last, not whole ones)
         assert size(*shape) is None
+    assert binding._qa_workspace(1000, 4096, 4096, INT8, INT8, cpu, None) == binding.mx_workspace_bytes("gemm_qa", 1000, 4096, 4096, INT8, INT8)
     assert size(8192, 4096, 4096, types.SimpleNamespace(cuda_stream=12)) is None
     capturing[0] = True
     assert size(8192, 4096, 4096) is None
+
+
+# three levels of sums and two; K with a partial step
+SHAPES = [(330, 12320, 2048), (1000, 4610, 2048), (520, 4103, 4640), (4100, 4360, 544), (4096, 4352, 576), (2304, 3840, 160)]
+SUMS = [(4096, 4096, 4096), (2048, 2304, 512), (2048, 2048, 160), (1000, 4096, 4096), (2000, 4100, 1024), (700, 2600, 8192),
+        (8192, 2200, 512), (3000, 2000, 2080)]
+TWO = [(1000, 4610, 2048), (4096, 4096, 512)]
+
+
+def test_shapes_below_take_the_values():
+    from paper_2310_10537_amd import binding
+    for M, N, K in SHAPES + SUMS + TWO:
+        assert binding.mx_workspace_bytes("gemm", M, N, K, INT8, INT8) > 0, (M, N, K)
 
 
 def operand(torch, g, rows, K, lo, hi):
@@ -62,9 +96,6 @@ def operand(torch, g, rows, K, lo, hi):
     q[1, 32:64], s[1, 1] = -128, hi
     q[2, :] = 127
     return q.to(torch.int8), s.to(torch.uint8)
-
-
-SHAPES = [(129, 12320, 4096), (1000, 2050, 1024), (515, 4103, 2080), (4100, 4360, 544), (4096, 4352, 576), (2304, 3840, 96)]
 
 
 @pytest.mark.gpu
@@ -100,8 +131,7 @@ def test_against_float64(shape, ranges):
 # terms is of the order of k^0.5, a rounding errs by 2^-24 times 0.41 in the mean square).  The integer kernels add a wave's K / 256 block sums
 # and then eight waves' sums, or (short K, or no multiple of 128) K / 32 block sums; the chains of E2M3 halves that whole tiles had, K / 16 terms.
 @pytest.mark.gpu
-@pytest.mark.parametrize("shape", [(4096, 4096, 4096), (2048, 2304, 512), (2048, 2048, 160), (1000, 4096, 4096), (1000, 4100, 1024),
-                                   (512, 4096, 8192), (8192, 1000, 512), (3000, 2000, 2080)], ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("shape", SUMS, ids=lambda s: "x".join(map(str, s)))
 @pytest.mark.parametrize("signs", ["random", "one"])
 def test_sums_err_no_more_than_block_sums_do(shape, signs):
     import torch
@@ -132,7 +162,7 @@ def test_sums_err_no_more_than_block_sums_do(shape, signs):
 def test_nan_scales(zeros):
     import torch
     from paper_2310_10537_amd import binding as mx
-    M, N, K = 1000, 2050, 1024
+    M, N, K = 1000, 4610, 2048
     g = torch.Generator(device="cuda")
     g.manual_seed(5)
     (qa, sa), (qb, sb) = operand(torch, g, M, K, 120, 130), operand(torch, g, N, K, 120, 130)
@@ -140,7 +170,7 @@ def test_nan_scales(zeros):
     sb[2049, 31] = 255
     if zeros:
         qa[700, 96:128] = 0
-        qb[2049, 992:] = 0
+        qb[2049, 992:1024] = 0
     C = mx.mx_gemm(qa.view(torch.uint8), sa, INT8, qb.view(torch.uint8), sb, INT8, K)
     nan = torch.isnan(C)
     assert bool(nan[700].all()) and bool(nan[:, 2049].all()) and int(nan.sum()) == M + N - 1
@@ -149,9 +179,6 @@ def test_nan_scales(zeros):
 def spread(torch, g, rows, K, lo=120, hi=136):
     q = torch.randint(-127, 128, (rows, K), generator=g, device="cuda", dtype=torch.int32).to(torch.int8)
     return q, torch.randint(lo, hi, (rows, K // 32), generator=g, device="cuda", dtype=torch.int32).to(torch.uint8)
-
-
-TWO = [(1000, 4100, 1024), (4096, 4096, 512)]                     # three levels of sums, two
 
 
 @pytest.mark.gpu

@@ -45,7 +45,8 @@ QA_CASES = [
     ("few_rows", 64, 1024, 1024, E2M3, FP8, 0, torch.float32),          # shared-K kernel
     ("ragged", 300, 520, 640, FP8, FP4, 0, torch.float32),              # interior + fringes, cast once
     ("int8", 512, 256, 512, INT8, INT8, 0, torch.float32),              # per-block integer kernel
-    ("int8_split", 4096, 4096, 1024, INT8, INT8, 0, torch.bfloat16),    # cast + the two E2M3 halves
+    ("int8_values", 4096, 4096, 1024, INT8, INT8, 0, torch.bfloat16),   # cast + the bf16 values of the blocks
+    ("int8_ragged", 1000, 4096, 2048, INT8, INT8, 0, torch.bfloat16),   # the same with other tiles
 ]
 
 
@@ -75,12 +76,12 @@ def test_gemm_qa_ws_matches_pool_route(mx, case):
     assert bits_equal(mx.mx_gemm_qa_ws(a, fa, rnd, gb[0], gb[1], fb, None, dtype=dt), want)
 
 
-@pytest.mark.parametrize("shape", [(4096, 4096, 1024), (2304, 2816, 512)], ids=["256_tiles", "99_tiles_short_k"])
-def test_int8_split_ws_matches_pool_route(mx, shape):
+@pytest.mark.parametrize("shape", [(4096, 4096, 1024), (2304, 2816, 512), (1000, 4100, 4096)], ids=["256_tiles", "99_tiles_short_k", "ragged"])
+def test_int8_ws_matches_pool_route(mx, shape):
     M, N, K = shape
     _, ga, gb = operands(mx, M, N, K, INT8, INT8, 310)
     need = mx.mx_workspace_bytes("gemm", M, N, K, INT8, INT8)
-    assert need >= (M + N) * K * 3
+    assert need >= (M + N) * K * 2
     want = mx.mx_gemm(ga[0], ga[1], INT8, gb[0], gb[1], INT8, K)
     ws = workspace(need)
     got = mx.mx_gemm_ws(ga[0], ga[1], INT8, gb[0], gb[1], INT8, K, ws[:need])
@@ -103,7 +104,7 @@ Q_CASES = [
     ("ragged", 300, 520, 640, FP8, E2M3, E3M2, 0),           # Float32 C in scratch, then the row cast
     ("few_rows", 32, 2048, 1024, FP4, FP4, FP8, 1),
     ("tiled_trunc", 512, 512, 512, FP8, FP8, FP8, 2),        # toward zero is not cast in the epilogue
-    ("int8_split", 4096, 4096, 1024, INT8, INT8, INT8, 0),   # Float32 C and the E2M3 halves side by side
+    ("int8_values", 4096, 4096, 1024, INT8, INT8, INT8, 0),  # Float32 C and the bf16 values side by side
 ]
 
 
