@@ -15,19 +15,28 @@ bool gemm_tiled_applies(int64_t M, int64_t N, int64_t K, int fmtA, int fmtB)
 
 bool gemm_tiled_fuses_cast(int fmtA, int fmtB) { return fmtA <= FP8_E5M2 && fmtB <= FP8_E5M2; }
 
-// Pairs of 6- and 4-bit formats with at least one 6-bit operand: the kernel of mx_gemm_tile16n.hpp needs 10 % less time per K step on a
-// full chip (it costs less energy and fetches every cache line once), but 2 us more per tile in front of and behind its loop, and with
-// one wave per SIMD it falls behind when the chip is partly idle and the clock high.  us, eight waves of 128 x 64 / this kernel (the
-// mixed pairs differ by 5 % from box to box, so their line lies where all are ahead):
-// E3M2 16384 x 2048 x K = 2048 51.9 / 53.2, 4096 92.6 / 87.0, 8192 178 / 162; 2048 x 8192 x 4096 51.7 / 47.8; 224 tiles x 3072 36.2 / 36.2 to
-// 38.2, x 4096 95 %; E3M2 x E2M1 8192^2 x 3072 level to 136 / 144, 4096 x 8192 x 4096 94 to 102 %, 6144 93 %, 4096 x 28672 x 8192 578 / 517 to 591 /
-// 554; 192 tiles x 4096 101 and 102 %, x 8192 96 and 97 %; 176 tiles x 8192 98 and 104 %.  4-bit pairs gain 4 % at most (K >= 8192) and
-// lose up to 20 % on one round of 135 tiles: they stay.
+// Pairs of 6- and 4-bit formats with at least one 6-bit operand: the kernel of mx_gemm_tile16n.hpp needs 3 to 10 % less time per K step on
+// a full chip (it costs less energy and fetches every cache line once), but 2 us more per tile in front of and behind its loop, and with
+// one wave per SIMD it falls behind when the chip is partly idle and the clock high.  So K has to be long, and where it is not very long
+// or the operands are light, the last round of tiles has to be nearly full (an emptier one than half of the chip goes to half tiles, and
+// the rounds in front of it are full).  Time over that of the eight waves of 128 x 64, per format pair A x B:
+//   6 x 6, K = 4096: full rounds 0.96, last round 144 to 208 of 256 1.00 to 1.02 with up to three full ones before it, 0.98 to 1.00 with
+//     more, 224 and 240 0.96 to 0.99; K = 6144 0.94 to 1.00, 8192 0.89 to 1.00 everywhere.  16384 x 2048 x 2048 51.9 -> 53.2 us.
+//   4 x 6, K = 6144: full 0.95, 144 to 192 1.00 to 1.02 with one or two full rounds, 0.97 to 1.00 with more; 8192 0.92 to 1.00 everywhere.
+//   6 x 4, K = 6144: full 0.97 with one or two rounds, 0.98 to 1.03 with more, else 1.01 to 1.10; K = 8192: full and 240 up 0.95 to 1.01, else 0.98 to
+//     1.05 (0.95 to 1.02 behind seven full rounds); 4096 x 28672 x 8192 (seven full) 581 -> 543 us.
+//   192 tiles x 4096 101 and 102 %, 176 tiles x 8192 98 and 104 %.  4 x 4 gains 4 % at most (K >= 8192) and loses up to 20 % on one
+//   round of 135 tiles: it stays.
 bool gemm_tiled16n_pays(int64_t M, int64_t N, int64_t K, int fmtA, int fmtB)
 {
     const bool six_a = fmtA == FP6_E3M2 || fmtA == FP6_E2M3, six_b = fmtB == FP6_E3M2 || fmtB == FP6_E2M3;
     if (!(six_a && (six_b || fmtB == FP4_E2M1)) && !(fmtA == FP4_E2M1 && six_b)) return false;
-    return K % (4 * TK) == 0 && K >= (six_a && six_b ? 4096 : 6144) && (M / TM) * (N / TN) >= 224;
+    const int64_t tiles = (M / TM) * (N / TN), last = tiles % 256;
+    if (K % (4 * TK) != 0 || tiles < 224) return false;
+    const bool full = last == 0 || last >= (six_b ? 224 : 240);
+    if (six_a && six_b) return K >= (full || tiles >= 1024 ? 4096 : 6144);
+    if (six_b) return K >= (full || tiles >= 768 ? 6144 : 8192);
+    return (full || tiles >= 1792) && K >= (tiles <= 512 ? 6144 : 8192);
 }
 
 // whole 256 x 256 tiles: four waves, on the 16 x 16 x 128 instruction for plain pairs of 8-bit formats with
