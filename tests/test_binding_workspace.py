@@ -35,6 +35,6 @@ def test_none_while_the_stream_is_captured(scratch):
 
 
 def test_none_where_the_bound_is_far_above_the_need(scratch):
-    assert scratch(17, 28672, 8192, 5, 5) is None                       # no split into halves: a 17 x 8192 cast only
+    assert scratch(17, 28672, 8192, 5, 5) is None                       # a 17 x 8192 cast, the product takes none
     assert scratch(65536, 256, 512) is None and scratch(32768, 512, 512) is None   # cast on load: no scratch
     assert scratch(65536, 255, 512) is not None and scratch(32768, 768, 512) is not None and scratch(32767, 512, 512) is not None

@@ -623,7 +623,7 @@ def test_int8_gemm_qa_equals_quantize_then_gemm(mx, oracle, rnd):
 
 
 def test_int8_gemm_whole_tiles_every_code_exact(mx, oracle):
-    """64 whole 256 x 256 tiles (the route that splits each code into two 6-bit halves): every code
+    """64 whole 256 x 256 tiles (the route by the bf16 values of the blocks): every code
     -128 .. 127 on both sides at X = 2^6 gives exactly known integers; one-hot rows pin positions."""
     M, N, K = 2048, 2048, 256
     rng = np.random.default_rng(6)
@@ -645,29 +645,36 @@ def test_int8_gemm_whole_tiles_every_code_exact(mx, oracle):
     assert np.array_equal(C, -Bd[:, (7 * np.arange(M)) % K].T.astype(np.float32))
 
 
-@pytest.mark.parametrize("low", [None, 0, 2, 3], ids=["plain", "scale0", "scale2", "scale3"])
-def test_int8_gemm_whole_tiles_scale_range_and_nan(mx, oracle, low):
-    """Whole tiles with block scales over a wide range, a NaN scale on each side and -- `low` --
-    scale bytes too small for the split route to lower (the exact pass behind it takes over)."""
+INT8_SCALES = {"plain": None, "scale0": (0, 150), "scale6": (6, 150), "scale7": (7, 150), "scale0_and_250": (0, 250),
+               "sum370": (185, 185), "sum371": (186, 185)}
+
+
+@pytest.mark.parametrize("nan", [False, True], ids=["finite", "nan"])
+@pytest.mark.parametrize("scales", INT8_SCALES.values(), ids=INT8_SCALES.keys())
+def test_int8_gemm_whole_tiles_scale_range_and_nan(mx, oracle, scales, nan):
+    """Whole tiles with block scales over a wide range, alone or with a NaN scale on each side, and blocks of chosen scale bytes: values
+    that bf16 holds as denormal numbers (below 7), the largest sum of two bytes that needs no second look (379 - 9 for K = 384) and
+    more, where tiles are recomputed block by block."""
     M, N, K = 4096, 1024, 384
     rng = np.random.default_rng(9)
     a = inputs.student_t_f32((M, K), seed=138) * np.exp2(rng.integers(-20, 20, (M, K // 32))).repeat(32, axis=1).astype(np.float32)
     b = inputs.gaussian_f32((N, K), seed=139) * np.exp2(rng.integers(-20, 20, (N, K // 32))).repeat(32, axis=1).astype(np.float32)
     ea, sa = oracle.quantize(a, 1, INT8)
     eb, sb = oracle.quantize(b, 1, INT8)
-    sa[300, 5] = 0xFF
-    sb[9, 0] = 0xFF
-    if low is not None:
-        sa[:, 3] = low
-        sb[:, 3] = 250          # lifts the products with the tiny blocks into the Float32 range
-        sb[:, 11] = low
-        sa[:, 11] = 250
+    if nan:
+        sa[300, 5] = 0xFF
+        sb[9, 0] = 0xFF
+    if scales is not None:
+        sa[:, 3], sb[:, 3] = scales      # (the partner lifts the products with the tiny blocks into the Float32 range)
+        sb[:, 11], sa[:, 11] = scales
     C_ref, C_abs = oracle.gemm(ea, sa, INT8, eb, sb, INT8, K, want_abs=True)
     C = to_host(mx.mx_gemm(to_dev(ea), to_dev(sa), INT8, to_dev(eb), to_dev(sb), INT8, K))
-    assert np.isnan(C[300]).all() and np.isnan(C[:, 9]).all() and np.isnan(C).sum() == N + M - 1
+    if nan:
+        assert np.isnan(C[300]).all() and np.isnan(C[:, 9]).all()
+    assert np.isnan(C).sum() == (N + M - 1 if nan else 0)
     ok = ~np.isnan(C_ref)
     assert np.isfinite(C_ref[ok]).all() and np.abs(C_ref[ok]).max() < 3e38
-    check_gemm(C, C_ref, np.nan_to_num(C_abs), f"int8 tiles low={low}")
+    check_gemm(C, C_ref, np.nan_to_num(C_abs), f"int8 tiles scales={scales}")
 
 
 def test_int8_gemm_full_size_sampled(mx, oracle):
@@ -710,7 +717,7 @@ def test_calls_on_a_side_stream(mx, oracle):
     """Every entry point enqueues on the stream it is given (workspaces included: they come from
     and go back to the memory pool in that stream's order).  A chain of calls on a side stream,
     with no synchronisation between them, must give what the same chain gives on the default
-    stream -- for the routes with a workspace (two-pass quantize-on-load, MXINT8 split) too."""
+    stream -- for the routes with a workspace (two-pass quantize-on-load, MXINT8 by bf16 values) too."""
     M, N, K = 2048, 2048, 512
     a = to_dev(inputs.student_t_bf16((M, K), seed=150))
     b = to_dev(inputs.gaussian_f32((N, K), seed=151, std=0.02))
@@ -815,7 +822,7 @@ def test_gemm_q_epilogue_int8_ties_away_one_ulp_below_a_tie(mx, oracle):
 @pytest.mark.parametrize("case", [(100, 72, 96, 0, 0, 0, RNE), (256, 256, 512, 0, 0, 5, RNE), (256, 256, 512, 2, 4, 4, 2),
                                   (64, 100, 64, 5, 5, 5, AWAY), (2048, 2048, 256, 5, 5, 0, RNE), (300, 520, 640, 0, 3, 2, AWAY),
                                   (2100, 1100, 512, 0, 0, 1, RNE), (512, 512, 640, 2, 4, 0, RNE)],
-                         ids=["ragged", "int8_out", "truncated", "int8_all", "int8_split_route", "small_ragged",
+                         ids=["ragged", "int8_out", "truncated", "int8_all", "int8_values", "small_ragged",
                               "tiled_interior_plus_fringe", "few_tiles"])
 def test_gemm_q_other_routes(mx, oracle, case):
     """Shapes, formats and modes the epilogue does not take go through a Float32 workspace: same bytes."""
