@@ -63,9 +63,9 @@ __device__ __forceinline__ void acc_settle(v4f_t (&acc)[8][8])
 #undef MX_ACC_ROW
 }
 
-// The wave's 128 x 128 accumulators to C, whose entry (row0, col0) is the first.
-template <int CDT>
-__device__ __forceinline__ void store_tile16(const v4f_t (&acc)[8][8], void *__restrict__ C, int64_t ldc, int64_t row0, int64_t col0, int i, int q)
+// The wave's 128 x 16 NY accumulators to C, whose entry (row0, col0) is the first.
+template <int CDT, int NY>
+__device__ __forceinline__ void store_tile16(const v4f_t (&acc)[8][NY], void *__restrict__ C, int64_t ldc, int64_t row0, int64_t col0, int i, int q)
 {
     // ---- epilogue: lane (i, q), register t of instruction tile (x, y) -> C[16x + i][16y + 4q + t]: four
     // consecutive columns per lane, stored 16 bytes at a time where the row pitch keeps them aligned.  bf16
@@ -82,14 +82,14 @@ __device__ __forceinline__ void store_tile16(const v4f_t (&acc)[8][8], void *__r
 #pragma unroll
             for (int x = 0; x < 8; x++)
 #pragma unroll
-                for (int y = 0; y < 8; y++)
+                for (int y = 0; y < NY; y++)
                     *reinterpret_cast<float4 *>(reinterpret_cast<float *>(C) + (r0 + x * 16) * ldc + c0 + y * 16) =
                         make_float4(acc[x][y][0], acc[x][y][1], acc[x][y][2], acc[x][y][3]);
         } else {
 #pragma unroll
             for (int x = 0; x < 8; x++)
 #pragma unroll
-                for (int y = 0; y < 8; y++) {
+                for (int y = 0; y < NY; y++) {
                     float *o = reinterpret_cast<float *>(C) + (r0 + x * 16) * ldc + c0 + y * 16;
                     o[0] = acc[x][y][0]; o[1] = acc[x][y][1]; o[2] = acc[x][y][2]; o[3] = acc[x][y][3];
                 }
@@ -104,7 +104,7 @@ __device__ __forceinline__ void store_tile16(const v4f_t (&acc)[8][8], void *__r
 #pragma unroll
         for (int x = 0; x < 8; x++)
 #pragma unroll
-            for (int y = 0; y < 8; y += 2) {
+            for (int y = 0; y < NY; y += 2) {
                 const auto lo = __builtin_amdgcn_permlane16_swap(pack2(acc[x][y][0], acc[x][y][1]), pack2(acc[x][y + 1][0], acc[x][y + 1][1]), false, false);
                 const auto hi = __builtin_amdgcn_permlane16_swap(pack2(acc[x][y][2], acc[x][y][3]), pack2(acc[x][y + 1][2], acc[x][y + 1][3]), false, false);
                 *reinterpret_cast<uint4 *>(reinterpret_cast<uint16_t *>(C) + (r0 + x * 16) * ldc + c1 + y * 16) = make_uint4(lo[0], hi[0], lo[1], hi[1]);
@@ -113,7 +113,7 @@ __device__ __forceinline__ void store_tile16(const v4f_t (&acc)[8][8], void *__r
 #pragma unroll
         for (int x = 0; x < 8; x++)
 #pragma unroll
-            for (int y = 0; y < 8; y++) {
+            for (int y = 0; y < NY; y++) {
                 const uint32_t p0 = pack2(acc[x][y][0], acc[x][y][1]), p1 = pack2(acc[x][y][2], acc[x][y][3]);
                 uint16_t *o = reinterpret_cast<uint16_t *>(C) + (r0 + x * 16) * ldc + c0 + y * 16;
                 o[0] = (uint16_t)p0; o[1] = (uint16_t)(p0 >> 16); o[2] = (uint16_t)p1; o[3] = (uint16_t)(p1 >> 16);

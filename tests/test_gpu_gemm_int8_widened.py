@@ -18,8 +18,13 @@ def test_routes(tmp_path):
         return status, [k[0] + "".join(k[1][2:4]) if k[0] == "gemm_mid_kernel" else k[0] for k in seen]
     widen, large, short, check = "int8_widen_kernel", "gemm_mid_kernel22", "gemm_mid_kernel21", "gemm_int8_repair_kernel"
     staged, direct = "gemm_int8_lds_kernel", "gemm_int8_kernel"
-    # whole 256 x 256 tiles: 128 x 128 tiles, two levels of sums; other sizes: 128 x 64 tiles, three levels
-    for M, N, K in ((8192, 4096, 4096), (4096, 4352, 512), (2048, 2048, 160)):
+    half = "gemm_bf16_half_kernel"
+    # whole 256 x 256 tiles: 256 x 128 tiles where K is long, for whole rounds of them, and 128 x 128 tiles; other sizes: 128 x 64 tiles
+    for M, N, K in ((8192, 4096, 4096), (2048, 3072, 2048), (4096, 4096, 2112), (5632, 4096, 2048)):
+        assert kernels(M, N, K) == (0, [widen, half, check])
+    for M, N, K in ((4096, 2304, 4096), (4096, 4608, 2112)):
+        assert kernels(M, N, K) == (0, [widen, half, large, check])
+    for M, N, K in ((4096, 4352, 512), (2048, 2048, 160), (4096, 4096, 1024), (4096, 4096, 2080)):
         assert kernels(M, N, K) == (0, [widen, large, check])
     for M, N, K in ((1000, 4096, 4096), (4100, 4352, 512), (8000, 6000, 416), (2048, 2048, 4096), (2847, 2624, 1248)):
         assert kernels(M, N, K) == (0, [widen, short, check])
@@ -76,11 +81,12 @@ def test_scratch_of_the_binding(monkeypatch):
     assert size(8192, 4096, 4096) is None
 
 
-# three levels of sums and two; K with a partial step
-SHAPES = [(330, 12320, 2048), (1000, 4610, 2048), (520, 4103, 4640), (4100, 4360, 544), (4096, 4352, 576), (2304, 3840, 160)]
+# 128 x 64 tiles, 128 x 128, 256 x 128 with and without others beside them; K with a partial step
+SHAPES = [(330, 12320, 2048), (1000, 4610, 2048), (520, 4103, 4640), (4100, 4360, 544), (4096, 4352, 576), (2304, 3840, 160),
+          (4096, 2304, 2112), (2048, 4096, 2240)]
 SUMS = [(4096, 4096, 4096), (2048, 2304, 512), (2048, 2048, 160), (1000, 4096, 4096), (2000, 4100, 1024), (700, 2600, 8192),
         (8192, 2200, 512), (3000, 2000, 2080)]
-TWO = [(1000, 4610, 2048), (4096, 4096, 512)]
+TWO = [(1000, 4610, 2048), (4096, 4096, 512), (2048, 4096, 2048)]
 
 
 def test_shapes_below_take_the_values():
@@ -220,7 +226,7 @@ def test_a_block_out_of_the_ordinary_leaves_the_other_rows_alone(shape):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("shape,total", [(TWO[0], 366), (TWO[0], 378), (TWO[0], 379), (TWO[1], 378), (TWO[1], 379)], ids=str)
+@pytest.mark.parametrize("shape,total", [(TWO[0], 366), (TWO[0], 378), (TWO[0], 379), (TWO[1], 378), (TWO[1], 379), (TWO[2], 378)], ids=str)
 def test_sums_that_cancel_inside_a_block(shape, total):
     """Sixteen products of 2^14 times the scales of one sign, then sixteen of the other: the block's sum is zero, and so it stays
     where the sum of half of them is beyond Float32 (or, in sums of one block at a time, so large that it would wipe out the others)."""
@@ -240,3 +246,24 @@ def test_sums_that_cancel_inside_a_block(shape, total):
     got = product()
     tol = float(without.square().mean().sqrt()) * 100 * K * 2.0 ** -24       # (the other blocks' sums in another order of magnitude at most)
     assert bool(torch.isfinite(got).all()) and float((got - without).abs().max()) <= tol
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", [(4096, 2304, 2112), (2048, 4096, 2240), (2048, 3072, 2048), (4096, 4096, 576), (1000, 4610, 2080)], ids=str)
+@pytest.mark.parametrize("dt", ["float32", "bfloat16"])
+def test_exact_integers_in_rows_of_any_pitch(shape, dt):
+    """Every sum is a whole number that Float32 holds, whatever the order: entries that differ are in the wrong place."""
+    import torch
+    from paper_2310_10537_amd import binding as mx
+    M, N, K = shape
+    dt = getattr(torch, dt)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M + N)
+    qa, qb = (torch.randint(-50, 51, (r, K), generator=g, device="cuda", dtype=torch.int32).to(torch.int8) for r in (M, N))
+    sa, sb = (torch.full((r, K // 32), 130, dtype=torch.uint8, device="cuda") for r in (M, N))       # 2^3 / 64 each
+    want = (qa.float() @ qb.float().T / 64).to(dt)                # (whole numbers below 2^24 as well)
+    assert K * 2500 < 1 << 24
+    for pitch in (N, N + 3, N + 8):
+        buf = torch.full((M, pitch), 7.0, dtype=dt, device="cuda")
+        mx.mx_gemm(qa.view(torch.uint8), sa, INT8, qb.view(torch.uint8), sb, INT8, K, out=buf[:, :N])
+        assert torch.equal(buf[:, :N], want) and bool((buf[:, N:] == 7.0).all()), pitch
