@@ -267,3 +267,33 @@ def test_exact_integers_in_rows_of_any_pitch(shape, dt):
         buf = torch.full((M, pitch), 7.0, dtype=dt, device="cuda")
         mx.mx_gemm(qa.view(torch.uint8), sa, INT8, qb.view(torch.uint8), sb, INT8, K, out=buf[:, :N])
         assert torch.equal(buf[:, :N], want) and bool((buf[:, N:] == 7.0).all()), pitch
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", [(1000, 4096, 4096), (2048, 4096, 2048)], ids=str)
+def test_captured(shape):
+    """A capture takes the scratch memory into the graph: every replay gives the eager bits, with eager products and new tensors between."""
+    import torch
+    from paper_2310_10537_amd import binding as mx
+    M, N, K = shape
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M)
+    (qa, sa), (qb, sb) = spread(torch, g, M, K), spread(torch, g, N, K)
+    out = torch.empty((M, N), dtype=torch.bfloat16, device="cuda")
+
+    def product(out=None):
+        return mx.mx_gemm(qa.view(torch.uint8), sa, INT8, qb.view(torch.uint8), sb, INT8, K, dtype=torch.bfloat16, out=out)
+    product(out)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        product(out)
+    need = mx.mx_workspace_bytes("gemm", M, N, K, INT8, INT8)
+    later = [torch.full((need,), 0xA5, dtype=torch.uint8, device="cuda") for _ in range(3)]
+    for seed in range(4):
+        qa.copy_(torch.roll(qa, 1, 0))                            # the graph reads what the operands hold now
+        want = product()
+        out.fill_(7.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want) and all(bool((t == 0xA5).all()) for t in later), seed
