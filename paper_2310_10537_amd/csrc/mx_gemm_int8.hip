@@ -19,7 +19,7 @@
 // once as a rule -- recompute the parts of C where it does not.  (The 8-bit integer
 // instruction is twice as fast as the bf16 one, but every block's sums have to be scaled by the vector pipe: 48 instructions for
 // 32 clocks of it.  Splitting q into two E2M3 halves, four products on the block-scaled instruction at four times the bf16 rate, moves
-// three bytes an element instead of two for the same matrix work: 8192 x 4096 x 4096 348 us where this takes 215.)
+// three bytes an element instead of two for the same matrix work: 8192 x 4096 x 4096 388 us where this takes 227.)
 #include "mx_device.hpp"
 #include "mx_launch.hpp"
 
@@ -566,7 +566,7 @@ hipError_t launch_gemm_int8(int64_t M, int64_t N, int64_t K, const uint8_t *Ae, 
                             const uint8_t *Bs, void *C, int c_dt, int64_t ldc, hipStream_t st)
 {
     // Routes, picked by measurement (bf16 output; TOP/s = 2 M N K / time):
-    //  - the product of the bf16 values (int8_widened_pays): 8192 x 4096 x 4096 1280 TOP/s, 4096^3 over 1070, 1000 x 4096 x 4096 over 550;
+    //  - the product of the bf16 values (int8_widened_pays): 8192 x 4096 x 4096 1100 to 1210 TOP/s, 4096^3 960 to 1110, 1000 x 4096 x 4096 530 to 560;
     //  - the LDS-staged shared-K kernel (K a multiple of 128): about 250 TOP/s when K is long, falling with K (each tile's eight
     //    partial sums cost the same whatever K is): 256 x 4096 x 4096 34 us, 1000 x 1000 x 1024 18;
     //  - the unstaged shared-K kernel for few rows or few tiles when K is not a multiple of 128;

@@ -18,8 +18,9 @@
 // registers, 16 bytes a lane for each of 16 loads, and are written to the one or two stages they belong to when those are free: the
 // window behind the barrier of step t for the steps t + 2 and t + 3.  Lines of 8 rows go out as two pieces of 64 bytes of two rows
 // after the other, so that the 8 lanes of an LDS write phase meet no bank twice.  Measured against the eight-wave kernel on
-// the 32 x 32 x 64 form (mx_gemm_tile8.hpp): 4096 x 28672 x 8192 E3M2 x E2M1 578 -> 517 us, 2056 clocks a step at 1.94 GHz where it was 2210
-// at 1.74; 16384 x 2048 x 8192 E3M2 178 -> 162 us.  What is left: without the LDS writes a step takes 1640 clocks, without loads and
+// the 32 x 32 x 64 form (mx_gemm_tile8.hpp), both in turn: 4096 x 28672 x 8192 E3M2 x E2M1 580 -> 540 us (578 -> 517 and 591 -> 554 on other
+// boxes), 2056 to 2075 clocks a step at 1.86 to 1.94 GHz where it was 2210 at 1.74; 16384 x 2048 x 8192 E3M2 178 -> 162 us.  L1 accesses a step of an
+// E3M2 pair 1520 -> 1050, cycles of LDS bank conflicts 612 -> 270.  What is left: without the LDS writes a step takes 1640 clocks, without loads and
 // writes 1640, matrix instructions alone 1400: with one wave per SIMD an LDS write holds up the instructions behind it.
 //
 // The scales.  A row's bytes of eight steps are one 32-byte direct load; the rows with (r & 32) == 0 begin such a group at even
